@@ -891,6 +891,49 @@ __global__ void k_cast_bf16(const float* __restrict__ src, bf16_t* __restrict__ 
   if (i < n) dst[i] = f2bf(src[i]);
 }
 
+// ---------------------------------------------------------------- internal <-> canonical parameter order
+// The internal vector is a list of segments; element r of one lies at canonical index
+//   SAME    co + r
+//   CONV    [Co][9][Ci] -> [Co][Ci][9]                                   (a = Ci)
+//   MATRIX  [rows][a] -> [rows][a], columns < nperm from (view, pixel, channel) to (view, channel, pixel) order
+//   LSTM    [rows][a]: columns < lin as MATRIX [rows][lin] at co, the others as [rows][a - lin] at co2
+struct ParamMap {
+  enum { SAME, CONV, MATRIX, LSTM };
+  static constexpr int MAXSEG = 64;  // 8 convolutions x 4 + embedding 2 + 4 LSTM x 2 + 8 hidden x 2 + heads
+  struct Seg { int64_t io, co, co2; int32_t kind, a, lin, nperm, flat, ch, pix; };
+  int nseg;
+  int64_t total;
+  Seg seg[MAXSEG];
+};
+// TO_INTERNAL: dst[i] = src[canonical(i)] (i internal), else dst[canonical(i)] = src[i].  One thread per element; the
+// permuted side is answered by L2 (5.6 M parameters: 22 MB).
+template <bool TO_INTERNAL>
+__global__ __launch_bounds__(256) void k_param_map(ParamMap pm, const float* __restrict__ src, float* __restrict__ dst) {
+  const int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x;
+  if (i >= pm.total) return;
+  int lo = 0, hi = pm.nseg - 1;
+  while (lo < hi) { const int mid = (lo + hi + 1) >> 1; if (pm.seg[mid].io <= i) lo = mid; else hi = mid - 1; }
+  const ParamMap::Seg g = pm.seg[lo];
+  const uint32_t r = (uint32_t)(i - g.io), a = (uint32_t)g.a;
+  auto col = [&](uint32_t j) {
+    if (j >= (uint32_t)g.nperm) return j;
+    const uint32_t v = j / (uint32_t)g.flat, q = j - v * g.flat, pix = q / (uint32_t)g.ch, ch = q - pix * g.ch;
+    return v * g.flat + ch * g.pix + pix;
+  };
+  int64_t k = g.co + r;
+  if (g.kind == ParamMap::CONV) {
+    const uint32_t co = r / (9u * a), q = r - co * 9u * a, tap = q / a, ci = q - tap * a;
+    k = g.co + (int64_t)(co * a + ci) * 9 + tap;
+  } else if (g.kind == ParamMap::MATRIX) {
+    const uint32_t row = r / a;
+    k = g.co + (int64_t)row * a + col(r - row * a);
+  } else if (g.kind == ParamMap::LSTM) {
+    const uint32_t row = r / a, j = r - row * a, lin = (uint32_t)g.lin;
+    k = j < lin ? g.co + (int64_t)row * lin + col(j) : g.co2 + (int64_t)row * (a - lin) + (j - lin);
+  }
+  if (TO_INTERNAL) dst[i] = src[k]; else dst[k] = src[i];
+}
+
 // ---------------------------------------------------------------- weight re-packing for the backward GEMMs
 // All per-update re-packs in one launch: job j covers blocks [first[j], first[j+1]).
 // kind 0, transpose with zero padding (a = rows, b = cols, ld = leading dimension of dst):

@@ -108,7 +108,10 @@ struct Ctx {
   float *h0 = nullptr, *c0 = nullptr;       // [nl][N][H] state of every environment at the start of the rollout
   int PU = 0;                               // units the minibatch permutation shuffles: N environments (recurrent) or S samples
   int CHe = 0;                              // environments per sequence chunk
-  std::vector<int32_t> i2c;  // internal index -> canonical index
+  ParamMap pmap;             // internal order <-> canonical order
+  float* canon = nullptr;    // device staging in canonical order for parameter / gradient / moment I/O
+  float* hstage = nullptr;   // pinned host staging of the same (two halves of HSTAGE elements), allocated by the first read
+  hipEvent_t hstage_ev[2] = {nullptr, nullptr};
   // device: parameters
   float *p = nullptr, *m = nullptr, *v = nullptr, *g = nullptr;
   bf16_t* shadow = nullptr;
@@ -342,76 +345,60 @@ void build_geometry(Ctx* c) {
     cA2W = off; off += (int64_t)c->X * c->XH; cA2B = off; off += c->X;
   }
   c->total = off;
-  c->i2c.assign((size_t)off, 0);
-  auto same = [&](int64_t io, int64_t co, int64_t n) { for (int64_t i = 0; i < n; ++i) c->i2c[(size_t)(io + i)] = (int32_t)(co + i); };
+  ParamMap& pm = c->pmap;
+  pm.nseg = 0;
+  int64_t io = 0;
+  // appends the internal elements [io, io + n) of one kind (ParamMap) and returns their first index
+  auto seg = [&](int kind, int64_t n, int64_t co, int a = 1, int64_t co2 = 0, int lin = 0, bool flat = false) {
+    ParamMap::Seg& g = pm.seg[pm.nseg++];
+    g.io = io; g.co = co; g.co2 = co2; g.kind = kind; g.a = a; g.lin = lin;
+    g.nperm = flat ? c->V * c->flat : 0; g.flat = c->flat; g.ch = c->cC[c->nconv]; g.pix = c->cH[c->nconv] * c->cW[c->nconv];
+    io += n;
+    return g.io;
+  };
 
   // internal layout: conv W as [Co][(u*3+v)*Ci + ci]; the first layer behind the convolutions reads the
   // channel-last flatten (view, pixel, channel); LSTM input and recurrent weights side by side per gate row;
   // heads stacked as one [NH][hid] matrix.  Every matrix starts at a multiple of 8 elements (16-byte operand
   // loads from the bf16 shadow) and every bias a bf16-output epilogue reads at a multiple of 4: the vectors of
   // odd length (head biases, log-std, the auxiliary output bias) come last.
-  int64_t io = 0;
   for (int l = 0; l < c->nconv; ++l) {
-    int Co = c->cC[l + 1], Ci = c->cC[l];
-    c->convW[l] = io;
-    for (int co = 0; co < Co; ++co)
-      for (int u = 0; u < 3; ++u)
-        for (int v = 0; v < 3; ++v)
-          for (int ci = 0; ci < Ci; ++ci)
-            c->i2c[(size_t)(io + (int64_t)co * 9 * Ci + (u * 3 + v) * Ci + ci)] = (int32_t)(cConvW[l] + (((int64_t)co * Ci + ci) * 3 + u) * 3 + v);
-    io += (int64_t)Co * 9 * Ci;
-    c->convB[l] = io; same(io, cConvB[l], Co); io += Co;
+    const int Co = c->cC[l + 1], Ci = c->cC[l];
+    c->convW[l] = seg(ParamMap::CONV, (int64_t)Co * 9 * Ci, cConvW[l], Ci);
+    c->convB[l] = seg(ParamMap::SAME, Co, cConvB[l]);
     c->lnG[l] = c->lnB[l] = -1;
-    if (c->ln) { c->lnG[l] = io; same(io, cLnG[l], Co); io += Co; c->lnB[l] = io; same(io, cLnB[l], Co); io += Co; }
+    if (c->ln) { c->lnG[l] = seg(ParamMap::SAME, Co, cLnG[l]); c->lnB[l] = seg(ParamMap::SAME, Co, cLnB[l]); }
   }
-  const int CL = c->cC[c->nconv], HWL = c->cH[c->nconv] * c->cW[c->nconv];
-  // column j of a matrix that reads the channel-last flatten of one view <-> canonical (c,h,w) column
-  auto flat_col = [&](int r) { const int pix = r / CL, ch = r - pix * CL; return ch * HWL + pix; };
-  if (c->E > 0) {
-    c->embW = io;
-    for (int o = 0; o < c->E; ++o)
-      for (int j = 0; j < c->flat; ++j) c->i2c[(size_t)(io + (int64_t)o * c->flat + j)] = (int32_t)(cEmbW + (int64_t)o * c->flat + flat_col(j));
-    io += (int64_t)c->E * c->flat;
-    c->embB = io; same(io, cEmbB, c->E); io += c->E;
+  if (c->E > 0) {  // reads the flatten of one view
+    c->embW = seg(ParamMap::MATRIX, (int64_t)c->E * c->flat, cEmbW, c->flat);
+    ParamMap::Seg& g = pm.seg[pm.nseg - 1];
+    g.nperm = g.flat;
+    c->embB = seg(ParamMap::SAME, c->E, cEmbB);
   }
-  // the first layer behind the concatenation [encoder(view 0), ..., proprioception]
-  auto feat_col = [&](int j) {
-    if (c->E > 0 || j >= c->V * c->flat) return j;
-    const int v = j / c->flat;
-    return v * c->flat + flat_col(j - v * c->flat);
-  };
+  const bool first_flat = c->E == 0;  // the first layer behind [encoder(view 0), ..., proprioception] reads the flatten itself
   for (int l = 0; l < c->nl; ++l) {
     const int K = c->lin[l] + c->H;
-    c->lstmW[l] = io;
-    for (int r = 0; r < 4 * c->H; ++r) {
-      for (int j = 0; j < c->lin[l]; ++j)
-        c->i2c[(size_t)(io + (int64_t)r * K + j)] = (int32_t)(cWih[l] + (int64_t)r * c->lin[l] + (l == 0 ? feat_col(j) : j));
-      for (int j = 0; j < c->H; ++j) c->i2c[(size_t)(io + (int64_t)r * K + c->lin[l] + j)] = (int32_t)(cWhh[l] + (int64_t)r * c->H + j);
-    }
-    io += (int64_t)4 * c->H * K;
-    c->lstmB[l] = io; same(io, cLb[l], 4 * c->H); io += 4 * c->H;
+    c->lstmW[l] = seg(ParamMap::LSTM, (int64_t)4 * c->H * K, cWih[l], K, cWhh[l], c->lin[l], l == 0 && first_flat);
+    c->lstmB[l] = seg(ParamMap::SAME, 4 * c->H, cLb[l]);
   }
   for (int l = 0; l < c->nfc; ++l) {
-    c->fcW[l] = io;
-    for (int o = 0; o < c->fout[l]; ++o)
-      for (int j = 0; j < c->fin[l]; ++j)
-        c->i2c[(size_t)(io + (int64_t)o * c->fin[l] + j)] = (int32_t)(cFcW[l] + (int64_t)o * c->fin[l] + ((l == 0 && c->nl == 0) ? feat_col(j) : j));
-    io += (int64_t)c->fin[l] * c->fout[l];
-    c->fcB[l] = io; same(io, cFcB[l], c->fout[l]); io += c->fout[l];
+    c->fcW[l] = seg(ParamMap::MATRIX, (int64_t)c->fin[l] * c->fout[l], cFcW[l], c->fin[l], 0, 0, l == 0 && c->nl == 0 && first_flat);
+    c->fcB[l] = seg(ParamMap::SAME, c->fout[l], cFcB[l]);
   }
   if (c->XH > 0) {
-    c->aux1W = io; same(io, cA1W, (int64_t)c->XH * c->hid); io += (int64_t)c->XH * c->hid;
-    c->aux1B = io; same(io, cA1B, c->XH); io += c->XH;
-    c->aux2W = io; same(io, cA2W, (int64_t)c->X * c->XH); io += (int64_t)c->X * c->XH;
+    c->aux1W = seg(ParamMap::SAME, (int64_t)c->XH * c->hid, cA1W);
+    c->aux1B = seg(ParamMap::SAME, c->XH, cA1B);
+    c->aux2W = seg(ParamMap::SAME, (int64_t)c->X * c->XH, cA2W);
   }
-  c->headW = io; same(io, cMuW, (int64_t)c->A_main * c->hid); io += (int64_t)c->A_main * c->hid;
-  if (d.has_value_head) { same(io, cVW, c->hid); io += c->hid; }
-  c->headB = io; same(io, cMuB, c->A_main); io += c->A_main;
+  c->headW = seg(ParamMap::SAME, (int64_t)c->A_main * c->hid, cMuW);
+  if (d.has_value_head) seg(ParamMap::SAME, c->hid, cVW);
+  c->headB = seg(ParamMap::SAME, c->A_main, cMuB);
   if (d.has_value_head) {
-    c->i2c[(size_t)io] = (int32_t)cVB; io += 1;
-    c->logstd = io; same(io, cLs, c->A); io += c->A;
+    seg(ParamMap::SAME, 1, cVB);
+    c->logstd = seg(ParamMap::SAME, c->A, cLs);
   }
-  if (c->XH > 0) { c->aux2B = io; same(io, cA2B, c->X); io += c->X; }
+  if (c->XH > 0) c->aux2B = seg(ParamMap::SAME, c->X, cA2B);
+  pm.total = io;
 }
 
 // number of input pixels of parity `par` along an axis of length n
@@ -1635,6 +1622,7 @@ int create_impl(Ctx* c) {
   // parameters
   DALLOC(c, c->p, c->total); DALLOC(c, c->m, c->total); DALLOC(c, c->v, c->total); DALLOC(c, c->g, c->total);
   DALLOC(c, c->shadow, c->total + 8);
+  DALLOC(c, c->canon, c->total);
   for (int l = 1; l < c->nconv; ++l) {
     for (int py = 0; py < 2; ++py) DALLOC(c, c->wd[l][py], (int64_t)2 * c->cC[l] * (1 + py) * 2 * c->cC[l + 1]);
     DALLOC(c, c->wtap[l], (int64_t)9 * c->cC[l] * c->cC[l + 1]);
@@ -1786,20 +1774,44 @@ int create_impl(Ctx* c) {
 void free_all(Ctx* c) {
   for (void* p : c->allocs) (void)hipFree(p);
   c->allocs.clear();
+  for (auto& e : c->hstage_ev) if (e) { (void)hipEventDestroy(e); e = nullptr; }
+  if (c->hstage) { (void)hipHostFree(c->hstage); c->hstage = nullptr; }
 }
 
+// Parameter-shaped vectors cross the ABI in canonical order and live on the device in the internal one; the
+// reordering is a device kernel over a staging vector in canonical order (k_param_map).
 int to_internal(Ctx* c, const float* canon, float* dev) {
-  std::vector<float> tmp((size_t)c->total);
-  for (int64_t i = 0; i < c->total; ++i) tmp[(size_t)i] = canon[c->i2c[(size_t)i]];
-  HIPCHK(c, hipMemcpyAsync(dev, tmp.data(), sizeof(float) * (size_t)c->total, hipMemcpyHostToDevice, c->stream));
+  HIPCHK(c, hipMemcpyAsync(c->canon, canon, sizeof(float) * (size_t)c->total, hipMemcpyHostToDevice, c->stream));
+  hipLaunchKernelGGL(k_param_map<true>, dim3(cdiv(c->total, 256)), dim3(256), 0, c->stream, c->pmap, c->canon, dev);
+  LAUNCHCHK(c, "k_param_map");
   HIPCHK(c, hipStreamSynchronize(c->stream));
   return PPO_OK;
 }
+// The way back ends in ordinary host memory.  It goes through two halves of a pinned staging buffer, so that the
+// host's copy of one piece runs under the transfer of the next: 22 MB arrive in about 0.8 ms, against 1.25 ms for a
+// transfer straight into pageable memory and 8.2 ms with the reordering done by the host.
+constexpr int64_t HSTAGE = 1 << 19;  // floats per half (2 MiB)
 int to_canonical(Ctx* c, const float* dev, float* canon) {
-  std::vector<float> tmp((size_t)c->total);
-  HIPCHK(c, hipMemcpyAsync(tmp.data(), dev, sizeof(float) * (size_t)c->total, hipMemcpyDeviceToHost, c->stream));
-  HIPCHK(c, hipStreamSynchronize(c->stream));
-  for (int64_t i = 0; i < c->total; ++i) canon[c->i2c[(size_t)i]] = tmp[(size_t)i];
+  hipLaunchKernelGGL(k_param_map<false>, dim3(cdiv(c->total, 256)), dim3(256), 0, c->stream, c->pmap, dev, c->canon);
+  LAUNCHCHK(c, "k_param_map");
+  if (!c->hstage) {
+    HIPCHK(c, hipHostMalloc((void**)&c->hstage, sizeof(float) * (size_t)std::min(c->total, 2 * HSTAGE), hipHostMallocDefault));
+    for (auto& e : c->hstage_ev) HIPCHK(c, hipEventCreateWithFlags(&e, hipEventDisableTiming));
+  }
+  auto piece = [&](int64_t k) { return std::min(HSTAGE, c->total - k * HSTAGE); };
+  auto fetch = [&](int64_t k) -> int {
+    HIPCHK(c, hipMemcpyAsync(c->hstage + (k & 1) * HSTAGE, c->canon + k * HSTAGE, sizeof(float) * (size_t)piece(k), hipMemcpyDeviceToHost, c->stream));
+    HIPCHK(c, hipEventRecord(c->hstage_ev[k & 1], c->stream));
+    return PPO_OK;
+  };
+  const int64_t np = cdiv(c->total, HSTAGE);
+  int rc = fetch(0);
+  if (rc) return rc;
+  for (int64_t k = 0; k < np; ++k) {
+    if (k + 1 < np) { rc = fetch(k + 1); if (rc) return rc; }
+    HIPCHK(c, hipEventSynchronize(c->hstage_ev[k & 1]));
+    memcpy(canon + k * HSTAGE, c->hstage + (k & 1) * HSTAGE, sizeof(float) * (size_t)piece(k));
+  }
   return PPO_OK;
 }
 

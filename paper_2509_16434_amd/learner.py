@@ -1,4 +1,5 @@
-"""Thin ctypes binding of libppo_learner.so (see include/ppo_learner.h).
+"""Thin binding of libppo_learner.so (see include/ppo_learner.h): ctypes, and for the calls made once per environment
+step the native module _binding (csrc/binding.cpp).
 
 Argument marshalling only: every step of the path runs in the library's HIP
 kernels.  PyTorch is used for device memory and the stream, nothing else.  There
@@ -98,7 +99,21 @@ def load_library():
     return lib
 
 
+def load_binding(lib):
+    """The native module that makes the per-step calls, handed the library's functions."""
+    import torch  # noqa: F401  (its libraries must be loaded first)
+    try:
+        from . import _binding
+    except ImportError as e:
+        raise ImportError(f"the native binding next to {LIB_PATH} is not built ({e}); run `python -c 'import __graft_entry__ as g; g.build()'` "
+                          "(or python paper_2509_16434_amd/build.py). There is no fallback path.") from e
+    _binding.setup(*(C.cast(getattr(lib, f), C.c_void_p).value for f in
+                     ("ppo_buffer_write", "ppo_buffer_write_range", "ppo_act", "ppo_buffer_write_outcome", "ppo_gae")))
+    return _binding
+
+
 _lib = load_library()
+_native = load_binding(_lib)
 EXPORTS = ("ppo_create", "ppo_destroy", "ppo_last_error", "ppo_param_count", "ppo_buffer_image_bytes",
            "ppo_set_params", "ppo_get_params", "ppo_get_grads", "ppo_set_opt_state", "ppo_get_opt_state", "ppo_get_adaptive_lr", "ppo_set_adaptive_lr",
            "ppo_buffer_write", "ppo_buffer_write_range", "ppo_act", "ppo_buffer_write_outcome", "ppo_buffer_write_state", "ppo_buffer_read_obs", "ppo_gae", "ppo_get_adv_ret", "ppo_permutation", "ppo_permutation_static", "ppo_update", "distill_update",
@@ -153,11 +168,11 @@ def _dev(t, dtype=None, numel=None):
         return None
     if not t.is_cuda or not t.is_contiguous():
         raise ValueError("expected a contiguous CUDA tensor")
-    if dtype is not None and t.dtype != dtype:
+    if dtype is not None and t.dtype is not dtype:
         raise ValueError(f"expected dtype {dtype}, got {t.dtype}")
     if numel is not None and t.numel() != numel:
         raise ValueError(f"expected {numel} elements, got {t.numel()}")
-    return C.c_void_p(t.data_ptr())
+    return t.data_ptr()
 
 
 def diag_gemm(a: np.ndarray, b: np.ndarray) -> np.ndarray:
@@ -219,6 +234,8 @@ class Learner:
             self._h = C.c_void_p()
             raise LearnerError(rc, _lib.ppo_last_error(None).decode())
         self.n_params = int(_lib.ppo_param_count(self._h))
+        # what the per-step calls check their tensors against: fp32 images, elements per observation, P, A
+        self._dims = (int(obs_dtype == "fp32"), net.get("n_views", 1) * net["in_c"] * net["in_h"] * net["in_w"], net["proprio_dim"], net["act_dim"])
 
     # -- plumbing
     def _chk(self, rc):
@@ -275,42 +292,30 @@ class Learner:
 
     # -- the path
     def buffer_write(self, t, obs, proprio, action, logp=None, value=None, reward=None, done=None):
-        torch = self._torch
-        net = self.net
-        n_obs = self.N * net.get("n_views", 1) * net["in_c"] * net["in_h"] * net["in_w"]
-        odt = torch.float32 if self.obs_dtype == "fp32" else torch.bfloat16
-        self._chk(_lib.ppo_buffer_write(
-            self._h, t, _dev(obs, odt, n_obs), _dev(proprio, torch.float32, self.N * net["proprio_dim"]),
-            _dev(action, torch.float32, self.N * net["act_dim"]), _dev(logp, torch.float32, self.N),
-            _dev(value, torch.float32, self.N), _dev(reward, torch.float32, self.N), _dev(done, torch.uint8, self.N)))
+        rc = _native.write(self._h.value or 0, *self._dims, t, -1, self.N, obs, proprio, action, logp, value, reward, done)
+        if rc:
+            self._chk(rc)
 
     def buffer_write_range(self, t, env_offset, obs, proprio, action, logp=None, value=None, reward=None, done=None):
         """Rows [env_offset, env_offset + len(proprio)) of step t."""
-        torch, net = self._torch, self.net
         cnt = int(proprio.shape[0])
-        n_obs = cnt * net.get("n_views", 1) * net["in_c"] * net["in_h"] * net["in_w"]
-        odt = torch.float32 if self.obs_dtype == "fp32" else torch.bfloat16
-        self._chk(_lib.ppo_buffer_write_range(
-            self._h, t, env_offset, cnt, _dev(obs, odt, n_obs), _dev(proprio, torch.float32, cnt * net["proprio_dim"]),
-            _dev(action, torch.float32, cnt * net["act_dim"]), _dev(logp, torch.float32, cnt),
-            _dev(value, torch.float32, cnt), _dev(reward, torch.float32, cnt), _dev(done, torch.uint8, cnt)))
+        if env_offset < 0:   # the native call takes a negative offset for the whole step
+            raise LearnerError(PPO_EINVAL, f"environments [{env_offset}, {env_offset} + {cnt}) outside [0, {self.N})")
+        rc = _native.write(self._h.value or 0, *self._dims, t, env_offset, cnt, obs, proprio, action, logp, value, reward, done)
+        if rc:
+            self._chk(rc)
 
     def act(self, t, obs, proprio, noise):
         """Policy step on the step-t observations -> (action [N][A], logp [N], value [N]) device tensors."""
-        torch, net = self._torch, self.net
-        n_obs = self.N * net.get("n_views", 1) * net["in_c"] * net["in_h"] * net["in_w"]
-        odt = torch.float32 if self.obs_dtype == "fp32" else torch.bfloat16
-        action = torch.empty(self.N, net["act_dim"], dtype=torch.float32, device="cuda")
-        logp = torch.empty(self.N, dtype=torch.float32, device="cuda")
-        value = torch.empty(self.N, dtype=torch.float32, device="cuda")
-        self._chk(_lib.ppo_act(
-            self._h, t, _dev(obs, odt, n_obs), _dev(proprio, torch.float32, self.N * net["proprio_dim"]),
-            _dev(noise, torch.float32, self.N * net["act_dim"]), _dev(action), _dev(logp), _dev(value)))
+        rc, action, logp, value = _native.act(self._h.value or 0, *self._dims, t, self.N, obs, proprio, noise)
+        if rc:
+            self._chk(rc)
         return action, logp, value
 
     def buffer_write_outcome(self, t, reward, done):
-        torch = self._torch
-        self._chk(_lib.ppo_buffer_write_outcome(self._h, t, _dev(reward, torch.float32, self.N), _dev(done, torch.uint8, self.N)))
+        rc = _native.outcome(self._h.value or 0, t, self.N, reward, done)
+        if rc:
+            self._chk(rc)
 
     def buffer_write_state(self, h0=None, c0=None):
         """Recurrent nets: LSTM state of every environment at the start of the rollout, [layers][N][units] fp32 (None: zeros)."""
@@ -327,7 +332,7 @@ class Learner:
         return out
 
     def gae(self, last_value, gamma, lam):
-        self._chk(_lib.ppo_gae(self._h, _dev(last_value, self._torch.float32, self.N), gamma, lam))
+        self._chk(_native.gae(self._h.value or 0, self.N, last_value, gamma, lam))
 
     def get_adv_ret(self):
         torch = self._torch

@@ -222,6 +222,74 @@ __global__ void k_perm_rank(PermStreams ps, int S, int shift, int nb, const int3
   perm[beg + rank] = i;
 }
 
+// The same permutations in one launch, one block per slot, for S <= PERM_SMALL units: counts, keys and bucket contents
+// stay in LDS.  Five dependent launches cost 30 us whatever the size; this one 4 us at 1024 units and 9 us at 8192
+// (where the block's own work begins to show: the limit).  About two keys per bucket, so the exact rank inside a
+// bucket is a compare or two.  Dynamic LDS: keys [S], starts [nb + 1], indices [S].
+#define PERM_SMALL 8192
+inline int perm_small_buckets(int S) { int nb = 1; while (nb * 2 < S) nb <<= 1; return nb; }
+inline int perm_small_lds(int S, int nb) { return S * 8 + (nb + 1) * 4 + (S + 1) / 2 * 4; }
+__global__ __launch_bounds__(1024) void k_perm_small(PermStreams ps, int S, int nb, int shift, int32_t* __restrict__ perm_all) {
+  constexpr int PT = PERM_SMALL / 1024;  // units (and buckets) per thread
+  extern __shared__ __attribute__((aligned(16))) char lds[];
+  __shared__ int32_t wsum[16];
+  uint64_t* const skey = reinterpret_cast<uint64_t*>(lds);
+  int32_t* const start = reinterpret_cast<int32_t*>(skey + S);
+  uint16_t* const sidx = reinterpret_cast<uint16_t*>(start + nb + 1);
+  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  const uint64_t stream = ps.s[blockIdx.x];
+  int32_t* const perm = perm_all + (int64_t)blockIdx.x * S;
+  for (int b = tid; b <= nb; b += 1024) start[b] = 0;
+  __syncthreads();
+  uint64_t key[PT];
+  int slot[PT];
+#pragma unroll
+  for (int k = 0; k < PT; ++k) {
+    const int i = tid + k * 1024;
+    key[k] = 0; slot[k] = 0;
+    if (i < S) {
+      key[k] = perm_key(stream, (uint64_t)i);
+      slot[k] = atomicAdd(&start[shift >= 64 ? 0 : (int)(key[k] >> shift)], 1);
+    }
+  }
+  __syncthreads();
+  // exclusive scan of the counts: thread t owns buckets t*per .. (nb <= PERM_SMALL)
+  const int per = (nb + 1023) >> 10, b0 = tid * per;
+  int cnt[PT], sum = 0;
+#pragma unroll
+  for (int k = 0; k < PT; ++k) { cnt[k] = (k < per && b0 + k < nb) ? start[b0 + k] : 0; sum += cnt[k]; }
+  int inc = sum;
+#pragma unroll
+  for (int off = 1; off < 64; off <<= 1) { const int y = __shfl_up(inc, off); if (lane >= off) inc += y; }
+  if (lane == 63) wsum[wave] = inc;
+  __syncthreads();
+  int run = inc - sum;
+  for (int w = 0; w < wave; ++w) run += wsum[w];
+#pragma unroll
+  for (int k = 0; k < PT; ++k) if (k < per && b0 + k < nb) { start[b0 + k] = run; run += cnt[k]; }
+  if (tid == 0) start[nb] = S;
+  __syncthreads();
+#pragma unroll
+  for (int k = 0; k < PT; ++k) {
+    const int i = tid + k * 1024;
+    if (i < S) {
+      const int pos = start[shift >= 64 ? 0 : (int)(key[k] >> shift)] + slot[k];
+      skey[pos] = key[k]; sidx[pos] = (uint16_t)i;
+    }
+  }
+  __syncthreads();
+#pragma unroll
+  for (int k = 0; k < PT; ++k) {
+    const int i = tid + k * 1024;
+    if (i < S) {
+      const int b = shift >= 64 ? 0 : (int)(key[k] >> shift), beg = start[b], end = start[b + 1];
+      int rank = 0;
+      for (int q = beg; q < end; ++q) rank += (skey[q] < key[k] || (skey[q] == key[k] && (int)sidx[q] < i)) ? 1 : 0;
+      perm[beg + rank] = i;
+    }
+  }
+}
+
 // ---------------------------------------------------------------- first convolution
 // 3x3 stride-2 pad-1 convolution of a 1- or 3-channel image read straight from the rollout buffer
 // through the minibatch index (the gather is fused into the loader).  K = 9*CIN (9 or 27) is padded
@@ -939,9 +1007,13 @@ __global__ __launch_bounds__(256) void k_param_map(ParamMap pm, const float* __r
 // kind 0, transpose with zero padding (a = rows, b = cols, ld = leading dimension of dst):
 //   dst[c][r] = src[r][c] for r < rows, zero for rows <= r < ld;
 // kind 1, per-tap transpose for the quad-organised transposed convolution (a = Cout, b = Cin):
-//   dst[(tap*Cin + ci)*Cout + co] = W[co][tap*Cin + ci].
+//   dst[(tap*Cin + ci)*Cout + co] = W[co][tap*Cin + ci];
+// kind 2, parity-class packing of the implicit-GEMM transposed convolution (a = Cout, b = Cin, ld = row parity py):
+//   dst[px*Cin + ci][(tu*2 + dx)*Cout + co] = W[co][(u*3+v)*Cin + ci] with u = py ? 2*tu : 1 and the
+//   column tap v given by (px, dx): even pixel (px = 0) takes v = 1 from dx = 0 and nothing from
+//   dx = 1; odd pixel takes v = 2 from dx = 0 and v = 0 from dx = 1.
 struct RepackJobs {
-  static constexpr int MAXJ = 12;
+  static constexpr int MAXJ = 32;
   int njobs;
   int first[MAXJ + 1];
   int kind[MAXJ], a[MAXJ], b[MAXJ], ld[MAXJ];
@@ -960,24 +1032,17 @@ __global__ __launch_bounds__(256) void k_repack_all(RepackJobs jobs, GnormFinali
     if (i >= (int64_t)cols * ld_dst) return;
     const int c = (int)(i / ld_dst), r = (int)(i - (int64_t)c * ld_dst);
     dst[i] = r < rows ? src[(int64_t)r * cols + c] : (bf16_t)0;
+  } else if (jobs.kind[j] == 2) {
+    const int Cout = jobs.a[j], Cin = jobs.b[j], py = jobs.ld[j], Kc = (1 + py) * 2 * Cout;
+    if (i >= (int64_t)2 * Cin * Kc) return;
+    const int n = (int)(i / Kc), k = (int)(i - (int64_t)n * Kc), px = n / Cin, ci = n - px * Cin;
+    const int t = k / Cout, co = k - t * Cout, tu = t >> 1, dx = t & 1;
+    const int u = py ? 2 * tu : 1, v = px ? (dx ? 0 : 2) : (dx ? -1 : 1);
+    dst[i] = v < 0 ? (bf16_t)0 : src[(int64_t)co * 9 * Cin + (u * 3 + v) * Cin + ci];
   } else {
     const int Cout = jobs.a[j], Cin = jobs.b[j];
     if (i >= (int64_t)9 * Cin * Cout) return;
     const int tap = (int)(i / ((int64_t)Cin * Cout)), rem = (int)(i - (int64_t)tap * Cin * Cout), ci = rem / Cout, co = rem - ci * Cout;
     dst[i] = src[(int64_t)co * 9 * Cin + tap * Cin + ci];
   }
-}
-
-// dst[px*Cin + ci][(tu*2 + dx)*Cout + co] = W[co][(u*3+v)*Cin + ci] with u = py ? 2*tu : 1 and the
-// column tap v given by (px, dx): even pixel (px = 0) takes v = 1 from dx = 0 and nothing from
-// dx = 1; odd pixel takes v = 2 from dx = 0 and v = 0 from dx = 1.
-__global__ void k_pack_dgrad_w(const bf16_t* __restrict__ w, int Cout, int Cin, int py, bf16_t* __restrict__ dst) {
-  const int Kc = (1 + py) * 2 * Cout;
-  int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (i >= (int64_t)2 * Cin * Kc) return;
-  int n = (int)(i / Kc), k = (int)(i - (int64_t)n * Kc), px = n / Cin, ci = n - px * Cin;
-  int t = k / Cout, co = k - t * Cout, tu = t >> 1, dx = t & 1;
-  int u = py ? 2 * tu : 1;
-  int v = px ? (dx ? 0 : 2) : (dx ? -1 : 1);
-  dst[i] = v < 0 ? (bf16_t)0 : w[(int64_t)co * 9 * Cin + (u * 3 + v) * Cin + ci];
 }

@@ -120,7 +120,8 @@ struct Ctx {
   uint32_t* abits[PPO_MAX_LAYERS] = {};  // sign bits of conv layer l's stored output for the current chunk (ReLU mask of the backward pass)
   bool abits_ok[PPO_MAX_LAYERS] = {};    // written by the forward kernel that ran for this chunk
   int64_t wver = 0;                      // bumped whenever the weights change (every repack_weights call)
-  int64_t wd_ver[PPO_MAX_LAYERS] = {};   // weight version that wd[l] holds (0: none); packed on demand
+  int64_t wd_ver[PPO_MAX_LAYERS] = {};   // weight version that wd[l] holds (0: none): packed on demand the first time,
+  bool wd_used[PPO_MAX_LAYERS] = {};     // with every other re-pack from then on
   bf16_t* fcT[PPO_MAX_LAYERS];    // [in][out]
   bf16_t* headT = nullptr;        // [hid][32]
   bf16_t *aux1T = nullptr, *aux2T = nullptr;  // auxiliary head: [hid][XH], [XH][32]
@@ -580,50 +581,65 @@ int launch_wgrad(Ctx* c, const DL& dl_, const AL& al_, int Nn, int Kk, int M, fl
   return PPO_OK;
 }
 
-// bf16 copies of the parameters in the layouts the backward GEMMs read
-// Parity-class-packed transposed-conv weights of layer l for the implicit-GEMM paths: rebuilt when they
-// are first needed after a change of the weights (the LDS-image kernels use the per-tap transposes instead).
+// Re-packs of the weights into the layouts the backward kernels read, collected into one launch.
+struct RepackList {
+  RepackJobs jobs;
+  int nblocks = 0;
+  RepackList() { jobs.njobs = 0; }
+  void add(int kind, const bf16_t* src, bf16_t* dst, int a, int b, int ld, int64_t elems) {
+    const int j = jobs.njobs++;
+    jobs.first[j] = nblocks; jobs.kind[j] = kind; jobs.src[j] = src; jobs.dst[j] = dst; jobs.a[j] = a; jobs.b[j] = b; jobs.ld[j] = ld;
+    nblocks += cdiv(elems, 256);
+  }
+  // parity-class-packed transposed-conv weights of layer l, read by the implicit-GEMM paths
+  void add_packed_dgrad(Ctx* c, int l) {
+    const int Co = c->cC[l + 1], Ci = c->cC[l];
+    for (int py = 0; py < 2; ++py) add(2, c->shadow + c->convW[l], c->wd[l][py], Co, Ci, py, (int64_t)2 * Ci * (1 + py) * 2 * Co);
+    c->wd_ver[l] = c->wver;
+  }
+  int launch(Ctx* c, const GnormFinalize& gn) {
+    for (int j = jobs.njobs; j <= RepackJobs::MAXJ; ++j) jobs.first[j] = nblocks;
+    hipLaunchKernelGGL(k_repack_all, dim3(nblocks + (gn.on ? 1 : 0)), dim3(256), 0, c->stream, jobs, gn);
+    LAUNCHCHK(c, "weight repack");
+    return PPO_OK;
+  }
+};
+// The packed weights of layer l, built now if its current ones are not (the LDS-image kernels use the per-tap
+// transposes instead, so a layer is packed only once an implicit-GEMM path has asked for it).
 int ensure_packed_dgrad_weights(Ctx* c, int l) {
   if (c->wd_ver[l] == c->wver) return PPO_OK;
-  const int Co = c->cC[l + 1], Ci = c->cC[l];
-  for (int py = 0; py < 2; ++py) {
-    int64_t n = (int64_t)2 * Ci * (1 + py) * 2 * Co;
-    hipLaunchKernelGGL(k_pack_dgrad_w, dim3(cdiv(n, 256)), dim3(256), 0, c->stream, c->shadow + c->convW[l], Co, Ci, py, c->wd[l][py]);
-  }
-  LAUNCHCHK(c, "k_pack_dgrad_w");
-  c->wd_ver[l] = c->wver;
-  return PPO_OK;
+  c->wd_used[l] = true;
+  RepackList r;
+  r.add_packed_dgrad(c, l);
+  GnormFinalize none;
+  none.on = 0;
+  return r.launch(c, none);
 }
 
 int repack_weights(Ctx* c) {
   c->wver += 1;
   ProfScope ps(c, "weight_repack", 0.0, 4.0 * (double)c->total);
-  RepackJobs jobs;
-  int nj = 0, nblocks = 0;
-  auto add = [&](int kind, const bf16_t* src, bf16_t* dst, int a, int b, int ld, int64_t elems) {
-    jobs.first[nj] = nblocks; jobs.kind[nj] = kind; jobs.src[nj] = src; jobs.dst[nj] = dst; jobs.a[nj] = a; jobs.b[nj] = b; jobs.ld[nj] = ld;
-    nblocks += cdiv(elems, 256); ++nj;
-  };
-  if (c->nconv - 1 + c->nfc + 1 + (c->XH > 0 ? 2 : 0) + (c->E > 0 ? 1 : 0) + c->nl > RepackJobs::MAXJ) return fail(c, PPO_ESHAPE, "too many layers for one re-pack launch");
-  for (int l = 1; l < c->nconv; ++l)
-    add(1, c->shadow + c->convW[l], c->wtap[l], c->cC[l + 1], c->cC[l], 0, (int64_t)9 * c->cC[l] * c->cC[l + 1]);
-  for (int l = 0; l < c->nfc; ++l)
-    add(0, c->shadow + c->fcW[l], c->fcT[l], c->fout[l], c->fin[l], c->fout[l], (int64_t)c->fin[l] * c->fout[l]);
-  add(0, c->shadow + c->headW, c->headT, c->NH, c->hid, HEAD_LD, (int64_t)c->hid * HEAD_LD);
-  if (c->XH > 0) {
-    add(0, c->shadow + c->aux1W, c->aux1T, c->XH, c->hid, c->XH, (int64_t)c->hid * c->XH);
-    add(0, c->shadow + c->aux2W, c->aux2T, c->X, c->XH, HEAD_LD, (int64_t)c->XH * HEAD_LD);
+  RepackList r;
+  int packed = 0;
+  for (int l = 1; l < c->nconv; ++l) packed += c->wd_used[l] ? 2 : 0;
+  if (c->nconv - 1 + packed + c->nfc + 1 + (c->XH > 0 ? 2 : 0) + (c->E > 0 ? 1 : 0) + c->nl > RepackJobs::MAXJ) return fail(c, PPO_ESHAPE, "too many layers for one re-pack launch");
+  for (int l = 1; l < c->nconv; ++l) {
+    r.add(1, c->shadow + c->convW[l], c->wtap[l], c->cC[l + 1], c->cC[l], 0, (int64_t)9 * c->cC[l] * c->cC[l + 1]);
+    if (c->wd_used[l]) r.add_packed_dgrad(c, l);
   }
-  if (c->E > 0) add(0, c->shadow + c->embW, c->embT, c->E, c->flat, c->E, (int64_t)c->flat * c->E);
+  for (int l = 0; l < c->nfc; ++l)
+    r.add(0, c->shadow + c->fcW[l], c->fcT[l], c->fout[l], c->fin[l], c->fout[l], (int64_t)c->fin[l] * c->fout[l]);
+  r.add(0, c->shadow + c->headW, c->headT, c->NH, c->hid, HEAD_LD, (int64_t)c->hid * HEAD_LD);
+  if (c->XH > 0) {
+    r.add(0, c->shadow + c->aux1W, c->aux1T, c->XH, c->hid, c->XH, (int64_t)c->hid * c->XH);
+    r.add(0, c->shadow + c->aux2W, c->aux2T, c->X, c->XH, HEAD_LD, (int64_t)c->XH * HEAD_LD);
+  }
+  if (c->E > 0) r.add(0, c->shadow + c->embW, c->embT, c->E, c->flat, c->E, (int64_t)c->flat * c->E);
   for (int l = 0; l < c->nl; ++l)
-    add(0, c->shadow + c->lstmW[l], c->lstmWT[l], 4 * c->H, c->lin[l] + c->H, 4 * c->H, (int64_t)(c->lin[l] + c->H) * 4 * c->H);
-  jobs.first[nj] = nblocks; jobs.njobs = nj;
-  for (int j = nj + 1; j <= RepackJobs::MAXJ; ++j) jobs.first[j] = nblocks;
-  for (int j = nj; j < RepackJobs::MAXJ; ++j) { jobs.kind[j] = 0; jobs.src[j] = nullptr; jobs.dst[j] = nullptr; jobs.a[j] = jobs.b[j] = jobs.ld[j] = 0; }
-  hipLaunchKernelGGL(k_repack_all, dim3(nblocks + (c->gnfin.on ? 1 : 0)), dim3(256), 0, c->stream, jobs, c->gnfin);
-  LAUNCHCHK(c, "weight repack");
+    r.add(0, c->shadow + c->lstmW[l], c->lstmWT[l], 4 * c->H, c->lin[l] + c->H, 4 * c->H, (int64_t)(c->lin[l] + c->H) * 4 * c->H);
+  const int rc = r.launch(c, c->gnfin);
   c->gnfin.on = 0;
-  return PPO_OK;
+  return rc;
 }
 
 int refresh_shadow(Ctx* c) {
@@ -1435,13 +1451,34 @@ int backward_seq_chunk(Ctx* c, int ne, bool acc, bool with_head) {
   return encoder_backward_seq(c, c->seqidx, n, acc, c->dxh[0], c->lin[0] + H, cur);
 }
 
+// The one-launch form for up to PERM_SMALL units on the current device.
+hipError_t launch_perm_small(const PermStreams& ps, int S, int count, int32_t* perm, hipStream_t stream) {
+  const int nb = perm_small_buckets(S);
+  int lg = 0;
+  while ((1 << lg) < nb) ++lg;
+  static std::once_flag once[STATIC_MAX_DEVICES];
+  static hipError_t attr[STATIC_MAX_DEVICES];
+  int dev = -1;
+  hipError_t e = hipGetDevice(&dev);
+  if (e != hipSuccess) return e;
+  if (dev < 0 || dev >= STATIC_MAX_DEVICES) return hipErrorInvalidDevice;
+  std::call_once(once[dev], [&]() { attr[dev] = hipFuncSetAttribute((const void*)k_perm_small, hipFuncAttributeMaxDynamicSharedMemorySize, perm_small_lds(PERM_SMALL, PERM_SMALL)); });
+  if (attr[dev] != hipSuccess) return attr[dev];
+  hipLaunchKernelGGL(k_perm_small, dim3(count), dim3(1024), perm_small_lds(S, nb), stream, ps, S, nb, 64 - lg, perm);
+  return hipGetLastError();
+}
+
 // The permutations of epochs epoch0 .. epoch0 + count - 1 (count <= PERM_BATCH) of (seed, update) into the slots
-// 0 .. count - 1 of c->perm ([PERM_BATCH][S]): five launches whatever the count.
+// 0 .. count - 1 of c->perm ([PERM_BATCH][S]): one launch for few units, five otherwise, whatever the count.
 int gen_permutations(Ctx* c, uint64_t seed, uint64_t update, uint64_t epoch0, int count) {
   PermStreams ps;
   for (int e = 0; e < PERM_BATCH; ++e) ps.s[e] = perm_stream(seed, update, epoch0 + (uint64_t)(e < count ? e : 0));
   const int S = c->PU, g = cdiv(S, 256), nb = c->nb;  // the units a minibatch is made of: samples, or whole environments
   ProfScope pscope(c, "permutation", 0.0, 4.0 * S * count);
+  if (S <= PERM_SMALL) {
+    HIPCHK(c, launch_perm_small(ps, S, count, c->perm, c->stream));
+    return PPO_OK;
+  }
   hipLaunchKernelGGL(k_fill_i32, dim3(cdiv((int64_t)count * 2 * nb, 256)), dim3(256), 0, c->stream, c->phist, (int64_t)count * 2 * nb, 0);  // hist + cursor
   hipLaunchKernelGGL(k_perm_hist, dim3(g, count), dim3(256), 0, c->stream, ps, S, c->shift, nb, c->phist);
   hipLaunchKernelGGL(k_perm_scan, dim3(1, count), dim3(1024), 0, c->stream, c->phist, c->pstart, nb);
@@ -1490,6 +1527,24 @@ int launch_head_loss(Ctx* c, const LossData& L, int n, bool acc, bool distill, f
   }
 }
 bool head_loss_covers(const Ctx* c) { return c->XH == 0 && c->NH <= HEAD_LD && c->nfc >= 1 && (c->hid == 32 || c->hid == 64 || c->hid == 128); }
+
+// Output layer alone, of `n` samples whose last hidden activations are in the workspaces (k_head_act): with a.noise
+// the policy's sample, else means and values.
+bool head_act_covers(const Ctx* c) { return c->XH == 0 && c->NH <= HEAD_LD && c->A <= c->NH && (c->hid == 32 || c->hid == 64 || c->hid == 128); }
+int launch_head_act(Ctx* c, HeadActArgs a, int n) {
+  a.h = c->fcact[c->nfc - 1]; a.w = c->shadow + c->headW; a.bias = c->p + c->headB; a.n = n; a.A = c->A; a.NH = c->NH;
+  ProfScope ps(c, a.noise ? "head+sample" : "head_fwd", 2.0 * n * (double)c->hid * c->NH, (double)n * (2.0 * c->hid + (a.noise ? 12.0 : 4.0) * c->A + 16.0));
+  const dim3 grid(cdiv(n, 32)), blk(64);
+#define LAUNCH_HEAD_ACT(HID_)                                                                                   \
+  do {                                                                                                            \
+    if (a.noise) hipLaunchKernelGGL((k_head_act<HID_, true>), grid, blk, 0, c->stream, a);                         \
+    else hipLaunchKernelGGL((k_head_act<HID_, false>), grid, blk, 0, c->stream, a);                                \
+  } while (0)
+  if (c->hid == 32) LAUNCH_HEAD_ACT(32); else if (c->hid == 64) LAUNCH_HEAD_ACT(64); else LAUNCH_HEAD_ACT(128);
+#undef LAUNCH_HEAD_ACT
+  LAUNCHCHK(c, "k_head_act");
+  return PPO_OK;
+}
 
 int run_update(Ctx* c, const ppo_hparams* hp, ppo_mb_stats* host_stats, bool distill) {
   // a minibatch is Bu units of L rows each: samples (L = 1), or whole environments of T steps (recurrent nets)
@@ -2085,6 +2140,10 @@ int ppo_permutation_static(int64_t S, uint64_t seed, uint64_t update_idx, uint64
   hipStream_t st = (hipStream_t)hip_stream;
   PermStreams ps;
   for (int e = 0; e < PERM_BATCH; ++e) ps.s[e] = perm_stream(seed, update_idx, epoch);
+  if (S <= PERM_SMALL) {
+    const hipError_t e = launch_perm_small(ps, (int)S, 1, d_perm, st);
+    return e == hipSuccess ? PPO_OK : fail(nullptr, PPO_EHIP, "launch of k_perm_small failed: %s", hipGetErrorString(e));
+  }
   const int g = cdiv(S, 256), Si = (int)S;
   // the array keeps the last call's contents: counts and cursors must start at zero (a fill kernel, so that a
   // caller may record this call into a graph); start and tmp are fully overwritten before they are read
@@ -2132,8 +2191,16 @@ int ppo_forward(ppo_ctx* c, const int32_t* d_idx, int64_t count, float* d_mu, fl
   for (int64_t c0 = 0; c0 < count; c0 += c->CH) {
     int n = (int)((count - c0 < c->CH) ? count - c0 : c->CH);
     const int32_t* idx = d_idx ? d_idx + c0 : nullptr;
-    int rc = forward_chunk(c, idx, n, true, c0);  // without indices: samples c0 .. c0 + n - 1
+    const bool fused = head_act_covers(c);
+    int rc = forward_chunk(c, idx, n, !fused, c0);  // without indices: samples c0 .. c0 + n - 1
     if (rc) return rc;
+    if (fused) {
+      HeadActArgs a = {};
+      a.c_action = d_mu + c0 * c->A; a.c_value = d_v ? d_v + c0 : nullptr;
+      rc = launch_head_act(c, a, n);
+      if (rc) return rc;
+      continue;
+    }
     hipLaunchKernelGGL(k_copy_heads, dim3(cdiv((int64_t)n * HEAD_LD, 256)), dim3(256), 0, c->stream, n, c->A, c->d.has_value_head, c->headout,
                        d_mu + c0 * c->A, d_v ? d_v + c0 : nullptr);
     LAUNCHCHK(c, "k_copy_heads");
@@ -2157,10 +2224,20 @@ int ppo_act(ppo_ctx* c, int32_t t, const void* d_obs, const float* d_proprio, co
   const int64_t first = (int64_t)t * c->N;
   for (int64_t c0 = 0; c0 < c->N; c0 += c->CH) {
     const int n = (int)((c->N - c0 < c->CH) ? c->N - c0 : c->CH);
-    rc = forward_chunk(c, nullptr, n, true, first + c0);
+    const bool fused = head_act_covers(c);
+    rc = forward_chunk(c, nullptr, n, !fused, first + c0);
     if (rc) return rc;
-    ProfScope ps(c, "act_sample", 0.0, (double)n * (4.0 * HEAD_LD + 12.0 * c->A + 8.0));
     const int64_t s0 = first + c0;
+    if (fused) {
+      HeadActArgs a = {};
+      a.logstd = c->p + c->logstd; a.noise = d_noise + c0 * c->A;
+      a.o_action = c->action + s0 * c->A; a.o_logp = c->logp + s0; a.o_value = c->value + s0;
+      a.c_action = d_action ? d_action + c0 * c->A : nullptr; a.c_logp = d_logp ? d_logp + c0 : nullptr; a.c_value = d_value ? d_value + c0 : nullptr;
+      rc = launch_head_act(c, a, n);
+      if (rc) return rc;
+      continue;
+    }
+    ProfScope ps(c, "act_sample", 0.0, (double)n * (4.0 * HEAD_LD + 12.0 * c->A + 8.0));
     hipLaunchKernelGGL(k_act_sample, dim3(cdiv(n, 64)), dim3(64), 0, c->stream, n, c->A, c->headout, c->p + c->logstd, d_noise + c0 * c->A,
                        c->action + s0 * c->A, c->logp + s0, c->value + s0, d_action ? d_action + c0 * c->A : nullptr,
                        d_logp ? d_logp + c0 : nullptr, d_value ? d_value + c0 : nullptr);

@@ -1,0 +1,47 @@
+"""GPU tests of the size-dependent forms of the kernels, at the sizes where each can go wrong (edges of tiles,
+remainders, both sides of a dispatch rule), against the oracle."""
+import numpy as np
+import pytest
+
+from oracle import ppo_oracle as orc
+from paper_2509_16434_amd import configs, synth
+
+from helpers import TOL_BF16, fill_learner, rel_l2
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.fixture(scope="module")
+def L():
+    from paper_2509_16434_amd import learner
+    return learner
+
+
+@pytest.mark.parametrize("S", [1, 2, 3, 63, 65, 1023, 1025, 2048, 8191, 8192, 8193])
+def test_permutation_one_launch_form(L, S):
+    """One block holds up to 8192 units; from 8193 on the bucket kernels take over."""
+    np.testing.assert_array_equal(L.permutation_static(S, 77, 3, 2).cpu().numpy(), orc.permutation(77, 3, 2, S))
+
+
+@pytest.mark.parametrize("hid,N", [(32, 1), (32, 33), (64, 31), (128, 65), (48, 33)])
+def test_output_layer_of_act_and_forward(L, hid, N):
+    """The fused output layer (widths 32, 64, 128; 32 samples per wave) and the GEMM form (48)."""
+    import torch
+    cfg = configs.get_config(0, num_envs=N, horizon=1)
+    net = cfg["net"]
+    net["fc_dim"] = [hid]
+    ro = synth.rollout(cfg)
+    params = synth.init_params(net, 5)
+    a0, a1, _ = synth.param_slices(net)["logstd"]
+    params[a0:a1] = np.linspace(-0.5, 0.5, net["act_dim"], dtype=np.float32)
+    lrn = L.Learner(net, N, 1, "fp32")
+    lrn.set_params(params)
+    noise = np.random.default_rng(1).standard_normal((N, net["act_dim"])).astype(np.float32)
+    dev = lambda x: torch.from_numpy(np.ascontiguousarray(x)).cuda()
+    a, lp, v = (x.cpu().numpy() for x in lrn.act(0, dev(ro["obs"][0]), dev(ro["proprio"][0]), dev(noise)))
+    oa, olp, ov = orc.act(net, params, ro["obs"][0], ro["proprio"][0], noise)
+    omu = oa - np.exp(params[a0:a1].astype(np.float64)) * noise
+    assert np.linalg.norm(a - oa) / np.linalg.norm(omu) <= TOL_BF16 and rel_l2(v, ov) <= TOL_BF16 and np.max(np.abs(lp - olp)) <= 1e-3
+    fill_learner(lrn, cfg, ro)
+    mu, v2 = (x.cpu().numpy() for x in lrn.forward())
+    assert rel_l2(mu, omu) <= TOL_BF16 and rel_l2(v2, ov) <= TOL_BF16

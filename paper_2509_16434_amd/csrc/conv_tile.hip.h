@@ -324,7 +324,9 @@ struct ConvWgradShape {
   static constexpr int PIX = CIN * 2, KT = 9 * CIN / 32, KTW = (KT + 3) / 4;
   static constexpr int MAXSEG = 6, MAXSTEP = (CIN == 32) ? 8 : 4, MAXBUF = 6, THREADS = 512;
   static_assert(3 + 4 * (KTW - 1) >= KT, "wave 3's last accumulator pair must be free for the bias sums");
-  static int image_bytes(int W, int TR) { return (2 * TR + 1) * (W + 2) * PIX; }
+  // rounded up to 128 bytes: the dY pixels behind the image are addressed by flipping bit 6 of the whole offset (an
+  // odd number of 64-byte pixel slots, i.e. an odd W at 32 channels, would leave them half a pixel off)
+  __host__ __device__ static int image_bytes(int W, int TR) { return ((2 * TR + 1) * (W + 2) * PIX + 127) & ~127; }
   static int buf_bytes(int W, int TR, int nstep) { return image_bytes(W, TR) + nstep * 16 * 128; }
   static int lds_bytes(int W, int TR, int nstep, int nbuf) { return nbuf * buf_bytes(W, TR, nstep) + 4 * 64 * 4; }
 };
@@ -347,7 +349,7 @@ __global__ __launch_bounds__(512) void k_conv_wgrad_tile(ConvWgradArgs a) {
   const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int W = a.W, WP = W + 2, TR = a.TR, Wo = a.Wo, nstep = NS ? NS : a.nstep, NBUF = a.nbuf;
   const int nrows = 2 * TR + 1, rowbytes = W * PIX, segs = (rowbytes + 1023) >> 10;
-  const int image_bytes = nrows * WP * PIX, dy_bytes = nstep * 16 * 128, buf_bytes = image_bytes + dy_bytes;
+  const int image_bytes = S::image_bytes(W, TR), dy_bytes = nstep * 16 * 128, buf_bytes = image_bytes + dy_bytes;
   const int vb = xcd_block((int)blockIdx.x, (int)gridDim.x);  // this block's number in the dealing of tiles
   const int nq = (a.ntiles > vb) ? (a.ntiles - 1 - vb) / (int)gridDim.x + 1 : 0;
   const int nb0 = blockIdx.y * 64;

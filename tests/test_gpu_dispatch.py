@@ -45,3 +45,33 @@ def test_output_layer_of_act_and_forward(L, hid, N):
     fill_learner(lrn, cfg, ro)
     mu, v2 = (x.cpu().numpy() for x in lrn.forward())
     assert rel_l2(mu, omu) <= TOL_BF16 and rel_l2(v2, ov) <= TOL_BF16
+
+
+@pytest.mark.parametrize("ci,h,w", [(1, 51, 61), (1, 49, 58), (1, 89, 117), (1, 31, 33), (1, 45, 90), (3, 49, 58), (2, 62, 101)])
+def test_gradients_odd_second_layer_width(L, ci, h, w):
+    """Widths whose first-layer output is odd: every tensor's gradient against the oracle's bf16-operand mode."""
+    import torch
+    cfg = configs.get_config(ci, num_envs=12, horizon=4)
+    cfg["net"].update(in_h=h, in_w=w)
+    net, hp = cfg["net"], dict(cfg["hp"], epochs=1, minibatches=1, seed=3)
+    ro = synth.rollout(cfg, conditioned=True)
+    params = synth.init_params(net, 9)
+    lrn = L.Learner(net, 12, 4, cfg["obs_dtype"])
+    lrn.set_params(params)
+    distill = cfg["kind"] == "distill"
+    fill_learner(lrn, cfg, ro, distill=distill)
+    fr = {k: v.reshape((48,) + v.shape[2:]) for k, v in ro.items() if k != "last_value"}
+    if distill:
+        lrn.distill_update(hp)
+        with orc.quant(1):
+            _, qg = orc.distill_loss_grad(net, params, fr["obs"], fr["proprio"], fr["action"])
+    else:
+        lrn.gae(torch.from_numpy(ro["last_value"]).cuda(), hp["gamma"], hp["lam"])
+        adv, ret = (x.cpu().numpy().reshape(-1) for x in lrn.get_adv_ret())
+        lrn.update(hp)
+        with orc.quant(1):
+            _, qg = orc.ppo_loss_grad(net, params, fr["obs"], fr["proprio"], fr["action"], fr["logp_old"], fr["value"], adv, ret,
+                                      clip_eps=hp["clip_eps"], vclip_eps=hp["vclip_eps"], vf_coef=hp["vf_coef"], ent_coef=hp["ent_coef"])
+    g = lrn.get_grads()
+    bad = {n: rel_l2(g[a:b], qg[a:b]) for n, (a, b, _) in synth.param_slices(net).items() if rel_l2(g[a:b], qg[a:b]) > TOL_BF16}
+    assert not bad, bad

@@ -228,13 +228,40 @@ struct MapDgrad {
 template <class MAP, typename OutT, bool BIAS, bool RELU, bool MASK>
 struct Ep {
   typedef OutT out_t;
-  static constexpr bool kBias = BIAS, kRelu = RELU, kMask = MASK;
+  static constexpr bool kBias = BIAS, kRelu = RELU, kMask = MASK, kSplit = false;
   MAP map; OutT* out; const float* bias; const bf16_t* mask; int N;
   const uint32_t* mbits = nullptr;
 };
 // all-ones halves of a bf16 pair for the set bits among bits (2d, 2d + 1) of b
 __device__ __forceinline__ uint32_t keep_halves(uint32_t b, int d) {
   return ((b >> (2 * d)) & 1u ? 0x0000ffffu : 0u) | ((b >> (2 * d + 1)) & 1u ? 0xffff0000u : 0u);
+}
+
+// Four consecutive columns n .. n+3 (n a multiple of 4) of one output row at element offset `off`, from fp32 sums.
+template <class EP>
+__device__ __forceinline__ void gemm_store4(const EP& ep, int64_t off, int n, int N, float4 s) {
+  typedef typename EP::out_t OutT;
+  if constexpr (sizeof(OutT) == 2) {
+    if (EP::kBias) { const float4 b = *reinterpret_cast<const float4*>(ep.bias + n); s.x += b.x; s.y += b.y; s.z += b.z; s.w += b.w; }
+    if (EP::kRelu) { s.x = fmaxf(s.x, 0.f); s.y = fmaxf(s.y, 0.f); s.z = fmaxf(s.z, 0.f); s.w = fmaxf(s.w, 0.f); }
+    uint2 o = make_uint2(pack2bf(s.x, s.y), pack2bf(s.z, s.w));
+    if (EP::kMask) {
+      const uint2 mk = *reinterpret_cast<const uint2*>(ep.mask + off + n);
+      auto keep = [](uint32_t m) -> uint32_t { return (((short)(m & 0xffffu) > 0) ? 0x0000ffffu : 0u) | (((short)(m >> 16) > 0) ? 0xffff0000u : 0u); };
+      o.x &= keep(mk.x); o.y &= keep(mk.y);
+    }
+    *reinterpret_cast<uint2*>(reinterpret_cast<bf16_t*>(ep.out) + off + n) = o;
+  } else {
+    float x[4] = {s.x, s.y, s.z, s.w};
+#pragma unroll
+    for (int q = 0; q < 4; ++q) {
+      if (n + q >= N) break;
+      if (EP::kBias) x[q] += ep.bias[n + q];
+      if (EP::kRelu) x[q] = x[q] > 0.f ? x[q] : 0.f;
+      if (EP::kMask) { if (!((short)ep.mask[off + n + q] > 0)) x[q] = 0.f; }
+      reinterpret_cast<float*>(ep.out)[off + n + q] = x[q];
+    }
+  }
 }
 
 // Epilogue shared by the tile kernels.  acc[i][j][g*4+q] = C[m][n] with m = m0 + (wm*TM+i)*32 +
@@ -315,6 +342,90 @@ __device__ __forceinline__ void gemm_epilogue(f32x16_t (&acc)[TM][TN], const EP&
           }
         }
     }
+  }
+}
+
+// The epilogue of one slice of a split reduction (k_gemm_rs with this type; plain rows, grid = tiles * splits in x):
+// block v (renumbered per XCD) takes slice v / tiles, `W` k-steps of 64 wide, of tile v % tiles - so that the blocks of
+// one XCD work on the same k range of neighbouring tiles and share their operands in its L2 - and leaves its
+// accumulators as they are: [slice][tile][32 x 32 subtile][g][lane] float4, 1 KiB per store instruction.
+// k_gemm_split_reduce sums the slices in order and applies the real epilogue.
+struct EpSplit {
+  typedef float out_t;
+  static constexpr bool kBias = false, kRelu = false, kMask = false, kSplit = true;
+  MapRows map;
+  float* part;
+  int W, tiles, gy;  // k-steps per slice; tiles in all; tiles along N (consecutive tile numbers)
+};
+template <int BM, int BN, class EP>
+__global__ __launch_bounds__(256) void k_gemm_split_reduce(const float* __restrict__ part, int splits, int tiles, int gy, int M, int N, EP ep) {
+  constexpr int CT = BN / 32, SUBS = (BM / 32) * CT;
+  const int lane = threadIdx.x & 63, w = blockIdx.x * 4 + (threadIdx.x >> 6), tile = w / SUBS, sub = w - tile * SUBS;
+  const int m = (tile / gy) * BM + (sub / CT) * 32 + (lane & 31), n0 = (tile % gy) * BN + (sub % CT) * 32;
+  if (tile >= tiles || m - (lane & 31) >= M || n0 >= N) return;
+  const float4* p = reinterpret_cast<const float4*>(part) + ((int64_t)tile * SUBS + sub) * 256 + lane;
+  const int64_t stride = (int64_t)tiles * SUBS * 256;
+  float4 s[4];
+#pragma unroll
+  for (int g = 0; g < 4; ++g) s[g] = p[g * 64];
+#pragma unroll 4
+  for (int z = 1; z < splits; ++z) {
+    p += stride;
+#pragma unroll
+    for (int g = 0; g < 4; ++g) { const float4 x = p[g * 64]; s[g].x += x.x; s[g].y += x.y; s[g].z += x.z; s[g].w += x.w; }
+  }
+  if (m >= M) return;
+  const int64_t off = ep.map.row_offset(m, ep.map.cls(0));
+#pragma unroll
+  for (int g = 0; g < 4; ++g) {
+    const int n = n0 + g * 8 + (lane >> 5) * 4;
+    if (n < N) gemm_store4(ep, off, n, N, s[g]);
+  }
+}
+
+// ---------------------------------------------------------------- C = A * B^T for few output tiles
+// Small batches leave most of the chip idle under 64 x 64 tiles, and what a tile then costs is a serial chain: one LDS
+// stage and barrier per 64 of K.  Here a block of NW waves takes a 32 x 32 tile, each wave a slice of K, operands
+// straight from global memory into MFMA registers eight k-steps at a time (one memory latency per 128 of a wave's
+// slice; the operands are small enough to sit in L2); the slices meet in LDS and are summed in wave order.
+// Plain rows only; rows beyond M and columns beyond N repeat row / column 0 and are not stored.
+template <int NW, class EP>
+__global__ __launch_bounds__(NW * 64) void k_gemm_small(const bf16_t* __restrict__ A, int64_t lda, int M, const bf16_t* __restrict__ Bm, int64_t ldb, int N,
+                                                        int K, EP ep) {
+  constexpr int U = 8, RP = 36;  // k-steps in flight; pitch of a row of partial sums
+  __shared__ __attribute__((aligned(16))) float red[NW][32 * RP];
+  const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6), l32 = lane & 31, h = lane >> 5;
+  const int m0 = blockIdx.x * 32, n0 = blockIdx.y * 32;
+  const int per = ((K + 15) / 16 + NW - 1) / NW * 16, kb = wave * per, ke = min(K, kb + per);
+  const bf16_t* const ar = A + (int64_t)(m0 + l32 < M ? m0 + l32 : 0) * lda + h * 8;
+  const bf16_t* const br = Bm + (int64_t)(n0 + l32 < N ? n0 + l32 : 0) * ldb + h * 8;
+  f32x16_t acc[2];
+#pragma unroll
+  for (int e = 0; e < 16; ++e) { acc[0][e] = 0.f; acc[1][e] = 0.f; }
+  const bf16x8_t zero = __builtin_bit_cast(bf16x8_t, make_uint4(0u, 0u, 0u, 0u));
+  for (int k0 = kb; k0 < ke; k0 += 16 * U) {
+    bf16x8_t a[U], b[U];
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+      const int k = k0 + u * 16;
+      const bool ok = k + h * 8 < ke;  // K is a multiple of 8: a lane's eight k exist together
+      a[u] = ok ? *reinterpret_cast<const bf16x8_t*>(ar + k) : zero;
+      b[u] = ok ? *reinterpret_cast<const bf16x8_t*>(br + k) : zero;
+    }
+#pragma unroll
+    for (int u = 0; u < U; ++u) acc[u & 1] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(b[u], a[u], acc[u & 1], 0, 0, 0);
+  }
+#pragma unroll
+  for (int g = 0; g < 4; ++g)
+    *reinterpret_cast<float4*>(&red[wave][l32 * RP + g * 8 + h * 4]) =
+        make_float4(acc[0][g * 4] + acc[1][g * 4], acc[0][g * 4 + 1] + acc[1][g * 4 + 1], acc[0][g * 4 + 2] + acc[1][g * 4 + 2], acc[0][g * 4 + 3] + acc[1][g * 4 + 3]);
+  __syncthreads();
+  for (int i = tid; i < 256; i += NW * 64) {
+    const int r = i >> 3, c = (i & 7) * 4, m = m0 + r, n = n0 + c;
+    float4 s = *reinterpret_cast<const float4*>(&red[0][r * RP + c]);
+#pragma unroll
+    for (int w = 1; w < NW; ++w) { const float4 x = *reinterpret_cast<const float4*>(&red[w][r * RP + c]); s.x += x.x; s.y += x.y; s.z += x.z; s.w += x.w; }
+    if (m < M && n < N) gemm_store4(ep, ep.map.row_offset(m, ep.map.cls(0)), n, N, s);
   }
 }
 

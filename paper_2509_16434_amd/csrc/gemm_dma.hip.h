@@ -64,9 +64,16 @@ __global__ __launch_bounds__((WGM * WGN + 4) * 64) void k_gemm_rs(AL al, const b
 
   const typename AL::Cls acls = al.cls(blockIdx.z);
   const auto mcls = ep.map.cls(blockIdx.z);
-  const int m0 = blockIdx.x * BM, n0 = blockIdx.y * BN;
+  const int K = acls.K;
+  int m0 = blockIdx.x * BM, n0 = blockIdx.y * BN, kbeg = 0, nk = (K + BK - 1) / BK;
+  int slice = 0, tile = 0;
+  if constexpr (EP::kSplit) {
+    const int v = xcd_block((int)blockIdx.x, (int)gridDim.x);
+    slice = v / ep.tiles; tile = v - slice * ep.tiles;
+    m0 = (tile / ep.gy) * BM; n0 = (tile % ep.gy) * BN;
+    kbeg = slice * ep.W * BK; nk = min(ep.W, nk - slice * ep.W);
+  }
   if (m0 >= acls.M) return;
-  const int K = acls.K, nk = (K + BK - 1) / BK;
   const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   char* const ring_b = reinterpret_cast<char*>(ring);
   const bool compute = wave < NCW;
@@ -85,14 +92,14 @@ __global__ __launch_bounds__((WGM * WGN + 4) * 64) void k_gemm_rs(AL al, const b
     for (int j = 0; j < AI; ++j) arow[j] = al.row(m0 + (lw * AI + j) * 8 + dr, acls);
     typename AL::KCur acur[2];
 #pragma unroll
-    for (int j = 0; j < 2; ++j) acur[j] = al.kcur((dpos ^ ((j * 4 + (dr >> 1)) & 7)) * 8, acls);
+    for (int j = 0; j < 2; ++j) acur[j] = al.kcur(kbeg + (dpos ^ ((j * 4 + (dr >> 1)) & 7)) * 8, acls);
     const bf16_t* brow[BI];
     int b_k[BI];
 #pragma unroll
     for (int j = 0; j < BI; ++j) {
       const int r = (lw * BI + j) * 8 + dr, n = n0 + r;
       brow[j] = (n < N) ? Bm + (int64_t)n * ldb : nullptr;
-      b_k[j] = (dpos ^ ((r >> 1) & 7)) * 8;
+      b_k[j] = kbeg + (dpos ^ ((r >> 1) & 7)) * 8;
     }
     // stages are issued in order of k, so the column cursors simply step along
     auto issue = [&](int stage, int k0) __attribute__((always_inline)) {
@@ -168,6 +175,19 @@ __global__ __launch_bounds__((WGM * WGN + 4) * 64) void k_gemm_rs(AL al, const b
       for (int e = 0; e < 16; ++e) acc[0][0][e] += acc2[e];
     }
   }
+  if constexpr (EP::kSplit) {
+    if (!compute) return;
+    float4* P = reinterpret_cast<float4*>(ep.part) + ((int64_t)slice * ep.tiles + tile) * (BM * BN / 4);
+#pragma unroll
+    for (int i = 0; i < TM; ++i)
+#pragma unroll
+      for (int j = 0; j < TN; ++j)
+#pragma unroll
+        for (int g = 0; g < 4; ++g)
+          P[((wm * TM + i) * (BN / 32) + wn * TN + j) * 256 + g * 64 + lane] =
+              make_float4(acc[i][j][g * 4], acc[i][j][g * 4 + 1], acc[i][j][g * 4 + 2], acc[i][j][g * 4 + 3]);
+    return;
+  }
   __syncthreads();  // every wave is done with the ring, which becomes the staging tile
-  gemm_epilogue<BM, BN, TM, TN, THREADS>(acc, ep, mcls, m0, n0, N, wm, wn, ring, rowoff, rowcols, compute);
+  if constexpr (!EP::kSplit) gemm_epilogue<BM, BN, TM, TN, THREADS>(acc, ep, mcls, m0, n0, N, wm, wn, ring, rowoff, rowcols, compute);
 }

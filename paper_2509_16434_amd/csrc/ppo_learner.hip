@@ -408,6 +408,60 @@ inline int class_len(int n, int par) { return (n - par + 1) / 2; }
 // ---------------------------------------------------------------- launch helpers
 inline int ilog2(int x) { int l = 0; while ((1 << l) < x) ++l; return l; }
 
+// How a product with plain rows (C [M][N] = A [M][K] B^T) is cut up.  Every form is a chain of k-steps of 64 per tile, of
+// measured length (us, operands in L2 / the last-level cache, chip full): 0.34 for a 64 x 64 tile, 0.60 for 128 x 128, 1.0
+// for 256 x 128, behind 3.5 us of launch, ring fill and epilogue; a reduction over `splits` slices of K costs another 3 us
+// and its fp32 partials at 6 TB/s.  The plan is the form with the smallest sum, blocks counted in rounds of 256 CUs: e.g.
+// 4096 x 512 x 10304 leaves two rounds of 64 x 64 tiles (107 us) for 64 tiles of 256 x 128 in four slices (53 us);
+// 16384 x 512 x 10304 stays one round of undivided 256 x 128 tiles (157 us).
+// With few tiles and short rows (<= 512 tiles of 32 x 32 at K <= 512, <= 128 at K <= 2048) the LDS ring's own
+// latency is the larger part, and k_gemm_small wins (64 x 64 x 1056: 7.9 -> 4.7 us; 1250 x 128 x 256: 5.1 -> 3.4 us;
+// beyond these lines its operand traffic, 32 x 32 per tile, loses: 4096 x 256 x 512: 7.0 against 9.6 us).
+struct GemmPlan { int bm, bn, splits, W; };  // bm = 32: k_gemm_small; splits > 1: W k-steps per slice
+GemmPlan plan_gemm(int M, int N, int K, int64_t partial_elems) {
+  const int64_t t32 = (int64_t)cdiv(M, 32) * cdiv(N, 32);
+  if ((t32 <= 512 && K <= 512) || (t32 <= 128 && K <= 2048)) return {32, 32, 1, 0};
+  const int nk = cdiv(K, 64);
+  GemmPlan best = {64, 64, 1, nk};
+  double tbest = 1e30;
+  auto consider = [&](int bm, int bn, double step) {
+    const int64_t tiles = (int64_t)cdiv(M, bm) * cdiv(N, bn);
+    for (int s = 1; s <= 16 && (s == 1 || nk / s >= 3); ++s) {
+      const int W = cdiv(nk, s);
+      if (s > 1 && (cdiv(nk, W) != s || s * tiles * bm * bn > partial_elems)) continue;
+      double t = 3.5 + (double)cdiv(tiles * s, 256) * W * step;
+      if (s > 1) t += 3.0 + 8e-6 * s * (double)tiles * bm * bn / 6.0;
+      if (t < tbest - 1e-9) { tbest = t; best = {bm, bn, s, W}; }
+    }
+  };
+  if (N <= 32) consider(128, 32, 0.45);
+  else if (N <= 64) { consider(64, 64, 0.34); consider(128, 64, 0.48); }
+  else { consider(64, 64, 0.34); consider(128, 128, 0.60); consider(256, 128, 1.0); }
+  return best;
+}
+
+// The LDS-ring kernel on tiles of BM x BN, undivided or in plan.splits slices of K.
+template <int BM, int BN, int WM, int WN, class EP>
+int launch_gemm_ring(Ctx* c, const ARows& al, int M, const bf16_t* Bm, int64_t ldb, int N, int K, const EP& ep, const GemmPlan& plan) {
+  constexpr int ncw = WM * WN, nst = (BM + BN) * 128 * 8 <= 128 * 1024 ? 8 : ((BM + BN) * 128 * 4 <= 128 * 1024 ? 4 : 3), lds = nst * (BM + BN) * 128;
+  static uint64_t attr_devs[2] = {0, 0};  // bit d: set on device d
+  const bool split = plan.splits > 1;
+  auto kfn = k_gemm_rs<BM, BN, WM, WN, nst, ARows, EP>;
+  auto kfs = k_gemm_rs<BM, BN, WM, WN, nst, ARows, EpSplit>;
+  const void* k = split ? (const void*)kfs : (const void*)kfn;
+  if (!((attr_devs[split] >> c->dev) & 1)) { HIPCHK(c, hipFuncSetAttribute(k, hipFuncAttributeMaxDynamicSharedMemorySize, lds)); attr_devs[split] |= 1ull << c->dev; }
+  if (!split) {
+    hipLaunchKernelGGL(kfn, dim3(cdiv(M, BM), cdiv(N, BN)), dim3((ncw + 4) * 64), lds, c->stream, al, Bm, ldb, N, ep, c->zpage);
+    return PPO_OK;
+  }
+  EpSplit es;
+  es.map = ep.map; es.part = reinterpret_cast<float*>((reinterpret_cast<uintptr_t>(c->partial) + 15) & ~(uintptr_t)15); es.W = plan.W; es.gy = cdiv(N, BN); es.tiles = cdiv(M, BM) * es.gy;
+  hipLaunchKernelGGL(kfs, dim3(es.tiles * plan.splits), dim3((ncw + 4) * 64), lds, c->stream, al, Bm, ldb, N, es, c->zpage);
+  hipLaunchKernelGGL((k_gemm_split_reduce<BM, BN, EP>), dim3(cdiv((int64_t)es.tiles * (BM / 32) * (BN / 32), 4)), dim3(256), 0, c->stream, es.part, plan.splits, es.tiles,
+                     es.gy, M, N, ep);
+  return PPO_OK;
+}
+
 template <class AL, class EP>
 int launch_gemm(Ctx* c, const AL& al_, int M, const bf16_t* Bm, int64_t ldb, int N, int K, const EP& ep_, const std::string& name, double abytes,
                 int zdim = 1, double flops = -1.0) {
@@ -417,6 +471,24 @@ int launch_gemm(Ctx* c, const AL& al_, int M, const bf16_t* Bm, int64_t ldb, int
   const char* what = name.c_str();
   ProfScope ps(c, name, flops >= 0.0 ? flops : 2.0 * M * (double)N * K, abytes);
   dim3 blk(256);
+  if constexpr (std::is_same<AL, ARows>::value) {
+    const GemmPlan plan = plan_gemm(M, N, K, c->partial_elems > 4 ? c->partial_elems - 4 : 0);
+    if (al.plain && (plan.bm == 32 || K >= 1024)) {
+      int rc = PPO_OK;
+      if (plan.bm == 32) {
+        const dim3 grid(cdiv(M, 32), cdiv(N, 32));
+        if (K <= 512) hipLaunchKernelGGL((k_gemm_small<4, EP>), grid, dim3(256), 0, c->stream, al.a.base, al.a.stride_b, M, Bm, ldb, N, K, ep);
+        else hipLaunchKernelGGL((k_gemm_small<8, EP>), grid, dim3(512), 0, c->stream, al.a.base, al.a.stride_b, M, Bm, ldb, N, K, ep);
+      } else if (plan.bn == 32) rc = launch_gemm_ring<128, 32, 4, 1>(c, al, M, Bm, ldb, N, K, ep, plan);
+      else if (plan.bm == 64) rc = launch_gemm_ring<64, 64, 2, 2>(c, al, M, Bm, ldb, N, K, ep, plan);
+      else if (plan.bn == 64) rc = launch_gemm_ring<128, 64, 2, 2>(c, al, M, Bm, ldb, N, K, ep, plan);
+      else if (plan.bm == 128) rc = launch_gemm_ring<128, 128, 2, 2>(c, al, M, Bm, ldb, N, K, ep, plan);
+      else rc = launch_gemm_ring<256, 128, 4, 2>(c, al, M, Bm, ldb, N, K, ep, plan);
+      if (rc) return rc;
+      LAUNCHCHK(c, what);
+      return PPO_OK;
+    }
+  }
   // Very deep reductions stream their operands through an LDS ring of up to eight stages, filled by
   // four loader waves while four or eight other waves compute (k_gemm_rs); medium ones take 64-wide
   // steps through registers, where the smaller LDS footprint lets more blocks share a CU and hide
@@ -2300,6 +2372,8 @@ int ppo_diag_gemm(int32_t M, int32_t N, int32_t K, const float* h_a, const float
     DALLOC(c, da, (int64_t)M * K); DALLOC(c, db, (int64_t)N * K); DALLOC(c, dc, (int64_t)M * N);
     DALLOC(c, ba, (int64_t)M * K); DALLOC(c, bb, (int64_t)N * K);
     DALLOC(c, c->zpage, 32768);
+    c->partial_elems = (int64_t)8 * (M + 256) * (N + 128) + 4;  // room for the split reductions
+    DALLOC(c, c->partial, c->partial_elems);
     HIPCHK(c, hipMemset(c->zpage, 0, 65536));
     HIPCHK(c, hipMemcpy(da, h_a, sizeof(float) * (size_t)M * K, hipMemcpyHostToDevice));
     HIPCHK(c, hipMemcpy(db, h_b, sizeof(float) * (size_t)N * K, hipMemcpyHostToDevice));

@@ -47,6 +47,18 @@ def test_output_layer_of_act_and_forward(L, hid, N):
     assert rel_l2(mu, omu) <= TOL_BF16 and rel_l2(v2, ov) <= TOL_BF16
 
 
+@pytest.mark.parametrize("M,N,K", [(1, 3, 8), (33, 40, 136), (512, 1024, 512), (65, 32, 2048), (64, 64, 1056),   # 32 x 32 tiles
+                                   (1250, 256, 4480), (129, 72, 4168), (4100, 32, 2056), (700, 40, 3000),       # slices of K
+                                   (4096, 512, 10304), (8400, 130, 4104), (256, 4096, 2048)])
+def test_gemm_plans(L, M, N, K):
+    """Products with plain rows in each form plan_gemm can choose: ragged rows, columns and last slices."""
+    rng = np.random.default_rng(M + N + K)
+    a = synth.narrow_bf16(rng.standard_normal((M, K), dtype=np.float32))
+    b = synth.narrow_bf16(rng.standard_normal((N, K), dtype=np.float32))
+    want = a @ b.T
+    assert np.abs(L.diag_gemm(a, b) - want).max() <= 1e-4 * np.abs(want).max()
+
+
 @pytest.mark.parametrize("ci,h,w", [(1, 51, 61), (1, 49, 58), (1, 89, 117), (1, 31, 33), (1, 45, 90), (3, 49, 58), (2, 62, 101)])
 def test_gradients_odd_second_layer_width(L, ci, h, w):
     """Widths whose first-layer output is odd: every tensor's gradient against the oracle's bf16-operand mode."""

@@ -26,76 +26,58 @@ __device__ __forceinline__ void write_scalars(int64_t i, const ScalarWrite& w) {
 }
 
 // ---------------------------------------------------------------- buffer append
-// One step's images [N][V][C][HW] (fp32 or bf16) -> bf16 channel-last [N][V][HW][C] at the
-// step's slab.  Each thread converts 8 consecutive pixels of one (n, v) image; the blocks behind
-// the last image block write the slab's scalars (one launch per rollout step).
-template <typename InT>
-__global__ void k_write_obs(const InT* __restrict__ src, bf16_t* __restrict__ dst, int64_t n_img, int C, int HW, int obs_blocks, ScalarWrite sw) {
-  const int groups = (HW + 7) / 8;
-  if ((int)blockIdx.x >= obs_blocks) {  // the blocks behind the images write the slab's scalars
+// One step's images [N][V][C][H][W] (fp32 or bf16) -> bf16 channel-last [N][V][H][WP][C] at the step's slab, WP = W
+// rounded up to a multiple of 8 with zeros behind the row.  The pad makes every stored row start at a multiple of 16
+// bytes, which is what the kernels that copy rows into LDS need (a 76-wide crop otherwise took the first layer and its
+// gradient to kernels of 2-byte loads, 115 us of a 450 us optimiser step), and stands for the convolution's own
+// zero padding on the right.  Each thread converts 8 consecutive pixels of one row; with W a multiple of 8 rows
+// follow each other and an image is walked as one row of H*W pixels.  The blocks behind the last image block write
+// the slab's scalars (one launch per rollout step).
+template <typename InT, int C>
+__global__ __launch_bounds__(256) void k_write_obs(const InT* __restrict__ src, bf16_t* __restrict__ dst, int64_t n_row, int W, FastDiv groups, FastDiv dvh, int obs_blocks, ScalarWrite sw) {
+  if ((int)blockIdx.x >= obs_blocks) {
     write_scalars((int64_t)((int)blockIdx.x - obs_blocks) * blockDim.x + threadIdx.x, sw);
     return;
   }
-  int64_t gid = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (gid >= n_img * groups) return;
-  int64_t img = gid / groups;
-  int p0 = (int)(gid - img * groups) * 8;
-  const InT* s = src + img * (int64_t)C * HW;
-  bf16_t* d = dst + img * (int64_t)C * HW;
-  auto cvt = [](InT x) -> bf16_t {
-    if constexpr (sizeof(InT) == 4) return f2bf((float)x); else return (bf16_t)x;
-  };
-  if (C == 1 && p0 + 8 <= HW) {
-    bf16_t o[8];
-    if constexpr (sizeof(InT) == 4) {
-      const float4* s4 = reinterpret_cast<const float4*>(s + p0);
-      float4 a = s4[0], b = s4[1];
-      o[0] = f2bf(a.x); o[1] = f2bf(a.y); o[2] = f2bf(a.z); o[3] = f2bf(a.w);
-      o[4] = f2bf(b.x); o[5] = f2bf(b.y); o[6] = f2bf(b.z); o[7] = f2bf(b.w);
-      *reinterpret_cast<uint4*>(d + p0) = *reinterpret_cast<uint4*>(o);
+  const uint32_t gid = blockIdx.x * 256u + threadIdx.x;  // (the host keeps the slab's group count below 2^31)
+  const uint32_t row = groups.div(gid);
+  if ((int64_t)row >= n_row) return;
+  const int x0 = (int)(gid - row * groups.d) * 8, live = W - x0;  // pixels of this group that exist (8 or more: all)
+  const uint32_t img = dvh.div(row);
+  const InT* s = src + ((int64_t)img * (C - 1) * dvh.d + row) * W + x0;  // plane 0; plane c is H*W further on
+  const int64_t plane = (int64_t)dvh.d * W;
+  bf16_t in[C][8];
+#pragma unroll
+  for (int c = 0; c < C; ++c) {
+    InT v[8];
+    if (live >= 8) {
+      __builtin_memcpy(v, __builtin_assume_aligned(s + c * plane, sizeof(InT)), sizeof v);  // 16-byte loads at any element offset
     } else {
-      *reinterpret_cast<uint4*>(d + p0) = *reinterpret_cast<const uint4*>(s + p0);
+#pragma unroll
+      for (int j = 0; j < 8; ++j) v[j] = j < live ? s[c * plane + j] : (InT)0;
     }
-    return;
-  }
-  if (C == 3 && p0 + 8 <= HW && (HW & 7) == 0) {
-    // planar RGB -> interleaved: three 8-pixel runs in (16 or 32 bytes each), 24 bf16 = three 16-byte stores out
-    bf16_t in[3][8];
 #pragma unroll
-    for (int c = 0; c < 3; ++c) {
-      if constexpr (sizeof(InT) == 4) {
-        const float4* s4 = reinterpret_cast<const float4*>(s + (int64_t)c * HW + p0);
-        const float4 a = s4[0], b = s4[1];
-        in[c][0] = f2bf(a.x); in[c][1] = f2bf(a.y); in[c][2] = f2bf(a.z); in[c][3] = f2bf(a.w);
-        in[c][4] = f2bf(b.x); in[c][5] = f2bf(b.y); in[c][6] = f2bf(b.z); in[c][7] = f2bf(b.w);
-      } else {
-        *reinterpret_cast<uint4*>(in[c]) = *reinterpret_cast<const uint4*>(s + (int64_t)c * HW + p0);
-      }
+    for (int j = 0; j < 8; ++j) {
+      if constexpr (sizeof(InT) == 4) in[c][j] = f2bf((float)v[j]); else in[c][j] = (bf16_t)v[j];
     }
-    bf16_t o[24];
-#pragma unroll
-    for (int j = 0; j < 8; ++j)
-#pragma unroll
-      for (int c = 0; c < 3; ++c) o[j * 3 + c] = in[c][j];
-    uint4* d4 = reinterpret_cast<uint4*>(d + (int64_t)p0 * 3);
-#pragma unroll
-    for (int q = 0; q < 3; ++q) d4[q] = reinterpret_cast<const uint4*>(o)[q];
-    return;
   }
-  for (int j = 0; j < 8; ++j) {
-    int p = p0 + j;
-    if (p >= HW) break;
-    for (int c = 0; c < C; ++c) d[(int64_t)p * C + c] = cvt(s[(int64_t)c * HW + p]);
-  }
+  bf16_t o[8 * C];
+#pragma unroll
+  for (int j = 0; j < 8; ++j)
+#pragma unroll
+    for (int c = 0; c < C; ++c) o[j * C + c] = in[c][j];
+  uint4* d4 = reinterpret_cast<uint4*>(dst + (int64_t)gid * 8 * C);
+#pragma unroll
+  for (int q = 0; q < C; ++q) d4[q] = reinterpret_cast<const uint4*>(o)[q];
 }
 
-// Inverse layout change of k_write_obs (no conversion): channel-last -> [img][C][HW].
-__global__ void k_read_obs(const bf16_t* __restrict__ src, bf16_t* __restrict__ dst, int64_t n_img, int C, int HW) {
-  int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  int64_t per = (int64_t)C * HW;
+// Inverse layout change of k_write_obs (no conversion): [img][H][WP][C] -> [img][C][H][W].
+__global__ void k_read_obs(const bf16_t* __restrict__ src, bf16_t* __restrict__ dst, int64_t n_img, int C, int H, int W, int WP) {
+  const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x, per = (int64_t)C * H * W;
   if (i >= n_img * per) return;
-  int64_t img = i / per; int r = (int)(i - img * per), c = r / HW, p = r - c * HW;
-  dst[i] = src[img * per + (int64_t)p * C + c];
+  const int64_t img = i / per;
+  const int r = (int)(i - img * per), c = r / (H * W), p = r - c * H * W, y = p / W, x = p - y * W;
+  dst[i] = src[(img * H * WP + (int64_t)y * WP + x) * C + c];
 }
 
 

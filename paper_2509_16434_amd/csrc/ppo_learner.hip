@@ -76,7 +76,7 @@ struct Ctx {
   int cC[PPO_MAX_LAYERS + 1], cH[PPO_MAX_LAYERS + 1], cW[PPO_MAX_LAYERS + 1];
   int fin[PPO_MAX_LAYERS], fout[PPO_MAX_LAYERS];
   int flat = 0, feat_ld = 0, hid = 0;
-  int64_t img_elems = 0;  // per view
+  int64_t img_elems = 0;  // stored elements per view (padded rows)
   // internal parameter layout (fp32 master, bf16 shadow share the offsets)
   int64_t convW[PPO_MAX_LAYERS], convB[PPO_MAX_LAYERS], fcW[PPO_MAX_LAYERS], fcB[PPO_MAX_LAYERS];
   int64_t headW = 0, headB = 0, logstd = -1, total = 0;
@@ -304,13 +304,15 @@ void build_geometry(Ctx* c) {
   c->ln = d.layer_norm != 0; c->E = d.embed_dim; c->nl = d.lstm_layers; c->H = d.lstm_layers > 0 ? d.lstm_units : 0;
   c->NH = c->A_main + (d.has_value_head ? 1 : 0);
   c->nconv = d.n_conv; c->nfc = d.n_fc;
-  c->cC[0] = d.in_c; c->cH[0] = d.in_h; c->cW[0] = d.in_w;
+  // stored image rows are padded with zeros to a multiple of 8 pixels (k_write_obs); every kernel takes the padded
+  // width for the image's own, the first layer's output width comes from the real one
+  c->cC[0] = d.in_c; c->cH[0] = d.in_h; c->cW[0] = (d.in_w + 7) / 8 * 8;
   for (int l = 0; l < c->nconv; ++l) {
     c->cC[l + 1] = d.conv_ch[l];
     c->cH[l + 1] = (c->cH[l] + 2 - 3) / 2 + 1;
-    c->cW[l + 1] = (c->cW[l] + 2 - 3) / 2 + 1;
+    c->cW[l + 1] = ((l == 0 ? d.in_w : c->cW[l]) + 2 - 3) / 2 + 1;
   }
-  c->img_elems = (int64_t)d.in_c * d.in_h * d.in_w;
+  c->img_elems = (int64_t)d.in_c * d.in_h * c->cW[0];
   c->flat = c->cC[c->nconv] * c->cH[c->nconv] * c->cW[c->nconv];
   c->enc = c->E > 0 ? c->E : c->flat;
   c->feat_cols = c->V * c->enc + c->P;
@@ -2121,9 +2123,9 @@ int ppo_buffer_read_obs(ppo_ctx* c, int32_t t, void* d_obs_bf16) {
   if (t < 0 || t >= c->T) return fail(c, PPO_EINVAL, "t = %d outside [0, %d)", t, c->T);
   if (!d_obs_bf16) return fail(c, PPO_EINVAL, "d_obs_bf16 is NULL");
   if (!c->written[(size_t)t]) return fail(c, PPO_ESTATE, "step %d has not been written", t);
-  const int64_t nimg = (int64_t)c->N * c->V, n = nimg * c->img_elems;
-  hipLaunchKernelGGL(k_read_obs, dim3(cdiv(n, 256)), dim3(256), 0, c->stream, c->obs + (int64_t)t * n, (bf16_t*)d_obs_bf16, nimg, c->d.in_c,
-                     c->d.in_h * c->d.in_w);
+  const int64_t nimg = (int64_t)c->N * c->V, n = nimg * c->d.in_c * c->d.in_h * c->d.in_w;
+  hipLaunchKernelGGL(k_read_obs, dim3(cdiv(n, 256)), dim3(256), 0, c->stream, c->obs + (int64_t)t * nimg * c->img_elems, (bf16_t*)d_obs_bf16, nimg, c->d.in_c,
+                     c->d.in_h, c->d.in_w, c->cW[0]);
   LAUNCHCHK(c, "k_read_obs");
   return PPO_OK;
 }
@@ -2137,8 +2139,10 @@ static int all_written(ppo_ctx* c) {
 // Environments [n0, n0 + cnt) of the step; the caller's arrays hold cnt rows.
 static int write_slab(ppo_ctx* c, int32_t t, int32_t n0, int32_t cnt, const void* d_obs, const float* d_proprio, const float* d_action,
                       const float* d_logp, const float* d_value, const float* d_reward, const uint8_t* d_done) {
-  const int N = cnt, V = c->V, HW = c->d.in_h * c->d.in_w, C = c->d.in_c;
-  const int64_t nimg = (int64_t)N * V, groups = (HW + 7) / 8;
+  const int N = cnt, V = c->V, C = c->d.in_c;
+  const int64_t nimg = (int64_t)N * V;
+  const bool flat = c->cW[0] == c->d.in_w;  // no pad: an image is one row
+  const int W = flat ? c->d.in_h * c->d.in_w : c->d.in_w, rows = flat ? 1 : c->d.in_h, groups = (W + 7) / 8;
   const int64_t off = (int64_t)t * c->N + n0;
   bf16_t* dst = c->obs + off * V * c->img_elems;
   ProfScope ps(c, "buffer_write", 0.0, (double)nimg * c->img_elems * (c->d.obs_dtype == 0 ? 6.0 : 4.0) + (double)N * (6.0 * c->P + 8.0 * c->A + 26.0));
@@ -2147,11 +2151,19 @@ static int write_slab(ppo_ctx* c, int32_t t, int32_t n0, int32_t cnt, const void
   sw.N = N; sw.P = c->P; sw.A = c->A; sw.proprio = d_proprio; sw.action = d_action; sw.logp = d_logp; sw.value = d_value; sw.reward = d_reward; sw.done = d_done;
   sw.o_proprio = c->proprio + off * c->P; sw.o_action = c->action + off * c->A; sw.o_logp = c->logp + off; sw.o_value = c->value + off;
   sw.o_reward = c->reward + off; sw.o_done = c->done + off;
-  const int obs_blocks = cdiv(nimg * groups, 256), sc_blocks = cdiv((int64_t)N * mx, 256);
-  if (c->d.obs_dtype == 0)
-    hipLaunchKernelGGL((k_write_obs<float>), dim3(obs_blocks + sc_blocks), dim3(256), 0, c->stream, (const float*)d_obs, dst, nimg, C, HW, obs_blocks, sw);
-  else
-    hipLaunchKernelGGL((k_write_obs<bf16_t>), dim3(obs_blocks + sc_blocks), dim3(256), 0, c->stream, (const bf16_t*)d_obs, dst, nimg, C, HW, obs_blocks, sw);
+  // 32-bit group numbers: a slab of more images than that goes out in several launches, the last with the scalars
+  const int64_t most = std::max<int64_t>(1, ((1LL << 31) - 256) / ((int64_t)rows * groups));
+  for (int64_t i0 = 0; i0 < nimg; i0 += most) {
+    const int64_t ni = std::min(most, nimg - i0), n_row = ni * rows;
+    const int obs_blocks = cdiv(n_row * groups, 256), sc_blocks = i0 + ni == nimg ? cdiv((int64_t)N * mx, 256) : 0;
+    const int64_t so = i0 * C * c->d.in_h * c->d.in_w;
+    bf16_t* const d0 = dst + i0 * c->img_elems;
+    const FastDiv dg = make_fastdiv(groups), dh = make_fastdiv(rows);
+#define LAUNCH_WRITE(T_, C_) hipLaunchKernelGGL((k_write_obs<T_, C_>), dim3(obs_blocks + sc_blocks), dim3(256), 0, c->stream, (const T_*)d_obs + so, d0, n_row, W, dg, dh, obs_blocks, sw)
+    if (c->d.obs_dtype == 0) { if (C == 1) LAUNCH_WRITE(float, 1); else LAUNCH_WRITE(float, 3); }
+    else { if (C == 1) LAUNCH_WRITE(bf16_t, 1); else LAUNCH_WRITE(bf16_t, 3); }
+#undef LAUNCH_WRITE
+  }
   LAUNCHCHK(c, "k_write_obs");
   return PPO_OK;
 }

@@ -87,3 +87,21 @@ def test_gradients_odd_second_layer_width(L, ci, h, w):
     g = lrn.get_grads()
     bad = {n: rel_l2(g[a:b], qg[a:b]) for n, (a, b, _) in synth.param_slices(net).items() if rel_l2(g[a:b], qg[a:b]) > TOL_BF16}
     assert not bad, bad
+
+
+@pytest.mark.parametrize("ci,dtype", [(0, "fp32"), (0, "bf16"), (3, "fp32"), (3, "bf16")])
+@pytest.mark.parametrize("h,w", [(5, 7), (6, 8), (4, 9), (3, 15), (9, 33)])
+def test_stored_images_bit_exact_at_any_width(L, ci, dtype, h, w):
+    """Stored rows are padded to multiples of 8 pixels: whole groups, a ragged last group, rows at odd addresses."""
+    import torch
+    cfg = configs.get_config(ci, num_envs=13, horizon=2)
+    cfg["net"].update(in_h=h, in_w=w)
+    net = cfg["net"]
+    lrn = L.Learner(net, 13, 2, dtype)
+    gen = torch.Generator(device="cuda")
+    gen.manual_seed(w)
+    for t in (1, 0):
+        obs = torch.randn(13, net["n_views"], net["in_c"], h, w, generator=gen, device="cuda").to(torch.float32 if dtype == "fp32" else torch.bfloat16)
+        z = torch.zeros(13, device="cuda")
+        lrn.buffer_write(t, obs, torch.zeros(13, net["proprio_dim"], device="cuda"), torch.zeros(13, net["act_dim"], device="cuda"), z, z, z, z.to(torch.uint8))
+        assert torch.equal(lrn.buffer_read_obs(t), obs.to(torch.bfloat16))

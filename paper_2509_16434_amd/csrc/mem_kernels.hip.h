@@ -986,8 +986,9 @@ __global__ __launch_bounds__(256) void k_param_map(ParamMap pm, const float* __r
 
 // ---------------------------------------------------------------- weight re-packing for the backward GEMMs
 // All per-update re-packs in one launch: job j covers blocks [first[j], first[j+1]).
-// kind 0, transpose with zero padding (a = rows, b = cols, ld = leading dimension of dst):
-//   dst[c][r] = src[r][c] for r < rows, zero for rows <= r < ld;
+// kind 0, transpose with zero padding (a = rows, b = cols, ld = leading dimension of dst; cols and ld multiples of 8):
+//   dst[c][r] = src[r][c] for r < rows, zero for rows <= r < ld; a block takes a 64 x 64 tile through LDS, 16 bytes per
+//   access on both sides (element by element the strided side cost a line per 2 bytes: 16 M weights 109 -> 20 us);
 // kind 1, per-tap transpose for the quad-organised transposed convolution (a = Cout, b = Cin):
 //   dst[(tap*Cin + ci)*Cout + co] = W[co][tap*Cin + ci];
 // kind 2, parity-class packing of the implicit-GEMM transposed convolution (a = Cout, b = Cin, ld = row parity py):
@@ -1010,10 +1011,28 @@ __global__ __launch_bounds__(256) void k_repack_all(RepackJobs jobs, GnormFinali
   const bf16_t* __restrict__ src = jobs.src[j];
   bf16_t* __restrict__ dst = jobs.dst[j];
   if (jobs.kind[j] == 0) {
-    const int rows = jobs.a[j], cols = jobs.b[j], ld_dst = jobs.ld[j];
-    if (i >= (int64_t)cols * ld_dst) return;
-    const int c = (int)(i / ld_dst), r = (int)(i - (int64_t)c * ld_dst);
-    dst[i] = r < rows ? src[(int64_t)r * cols + c] : (bf16_t)0;
+    constexpr int P = 66;  // pitch: eight rows apart, eight columns side by side fall into different banks
+    __shared__ bf16_t tile[64 * P];
+    const int rows = jobs.a[j], cols = jobs.b[j], ld_dst = jobs.ld[j], tc = (cols + 63) >> 6, t = (int)blockIdx.x - jobs.first[j];
+    const int r0 = (t / tc) * 64, c0 = (t % tc) * 64;
+#pragma unroll
+    for (int h = 0; h < 2; ++h) {
+      const int ch = threadIdx.x + h * 256, r = ch >> 3, c = (ch & 7) * 8;
+      uint4 v = make_uint4(0u, 0u, 0u, 0u);
+      if (r0 + r < rows && c0 + c < cols) v = *reinterpret_cast<const uint4*>(src + (int64_t)(r0 + r) * cols + c0 + c);
+      uint32_t* d = reinterpret_cast<uint32_t*>(tile + r * P + c);
+      d[0] = v.x; d[1] = v.y; d[2] = v.z; d[3] = v.w;
+    }
+    __syncthreads();
+#pragma unroll
+    for (int h = 0; h < 2; ++h) {
+      const int ch = threadIdx.x + h * 256, c = ch >> 3, r = (ch & 7) * 8;
+      if (c0 + c >= cols || r0 + r >= ld_dst) continue;
+      uint32_t o[4];
+#pragma unroll
+      for (int q = 0; q < 4; ++q) o[q] = (uint32_t)tile[(r + 2 * q) * P + c] | ((uint32_t)tile[(r + 2 * q + 1) * P + c] << 16);
+      *reinterpret_cast<uint4*>(dst + (int64_t)(c0 + c) * ld_dst + r0 + r) = make_uint4(o[0], o[1], o[2], o[3]);
+    }
   } else if (jobs.kind[j] == 2) {
     const int Cout = jobs.a[j], Cin = jobs.b[j], py = jobs.ld[j], Kc = (1 + py) * 2 * Cout;
     if (i >= (int64_t)2 * Cin * Kc) return;

@@ -38,7 +38,7 @@ struct Conv0Shape {
   static int lds_bytes(int W, int TR, int Cout) { return NBUF * image_bytes(W, TR) + 16 + NCW * 32 * (Cout + 8) * 2; }
 };
 
-template <int C0>
+template <int C0, bool RELU = true>  // RELU = false: a layer normalisation follows
 __global__ __launch_bounds__(512) void k_conv0_fwd_tile(Conv0Args a) {
   typedef Conv0Shape<C0> S;
   constexpr int K = S::K, KS = S::KS, NBUF = S::NBUF, NCW = S::NCW;
@@ -178,15 +178,15 @@ __global__ __launch_bounds__(512) void k_conv0_fwd_tile(Conv0Args a) {
             // Cout is a multiple of 8: the eight columns of (jn, g) exist together, for both lane halves
             if (jn * 32 + g * 8 < Cout) {
               uint2 o;
-              o.x = relu_pack2bf(acc[g * 4], acc[g * 4 + 1]);
-              o.y = relu_pack2bf(acc[g * 4 + 2], acc[g * 4 + 3]);
+              o.x = RELU ? relu_pack2bf(acc[g * 4], acc[g * 4 + 1]) : pack2bf(acc[g * 4], acc[g * 4 + 1]);
+              o.y = RELU ? relu_pack2bf(acc[g * 4 + 2], acc[g * 4 + 3]) : pack2bf(acc[g * 4 + 2], acc[g * 4 + 3]);
               *reinterpret_cast<uint2*>(&stage[l32 * SP + jn * 32 + g * 8 + h * 4]) = o;
-              pw[jn] |= nonzero4(o.x, o.y, negw) << (g * 8);
+              if (RELU) pw[jn] |= nonzero4(o.x, o.y, negw) << (g * 8);
             }
           }
         }
       }
-      if (a.bits) {
+      if (RELU && a.bits) {
         const int wpp = (Cout + 31) >> 5;
         uint32_t* const bw0 = a.bits + ((int64_t)img * a.Ho * Wo + (int64_t)band * TR * Wo) * wpp;  // the band's words
 #pragma unroll

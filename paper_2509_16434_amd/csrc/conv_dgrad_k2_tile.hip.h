@@ -40,6 +40,7 @@ __device__ __forceinline__ uint4 add_bf16x8(const uint4& x, const uint4& y) {
   return make_uint4(add2(x.x, y.x), add2(x.y, y.y), add2(x.z, y.z), add2(x.w, y.w));
 }
 
+template <bool MASK>  // false: as in k_conv_dgrad_tile
 __global__ __launch_bounds__(512) void k_conv_dgrad_k2_tile(ConvDgradArgs a) {
   typedef ConvDgradK2Shape S;
   constexpr int CI = S::CI, CO = S::CO, PB = S::PB, CC = 4, NBUF = S::NBUF, MT = S::MT;  // CC: 16-deep steps over a wave's 64 gradient channels
@@ -109,6 +110,7 @@ __global__ __launch_bounds__(512) void k_conv_dgrad_k2_tile(ConvDgradArgs a) {
       band_off[SET] = (int64_t)b * a.x_stride_b + (int64_t)vw * a.x_stride_v + (int64_t)(2 * band * TQ) * W * CI;
       nvalid[SET] = rows * W * CI / 8;
       // mask words of the band: pixel (band-linear) c / (CI/8), word (c % (CI/8)) / 4
+      if constexpr (!MASK) return;
       const uint32_t* wb = a.xbits + ((int64_t)img * a.H + 2 * band * TQ) * W * (CI / 32);
 #pragma unroll
       for (int i = 0; i < S::MAXCH; ++i) {
@@ -128,8 +130,10 @@ __global__ __launch_bounds__(512) void k_conv_dgrad_k2_tile(ConvDgradArgs a) {
         if (c < nchunk && c < nvalid[SET]) {
           const uint32_t L = (uint32_t)c * 16u, ph = L ^ tile_swz_bits<CI>(L);
           uint4 v = add_bf16x8(*reinterpret_cast<const uint4*>(st + ph), *reinterpret_cast<const uint4*>(st + stage_bytes + ph));
-          const uint32_t b8 = mk[SET][i] >> ((c & 3) * 8);  // this chunk's eight bits
-          v.x &= keep_pair(b8, 0); v.y &= keep_pair(b8, 1); v.z &= keep_pair(b8, 2); v.w &= keep_pair(b8, 3);
+          if constexpr (MASK) {
+            const uint32_t b8 = mk[SET][i] >> ((c & 3) * 8);  // this chunk's eight bits
+            v.x &= keep_pair(b8, 0); v.y &= keep_pair(b8, 1); v.z &= keep_pair(b8, 2); v.w &= keep_pair(b8, 3);
+          }
           uint32_t off = L;
           asm volatile("" : "+v"(off));
           store_stream16(reinterpret_cast<bf16_t*>(reinterpret_cast<char*>(a.dx + band_off[SET]) + off), v);

@@ -76,9 +76,10 @@ __device__ __forceinline__ uint32_t keep_pair(uint32_t b, int d) {
   return __builtin_amdgcn_perm(hi, lo, 0x07060100u);  // bytes 0, 1 of lo; bytes 2, 3 of hi
 }
 
-template <int CI, int C0>
+// MASK = false: the gradient leaves unmasked (a layer normalisation's backward applies the ReLU behind it itself)
+template <int CI, int C0, bool MASK = true>
 __global__ __launch_bounds__(512) void k_conv_dgrad_tile(ConvDgradArgs a) {
-  static_assert(C0 == 0 || CI == 32, "the fused form is written for 32 input channels");
+  static_assert(C0 == 0 || (CI == 32 && MASK), "the fused form is written for 32 input channels");
   typedef ConvDgradShape<CI> S;
   constexpr int CO = S::CO, CC = CO / 16, WGN = S::WGN, NBUF = S::NBUF;
   extern __shared__ __attribute__((aligned(16))) char lds[];
@@ -194,6 +195,7 @@ __global__ __launch_bounds__(512) void k_conv_dgrad_tile(ConvDgradArgs a) {
       band_off[SET] = (int64_t)b * a.x_stride_b + (int64_t)vw * a.x_stride_v + (int64_t)(2 * band * TQ) * W * CI;
       nvalid[SET] = rows * W * CI / 8;
       // mask words of the band: pixel (band-linear) c / (CI/8), word (c % (CI/8)) / 4
+      if constexpr (!MASK) return;
       const uint32_t* wb = a.xbits + ((int64_t)img * a.H + 2 * band * TQ) * W * (CI / 32);
 #pragma unroll
       for (int i = 0; i < S::MAXCH; ++i) {
@@ -256,8 +258,10 @@ __global__ __launch_bounds__(512) void k_conv_dgrad_tile(ConvDgradArgs a) {
         if (chunk_mine(i) && (C0 > 0 || c < nvalid[SET])) {
           const uint32_t L = (uint32_t)c * 16u, ph = L ^ tile_swz_bits<CI>(L);
           uint4 v = *reinterpret_cast<const uint4*>(st + ph);
-          const uint32_t b8 = mk[SET][i] >> ((c & 3) * 8);  // this chunk's eight bits
-          v.x &= keep_pair(b8, 0); v.y &= keep_pair(b8, 1); v.z &= keep_pair(b8, 2); v.w &= keep_pair(b8, 3);
+          if constexpr (MASK) {
+            const uint32_t b8 = mk[SET][i] >> ((c & 3) * 8);  // this chunk's eight bits
+            v.x &= keep_pair(b8, 0); v.y &= keep_pair(b8, 1); v.z &= keep_pair(b8, 2); v.w &= keep_pair(b8, 3);
+          }
           if constexpr (C0 > 0) *reinterpret_cast<uint4*>(st + ph) = v;  // chunks outside the image become zeros
           else {
             uint32_t off = L;

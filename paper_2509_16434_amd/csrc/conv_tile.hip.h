@@ -107,8 +107,9 @@ __device__ __forceinline__ uint32_t fwd_swz_bits(uint32_t off, uint32_t rowkey) 
   return (((off >> 8) + rowkey) & 7u) << 4;
 }
 
-// AUX: cache policy of the band loads (LOAD_NT where a band shares few rows with its neighbours)
-template <int CIN, int AUX, int WIDE = 0>
+// AUX: cache policy of the band loads (LOAD_NT where a band shares few rows with its neighbours); RELU = false: the sums
+// pass as they are (a layer normalisation follows)
+template <int CIN, int AUX, int WIDE = 0, bool RELU = true>
 __global__ __launch_bounds__(512) void k_conv_fwd_tile(ConvTileArgs a) {
   typedef ConvTileShape<CIN, WIDE> S;
   constexpr int NW = S::NW, WGN = S::WGN, TN = NW / 32, TM = S::TM, PIX = S::PIX, SP = S::SP;
@@ -265,13 +266,13 @@ __global__ __launch_bounds__(512) void k_conv_fwd_tile(ConvTileArgs a) {
         for (int g = 0; g < 4; ++g) {
           const int cl = j * 32 + g * 8 + h * 4;
           uint2 o;
-          o.x = relu_pack2bf(acc[i][j][g * 4], acc[i][j][g * 4 + 1]);
-          o.y = relu_pack2bf(acc[i][j][g * 4 + 2], acc[i][j][g * 4 + 3]);
+          o.x = RELU ? relu_pack2bf(acc[i][j][g * 4], acc[i][j][g * 4 + 1]) : pack2bf(acc[i][j][g * 4], acc[i][j][g * 4 + 1]);
+          o.y = RELU ? relu_pack2bf(acc[i][j][g * 4 + 2], acc[i][j][g * 4 + 3]) : pack2bf(acc[i][j][g * 4 + 2], acc[i][j][g * 4 + 3]);
           *reinterpret_cast<uint2*>(stage + (l32 * SP + cl) * 2) = o;
-          pw[j] |= nonzero4(o.x, o.y, negw) << (g * 8);
+          if (RELU) pw[j] |= nonzero4(o.x, o.y, negw) << (g * 8);
         }
       }
-      if (a.bits) {
+      if (RELU && a.bits) {
         // the other half of the columns sits in lane ^ 32; lanes 0..31 write the pixel's words
         const int wpp = (a.Cout + 31) >> 5, p = p0 + l32;
 #pragma unroll

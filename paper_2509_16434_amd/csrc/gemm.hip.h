@@ -225,10 +225,11 @@ struct MapDgrad {
 // output's own offset (the stored activation whose gradient is being formed).  With `mbits` set the
 // mask comes from the sign-bit words the forward kernel left instead (one bit per element, a
 // sixteenth of the bytes): bit (off + n) of the bit string; the output must then be dense.
-template <class MAP, typename OutT, bool BIAS, bool RELU, bool MASK>
+// STREAM: a large result that is read once by the next kernel (non-temporal stores).
+template <class MAP, typename OutT, bool BIAS, bool RELU, bool MASK, bool STREAM = MASK>
 struct Ep {
   typedef OutT out_t;
-  static constexpr bool kBias = BIAS, kRelu = RELU, kMask = MASK, kSplit = false;
+  static constexpr bool kBias = BIAS, kRelu = RELU, kMask = MASK, kStream = STREAM, kSplit = false;
   MAP map; OutT* out; const float* bias; const bf16_t* mask; int N;
   const uint32_t* mbits = nullptr;
 };
@@ -316,7 +317,7 @@ __device__ __forceinline__ void gemm_epilogue(f32x16_t (&acc)[TM][TN], const EP&
         };
         v.x &= keep(mk.x); v.y &= keep(mk.y); v.z &= keep(mk.z); v.w &= keep(mk.w);
       }
-      if (EP::kMask) store_stream16(out + off + n, v);  // an activation gradient: large, read once by the layer below
+      if (EP::kStream) store_stream16(out + off + n, v);  // an activation gradient: large, read once by the layer below
       else *reinterpret_cast<uint4*>(out + off + n) = v;
     }
   } else {
@@ -352,7 +353,7 @@ __device__ __forceinline__ void gemm_epilogue(f32x16_t (&acc)[TM][TN], const EP&
 // k_gemm_split_reduce sums the slices in order and applies the real epilogue.
 struct EpSplit {
   typedef float out_t;
-  static constexpr bool kBias = false, kRelu = false, kMask = false, kSplit = true;
+  static constexpr bool kBias = false, kRelu = false, kMask = false, kStream = false, kSplit = true;
   MapRows map;
   float* part;
   int W, tiles, gy;  // k-steps per slice; tiles in all; tiles along N (consecutive tile numbers)

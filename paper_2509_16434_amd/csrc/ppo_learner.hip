@@ -26,6 +26,7 @@
 #include "conv_dgrad_wgrad0_tile.hip.h"
 #include "conv_dgrad_k2_tile.hip.h"
 #include "conv0_tile.hip.h"
+#include "conv0_wgrad_tile.hip.h"
 #include "head_loss.hip.h"
 #include "wgrad_rs.hip.h"
 #include "peaks.hip.h"
@@ -733,7 +734,7 @@ ImgAddr conv_out_addr(Ctx* c, int l, const bf16_t* contiguous, const bf16_t* str
 
 // Forward convolution through the LDS-image kernel; returns 1 when the layer's shape is not one
 // it covers (the caller then takes the implicit-GEMM path).
-template <int CIN, int WIDE>
+template <int CIN, int WIDE, bool RELU>
 int launch_conv_fwd_tile_t(Ctx* c, ConvTileArgs a, const std::string& name, double flops, double abytes) {
   typedef ConvTileShape<CIN, WIDE> S;
   const int segs = cdiv(a.W * S::PIX, 1024), ni = cdiv(2 * a.TR + 1, 4) * segs;  // loads per loader wave per band
@@ -746,7 +747,7 @@ int launch_conv_fwd_tile_t(Ctx* c, ConvTileArgs a, const std::string& name, doub
   int gx = 256 / gy; if (gx > a.ntiles) gx = a.ntiles; if (gx < 1) gx = 1;
   // bands of four or more output rows share at most an eighth of their input rows with a neighbour: read once, non-temporal
   const bool nt = a.TR >= 4;
-  auto kfn = nt ? k_conv_fwd_tile<CIN, LOAD_NT, WIDE> : k_conv_fwd_tile<CIN, 0, WIDE>;
+  auto kfn = nt ? k_conv_fwd_tile<CIN, LOAD_NT, WIDE, RELU> : k_conv_fwd_tile<CIN, 0, WIDE, RELU>;
   static uint64_t attr_devs[2] = {0, 0};  // bit d: set on device d
   if (!((attr_devs[nt] >> c->dev) & 1)) { HIPCHK(c, hipFuncSetAttribute((const void*)kfn, hipFuncAttributeMaxDynamicSharedMemorySize, 160 * 1024)); attr_devs[nt] |= 1ull << c->dev; }
   ProfScope ps(c, name, flops, abytes);
@@ -755,7 +756,7 @@ int launch_conv_fwd_tile_t(Ctx* c, ConvTileArgs a, const std::string& name, doub
   return PPO_OK;
 }
 int launch_conv_fwd_tile(Ctx* c, const AConvFwd& al, const ImgAddr& o, int Cout, const bf16_t* w, const float* bias, int nimg,
-                         const std::string& name, double abytes, uint32_t* bits) {
+                         const std::string& name, double abytes, uint32_t* bits, bool relu = true) {
   if ((al.Cin != 32 && al.Cin != 64) || Cout % 8 || nimg < 1 || al.in.idx) return 1;
   const int BM = al.Cin == 32 ? 128 : 64;
   if (al.Wo > BM) return 1;
@@ -767,9 +768,13 @@ int launch_conv_fwd_tile(Ctx* c, const AConvFwd& al, const ImgAddr& o, int Cout,
   a.NB = cdiv(al.Ho, trmax); a.TR = cdiv(al.Ho, a.NB);  // balanced bands
   a.ntiles = nimg * a.NB; a.nbuf = 3;
   const double flops = 2.0 * (double)al.M * Cout * al.K;
-  if (al.Cin == 32) return launch_conv_fwd_tile_t<32, 0>(c, a, name, flops, abytes);
   // more than 64 output channels: the 64 x 128 form reads the input once
-  return Cout > 64 ? launch_conv_fwd_tile_t<64, 1>(c, a, name, flops, abytes) : launch_conv_fwd_tile_t<64, 0>(c, a, name, flops, abytes);
+#define LAUNCH_FWD(R_)                                                                       \
+  (al.Cin == 32 ? launch_conv_fwd_tile_t<32, 0, R_>(c, a, name, flops, abytes)                \
+   : Cout > 64  ? launch_conv_fwd_tile_t<64, 1, R_>(c, a, name, flops, abytes)                \
+                : launch_conv_fwd_tile_t<64, 0, R_>(c, a, name, flops, abytes))
+  return relu ? LAUNCH_FWD(true) : LAUNCH_FWD(false);
+#undef LAUNCH_FWD
 }
 
 // Weight (and bias) gradient of conv layer with 32 or 64 input channels through the LDS-image
@@ -828,7 +833,7 @@ int launch_conv_wgrad_tile(Ctx* c, const ImgAddr& dy, const AConvFwd& xl, int Co
 // not covered (the caller then takes the implicit-GEMM path).  With C0 > 0 the kernel also forms
 // the first layer's weight-gradient partials (a.img0, a.H0, a.W0 set by the caller) and *grid_out
 // receives the number of partials.
-template <int CI, int C0>
+template <int CI, int C0, bool MASK = true>
 int launch_conv_dgrad_tile_t(Ctx* c, ConvDgradArgs a, int nimg, const std::string& name, double flops, double abytes, int* grid_out) {
   typedef ConvDgradShape<CI> S;
   if (a.Wo > S::BQ) return 1;
@@ -861,7 +866,7 @@ int launch_conv_dgrad_tile_t(Ctx* c, ConvDgradArgs a, int nimg, const std::strin
     a.partial0 = c->partial;
     *grid_out = gx;
   }
-  auto kfn = k_conv_dgrad_tile<CI, C0>;
+  auto kfn = k_conv_dgrad_tile<CI, C0, MASK>;
   static uint64_t attr_devs = 0;  /* bit d: set on device d */
   if (!((attr_devs >> c->dev) & 1)) { HIPCHK(c, hipFuncSetAttribute((const void*)kfn, hipFuncAttributeMaxDynamicSharedMemorySize, 160 * 1024)); attr_devs |= 1ull << c->dev; }
   ProfScope ps(c, name, flops, abytes);
@@ -878,6 +883,7 @@ ConvDgradArgs conv_dgrad_args(Ctx* c, const ImgAddr& dy, const ImgAddr& xa, cons
   return a;
 }
 // The form for 128 gradient channels and 64 result channels (the contraction split over two pairs of compute waves).
+template <bool MASK>
 int launch_conv_dgrad_k2_tile(Ctx* c, ConvDgradArgs a, int nimg, const std::string& name, double flops, double abytes) {
   typedef ConvDgradK2Shape S;
   if (a.Wo > S::BQ) return 1;
@@ -890,7 +896,7 @@ int launch_conv_dgrad_k2_tile(Ctx* c, ConvDgradArgs a, int nimg, const std::stri
   const int segs = cdiv(a.Wo * S::PB, 1024);
   if (segs > S::MAXSEG || (a.TQ + 1) * segs > 63) return 1;
   const int gx = a.ntiles < 256 ? a.ntiles : 256;
-  auto kfn = k_conv_dgrad_k2_tile;
+  auto kfn = k_conv_dgrad_k2_tile<MASK>;
   static uint64_t attr_devs = 0;  /* bit d: set on device d */
   if (!((attr_devs >> c->dev) & 1)) { HIPCHK(c, hipFuncSetAttribute((const void*)kfn, hipFuncAttributeMaxDynamicSharedMemorySize, 160 * 1024)); attr_devs |= 1ull << c->dev; }
   ProfScope ps(c, name, flops, abytes);
@@ -898,16 +904,15 @@ int launch_conv_dgrad_k2_tile(Ctx* c, ConvDgradArgs a, int nimg, const std::stri
   LAUNCHCHK(c, "k_conv_dgrad_k2_tile");
   return PPO_OK;
 }
+// (xbits NULL: the gradient is left unmasked)
 int launch_conv_dgrad_tile(Ctx* c, const ImgAddr& dy, const ImgAddr& xa, const uint32_t* xbits, bf16_t* dx, const bf16_t* wt, int Co, int Ci, int H, int W, int Ho, int Wo,
                            int nimg, const std::string& name, double flops, double abytes) {
-  if (Co == 128 && Ci == 64 && !dy.idx && nimg >= 1 && xbits) {
-    ConvDgradArgs a2 = conv_dgrad_args(c, dy, xa, xbits, dx, wt, H, W, Ho, Wo);
-    return launch_conv_dgrad_k2_tile(c, a2, nimg, name, flops, abytes);
-  }
-  if (Co != 64 || (Ci != 32 && Ci != 64) || dy.idx || nimg < 1 || !xbits) return 1;
-  ConvDgradArgs a = conv_dgrad_args(c, dy, xa, xbits, dx, wt, H, W, Ho, Wo);
-  return Ci == 32 ? launch_conv_dgrad_tile_t<32, 0>(c, a, nimg, name, flops, abytes, nullptr)
-                  : launch_conv_dgrad_tile_t<64, 0>(c, a, nimg, name, flops, abytes, nullptr);
+  if (dy.idx || nimg < 1) return 1;
+  const ConvDgradArgs a = conv_dgrad_args(c, dy, xa, xbits, dx, wt, H, W, Ho, Wo);
+  if (Co == 128 && Ci == 64) return xbits ? launch_conv_dgrad_k2_tile<true>(c, a, nimg, name, flops, abytes) : launch_conv_dgrad_k2_tile<false>(c, a, nimg, name, flops, abytes);
+  if (Co != 64 || (Ci != 32 && Ci != 64)) return 1;
+  if (xbits) return Ci == 32 ? launch_conv_dgrad_tile_t<32, 0>(c, a, nimg, name, flops, abytes, nullptr) : launch_conv_dgrad_tile_t<64, 0>(c, a, nimg, name, flops, abytes, nullptr);
+  return Ci == 32 ? launch_conv_dgrad_tile_t<32, 0, false>(c, a, nimg, name, flops, abytes, nullptr) : launch_conv_dgrad_tile_t<64, 0, false>(c, a, nimg, name, flops, abytes, nullptr);
 }
 // Register-fused form of the same pair of layers (conv_dgrad_wgrad0_tile.hip.h); returns 1 when the shape is not covered.
 template <int C0, int NCW, int WC = 0>
@@ -962,7 +967,7 @@ int launch_conv_dgrad_wgrad0_tile(Ctx* c, const ImgAddr& dy, const ImgAddr& xa, 
 }
 
 // First convolution forward through the LDS-ring kernel; returns 1 when the shape is not covered.
-template <int C0>
+template <int C0, bool RELU = true>
 int launch_conv0_fwd_tile_t(Ctx* c, Conv0Args a, int nimg) {
   typedef Conv0Shape<C0> S;
   const int rb = a.W * C0 * 2;
@@ -976,11 +981,68 @@ int launch_conv0_fwd_tile_t(Ctx* c, Conv0Args a, int nimg) {
   int gx = a.ntiles < 512 ? a.ntiles : 512;
   a.tile_blocks = gx;
   if (a.gather_blocks > 0) a.gather_blocks = (int)std::min<int64_t>(32, cdiv((int64_t)a.pB * a.P, 512));
-  auto kfn = k_conv0_fwd_tile<C0>;
+  auto kfn = k_conv0_fwd_tile<C0, RELU>;
   static uint64_t attr_devs = 0;  /* bit d: set on device d */
   if (!((attr_devs >> c->dev) & 1)) { HIPCHK(c, hipFuncSetAttribute((const void*)kfn, hipFuncAttributeMaxDynamicSharedMemorySize, 64 * 1024)); attr_devs |= 1ull << c->dev; }
   hipLaunchKernelGGL(kfn, dim3(gx + a.gather_blocks), dim3(S::THREADS), S::lds_bytes(a.W, a.TR, a.Cout), c->stream, a);
   LAUNCHCHK(c, "k_conv0_fwd_tile");
+  return PPO_OK;
+}
+
+// First convolution's weight and bias gradient from a stored output gradient through the LDS-ring kernel; returns 1 when
+// the shape is not covered.  *grid_out receives the number of partials.
+template <int C0, int CO>
+int launch_conv0_wgrad_tile_t(Ctx* c, Conv0WgradArgs a, int nimg, int* grid_out) {
+  typedef Conv0WgradShape<C0, CO> S;
+  const int rb = a.W * C0 * 2;
+  if (rb % 16) return 1;
+  // two blocks of four compute waves per CU; as many rows per band as three ring slots of half the LDS hold
+  int TR = 0;
+  for (int tr = a.Ho; tr >= 1; --tr)
+    if (S::lds_bytes(a.W, a.Wo, tr) <= 79 * 1024 && cdiv(cdiv((2 * tr + 1) * rb, 1024), 4) + cdiv(cdiv(S::dy_bytes(a.Wo, tr), 1024), 4) <= 63) { TR = tr; break; }
+  if (TR == 0) return 1;
+  a.NB = cdiv(a.Ho, TR); a.TR = cdiv(a.Ho, a.NB); a.ntiles = nimg * a.NB;
+  a.dv_rb = make_fastdiv(rb);
+  int gx = a.ntiles < 512 ? a.ntiles : 512;
+  const int64_t npair = (int64_t)CO * (S::K0 + 1);
+  { const int erc = ensure_partial(c, gx * npair, 0); if (erc) return erc; }
+  if (gx * npair > c->partial_elems) gx = (int)(c->partial_elems / npair);
+  if (gx < 1) return 1;
+  a.partial = c->partial; *grid_out = gx;
+  auto kfn = k_conv0_wgrad_tile<C0, CO>;
+  static uint64_t attr_devs = 0;  /* bit d: set on device d */
+  if (!((attr_devs >> c->dev) & 1)) { HIPCHK(c, hipFuncSetAttribute((const void*)kfn, hipFuncAttributeMaxDynamicSharedMemorySize, 80 * 1024)); attr_devs |= 1ull << c->dev; }
+  hipLaunchKernelGGL(kfn, dim3(gx), dim3(S::THREADS), S::lds_bytes(a.W, a.Wo, a.TR), c->stream, a);
+  LAUNCHCHK(c, "k_conv0_wgrad_tile");
+  return PPO_OK;
+}
+// The same with any kernel: leaves the partials at the cursor and queues their reduction.
+int conv0_wgrad(Ctx* c, ImgAddr in, const bf16_t* dy, int nimg, bool acc) {
+  in.prepare();
+  const int Co = c->cC[1], Ho = c->cH[1], Wo = c->cW[1], C0 = c->cC[0], K = 9 * C0, npair = Co * (K + 1);
+  const int64_t M = (int64_t)nimg * Ho * Wo;
+  ProfScope ps(c, "conv_wgrad.0", 2.0 * (double)M * Co * (K + 1), 2.0 * ((double)M * Co + (double)nimg * c->img_elems));
+  Conv0WgradArgs wa;
+  wa.in = in; wa.dy = dy; wa.zpage = c->zpage; wa.partial = nullptr; wa.H = c->cH[0]; wa.W = c->cW[0]; wa.Ho = Ho; wa.Wo = Wo; wa.TR = wa.NB = wa.ntiles = 0;
+  int nblk = 0;
+#define WGRAD0_CO(C0_) (Co == 8 ? launch_conv0_wgrad_tile_t<C0_, 8>(c, wa, nimg, &nblk) : Co == 16 ? launch_conv0_wgrad_tile_t<C0_, 16>(c, wa, nimg, &nblk) \
+                        : Co == 32 ? launch_conv0_wgrad_tile_t<C0_, 32>(c, wa, nimg, &nblk) : Co == 64 ? launch_conv0_wgrad_tile_t<C0_, 64>(c, wa, nimg, &nblk) : 1)
+  const int rc = C0 == 1 ? WGRAD0_CO(1) : WGRAD0_CO(3);
+#undef WGRAD0_CO
+  if (rc != PPO_OK && rc != 1) return rc;
+  if (rc == 1) {
+    { const int erc = ensure_partial(c, (int64_t)2048 * npair, 0); if (erc) return erc; }
+    int64_t max_blocks = c->partial_elems / npair;
+    if (max_blocks > 2048) max_blocks = 2048;
+    if (max_blocks < 1) return fail(c, PPO_ENOMEM, "weight-gradient workspace too small for the first convolution");
+    int64_t ppb = (M + max_blocks - 1) / max_blocks;
+    ppb = (ppb + 63) / 64 * 64;
+    nblk = cdiv(M, ppb);
+    if (C0 == 1) hipLaunchKernelGGL((k_conv1_wgrad<1>), dim3(nblk), dim3(256), 0, c->stream, in, nimg, c->cH[0], c->cW[0], Ho, Wo, Co, dy, (int)ppb, c->partial);
+    else hipLaunchKernelGGL((k_conv1_wgrad<3>), dim3(nblk), dim3(256), 0, c->stream, in, nimg, c->cH[0], c->cW[0], Ho, Wo, Co, dy, (int)ppb, c->partial);
+    LAUNCHCHK(c, "k_conv1_wgrad");
+  }
+  defer_reduce(c, 2, nblk, npair, Co, K, c->g + c->convW[0], c->g + c->convB[0], acc, false, 0, nullptr);
   return PPO_OK;
 }
 
@@ -1227,7 +1289,7 @@ int encoder_backward_ff(Ctx* c, const int32_t* idx, int n, bool acc, int cur) {
     }
     double ab = 2.0 * ((double)nimg * Ho * Wo * Co + pix * Ci + 9.0 * Ci * Co) + (c->abits_ok[l - 1] && (Co == 64 || ep.mbits) ? pix * Ci / 8.0 : 2.0 * pix * Ci);
     const double dflops = 2.0 * (double)nimg * Ho * Wo * 9.0 * Ci * Co;
-    rc = launch_conv_dgrad_tile(c, dy, xa, c->abits_ok[l - 1] ? c->abits[l - 1] : nullptr, c->gbuf[cur ^ 1], c->wtap[l], Co, Ci, H, W, Ho, Wo, nimg, "conv_dgrad." + std::to_string(l), dflops, ab);
+    rc = !c->abits_ok[l - 1] ? 1 : launch_conv_dgrad_tile(c, dy, xa, c->abits[l - 1], c->gbuf[cur ^ 1], c->wtap[l], Co, Ci, H, W, Ho, Wo, nimg, "conv_dgrad." + std::to_string(l), dflops, ab);
     if (rc == PPO_OK + 1) {
       rc = ensure_packed_dgrad_weights(c, l);
       if (rc) return rc;
@@ -1238,22 +1300,8 @@ int encoder_backward_ff(Ctx* c, const int32_t* idx, int n, bool acc, int cur) {
   }
   {  // first convolution: weight and bias gradient only
     ImgAddr in; in.base = c->obs; in.idx = idx; in.stride_b = c->img_elems * V; in.stride_v = c->img_elems; in.V = V;
-    const int Co = c->cC[1], Ho = c->cH[1], Wo = c->cW[1], K = 9 * c->cC[0];
-    int64_t M = (int64_t)nimg * Ho * Wo;
-    const int npair = Co * (K + 1);
-    { const int erc = ensure_partial(c, (int64_t)2048 * npair, 0); if (erc) return erc; }
-    int64_t max_blocks = c->partial_elems / npair;
-    if (max_blocks > 2048) max_blocks = 2048;
-    int64_t ppb = (M + max_blocks - 1) / max_blocks;
-    ppb = (ppb + 63) / 64 * 64;
-    int nblk = cdiv(M, ppb);
-    ProfScope ps(c, "conv_wgrad.0", 2.0 * (double)M * Co * (K + 1), 2.0 * ((double)M * Co + (double)nimg * c->img_elems));
-    if (c->cC[0] == 1)
-      hipLaunchKernelGGL((k_conv1_wgrad<1>), dim3(nblk), dim3(256), 0, c->stream, in, nimg, c->cH[0], c->cW[0], Ho, Wo, Co, c->gbuf[cur], (int)ppb, c->partial);
-    else
-      hipLaunchKernelGGL((k_conv1_wgrad<3>), dim3(nblk), dim3(256), 0, c->stream, in, nimg, c->cH[0], c->cW[0], Ho, Wo, Co, c->gbuf[cur], (int)ppb, c->partial);
-    LAUNCHCHK(c, "k_conv1_wgrad");
-    defer_reduce(c, 2, nblk, npair, Co, K, c->g + c->convW[0], c->g + c->convB[0], acc, false, 0, nullptr);
+    const int rc = conv0_wgrad(c, in, c->gbuf[cur], nimg, acc);
+    if (rc) return rc;
   }
   return flush_reduces(c);
 }
@@ -1287,8 +1335,10 @@ static ImgAddr act_addr(Ctx* c, int l) {
 
 int encoder_forward_generic(Ctx* c, const int32_t* idx, int n, int64_t first) {
   const int V = c->V, nimg = n * V;
+  bool proprio_done = false;
   if (idx) first = 0;
   for (int l = 0; l < c->nconv; ++l) {
+    bool have_bits = false;
     const int Co = c->cC[l + 1], Ho = c->cH[l + 1], Wo = c->cW[l + 1], Ci = c->cC[l];
     const int64_t e = (int64_t)Co * Ho * Wo, M = (int64_t)nimg * Ho * Wo;
     const ImgAddr oa = act_addr(c, l);
@@ -1299,23 +1349,37 @@ int encoder_forward_generic(Ctx* c, const int32_t* idx, int n, int64_t first) {
       in.prepare();
       if (conv_to.stride_v != e || conv_to.stride_b != e * V) return fail(c, PPO_ESHAPE, "the first convolution needs a contiguous output (n_conv >= 2 or an embedding)");
       ProfScope ps(c, name, 2.0 * (double)M * Co * 9 * Ci, 2.0 * ((double)nimg * c->img_elems + (double)M * Co));
-      constexpr int TPW = 4;
-      const int grid = cdiv(M, 32 * 4 * TPW);
       bf16_t* out = const_cast<bf16_t*>(conv_to.base);
       const bf16_t* w = c->shadow + c->convW[0];
       const float* b = c->p + c->convB[0];
+      Conv0Args ca;
+      ca.in = in; ca.out = out; ca.w = w; ca.bias = b; ca.zpage = c->zpage; ca.bits = !c->ln && c->nconv > 1 ? c->abits[0] : nullptr;
+      ca.H = c->cH[0]; ca.W = c->cW[0]; ca.Ho = Ho; ca.Wo = Wo; ca.Cout = Co; ca.TR = 0; ca.NB = 0; ca.ntiles = 0;
+      ca.tile_blocks = 0; ca.gather_blocks = 1; ca.pB = n; ca.P = c->P; ca.pcol0 = V * c->enc; ca.proprio = c->proprio + first * c->P; ca.feat = c->feat; ca.feat_ld = c->feat_ld;
+      const int trc = c->ln ? (Ci == 1 ? launch_conv0_fwd_tile_t<1, false>(c, ca, nimg) : launch_conv0_fwd_tile_t<3, false>(c, ca, nimg))
+                            : (Ci == 1 ? launch_conv0_fwd_tile_t<1>(c, ca, nimg) : launch_conv0_fwd_tile_t<3>(c, ca, nimg));
+      if (trc != PPO_OK && trc != 1) return trc;
+      proprio_done = trc == PPO_OK;
+      have_bits = trc == PPO_OK && ca.bits;
+      if (trc == 1) {
+        constexpr int TPW = 4;
+        const int grid = cdiv(M, 32 * 4 * TPW);
 #define LAUNCH_C1(CIN_, RELU_) hipLaunchKernelGGL((k_conv1_fwd<CIN_, TPW, RELU_>), dim3(grid), dim3(256), 0, c->stream, in, nimg, c->cH[0], c->cW[0], Ho, Wo, Co, w, b, out)
-      if (Ci == 1) { if (c->ln) LAUNCH_C1(1, false); else LAUNCH_C1(1, true); }
-      else { if (c->ln) LAUNCH_C1(3, false); else LAUNCH_C1(3, true); }
+        if (Ci == 1) { if (c->ln) LAUNCH_C1(1, false); else LAUNCH_C1(1, true); }
+        else { if (c->ln) LAUNCH_C1(3, false); else LAUNCH_C1(3, true); }
 #undef LAUNCH_C1
+      }
       LAUNCHCHK(c, "k_conv1_fwd");
     } else {
       AConvFwd al;
       al.in = act_addr(c, l - 1);
       al.H = c->cH[l]; al.W = c->cW[l]; al.Cin = Ci; al.lc = ilog2(Ci); al.Ho = Ho; al.Wo = Wo; al.M = (int)M; al.K = 9 * Ci;
       const double ab = 2.0 * ((double)nimg * al.H * al.W * Ci + (double)M * Co + (double)al.K * Co);
-      int rc;
-      if (c->ln) {
+      uint32_t* const bits = !c->ln && l < c->nconv - 1 ? c->abits[l] : nullptr;
+      int rc = launch_conv_fwd_tile(c, al, conv_to, Co, c->shadow + c->convW[l], c->p + c->convB[l], nimg, name, ab, bits, !c->ln);
+      have_bits = rc == PPO_OK && bits;
+      if (rc != 1) {
+      } else if (c->ln) {
         Ep<MapRows, bf16_t, true, false, false> ep;
         ep.map.stride_b = conv_to.stride_b; ep.map.stride_v = conv_to.stride_v; ep.map.V = V; ep.map.HW = Ho * Wo; ep.map.C = Co; ep.map.M = (int)M;
         ep.out = const_cast<bf16_t*>(conv_to.base); ep.bias = c->p + c->convB[l]; ep.mask = nullptr; ep.N = Co;
@@ -1328,7 +1392,7 @@ int encoder_forward_generic(Ctx* c, const int32_t* idx, int n, int64_t first) {
       }
       if (rc) return rc;
     }
-    c->abits_ok[l] = false;
+    c->abits_ok[l] = have_bits;
     if (c->ln) {
       ProfScope ps(c, "layer_norm_fwd", 8.0 * (double)nimg * e, 4.0 * (double)nimg * e);
       // an image that fits one block's registers is read once
@@ -1350,9 +1414,11 @@ int encoder_forward_generic(Ctx* c, const int32_t* idx, int n, int64_t first) {
       if (rc) return rc;
     }
   }
-  hipLaunchKernelGGL(k_gather_proprio, dim3(cdiv((int64_t)n * c->P, 256)), dim3(256), 0, c->stream, c->proprio + first * c->P, idx, n, c->P, c->feat,
-                     (int64_t)c->feat_ld, V * c->enc);
-  LAUNCHCHK(c, "k_gather_proprio");
+  if (!proprio_done) {
+    hipLaunchKernelGGL(k_gather_proprio, dim3(cdiv((int64_t)n * c->P, 256)), dim3(256), 0, c->stream, c->proprio + first * c->P, idx, n, c->P, c->feat,
+                       (int64_t)c->feat_ld, V * c->enc);
+    LAUNCHCHK(c, "k_gather_proprio");
+  }
   return PPO_OK;
 }
 
@@ -1405,43 +1471,45 @@ int encoder_backward_seq(Ctx* c, const int32_t* idx, int n, bool acc, const bf16
     if (l == 0) {
       ImgAddr in; in.base = c->obs; in.idx = idx; in.stride_b = c->img_elems * V; in.stride_v = c->img_elems; in.V = V;
       if (dconv.stride_v != e || dconv.stride_b != e * V) return fail(c, PPO_ESHAPE, "the first convolution's gradient needs a contiguous layout");
-      const int K = 9 * Ci;
-      int64_t M = (int64_t)nimg * Ho * Wo;
-      const int npair = Co * (K + 1);
-      { const int erc = ensure_partial(c, (int64_t)2048 * npair, 0); if (erc) return erc; }
-      int64_t max_blocks = c->partial_elems / npair;
-      if (max_blocks > 2048) max_blocks = 2048;
-      if (max_blocks < 1) return fail(c, PPO_ENOMEM, "weight-gradient workspace too small for the first convolution");
-      int64_t ppb = (M + max_blocks - 1) / max_blocks;
-      ppb = (ppb + 63) / 64 * 64;
-      const int nblk = cdiv(M, ppb);
-      ProfScope ps(c, "conv_wgrad.0", 2.0 * (double)M * Co * (K + 1), 2.0 * ((double)M * Co + (double)nimg * c->img_elems));
-      if (Ci == 1) hipLaunchKernelGGL((k_conv1_wgrad<1>), dim3(nblk), dim3(256), 0, c->stream, in, nimg, H, W, Ho, Wo, Co, dconv.base, (int)ppb, c->partial);
-      else hipLaunchKernelGGL((k_conv1_wgrad<3>), dim3(nblk), dim3(256), 0, c->stream, in, nimg, H, W, Ho, Wo, Co, dconv.base, (int)ppb, c->partial);
-      LAUNCHCHK(c, "k_conv1_wgrad");
-      defer_reduce(c, 2, nblk, npair, Co, K, c->g + c->convW[0], c->g + c->convB[0], acc, false, 0, nullptr);
+      const int rc = conv0_wgrad(c, in, dconv.base, nimg, acc);
+      if (rc) return rc;
       break;
     }
     ARows dl; dl.a = dconv; dl.HW = Ho * Wo; dl.C = Co; dl.M = nimg * Ho * Wo; dl.K = Co; dl.plain = false;
     AConvFwd xl; xl.in = act_addr(c, l - 1);
     xl.H = H; xl.W = W; xl.Cin = Ci; xl.lc = ilog2(Ci); xl.Ho = Ho; xl.Wo = Wo; xl.M = dl.M; xl.K = 9 * Ci;
     const double wab = 2.0 * ((double)dl.M * Co + (double)nimg * H * W * Ci) + 4.0 * 9.0 * Ci * Co;
-    int rc = launch_wgrad(c, dl, xl, Co, 9 * Ci, dl.M, c->g + c->convW[l], c->g + c->convB[l], acc, "conv_wgrad." + std::to_string(l), wab);
+    int rc = launch_conv_wgrad_tile(c, dconv, xl, Co, nimg, c->g + c->convW[l], c->g + c->convB[l], acc, "conv_wgrad." + std::to_string(l), wab);
+    if (rc == 1) rc = launch_wgrad(c, dl, xl, Co, 9 * Ci, dl.M, c->g + c->convW[l], c->g + c->convB[l], acc, "conv_wgrad." + std::to_string(l), wab);
     if (rc) return rc;
+    const double pix = (double)nimg * H * W, dflops = 2.0 * (double)nimg * Ho * Wo * 9.0 * Ci * Co;
+    const double dab = 2.0 * ((double)nimg * Ho * Wo * Co + pix * Ci + 9.0 * Ci * Co);
+    const ImgAddr xa = act_addr(c, l - 1);
+    // with layer normalisation the gradient may stay unmasked: k_ln_bwd applies the ReLU itself
+    const uint32_t* const xbits = c->ln ? nullptr : c->abits[l - 1];
+    if (c->ln || c->abits_ok[l - 1]) {
+      rc = launch_conv_dgrad_tile(c, dconv, xa, xbits, c->gbuf[cur ^ 1], c->wtap[l], Co, Ci, H, W, Ho, Wo, nimg, "conv_dgrad." + std::to_string(l), dflops,
+                                  dab + (xbits ? pix * Ci / 8.0 : 0.0));
+      if (rc != PPO_OK && rc != 1) return rc;
+      if (rc == PPO_OK) {
+        cur ^= 1;
+        dy = contiguous_imgs(c->gbuf[cur], (int64_t)Ci * H * W, V);
+        continue;
+      }
+    }
     AConvDgrad al; al.dy = dconv; al.Ho = Ho; al.Wo = Wo; al.Cout = Co; al.lco = ilog2(Co); al.H = H; al.W = W; al.dy_imgs = nimg;
     rc = ensure_packed_dgrad_weights(c, l);
     if (rc) return rc;
     al.w0 = c->wd[l][0]; al.w1 = c->wd[l][1];
     const int M0 = nimg * class_len(H, 0) * class_len(W, 0);
-    const ImgAddr xa = act_addr(c, l - 1);
-    Ep<MapDgrad, bf16_t, false, false, true> ep;
-    ep.map.stride_b = xa.stride_b; ep.map.stride_v = xa.stride_v; ep.map.V = V; ep.map.H = H; ep.map.W = W; ep.map.Cin = Ci; ep.map.imgs = nimg;
-    ep.out = c->gbuf[cur ^ 1]; ep.bias = nullptr; ep.mask = xa.base; ep.N = 2 * Ci;
-    const bool dense_in = xa.stride_v == (int64_t)H * W * Ci && xa.stride_b == (int64_t)V * H * W * Ci;
-    if (c->abits_ok[l - 1] && Ci % 32 == 0 && dense_in) ep.mbits = c->abits[l - 1];  // bit index = element offset of the dense activation
-    const double pix = (double)nimg * H * W;
-    rc = launch_gemm(c, al, M0, nullptr, 0, 2 * Ci, 4 * Co, ep, "conv_dgrad." + std::to_string(l),
-                     2.0 * ((double)nimg * Ho * Wo * Co + 2.0 * pix * Ci + 9.0 * Ci * Co), 2, 2.0 * (double)nimg * Ho * Wo * 9.0 * Ci * Co);
+    auto gemm = [&](auto ep) {
+      ep.map.stride_b = xa.stride_b; ep.map.stride_v = xa.stride_v; ep.map.V = V; ep.map.H = H; ep.map.W = W; ep.map.Cin = Ci; ep.map.imgs = nimg;
+      ep.out = c->gbuf[cur ^ 1]; ep.bias = nullptr; ep.mask = xa.base; ep.N = 2 * Ci;
+      const bool dense_in = xa.stride_v == (int64_t)H * W * Ci && xa.stride_b == (int64_t)V * H * W * Ci;
+      if (c->abits_ok[l - 1] && Ci % 32 == 0 && dense_in) ep.mbits = c->abits[l - 1];  // bit index = element offset of the dense activation
+      return launch_gemm(c, al, M0, nullptr, 0, 2 * Ci, 4 * Co, ep, "conv_dgrad." + std::to_string(l), dab + (c->ln ? 0.0 : 2.0 * pix * Ci), 2, dflops);
+    };
+    rc = c->ln ? gemm(Ep<MapDgrad, bf16_t, false, false, false, true>()) : gemm(Ep<MapDgrad, bf16_t, false, false, true>());
     if (rc) return rc;
     cur ^= 1;
     dy = contiguous_imgs(c->gbuf[cur], (int64_t)Ci * H * W, V);

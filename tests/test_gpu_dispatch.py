@@ -59,20 +59,17 @@ def test_gemm_plans(L, M, N, K):
     assert np.abs(L.diag_gemm(a, b) - want).max() <= 1e-4 * np.abs(want).max()
 
 
-@pytest.mark.parametrize("ci,h,w", [(1, 51, 61), (1, 49, 58), (1, 89, 117), (1, 31, 33), (1, 45, 90), (3, 49, 58), (2, 62, 101)])
-def test_gradients_odd_second_layer_width(L, ci, h, w):
-    """Widths whose first-layer output is odd: every tensor's gradient against the oracle's bf16-operand mode."""
+def _check_gradients(L, cfg, N, T):
+    """One minibatch of a conditioned rollout: every tensor's gradient against the oracle's bf16-operand mode."""
     import torch
-    cfg = configs.get_config(ci, num_envs=12, horizon=4)
-    cfg["net"].update(in_h=h, in_w=w)
     net, hp = cfg["net"], dict(cfg["hp"], epochs=1, minibatches=1, seed=3)
     ro = synth.rollout(cfg, conditioned=True)
     params = synth.init_params(net, 9)
-    lrn = L.Learner(net, 12, 4, cfg["obs_dtype"])
+    lrn = L.Learner(net, N, T, cfg["obs_dtype"])
     lrn.set_params(params)
     distill = cfg["kind"] == "distill"
     fill_learner(lrn, cfg, ro, distill=distill)
-    fr = {k: v.reshape((48,) + v.shape[2:]) for k, v in ro.items() if k != "last_value"}
+    fr = {k: v.reshape((N * T,) + v.shape[2:]) for k, v in ro.items() if k != "last_value"}
     if distill:
         lrn.distill_update(hp)
         with orc.quant(1):
@@ -87,6 +84,25 @@ def test_gradients_odd_second_layer_width(L, ci, h, w):
     g = lrn.get_grads()
     bad = {n: rel_l2(g[a:b], qg[a:b]) for n, (a, b, _) in synth.param_slices(net).items() if rel_l2(g[a:b], qg[a:b]) > TOL_BF16}
     assert not bad, bad
+
+
+@pytest.mark.parametrize("ci,h,w", [(1, 51, 61), (1, 49, 58), (1, 89, 117), (1, 31, 33), (1, 45, 90), (3, 49, 58), (2, 62, 101)])
+def test_gradients_odd_second_layer_width(L, ci, h, w):
+    """Widths whose first-layer output is odd."""
+    cfg = configs.get_config(ci, num_envs=12, horizon=4)
+    cfg["net"].update(in_h=h, in_w=w)
+    _check_gradients(L, cfg, 12, 4)
+
+
+@pytest.mark.parametrize("c0,conv,h,w", [(1, (8, 16), 33, 47), (1, (16, 32, 64, 128), 40, 64), (1, (32, 64), 16, 130), (1, (64, 64), 21, 24),
+                                         (3, (16, 32), 18, 66), (3, (32, 64, 64), 37, 53), (1, (16, 64), 9, 16)])
+def test_gradients_with_layer_norm(L, c0, conv, h, w):
+    """Convolutions that store their output before a layer normalisation: the first layer's weight gradient from a stored
+    gradient (rows of one ragged 32-pixel step, several steps, several bands), unmasked transposed convolutions."""
+    cfg = configs.get_config(1, num_envs=10, horizon=4)
+    cfg["net"].update(in_c=c0, in_h=h, in_w=w, conv_ch=list(conv), layer_norm=1)
+    _check_gradients(L, cfg, 10, 4)
+
 
 
 @pytest.mark.parametrize("ci,dtype", [(0, "fp32"), (0, "bf16"), (3, "fp32"), (3, "bf16")])

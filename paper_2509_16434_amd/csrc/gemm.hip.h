@@ -60,6 +60,24 @@ struct ARows {
   }
 };
 
+// Up to four plain matrices with their own weights (row stride = K): one product per grid.z.
+struct ARowsSet {
+  const bf16_t* a[4];
+  const bf16_t* w[4];
+  int64_t lda[4];
+  int M[4], K[4];
+  void prepare() {}
+  struct Row { const bf16_t* p; };
+  struct KCur { int k; };
+  struct Cls { int M, K; const bf16_t *a, *w; int64_t lda; };
+  __device__ __forceinline__ Cls cls(int z) const { Cls c; c.M = M[z]; c.K = K[z]; c.a = a[z]; c.w = w[z]; c.lda = lda[z]; return c; }
+  __device__ __forceinline__ const bf16_t* bmat(const Cls& c, const bf16_t*) const { return c.w; }
+  __device__ __forceinline__ Row row(int m, const Cls& c) const { Row r; r.p = m < c.M ? c.a + (int64_t)m * c.lda : nullptr; return r; }
+  __device__ __forceinline__ KCur kcur(int k, const Cls&) const { KCur c; c.k = k; return c; }
+  __device__ __forceinline__ void kstep(KCur& c, int dk, const Cls&) const { c.k += dk; }
+  __device__ __forceinline__ const bf16_t* addr(const Row& r, const KCur& k, const Cls& c) const { return (!r.p || k.k >= c.K) ? nullptr : r.p + k.k; }
+};
+
 // Row m = (img, oy, ox) of the im2col matrix of a channel-last image under a 3x3 stride-2 pad-1
 // window; k = (u*3+v)*Cin + ci.  Cin is a power of two (lc = log2 Cin).  A row keeps the element
 // offset of its window's corner pixel (iy0, ix0) = (2oy-1, 2ox-1), which may lie outside the
@@ -346,17 +364,18 @@ __device__ __forceinline__ void gemm_epilogue(f32x16_t (&acc)[TM][TN], const EP&
   }
 }
 
-// The epilogue of one slice of a split reduction (k_gemm_rs with this type; plain rows, grid = tiles * splits in x):
-// block v (renumbered per XCD) takes slice v / tiles, `W` k-steps of 64 wide, of tile v % tiles - so that the blocks of
-// one XCD work on the same k range of neighbouring tiles and share their operands in its L2 - and leaves its
-// accumulators as they are: [slice][tile][32 x 32 subtile][g][lane] float4, 1 KiB per store instruction.
-// k_gemm_split_reduce sums the slices in order and applies the real epilogue.
+// The epilogue of one slice of a split reduction (k_gemm_rs with this type; plain rows, grid = tiles * splits in x, up to
+// MAXP independent products in z): block v (renumbered per XCD) takes slice v / tiles, `W` k-steps of 64 wide, of tile
+// v % tiles - so that the blocks of one XCD work on the same k range of neighbouring tiles and share their operands in
+// its L2 - and leaves its accumulators as they are: [slice][tile][32 x 32 subtile][g][lane] float4, 1 KiB per store
+// instruction.  k_gemm_split_reduce (or a cell kernel of recurrent.hip.h) sums the slices in order.
 struct EpSplit {
   typedef float out_t;
   static constexpr bool kBias = false, kRelu = false, kMask = false, kStream = false, kSplit = true;
+  static constexpr int MAXP = 4;
   MapRows map;
-  float* part;
-  int W, tiles, gy;  // k-steps per slice; tiles in all; tiles along N (consecutive tile numbers)
+  float* part[MAXP];
+  int N[MAXP], W[MAXP], tiles[MAXP], gy[MAXP], blocks[MAXP];  // k-steps per slice; tiles in all; tiles along N (consecutive tile numbers); tiles * slices
 };
 template <int BM, int BN, class EP>
 __global__ __launch_bounds__(256) void k_gemm_split_reduce(const float* __restrict__ part, int splits, int tiles, int gy, int M, int N, EP ep) {

@@ -46,7 +46,7 @@ __device__ __forceinline__ void vm_wait_dyn(int n) {
 // barrier per k-step: the loaders arrive when their part of stage kt has landed, the compute waves
 // when they are done with stage kt-1 (whose slot the loaders refill next).
 template <int BM, int BN, int WGM, int WGN, int NST, class AL, class EP>
-__global__ __launch_bounds__((WGM * WGN + 4) * 64) void k_gemm_rs(AL al, const bf16_t* __restrict__ Bm_, int64_t ldb_, int N, EP ep,
+__global__ __launch_bounds__((WGM * WGN + 4) * 64) void k_gemm_rs(AL al, const bf16_t* __restrict__ Bm_, int64_t ldb_, int N_, EP ep,
                                                                   const bf16_t* __restrict__ zpage) {
   constexpr int NCW = WGM * WGN, NLW = 4, THREADS = (NCW + NLW) * 64;
   constexpr int TM = BM / (WGM * 32), TN = BN / (WGN * 32);
@@ -66,12 +66,13 @@ __global__ __launch_bounds__((WGM * WGN + 4) * 64) void k_gemm_rs(AL al, const b
   const auto mcls = ep.map.cls(blockIdx.z);
   const int K = acls.K;
   int m0 = blockIdx.x * BM, n0 = blockIdx.y * BN, kbeg = 0, nk = (K + BK - 1) / BK;
-  int slice = 0, tile = 0;
+  int slice = 0, tile = 0, N = N_;
   if constexpr (EP::kSplit) {
-    const int v = xcd_block((int)blockIdx.x, (int)gridDim.x);
-    slice = v / ep.tiles; tile = v - slice * ep.tiles;
-    m0 = (tile / ep.gy) * BM; n0 = (tile % ep.gy) * BN;
-    kbeg = slice * ep.W * BK; nk = min(ep.W, nk - slice * ep.W);
+    const int z = blockIdx.z, v = xcd_block((int)blockIdx.x, (int)gridDim.x), tiles = ep.tiles[z], W = ep.W[z];
+    if (v >= ep.blocks[z]) return;
+    slice = v / tiles; tile = v - slice * tiles;
+    m0 = (tile / ep.gy[z]) * BM; n0 = (tile % ep.gy[z]) * BN;
+    kbeg = slice * W * BK; nk = min(W, nk - slice * W); N = ep.N[z];
   }
   if (m0 >= acls.M) return;
   const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -177,7 +178,7 @@ __global__ __launch_bounds__((WGM * WGN + 4) * 64) void k_gemm_rs(AL al, const b
   }
   if constexpr (EP::kSplit) {
     if (!compute) return;
-    float4* P = reinterpret_cast<float4*>(ep.part) + ((int64_t)slice * ep.tiles + tile) * (BM * BN / 4);
+    float4* P = reinterpret_cast<float4*>(ep.part[blockIdx.z]) + ((int64_t)slice * ep.tiles[blockIdx.z] + tile) * (BM * BN / 4);
 #pragma unroll
     for (int i = 0; i < TM; ++i)
 #pragma unroll

@@ -103,8 +103,9 @@ struct Ctx {
   float* gates[4] = {};                     // [CH][4H] gate activations
   float* c_enter[4] = {};                   // [CH][H] cell state entering each step
   float* lstm_pre = nullptr;                // [CHe][4H] gate pre-activations of one step
-  bf16_t* da = nullptr;                     // [CH][4H] gate pre-activation gradients of one layer
-  float* dc_carry = nullptr;                // [CHe][H]
+  bf16_t* da[4] = {};                       // [CH][4H] gate pre-activation gradients
+  float* dc_carry[4] = {};                  // [CHe][H]
+  float* lstm_part = nullptr;               // slices of the products of the layers that run side by side
   bf16_t* htop = nullptr;                   // [CH][H] top layer's h: the trunk's input
   int32_t* seqidx = nullptr;                // [CH] rollout sample of each row of a sequence chunk
   float *h0 = nullptr, *c0 = nullptr;       // [nl][N][H] state of every environment at the start of the rollout
@@ -459,10 +460,11 @@ int launch_gemm_ring(Ctx* c, const ARows& al, int M, const bf16_t* Bm, int64_t l
     return PPO_OK;
   }
   EpSplit es;
-  es.map = ep.map; es.part = reinterpret_cast<float*>((reinterpret_cast<uintptr_t>(c->partial) + 15) & ~(uintptr_t)15); es.W = plan.W; es.gy = cdiv(N, BN); es.tiles = cdiv(M, BM) * es.gy;
-  hipLaunchKernelGGL(kfs, dim3(es.tiles * plan.splits), dim3((ncw + 4) * 64), lds, c->stream, al, Bm, ldb, N, es, c->zpage);
-  hipLaunchKernelGGL((k_gemm_split_reduce<BM, BN, EP>), dim3(cdiv((int64_t)es.tiles * (BM / 32) * (BN / 32), 4)), dim3(256), 0, c->stream, es.part, plan.splits, es.tiles,
-                     es.gy, M, N, ep);
+  es.map = ep.map; es.part[0] = reinterpret_cast<float*>((reinterpret_cast<uintptr_t>(c->partial) + 15) & ~(uintptr_t)15);
+  es.N[0] = N; es.W[0] = plan.W; es.gy[0] = cdiv(N, BN); es.tiles[0] = cdiv(M, BM) * es.gy[0]; es.blocks[0] = es.tiles[0] * plan.splits;
+  hipLaunchKernelGGL(kfs, dim3(es.blocks[0]), dim3((ncw + 4) * 64), lds, c->stream, al, Bm, ldb, N, es, c->zpage);
+  hipLaunchKernelGGL((k_gemm_split_reduce<BM, BN, EP>), dim3(cdiv((int64_t)es.tiles[0] * (BM / 32) * (BN / 32), 4)), dim3(256), 0, c->stream, es.part[0], plan.splits, es.tiles[0],
+                     es.gy[0], M, N, ep);
   return PPO_OK;
 }
 
@@ -1521,6 +1523,162 @@ int encoder_backward_generic(Ctx* c, const int32_t* idx, int n, bool acc, int cu
 }
 
 // ---------------------------------------------------------------- recurrent core
+// The layers' steps side by side (recurrent.hip.h): needs units in multiples of 32.
+bool lstm_side_by_side(const Ctx* c) { return c->H % 32 == 0; }
+int64_t lstm_tiled_rows(const Ctx* c, int ne) { return (int64_t)cdiv(ne, 32) * 32; }  // rows of one step in the tiled arrays
+
+struct LstmProducts {
+  ARowsSet al;
+  EpSplit ep;
+  int n = 0;
+  void add(const bf16_t* a, int64_t lda, int M, const bf16_t* w, int N, int K) {
+    al.a[n] = a; al.lda[n] = lda; al.w[n] = w; al.M[n] = M; al.K[n] = K; ep.N[n] = N;
+    ++n;
+  }
+};
+// All products of an iteration in one launch.  Slices of one length W for all of them, so that the blocks finish
+// together: the W with the smallest sum of k-steps per round of 256 blocks (lengths as in plan_gemm) and of the slices'
+// way through memory (written and read once, 6 TB/s).
+template <int BM, int BN>
+int launch_lstm_products(Ctx* c, LstmProducts& P, LstmPart (&out)[EpSplit::MAXP], const std::string& name) {
+  constexpr int nst = BM == 64 ? 8 : 4, lds = nst * (BM + BN) * 128;
+  const double step = BM == 64 ? 0.34 : 0.60;  // us per k-step, as in plan_gemm
+  int nk[EpSplit::MAXP], kmax = 0;
+  double flops = 0.0, bytes = 0.0;
+  for (int i = 0; i < P.n; ++i) {
+    P.ep.gy[i] = cdiv(P.ep.N[i], BN); P.ep.tiles[i] = cdiv(P.al.M[i], BM) * P.ep.gy[i]; nk[i] = cdiv(P.al.K[i], 64);
+    if (nk[i] > kmax) kmax = nk[i];
+    flops += 2.0 * P.al.M[i] * (double)P.ep.N[i] * P.al.K[i];
+    bytes += 2.0 * ((double)P.al.M[i] * P.al.K[i] + (double)P.ep.N[i] * P.al.K[i]);
+  }
+  int W = kmax;
+  double tbest = 1e30;
+  for (int w = kmax; w >= 3 || w == kmax; --w) {
+    int64_t blocks = 0;
+    for (int i = 0; i < P.n; ++i) blocks += (int64_t)P.ep.tiles[i] * cdiv(nk[i], w);
+    if (w < kmax && blocks > 512) break;   // (what lstm_part holds)
+    const double t = step * w * cdiv(blocks, 256) + 8e-6 * (double)blocks * BM * BN / 6.0;
+    if (t < tbest - 1e-9) { tbest = t; W = w; }
+  }
+  int gx = 0;
+  float* part = c->lstm_part;
+  for (int i = 0; i < P.n; ++i) {
+    P.ep.W[i] = W;
+    const int splits = cdiv(nk[i], W);
+    P.ep.blocks[i] = P.ep.tiles[i] * splits; P.ep.part[i] = part;
+    out[i].part = reinterpret_cast<const float4*>(part); out[i].splits = splits; out[i].tiles = P.ep.tiles[i]; out[i].gy = P.ep.gy[i];
+    part += (int64_t)P.ep.blocks[i] * BM * BN;
+    if (P.ep.blocks[i] > gx) gx = P.ep.blocks[i];
+  }
+  P.ep.map = plain_map(0, 0);
+  gx = (gx + 7) / 8 * 8;
+  auto kfn = k_gemm_rs<BM, BN, 2, 2, nst, ARowsSet, EpSplit>;
+  static uint64_t attr_devs = 0;  /* bit d: set on device d */
+  if (!((attr_devs >> c->dev) & 1)) { HIPCHK(c, hipFuncSetAttribute((const void*)kfn, hipFuncAttributeMaxDynamicSharedMemorySize, lds)); attr_devs |= 1ull << c->dev; }
+  ProfScope ps(c, name, flops, bytes);
+  hipLaunchKernelGGL(kfn, dim3(gx, 1, P.n), dim3(512), lds, c->stream, P.al, (const bf16_t*)nullptr, (int64_t)0, 0, P.ep, c->zpage);
+  LAUNCHCHK(c, "lstm products");
+  return PPO_OK;
+}
+// room of lstm_part: the undivided tiles of every layer's largest product, or 512 blocks of slices
+int64_t lstm_part_elems(const Ctx* c) {
+  auto blocks = [&](int bm, int bn) {
+    int64_t t = 0;
+    for (int l = 0; l < c->nl; ++l) t += (int64_t)cdiv(c->CHe, bm) * std::max(cdiv(4 * c->H, bn), cdiv(c->lin[l] + c->H, bn));
+    return std::max<int64_t>(t, 512) * bm * bn;
+  };
+  return std::max(blocks(64, 64), blocks(128, 128));
+}
+
+template <int BM, int BN>
+int lstm_forward_side_by_side(Ctx* c, int ne) {
+  const int T = c->T, H = c->H, L = c->nl;
+  const int64_t R = lstm_tiled_rows(c, ne);
+  for (int s = 0; s < T + L - 1; ++s) {
+    LstmProducts P;
+    LstmFwdJobs J;
+    LstmPart parts[EpSplit::MAXP];
+    int lay[4];
+    for (int l = 0; l < L; ++l) {
+      const int t = s - l, K = c->lin[l] + H;
+      if (t < 0 || t >= T) continue;
+      lay[P.n] = l;
+      P.add(c->xh[l] + (int64_t)t * ne * K, K, ne, c->shadow + c->lstmW[l], 4 * H, K);
+    }
+    int rc = launch_lstm_products<BM, BN>(c, P, parts, "lstm_fwd");
+    if (rc) return rc;
+    J.ne = ne; J.H = H; J.done = c->done;
+    for (int i = 0; i < P.n; ++i) {
+      const int l = lay[i], t = s - l, K = c->lin[l] + H;
+      const bool last = t == T - 1, top = l == L - 1;
+      const int64_t r0 = (int64_t)t * ne;
+      auto& q = J.job[i];
+      q.pre = parts[i]; q.bias = c->p + c->lstmB[l]; q.idx = c->seqidx + r0;
+      q.c_enter = reinterpret_cast<const float4*>(c->c_enter[l] + t * R * H);
+      q.c_next = last ? nullptr : reinterpret_cast<float4*>(c->c_enter[l] + (t + 1) * R * H);
+      q.gates = reinterpret_cast<float4*>(c->gates[l] + t * R * 4 * H);
+      q.ld_out = top ? H : c->lin[l + 1] + H; q.h_out = (top ? c->htop : c->xh[l + 1]) + r0 * q.ld_out;
+      q.ld_next = K; q.h_next = last ? nullptr : c->xh[l] + (r0 + ne) * K + c->lin[l];
+    }
+    ProfScope ps(c, "lstm_cell_fwd", 30.0 * P.n * ne * H, (double)P.n * ne * H * 44.0);
+    hipLaunchKernelGGL((k_lstm_cells_fwd<BM, BN>), dim3((int)(R / 32) * (H / 32), P.n), dim3(256), 0, c->stream, J);
+    LAUNCHCHK(c, "k_lstm_cells_fwd");
+  }
+  return PPO_OK;
+}
+
+// dtop [T*ne][H]: gradient of the top layer's h.  Leaves every layer's gate gradients in da.
+template <int BM, int BN>
+int lstm_backward_side_by_side(Ctx* c, const bf16_t* dtop, int ne) {
+  const int T = c->T, H = c->H, L = c->nl;
+  const int64_t R = lstm_tiled_rows(c, ne);
+  LstmPart parts[EpSplit::MAXP], prev[EpSplit::MAXP];
+  bool have[4] = {false, false, false, false};   // layer l's product of the previous iteration is in prev[l]
+  for (int s = 0; s < T + L - 1; ++s) {
+    LstmBwdJobs J;
+    int lay[4], nj = 0;
+    J.ne = ne; J.H = H; J.done = c->done;
+    for (int l = L - 1; l >= 0; --l) {
+      const int t = T - 1 - (s - (L - 1 - l));
+      if (t < 0 || t >= T) continue;
+      const int64_t r0 = (int64_t)t * ne;
+      auto& q = J.job[nj];
+      lay[nj++] = l;
+      q.above.part = nullptr; q.dh = nullptr; q.ld_dh = H; q.rec.part = nullptr; q.rec_col = l > 0 ? c->lin[l] : 0;
+      if (l == L - 1) q.dh = dtop + r0 * H;
+      else q.above = prev[l + 1];
+      if (t < T - 1 && have[l]) q.rec = prev[l];
+      q.idx = c->seqidx + r0;
+      q.c_enter = reinterpret_cast<const float4*>(c->c_enter[l] + t * R * H);
+      q.gates = reinterpret_cast<const float4*>(c->gates[l] + t * R * 4 * H);
+      q.dc = reinterpret_cast<float4*>(c->dc_carry[l]);
+      q.da = c->da[l] + r0 * 4 * H;
+    }
+    {
+      ProfScope ps(c, "lstm_cell_bwd", 40.0 * nj * ne * H, (double)nj * ne * H * 40.0);
+      hipLaunchKernelGGL((k_lstm_cells_bwd<BM, BN>), dim3((int)(R / 32) * (H / 32), nj), dim3(256), 0, c->stream, J);
+      LAUNCHCHK(c, "k_lstm_cells_bwd");
+    }
+    // gate gradients -> gradient of the operand row: of the h half for the step before, and of the x half for the layer
+    // below (the bottom layer's x half is one product over all steps afterwards; at step 0 nothing needs the h half)
+    LstmProducts P;
+    int pl[4];
+    for (int i = 0; i < nj; ++i) {
+      const int l = lay[i], t = T - 1 - (s - (L - 1 - l));
+      have[l] = false;
+      if (t == 0 && l == 0) continue;
+      const int64_t skip = l > 0 ? 0 : (int64_t)c->lin[0] * 4 * H;
+      pl[P.n] = l;
+      P.add(c->da[l] + (int64_t)t * ne * 4 * H, 4 * H, ne, c->lstmWT[l] + skip, l > 0 ? c->lin[l] + H : H, 4 * H);
+    }
+    if (P.n == 0) continue;
+    const int rc = launch_lstm_products<BM, BN>(c, P, parts, "lstm_dgrad");
+    if (rc) return rc;
+    for (int i = 0; i < P.n; ++i) { prev[pl[i]] = parts[i]; have[pl[i]] = true; }
+  }
+  return PPO_OK;
+}
+
 // Forward of a chunk of `ne` whole environments (device list env) x T steps, rows time-major.  Encoder on all
 // ne*T rows at once, then per LSTM layer and step one GEMM (the operand row [x_t, h_enter] against the layer's
 // [W_ih, W_hh]) and one cell kernel, then hidden layers and heads on all rows.
@@ -1530,11 +1688,18 @@ int forward_seq_chunk(Ctx* c, const int32_t* env, int ne, bool with_head) {
   LAUNCHCHK(c, "k_seq_index");
   int rc = (c->ln || c->E > 0) ? encoder_forward_generic(c, c->seqidx, n, 0) : encoder_forward_ff(c, c->seqidx, n, 0);
   if (rc) return rc;
+  const bool side = lstm_side_by_side(c);
   for (int l = 0; l < c->nl; ++l) {
-    const int K = c->lin[l] + H;
     hipLaunchKernelGGL(k_lstm_init, dim3(cdiv(ne * H, 256)), dim3(256), 0, c->stream, env, ne, H, c->h0 + (int64_t)l * c->N * H, c->c0 + (int64_t)l * c->N * H,
-                       c->xh[l], (int64_t)K, c->lin[l], c->c_enter[l]);
+                       c->xh[l], (int64_t)(c->lin[l] + H), c->lin[l], c->c_enter[l], side ? 1 : 0);
     LAUNCHCHK(c, "k_lstm_init");
+  }
+  if (side) {
+    rc = ne <= 64 ? lstm_forward_side_by_side<64, 64>(c, ne) : lstm_forward_side_by_side<128, 128>(c, ne);
+    if (rc) return rc;
+  }
+  for (int l = 0; l < c->nl && !side; ++l) {
+    const int K = c->lin[l] + H;
     const bool top = l == c->nl - 1;
     bf16_t* outm = top ? c->htop : c->xh[l + 1];
     const int64_t ld_out = top ? H : c->lin[l + 1] + H;
@@ -1567,25 +1732,36 @@ int backward_seq_chunk(Ctx* c, int ne, bool acc, bool with_head) {
   if (rc) return rc;
   const bf16_t* dabove = c->gbuf[cur];
   int64_t ld_above = H;
+  const bool side = lstm_side_by_side(c);
+  if (side) {
+    rc = ne <= 64 ? lstm_backward_side_by_side<64, 64>(c, dabove, ne) : lstm_backward_side_by_side<128, 128>(c, dabove, ne);
+    if (rc) return rc;
+    // the bottom layer's input gradient, all steps at once
+    ARows dl = plain_arows(c->da[0], 4 * H, n, 4 * H);
+    Ep<MapRows, bf16_t, false, false, false> ep;
+    ep.map = plain_map(c->lin[0] + H, n); ep.out = c->dxh[0]; ep.bias = nullptr; ep.mask = nullptr; ep.N = c->lin[0];
+    rc = launch_gemm(c, dl, n, c->lstmWT[0], 4 * H, c->lin[0], 4 * H, ep, "lstm_dgrad.x", 2.0 * ((double)n * 4 * H + (double)n * c->lin[0] + (double)c->lin[0] * 4 * H));
+    if (rc) return rc;
+  }
   for (int l = c->nl - 1; l >= 0; --l) {
     const int K = c->lin[l] + H;
-    for (int t = T - 1; t >= 0; --t) {
+    for (int t = T - 1; t >= 0 && !side; --t) {
       const int64_t r0 = (int64_t)t * ne;
       const bool last = t == T - 1;
       {
         ProfScope ps(c, "lstm_cell_bwd", 40.0 * ne * H, (double)ne * H * (16.0 + 4.0 + 4.0 + 8.0 + 8.0));
         hipLaunchKernelGGL(k_lstm_cell_bwd, dim3(cdiv(ne * H, 256)), dim3(256), 0, c->stream, ne, H, c->gates[l] + r0 * 4 * H, c->c_enter[l] + r0 * H, c->done,
-                           c->seqidx + r0, dabove + r0 * ld_above, ld_above, last ? nullptr : c->dxh[l] + (r0 + ne) * K + c->lin[l], (int64_t)K, c->dc_carry,
-                           last ? 1 : 0, c->da + r0 * 4 * H);
+                           c->seqidx + r0, dabove + r0 * ld_above, ld_above, last ? nullptr : c->dxh[l] + (r0 + ne) * K + c->lin[l], (int64_t)K, c->dc_carry[l],
+                           last ? 1 : 0, c->da[l] + r0 * 4 * H);
         LAUNCHCHK(c, "k_lstm_cell_bwd");
       }
-      ARows dl = plain_arows(c->da + r0 * 4 * H, 4 * H, ne, 4 * H);
+      ARows dl = plain_arows(c->da[l] + r0 * 4 * H, 4 * H, ne, 4 * H);
       Ep<MapRows, bf16_t, false, false, false> ep;
       ep.map = plain_map(K, ne); ep.out = c->dxh[l] + r0 * K; ep.bias = nullptr; ep.mask = nullptr; ep.N = K;
       rc = launch_gemm(c, dl, ne, c->lstmWT[l], 4 * H, K, 4 * H, ep, "lstm_dgrad." + std::to_string(l), 2.0 * ((double)ne * 4 * H + (double)ne * K + (double)K * 4 * H));
       if (rc) return rc;
     }
-    ARows dl = plain_arows(c->da, 4 * H, n, 4 * H);
+    ARows dl = plain_arows(c->da[l], 4 * H, n, 4 * H);
     ARows xl = plain_arows(c->xh[l], K, n, K);
     rc = launch_wgrad(c, dl, xl, 4 * H, K, n, c->g + c->lstmW[l], c->g + c->lstmB[l], acc, "lstm_wgrad." + std::to_string(l), 2.0 * n * ((double)K + 4 * H) + 4.0 * (double)K * 4 * H);
     if (rc) return rc;
@@ -1872,9 +2048,12 @@ int create_impl(Ctx* c) {
       DALLOC(c, c->lstmWT[l], K * 4 * H);
       if (l > 0) DALLOC(c, c->xh[l], (int64_t)CH * K);
       DALLOC(c, c->dxh[l], (int64_t)CH * K);
-      DALLOC(c, c->gates[l], (int64_t)CH * 4 * H); DALLOC(c, c->c_enter[l], (int64_t)CH * H);
+      const int64_t rows = std::max<int64_t>(CH, c->T * lstm_tiled_rows(c, c->CHe));
+      DALLOC(c, c->gates[l], rows * 4 * H); DALLOC(c, c->c_enter[l], rows * H);
+      DALLOC(c, c->da[l], (int64_t)CH * 4 * H); DALLOC(c, c->dc_carry[l], lstm_tiled_rows(c, c->CHe) * H);
     }
-    DALLOC(c, c->lstm_pre, (int64_t)c->CHe * 4 * H); DALLOC(c, c->da, (int64_t)CH * 4 * H); DALLOC(c, c->dc_carry, (int64_t)c->CHe * H);
+    if (lstm_side_by_side(c)) DALLOC(c, c->lstm_part, lstm_part_elems(c));
+    else DALLOC(c, c->lstm_pre, (int64_t)c->CHe * 4 * H);
     DALLOC(c, c->htop, (int64_t)CH * H); DALLOC(c, c->seqidx, CH);
     DALLOC(c, c->h0, (int64_t)c->nl * c->N * H); DALLOC(c, c->c0, (int64_t)c->nl * c->N * H);
     HIPCHK(c, hipMemsetAsync(c->h0, 0, sizeof(float) * (size_t)c->nl * c->N * H, c->stream));

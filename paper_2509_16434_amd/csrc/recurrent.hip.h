@@ -5,6 +5,7 @@
 // Rows of a sequence chunk are time-major: row = t * ne + j for environment j of the chunk's ne environments.
 #pragma once
 #include "common.hip.h"
+#include "gemm.hip.h"
 
 #define LN_EPS 1e-5f
 #define LN_THREADS 512
@@ -184,17 +185,22 @@ __global__ __launch_bounds__(LN_RTHREADS) void k_ln_fwd_reg(const bf16_t* __rest
   }
 }
 
+// LSTM layers side by side (below): this lane's float4 of subtile (32 environments rb, 32 units ub), group g, in an array of `ub_n` unit blocks
+__device__ __forceinline__ int64_t lstm_pos(int rb, int ub, int ub_n, int g, int lane) { return (((int64_t)rb * ub_n + ub) * 4 + g) * 64 + lane; }
+
 // State that enters the first step of the chunk's environments: h (as bf16, into the h columns of row block 0 of
 // the layer's input matrix xh [rows][ld], columns [col_h, col_h + H)) and c (fp32, c_enter row block 0), gathered
 // from the per-environment initial states h0 / c0 [N][H] of this layer.
 __global__ void k_lstm_init(const int32_t* __restrict__ env, int ne, int H, const float* __restrict__ h0, const float* __restrict__ c0,
-                            bf16_t* __restrict__ xh, int64_t ld, int col_h, float* __restrict__ c_enter) {
+                            bf16_t* __restrict__ xh, int64_t ld, int col_h, float* __restrict__ c_enter, int tiled) {
   const int i = blockIdx.x * blockDim.x + threadIdx.x;
   if (i >= ne * H) return;
   const int j = i / H, k = i - j * H;
   const int64_t e = env[j];
   xh[(int64_t)j * ld + col_h + k] = f2bf(h0[e * H + k]);
-  c_enter[i] = c0[e * H + k];
+  // `tiled`: in the order of the cells that run side by side
+  const int64_t o = tiled ? lstm_pos(j >> 5, k >> 5, H >> 5, (k & 31) >> 3, ((k & 7) >> 2) * 32 + (j & 31)) * 4 + (k & 3) : (int64_t)i;
+  c_enter[o] = c0[e * H + k];
 }
 
 __device__ __forceinline__ float sigmoidf_(float x) { return 1.f / (1.f + __expf(-x)); }
@@ -251,6 +257,137 @@ __global__ void k_lstm_cell_bwd(int ne, int H, const float* __restrict__ gates, 
   d[2 * H + k] = f2bf(dc * ig * (1.f - gg * gg));
   d[3 * H + k] = f2bf(dh * tc * og * (1.f - og));
   dc_carry[i] = dc * fg;
+}
+
+// ---------------------------------------------------------------- LSTM layers side by side
+// Step t of layer l needs step t - 1 of its own layer and step t of the layer below: iteration s of the forward pass
+// runs step s - l of every layer l at once (backward: mirrored), one launch for the layers' products (k_gemm_rs on an
+// ARowsSet, slices of K over the whole chip) and one for their cells, which sum the slices: T + layers - 1 iterations of
+// two launches where layer after layer took 2 * T * layers of two, each product too small for the chip.
+// The cells work in the products' accumulator order.  Of a 32 x 32 subtile (32 environments x 32 units, or gate columns)
+// lane holds row lane % 32, columns g*8 + (lane/32)*4 .. +3; gate activations, cell states and the carried cell-state
+// gradient are kept in that order too, [32 environments][32 units][(gate)][g][lane] float4, so that every access of
+// these kernels but the bf16 rows is 16 bytes per lane and 1 KiB per wave.  A block takes one subtile, wave g its group.
+// Needs units % 32 == 0 (a gate's columns must not straddle subtiles).
+struct LstmPart {     // a product's slices
+  const float4* part;
+  int splits, tiles, gy;
+};
+template <int BM, int BN>
+__device__ __forceinline__ float4 lstm_sum(const LstmPart& p, int row32, int n, int g, int lane) {  // row32: environments / 32; n: first column (multiple of 32)
+  constexpr int SUBS = (BM / 32) * (BN / 32), CT = BN / 32, RT = BM / 32;
+  const int tile = (row32 / RT) * p.gy + n / BN, sub = (row32 % RT) * CT + (n % BN) / 32;
+  const float4* q = p.part + ((int64_t)tile * SUBS + sub) * 256 + g * 64 + lane;
+  const int64_t stride = (int64_t)p.tiles * SUBS * 256;
+  float4 s = *q;
+  for (int z = 1; z < p.splits; ++z) { q += stride; const float4 x = *q; s.x += x.x; s.y += x.y; s.z += x.z; s.w += x.w; }
+  return s;
+}
+
+struct LstmFwdJobs {
+  static constexpr int MAXL = 4;
+  int ne, H;
+  const uint8_t* done;
+  struct Job {
+    LstmPart pre;                 // W_ih x + W_hh h_enter
+    const float* bias;            // [4H]
+    const int32_t* idx;           // rollout samples of this step's rows
+    const float4* c_enter;
+    float4 *c_next, *gates;       // c_next NULL at the last step
+    bf16_t *h_out, *h_next;       // rows of the next layer's input (or the trunk's) / of this layer's next step (NULL at the last)
+    int64_t ld_out, ld_next;
+  } job[MAXL];
+};
+template <int BM, int BN>
+__global__ __launch_bounds__(256) void k_lstm_cells_fwd(LstmFwdJobs a) {
+  const LstmFwdJobs::Job& J = a.job[blockIdx.y];
+  const int H = a.H, ubn = H >> 5, rb = blockIdx.x / ubn, ub = blockIdx.x - rb * ubn, lane = threadIdx.x & 63, g = threadIdx.x >> 6;
+  const int j = rb * 32 + (lane & 31), k = ub * 32 + g * 8 + (lane >> 5) * 4;
+  float4 pre[4];
+#pragma unroll
+  for (int q = 0; q < 4; ++q) pre[q] = lstm_sum<BM, BN>(J.pre, rb, q * H + ub * 32, g, lane);
+  const int64_t pos = lstm_pos(rb, ub, ubn, g, lane);
+  const float4 ce = J.c_enter[pos];
+  const bool live = j < a.ne, reset = live && a.done[J.idx[j]] != 0;
+  float4 act[4], cn;
+  float hv[4];
+#pragma unroll
+  for (int e = 0; e < 4; ++e) {
+    auto at = [e](float4& v) -> float& { return (&v.x)[e]; };
+    auto val = [e](const float4& v) { return (&v.x)[e]; };
+    float x[4];
+#pragma unroll
+    for (int q = 0; q < 4; ++q) x[q] = val(pre[q]) + J.bias[q * H + k + e];
+    const float ig = sigmoidf_(x[0]), fg = sigmoidf_(x[1]), gg = tanhf(x[2]), og = sigmoidf_(x[3]);
+    at(act[0]) = ig; at(act[1]) = fg; at(act[2]) = gg; at(act[3]) = og;
+    const float c = fg * val(ce) + ig * gg;
+    hv[e] = og * tanhf(c);
+    at(cn) = reset ? 0.f : c;
+  }
+#pragma unroll
+  for (int q = 0; q < 4; ++q) J.gates[(((int64_t)rb * ubn + ub) * 4 + q) * 256 + g * 64 + lane] = act[q];
+  if (J.c_next) J.c_next[pos] = cn;
+  if (!live) return;
+  const uint2 h2 = make_uint2(pack2bf(hv[0], hv[1]), pack2bf(hv[2], hv[3]));
+  *reinterpret_cast<uint2*>(J.h_out + (int64_t)j * J.ld_out + k) = h2;
+  if (J.h_next) *reinterpret_cast<uint2*>(J.h_next + (int64_t)j * J.ld_next + k) = reset ? make_uint2(0u, 0u) : h2;
+}
+
+struct LstmBwdJobs {
+  static constexpr int MAXL = 4;
+  int ne, H;
+  const uint8_t* done;
+  struct Job {
+    LstmPart above;               // gradient w.r.t. h from the layer above (part NULL: the bf16 rows dh)
+    const bf16_t* dh;
+    int64_t ld_dh;
+    LstmPart rec;                 // gradient w.r.t. the state that entered the next step (part NULL at the last step)
+    int rec_col;                  // its first column
+    const int32_t* idx;
+    const float4 *c_enter, *gates;
+    float4* dc;                   // gradient w.r.t. the cell state that entered the next step (in) / this one (out)
+    bf16_t* da;                   // [ne][4H] gate pre-activation gradients
+  } job[MAXL];
+};
+template <int BM, int BN>
+__global__ __launch_bounds__(256) void k_lstm_cells_bwd(LstmBwdJobs a) {
+  const LstmBwdJobs::Job& J = a.job[blockIdx.y];
+  const int H = a.H, ubn = H >> 5, rb = blockIdx.x / ubn, ub = blockIdx.x - rb * ubn, lane = threadIdx.x & 63, g = threadIdx.x >> 6;
+  const int j = rb * 32 + (lane & 31), k = ub * 32 + g * 8 + (lane >> 5) * 4;
+  const bool live = j < a.ne, cut = live && a.done[J.idx[j]] != 0;
+  float4 dh = make_float4(0.f, 0.f, 0.f, 0.f), dc_in = dh;
+  if (J.above.part) dh = lstm_sum<BM, BN>(J.above, rb, ub * 32, g, lane);
+  else if (live) {
+    const uint2 v = *reinterpret_cast<const uint2*>(J.dh + (int64_t)j * J.ld_dh + k);
+    dh = make_float4(bf2f((bf16_t)(v.x & 0xffffu)), bf2f((bf16_t)(v.x >> 16)), bf2f((bf16_t)(v.y & 0xffffu)), bf2f((bf16_t)(v.y >> 16)));
+  }
+  const int64_t pos = lstm_pos(rb, ub, ubn, g, lane);
+  if (J.rec.part) {
+    const float4 r = lstm_sum<BM, BN>(J.rec, rb, J.rec_col + ub * 32, g, lane), d = J.dc[pos];
+    if (!cut) { dh.x += r.x; dh.y += r.y; dh.z += r.z; dh.w += r.w; dc_in = d; }
+  }
+  float4 act[4];
+#pragma unroll
+  for (int q = 0; q < 4; ++q) act[q] = J.gates[(((int64_t)rb * ubn + ub) * 4 + q) * 256 + g * 64 + lane];
+  const float4 ce4 = J.c_enter[pos];
+  float d[4][4];
+  float4 dco;
+#pragma unroll
+  for (int e = 0; e < 4; ++e) {
+    auto val = [e](const float4& v) { return (&v.x)[e]; };
+    const float ig = val(act[0]), fg = val(act[1]), gg = val(act[2]), og = val(act[3]), ce = val(ce4), dhe = val(dh);
+    const float tc = tanhf(fg * ce + ig * gg), dc = dhe * og * (1.f - tc * tc) + val(dc_in);
+    d[0][e] = dc * gg * ig * (1.f - ig);
+    d[1][e] = dc * ce * fg * (1.f - fg);
+    d[2][e] = dc * ig * (1.f - gg * gg);
+    d[3][e] = dhe * tc * og * (1.f - og);
+    (&dco.x)[e] = dc * fg;
+  }
+  J.dc[pos] = dco;
+  if (!live) return;
+#pragma unroll
+  for (int q = 0; q < 4; ++q)
+    *reinterpret_cast<uint2*>(J.da + (int64_t)j * 4 * H + q * H + k) = make_uint2(pack2bf(d[q][0], d[q][1]), pack2bf(d[q][2], d[q][3]));
 }
 
 // d[r][0..cols) = 0 where x[r][0..cols) <= 0 (rows of stride ld_d / ld_x): the ReLU mask of a stored activation

@@ -121,3 +121,32 @@ def test_stored_images_bit_exact_at_any_width(L, ci, dtype, h, w):
         z = torch.zeros(13, device="cuda")
         lrn.buffer_write(t, obs, torch.zeros(13, net["proprio_dim"], device="cuda"), torch.zeros(13, net["act_dim"], device="cuda"), z, z, z, z.to(torch.uint8))
         assert torch.equal(lrn.buffer_read_obs(t), obs.to(torch.bfloat16))
+
+
+@pytest.mark.parametrize("layers,units,N,T,P", [(2, 64, 33, 5, 8), (1, 96, 70, 3, 40), (3, 32, 9, 4, 16), (2, 24, 40, 4, 8), (4, 32, 130, 2, 8), (2, 160, 65, 1, 8), (2, 64, 200, 6, 8)])
+def test_gradients_recurrent(L, layers, units, N, T, P):
+    """LSTM layers side by side (units in multiples of 32; up to 64 environments: 64 x 64 tiles, more: 128 x 128) and one
+    after the other (24 units): one minibatch with episode ends and initial states against the oracle's
+    bf16-operand mode (a wide clip range: no sample sits on a decision)."""
+    import torch
+    cfg = configs.get_config(1, num_envs=N, horizon=T)
+    cfg["net"].update(in_h=16, in_w=20, conv_ch=[8, 16], fc_dim=[32], proprio_dim=P, embed_dim=16, layer_norm=1, lstm_layers=layers, lstm_units=units)
+    net, hp = cfg["net"], dict(cfg["hp"], epochs=1, minibatches=1, seed=3, clip_eps=1e3)
+    ro = synth.rollout(cfg, conditioned=True)
+    rng = np.random.default_rng(units)
+    ro["done"] = (rng.random((T, N)) < 0.1).astype(np.uint8)
+    h0, c0 = (0.3 * rng.standard_normal((2, layers, N, units))).astype(np.float32)
+    params = synth.init_params(net, 4)
+    lrn = L.Learner(net, N, T, "bf16")
+    lrn.set_params(params)
+    fill_learner(lrn, cfg, ro)
+    lrn.buffer_write_state(torch.from_numpy(h0).cuda(), torch.from_numpy(c0).cuda())
+    lrn.gae(torch.from_numpy(ro["last_value"]).cuda(), hp["gamma"], hp["lam"])
+    lrn.update(hp)
+    adv, ret = orc.gae(ro["reward"], ro["done"], ro["value"], ro["last_value"], hp["gamma"], hp["lam"])
+    with orc.quant(1):
+        _, qg = orc.seq_ppo_loss_grad(net, params, ro["obs"], ro["proprio"], ro["action"], ro["logp_old"], ro["value"], adv, ret, ro["done"], h0, c0,
+                                      clip_eps=hp["clip_eps"], vclip_eps=hp["vclip_eps"], vf_coef=hp["vf_coef"], ent_coef=hp["ent_coef"])
+    g = lrn.get_grads()
+    bad = {n: rel_l2(g[a:b], qg[a:b]) for n, (a, b, _) in synth.param_slices(net).items() if rel_l2(g[a:b], qg[a:b]) > TOL_BF16}
+    assert not bad, bad

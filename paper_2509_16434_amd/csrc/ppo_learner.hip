@@ -1464,7 +1464,11 @@ int encoder_backward_seq(Ctx* c, const int32_t* idx, int n, bool acc, const bf16
       {
         ProfScope ps(c, "layer_norm_bwd", 14.0 * (double)nimg * e, 6.0 * (double)nimg * e);
         dy.prepare();
-        hipLaunchKernelGGL(k_ln_bwd, dim3(grid), dim3(LN_THREADS), 0, c->stream, dy, c->pre[l], c->lnstat[l], nimg, (int)e, Co, c->p + c->lnG[l], c->p + c->lnB[l], c->dpre, c->partial);
+        // an image whose input and gradient fit one block's registers is read once
+        const int64_t pch = cdiv(e / 8, LN_THREADS);  // 16-byte chunks per thread
+        const bool rows16 = dy.stride_b % 8 == 0 && dy.stride_v % 8 == 0;
+        auto kfn = !rows16 ? k_ln_bwd : pch <= 3 ? k_ln_bwd_reg<3> : pch <= 5 ? k_ln_bwd_reg<5> : pch <= 10 ? k_ln_bwd_reg<10> : pch <= 19 ? k_ln_bwd_reg<19> : k_ln_bwd;
+        hipLaunchKernelGGL(kfn, dim3(grid), dim3(LN_THREADS), 0, c->stream, dy, c->pre[l], c->lnstat[l], nimg, (int)e, Co, c->p + c->lnG[l], c->p + c->lnB[l], c->dpre, c->partial);
         LAUNCHCHK(c, "k_ln_bwd");
       }
       defer_reduce(c, 0, grid, 2 * Co, 0, 0, c->g + c->lnG[l], nullptr, acc, false, 0, nullptr);  // gain and shift gradients are adjacent

@@ -74,6 +74,23 @@ __global__ __launch_bounds__(LN_THREADS) void k_ln_fwd(const bf16_t* __restrict_
   }
 }
 
+// This block's gain and shift gradients: the threads' channel sums, added in thread order.
+__device__ __forceinline__ void ln_bwd_partial(const float (&dg)[8], const float (&db)[8], float (*acc)[17], int C, float* __restrict__ partial) {
+  const int tid = threadIdx.x;
+  __syncthreads();
+#pragma unroll
+  for (int j = 0; j < 8; ++j) { acc[tid][j] = dg[j]; acc[tid][8 + j] = db[j]; }
+  __syncthreads();
+  // channel c is held by the threads t with (8 t) mod C = 8 floor(c / 8): t = c/8 + k C/8
+  const int groups = C >> 3;
+  for (int o = tid; o < 2 * C; o += LN_THREADS) {
+    const int c = o < C ? o : o - C, col = (o < C ? 0 : 8) + (c & 7);
+    float s = 0.f;
+    for (int t = c >> 3; t < LN_THREADS; t += groups) s += acc[t][col];
+    partial[(int64_t)blockIdx.x * 2 * C + o] = s;
+  }
+}
+
 // Backward of the layer normalisation and of the ReLU behind it.  dy: gradient w.r.t. the rectified output,
 // addressed like the forward's output; x, stats: the forward's input and statistics.  The ReLU passes gradient
 // where gain[c] xhat + shift[c] > 0 (recomputed here exactly as the forward formed it, so dy may or may not have
@@ -123,18 +140,96 @@ __global__ __launch_bounds__(LN_THREADS) void k_ln_bwd(ImgAddr dy, const bf16_t*
       dxo[k] = make_uint4(pack2bf(o[0], o[1]), pack2bf(o[2], o[3]), pack2bf(o[4], o[5]), pack2bf(o[6], o[7]));
     }
   }
-  __syncthreads();
+  ln_bwd_partial(dg, db, acc, C, partial);
+}
+
+// The same for images whose input and gradient both fit the registers of one block (NCH 16-byte chunks of each per
+// thread, m <= 4096 * NCH): both are read once, all of an image's loads in flight together, instead of twice (the second
+// time from L2 or the last-level cache).  Bound by memory; an 8-wave block with up to 256 registers per thread holds
+// 76 800 elements of both (60x80x16), and CUs that load overlap with CUs that store.
+// The teacher's four layers, 4096 images: 886 -> 702 us (4.0 -> 5.1 TB/s of the three streams' bytes).
+// What the optimiser must not see through between the two passes: it would widen a chunk to floats once and keep those,
+// and sink the channel sums' updates below the barrier with their operands alive - 26 registers per chunk instead of 8.
+#define LN_OPAQUE(v) asm volatile("" : "+v"((v).x), "+v"((v).y), "+v"((v).z), "+v"((v).w))
+template <int NCH>
+__global__ __launch_bounds__(LN_THREADS, 2) void k_ln_bwd_reg(ImgAddr dy, const bf16_t* __restrict__ x, const float2* __restrict__ stats, int nimg, int m,
+                                                              int C, const float* __restrict__ gain, const float* __restrict__ shift, bf16_t* __restrict__ dx,
+                                                              float* __restrict__ partial) {
+  __shared__ float red[2][LN_THREADS / 64];
+  __shared__ float acc[LN_THREADS][17];  // per-thread channel sums (padded rows: conflict-free column walks)
+  const int tid = threadIdx.x, wave = tid >> 6;
+  const int c0 = (tid * 8) & (C - 1);
+  const uint32_t bytes = (uint32_t)m * 2u, off0 = (uint32_t)tid * 16u;
+  float dg[8], db[8];
 #pragma unroll
-  for (int j = 0; j < 8; ++j) { acc[tid][j] = dg[j]; acc[tid][8 + j] = db[j]; }
-  __syncthreads();
-  // channel c is held by the threads t with (8 t) mod C = 8 floor(c / 8): t = c/8 + k C/8
-  const int groups = C >> 3;
-  for (int o = tid; o < 2 * C; o += LN_THREADS) {
-    const int c = o < C ? o : o - C, col = (o < C ? 0 : 8) + (c & 7);
-    float s = 0.f;
-    for (int t = c >> 3; t < LN_THREADS; t += groups) s += acc[t][col];
-    partial[(int64_t)blockIdx.x * 2 * C + o] = s;
+  for (int j = 0; j < 8; ++j) { dg[j] = 0.f; db[j] = 0.f; }
+  for (int img = blockIdx.x; img < nimg; img += gridDim.x) {
+    // buffer descriptors: one 32-bit offset per lane for every chunk (64-bit addresses would cost the registers that the
+    // data needs), and the hardware's bounds check returns zeros - no gradient - beyond the image and drops the stores
+    typedef uint32_t u32x4_t __attribute__((ext_vector_type(4)));
+    auto rsrc = [bytes](const bf16_t* p) { return __builtin_amdgcn_make_buffer_rsrc(const_cast<bf16_t*>(p), 0, bytes, 0x00027000); };
+    const auto rx = rsrc(x + (int64_t)img * m), rd = rsrc(dy.ptr_uniform(img)), ro = rsrc(dx + (int64_t)img * m);
+    uint4 xv[NCH], dv[NCH];
+#pragma unroll
+    for (int j = 0; j < NCH; ++j) {
+      xv[j] = __builtin_bit_cast(uint4, __builtin_amdgcn_raw_buffer_load_b128(rx, off0 + j * LN_THREADS * 16, 0, 0));
+      dv[j] = __builtin_bit_cast(uint4, __builtin_amdgcn_raw_buffer_load_b128(rd, off0 + j * LN_THREADS * 16, 0, 0));
+    }
+    __builtin_amdgcn_sched_barrier(0);
+    const float2 st = stats[img];
+    const float rstd = st.y, mr = st.x * rstd;
+    float gr[8], br[8];   // the forward's y = x * gr + br
+#pragma unroll
+    for (int j = 0; j < 8; ++j) { gr[j] = gain[c0 + j] * rstd; br[j] = shift[c0 + j] - st.x * gr[j]; }
+    float s1 = 0.f, s2 = 0.f;  // sums of dxhat * rstd and of that times xhat
+#pragma unroll
+    for (int j = 0; j < NCH; ++j) {
+      const uint32_t xw[4] = {xv[j].x, xv[j].y, xv[j].z, xv[j].w}, dw[4] = {dv[j].x, dv[j].y, dv[j].z, dv[j].w};
+#pragma unroll
+      for (int e = 0; e < 8; ++e) {
+        const float f = __uint_as_float(e & 1 ? xw[e >> 1] & 0xffff0000u : xw[e >> 1] << 16), d = __uint_as_float(e & 1 ? dw[e >> 1] & 0xffff0000u : dw[e >> 1] << 16);
+        const float dj = (f * gr[e] + br[e] > 0.f) ? d : 0.f;
+        const float xh = f * rstd - mr, dxh = dj * gr[e];
+        s1 += dxh; s2 += dxh * xh;
+        dg[e] += dj * xh; db[e] += dj;
+      }
+      LN_OPAQUE(xv[j]); LN_OPAQUE(dv[j]);
+#pragma unroll
+      for (int e = 0; e < 8; ++e) asm volatile("" : "+v"(dg[e]), "+v"(db[e]));
+      __builtin_amdgcn_sched_barrier(0);
+    }
+#pragma unroll
+    for (int off = 32; off > 0; off >>= 1) { s1 += __shfl_xor(s1, off); s2 += __shfl_xor(s2, off); }
+    __syncthreads();  // the previous image's sums have been read
+    if ((tid & 63) == 0) { red[0][wave] = s1; red[1][wave] = s2; }
+    __syncthreads();
+    float a1 = 0.f, a2 = 0.f;
+#pragma unroll
+    for (int w = 0; w < LN_THREADS / 64; ++w) { a1 += red[0][w]; a2 += red[1][w]; }
+    a1 /= (float)m; a2 /= (float)m;
+    const float xs = -a2 * rstd, xc = a2 * mr - a1;  // dx = dj * gr - (a1 + xhat a2)
+#pragma unroll
+    for (int j = 0; j < NCH; ++j) {
+      const uint32_t xw[4] = {xv[j].x, xv[j].y, xv[j].z, xv[j].w}, dw[4] = {dv[j].x, dv[j].y, dv[j].z, dv[j].w};
+      uint32_t ow[4];
+#pragma unroll
+      for (int q = 0; q < 4; ++q) {
+        float r[2];
+#pragma unroll
+        for (int h = 0; h < 2; ++h) {
+          const int e = 2 * q + h;
+          const float f = __uint_as_float(h ? xw[q] & 0xffff0000u : xw[q] << 16), d = __uint_as_float(h ? dw[q] & 0xffff0000u : dw[q] << 16);
+          const float dj = (f * gr[e] + br[e] > 0.f) ? d : 0.f;
+          r[h] = dj * gr[e] + (f * xs + xc);
+        }
+        ow[q] = pack2bf(r[0], r[1]);
+      }
+      const u32x4_t o4 = {ow[0], ow[1], ow[2], ow[3]};
+      __builtin_amdgcn_raw_buffer_store_b128(o4, ro, off0 + j * LN_THREADS * 16, 0, 0);
+      __builtin_amdgcn_sched_barrier(0);
+    }
   }
+  ln_bwd_partial(dg, db, acc, C, partial);
 }
 
 // The forward kernel for images that fit the registers of one 1024-thread block (NCH 16-byte chunks per thread,

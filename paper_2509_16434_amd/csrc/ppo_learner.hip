@@ -27,6 +27,7 @@
 #include "conv_dgrad_k2_tile.hip.h"
 #include "conv0_tile.hip.h"
 #include "conv0_wgrad_tile.hip.h"
+#include "conv_small.hip.h"
 #include "head_loss.hip.h"
 #include "wgrad_rs.hip.h"
 #include "peaks.hip.h"
@@ -560,7 +561,7 @@ int flush_reduces(Ctx* c) {
 }
 // Make room for a kernel that would like `need` partial and `bneed` bias-partial elements.
 int ensure_partial(Ctx* c, int64_t need, int64_t bneed) {
-  if (need > c->partial_elems || bneed > c->bias_partial_elems || c->rjobs.njobs + 2 > ReduceJobs::MAXJ) return flush_reduces(c);
+  if (need > c->partial_elems || bneed > c->bias_partial_elems || c->rjobs.njobs + 3 > ReduceJobs::MAXJ) return flush_reduces(c);
   return PPO_OK;
 }
 // Queue the reduction of `splits` partials of n elements that start at the cursor (kind as in ReduceJobs) and
@@ -1090,6 +1091,75 @@ int aux_head_backward(Ctx* c, const bf16_t* h, int n, bool acc, bf16_t* dh, bf16
   return PPO_OK;
 }
 
+// Both convolutions of a small network in one kernel (conv_small.hip.h): one-channel images whose pixels, activation and
+// gradient fit half of the LDS (up to about 96 x 96).
+bool conv_small_covers(const Ctx* c) {
+  return c->nconv == 2 && c->cC[0] == 1 && c->cC[1] == 8 && c->cC[2] == 16 && !c->ln && c->E == 0 && c->nl == 0 &&
+         ConvSmallShape::covers(c->cH[0], c->cW[0], c->cH[1], c->cH[2], c->cW[2]);
+}
+ConvSmallArgs conv_small_args(Ctx* c, const int32_t* idx, int nimg, int64_t first) {
+  ConvSmallArgs a = {};
+  a.in.base = c->obs + first * c->img_elems * c->V; a.in.idx = idx; a.in.stride_b = c->img_elems * c->V; a.in.stride_v = c->img_elems; a.in.V = c->V;
+  a.in.prepare();
+  a.w0 = c->shadow + c->convW[0]; a.w1 = c->shadow + c->convW[1]; a.w1t = c->wtap[1]; a.b0 = c->p + c->convB[0]; a.b1 = c->p + c->convB[1];
+  a.feat_ld = c->feat_ld; a.V = c->V; a.flat = c->flat; a.nimg = nimg;
+  a.H = c->cH[0]; a.W = c->cW[0]; a.Ho0 = c->cH[1]; a.Wo0 = c->cW[1]; a.Ho1 = c->cH[2]; a.Wo1 = c->cW[2];
+  a.dv0 = make_fastdiv(a.Wo0); a.dv1 = make_fastdiv(a.Wo1); a.dvr = make_fastdiv(a.W / 8);
+  return a;
+}
+// Blocks per CU: what the LDS and the registers (two waves per SIMD backward, three forward) hold at once.
+int conv_small_grid(Ctx* c, const ConvSmallArgs& a, bool bwd, int* grid, int* lds, int* ch) {
+  static uint64_t attr_devs = 0;  /* bit d: set on device d */
+  if (!((attr_devs >> c->dev) & 1)) {
+    for (const void* k : {(const void*)k_conv_small_fwd<1>, (const void*)k_conv_small_fwd<2>, (const void*)k_conv_small_fwd<ConvSmallShape::CHUNKS>,
+                          (const void*)k_conv_small_bwd<1>, (const void*)k_conv_small_bwd<2>, (const void*)k_conv_small_bwd<ConvSmallShape::CHUNKS>})
+      HIPCHK(c, hipFuncSetAttribute(k, hipFuncAttributeMaxDynamicSharedMemorySize, 80 * 1024));
+    attr_devs |= 1ull << c->dev;
+  }
+  *ch = cdiv(std::max(a.H * (a.W / 8), bwd ? a.Ho1 * a.Wo1 * 2 : 0), 256);
+  *lds = std::max(ConvSmallShape::block_bytes(a.W, a.Ho0, a.Ho1, a.Wo1, bwd), bwd ? 4 * ConvSmallShape::RED * 4 : 0);
+  *grid = std::min(a.nimg, 256 * std::min(bwd ? 2 : 3, 160 * 1024 / *lds));
+  return PPO_OK;
+}
+int conv_small_forward(Ctx* c, const int32_t* idx, int n, int64_t first) {
+  const int nimg = n * c->V;
+  ConvSmallArgs a = conv_small_args(c, idx, nimg, first);
+  a.feat = c->feat; a.proprio = c->proprio + first * c->P; a.P = c->P;
+  int grid, lds, ch;
+  { const int erc = conv_small_grid(c, a, false, &grid, &lds, &ch); if (erc) return erc; }
+  const double m0 = (double)nimg * a.Ho0 * a.Wo0, m1 = (double)nimg * a.Ho1 * a.Wo1;
+  ProfScope ps(c, "conv_small_fwd", 2.0 * (m0 * 72 + m1 * 1152), 2.0 * ((double)nimg * c->img_elems + m1 * 16));
+  if (ch <= 1) hipLaunchKernelGGL(k_conv_small_fwd<1>, dim3(grid), dim3(256), lds, c->stream, a);
+  else if (ch <= 2) hipLaunchKernelGGL(k_conv_small_fwd<2>, dim3(grid), dim3(256), lds, c->stream, a);
+  else hipLaunchKernelGGL(k_conv_small_fwd<ConvSmallShape::CHUNKS>, dim3(grid), dim3(256), lds, c->stream, a);
+  LAUNCHCHK(c, "k_conv_small_fwd");
+  c->abits_ok[0] = false;
+  return PPO_OK;
+}
+// from the masked gradient of the feature matrix in gbuf[cur]
+int conv_small_backward(Ctx* c, const int32_t* idx, int n, bool acc, int cur) {
+  const int nimg = n * c->V;
+  ConvSmallArgs a = conv_small_args(c, idx, nimg, 0);
+  a.dfeat = c->gbuf[cur];
+  int grid, lds, ch;
+  { const int erc = conv_small_grid(c, a, true, &grid, &lds, &ch); if (erc) return erc; }
+  { const int erc = ensure_partial(c, (int64_t)grid * (1152 + 80), (int64_t)grid * 16); if (erc) return erc; }
+  grid = (int)std::min<int64_t>(grid, std::min(c->partial_elems / (1152 + 80), c->bias_partial_elems / 16));
+  if (grid < 1) return fail(c, PPO_ENOMEM, "weight-gradient workspace too small for the convolutions");
+  a.part1 = c->partial; a.bpart1 = c->bias_partial; a.part0 = c->partial + (int64_t)grid * 1152;
+  {
+    const double m0 = (double)nimg * a.Ho0 * a.Wo0, m1 = (double)nimg * a.Ho1 * a.Wo1;
+    ProfScope ps(c, "conv_small_bwd", 2.0 * (2.0 * m0 * 72 + 2.0 * m1 * 1152), 2.0 * ((double)nimg * c->img_elems + m1 * 16));
+    if (ch <= 1) hipLaunchKernelGGL(k_conv_small_bwd<1>, dim3(grid), dim3(256), lds, c->stream, a);
+    else if (ch <= 2) hipLaunchKernelGGL(k_conv_small_bwd<2>, dim3(grid), dim3(256), lds, c->stream, a);
+    else hipLaunchKernelGGL(k_conv_small_bwd<ConvSmallShape::CHUNKS>, dim3(grid), dim3(256), lds, c->stream, a);
+    LAUNCHCHK(c, "k_conv_small_bwd");
+  }
+  defer_reduce(c, 0, grid, 1152, 0, 0, c->g + c->convW[1], nullptr, acc, true, 16, c->g + c->convB[1]);
+  defer_reduce(c, 2, grid, 80, 8, 9, c->g + c->convW[0], c->g + c->convB[0], acc, false, 0, nullptr);
+  return PPO_OK;
+}
+
 // Encoder of the feed-forward configurations: convolutions with fused bias + ReLU, the last one writing into the
 // feature matrix, whose tail columns receive the proprioception.  `n` samples selected by device indices idx
 // (NULL: samples first .. first + n - 1 of the buffer).
@@ -1097,6 +1167,7 @@ int encoder_forward_ff(Ctx* c, const int32_t* idx, int n, int64_t first) {
   const int V = c->V, nimg = n * V;
   bool proprio_done = false;
   if (idx) first = 0;
+  if (conv_small_covers(c)) return conv_small_forward(c, idx, n, first);
   const bf16_t* const proprio = c->proprio + first * c->P;
   {  // first convolution straight from the rollout buffer
     ImgAddr in; in.base = c->obs + first * c->img_elems * V; in.idx = idx; in.stride_b = c->img_elems * V; in.stride_v = c->img_elems; in.V = V;
@@ -1227,6 +1298,10 @@ int trunk_backward(Ctx* c, const bf16_t* xin, int64_t ldin, bool mask_in, int n,
 // by the last conv layer's ReLU).
 int encoder_backward_ff(Ctx* c, const int32_t* idx, int n, bool acc, int cur) {
   const int V = c->V, nimg = n * V;
+  if (conv_small_covers(c)) {
+    const int rc = conv_small_backward(c, idx, n, acc, cur);
+    return rc ? rc : flush_reduces(c);
+  }
   for (int l = c->nconv - 1; l >= 1; --l) {
     const int Co = c->cC[l + 1], Ci = c->cC[l], Ho = c->cH[l + 1], Wo = c->cW[l + 1], H = c->cH[l], W = c->cW[l];
     ImgAddr dy = conv_out_addr(c, l, c->gbuf[cur], c->gbuf[cur]);
@@ -2116,6 +2191,7 @@ int create_impl(Ctx* c) {
     if (16 * (int64_t)c->H > bneed) bneed = 16 * (int64_t)c->H;
     pe_sum += need; bpe_sum += bneed;
   }
+  if (conv_small_covers(c)) { pe_sum += 1024LL * (1152 + 80); bpe_sum += 1024LL * 16; }
   if (c->ln) pe_sum += 1024LL * 2 * 1024;  // layer-norm gain / shift partials: one per block of k_ln_bwd
   if (c->XH > 0) {
     int64_t need, bneed;

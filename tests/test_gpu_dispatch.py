@@ -150,3 +150,11 @@ def test_gradients_recurrent(L, layers, units, N, T, P):
     g = lrn.get_grads()
     bad = {n: rel_l2(g[a:b], qg[a:b]) for n, (a, b, _) in synth.param_slices(net).items() if rel_l2(g[a:b], qg[a:b]) > TOL_BF16}
     assert not bad, bad
+
+
+@pytest.mark.parametrize("h,w,N,T", [(32, 32, 16, 8), (28, 31, 33, 4), (29, 42, 5, 3), (64, 64, 300, 4), (60, 89, 40, 4), (33, 65, 1100, 2)])
+def test_small_network_convolutions(L, h, w, N, T):
+    """Both convolutions of the small network in one kernel: odd sizes, ragged last pixels, fewer and more images than waves."""
+    cfg = configs.get_config(0, num_envs=N, horizon=T)
+    cfg["net"]["in_h"], cfg["net"]["in_w"] = h, w
+    _check_gradients(L, cfg, N, T)

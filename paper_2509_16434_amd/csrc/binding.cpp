@@ -25,12 +25,17 @@ bool device_ptr(PyObject* o, at::ScalarType dt, int64_t numel, void** out) {
   *out = nullptr;
   if (o == Py_None) return true;
   if (!THPVariable_Check(o)) { PyErr_Format(PyExc_TypeError, "expected a torch.Tensor or None, got %s", Py_TYPE(o)->tp_name); return false; }
-  const at::Tensor& t = THPVariable_Unpack(o);
-  if (!t.is_cuda() || !t.is_contiguous()) { PyErr_SetString(PyExc_ValueError, "expected a contiguous CUDA tensor"); return false; }
-  if (t.scalar_type() != dt) { PyErr_Format(PyExc_ValueError, "expected dtype %s, got %s", dtype_name(dt), dtype_name(t.scalar_type())); return false; }
-  if (t.numel() != numel) { PyErr_Format(PyExc_ValueError, "expected %lld elements, got %lld", (long long)numel, (long long)t.numel()); return false; }
-  *out = t.data_ptr();
-  return true;
+  try {  // a tensor without storage of its own (a tracer's stand-in) throws when asked for its address
+    const at::Tensor& t = THPVariable_Unpack(o);
+    if (!t.is_cuda() || !t.is_contiguous()) { PyErr_SetString(PyExc_ValueError, "expected a contiguous CUDA tensor"); return false; }
+    if (t.scalar_type() != dt) { PyErr_Format(PyExc_ValueError, "expected dtype %s, got %s", dtype_name(dt), dtype_name(t.scalar_type())); return false; }
+    if (t.numel() != numel) { PyErr_Format(PyExc_ValueError, "expected %lld elements, got %lld", (long long)numel, (long long)t.numel()); return false; }
+    *out = t.data_ptr();
+    return true;
+  } catch (const std::exception& e) {
+    PyErr_SetString(PyExc_RuntimeError, e.what());
+    return false;
+  }
 }
 
 bool integers(PyObject* const* args, int n, long long* out) {

@@ -141,3 +141,20 @@ def test_binding_refuses_host_tensors():
         L._dev(torch.zeros(4))
     with pytest.raises(ValueError):
         L._dev(torch.zeros(4, device="meta") if False else torch.zeros(2, 2).t())
+
+
+def test_native_binding_turns_tensor_errors_into_exceptions():
+    """A tensor that has no address (inside vmap) is an exception of the call, not the end of the process."""
+    import torch
+    from torch._subclasses import FakeTensorMode
+    seen = []
+
+    def call(x):
+        with pytest.raises(RuntimeError):
+            L._native.outcome(0, 0, 4, x, None)
+        seen.append(1)
+        return x
+
+    with FakeTensorMode():
+        torch.func.vmap(call)(torch.empty(3, 4, device="cuda"))
+    assert seen

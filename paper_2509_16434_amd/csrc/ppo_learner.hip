@@ -2255,6 +2255,13 @@ int to_canonical(Ctx* c, const float* dev, float* canon) {
   LAUNCHCHK(c, "k_param_map");
   const int64_t np = cdiv(c->total, HSTAGE);
   const int team = np < 2 * HSTAGE_TEAM ? 1 : HSTAGE_TEAM;
+  // One piece has nothing to overlap with: straight into the caller's memory (70 k parameters 44 -> 38 us, 235 k 73 -> 66;
+  // a context's first read, which would allocate the staging, 72 -> 41 and 96 -> 67).
+  if (np == 1) {
+    HIPCHK(c, hipMemcpyAsync(canon, c->canon, sizeof(float) * (size_t)c->total, hipMemcpyDeviceToHost, c->stream));
+    HIPCHK(c, hipStreamSynchronize(c->stream));
+    return PPO_OK;
+  }
   if (!c->hstage) {
     HIPCHK(c, hipHostMalloc((void**)&c->hstage, sizeof(float) * (size_t)std::min(np, (int64_t)2 * team) * HSTAGE, hipHostMallocDefault));
     for (int i = 0; i < 2 * team; ++i) HIPCHK(c, hipEventCreateWithFlags(&c->hstage_ev[i], hipEventDisableTiming));

@@ -158,3 +158,15 @@ def test_small_network_convolutions(L, h, w, N, T):
     cfg = configs.get_config(0, num_envs=N, horizon=T)
     cfg["net"]["in_h"], cfg["net"]["in_w"] = h, w
     _check_gradients(L, cfg, N, T)
+
+
+@pytest.mark.parametrize("ci,hw", [(0, 28), (0, 60), (0, 64), (1, 64), (2, 120)])
+def test_parameter_read_back(L, ci, hw):
+    """Read-back of one piece (straight into the caller's memory), of two and five (staged by one thread) and of many (by four)."""
+    net = configs.get_config(ci)["net"]
+    net["in_h"] = net["in_w"] = hw
+    params = synth.init_params(net, 2)
+    lrn = L.Learner(net, 4, 1, "bf16")
+    lrn.set_params(params)
+    for _ in range(2):
+        np.testing.assert_array_equal(lrn.get_params(), params)

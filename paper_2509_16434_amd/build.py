@@ -48,15 +48,15 @@ def build_lib(force: bool = True, verbose: bool = False) -> str:
             for cmd in cmds.values():
                 print(" ".join(cmd))
         runs = {n: subprocess.Popen(cmd, stdout=subprocess.DEVNULL, stderr=subprocess.PIPE, text=True) for n, cmd in cmds.items()}
-        for name, r in runs.items():
-            _, err = r.communicate()
-            err = "\n".join(l for l in err.splitlines() if "packed-fp32-ops" not in l)
-            if r.returncode != 0:
-                for other in runs.values():
-                    other.wait()
-                raise RuntimeError(f"{name} failed:\n" + err)
-            if verbose and err.strip():
-                print(err)
+        # every process is read to its end before any failure is reported: one left with a full pipe never ends
+        errs = {n: "\n".join(l for l in r.communicate()[1].splitlines() if "packed-fp32-ops" not in l) for n, r in runs.items()}
+        failed = [f"{n} failed:\n{errs[n]}" for n, r in runs.items() if r.returncode != 0]
+        if failed:
+            raise RuntimeError("\n".join(failed))
+        if verbose:
+            for err in errs.values():
+                if err.strip():
+                    print(err)
     return LIB
 
 

@@ -4,6 +4,7 @@ import ctypes as C
 import os
 import re
 import subprocess
+import sys
 
 import pytest
 
@@ -158,3 +159,14 @@ def test_native_binding_turns_tensor_errors_into_exceptions():
     with FakeTensorMode():
         torch.func.vmap(call)(torch.empty(3, 4, device="cuda"))
     assert seen
+
+
+def test_build_reports_failures_of_both_compilers(tmp_path):
+    """A compiler that fails while the other still has more to say than a pipe holds: the build ends, with both messages."""
+    noisy = tmp_path / "cc"
+    noisy.write_text("#!/bin/sh\nhead -c 300000 /dev/zero | tr '\\0' x >&2\necho >&2\necho last line of $1 >&2\nexit 1\n")
+    noisy.chmod(0o755)
+    # in a child: a build that hangs is killed, not waited for
+    code = "import os, sys\nfrom paper_2509_16434_amd import build\nbuild.HIPCC = 'false'\nbuild.binding_command = lambda: [sys.argv[1], 'binding']\nbuild.build_lib()\n"
+    r = subprocess.run([sys.executable, "-c", code, str(noisy)], cwd=ROOT, capture_output=True, text=True, timeout=60)
+    assert r.returncode == 1 and "hipcc failed" in r.stderr and "last line of binding" in r.stderr

@@ -2,6 +2,7 @@
 // permutation, first-layer convolution (K = 9 or 27: too thin for MFMA), losses, Adam and
 // weight re-packing.
 #pragma once
+#include "../../include/ppo_learner.h"
 #include "common.hip.h"
 #include "gemm.hip.h"
 
@@ -996,7 +997,8 @@ __global__ __launch_bounds__(256) void k_param_map(ParamMap pm, const float* __r
 //   column tap v given by (px, dx): even pixel (px = 0) takes v = 1 from dx = 0 and nothing from
 //   dx = 1; odd pixel takes v = 2 from dx = 0 and v = 0 from dx = 1.
 struct RepackJobs {
-  static constexpr int MAXJ = 32;
+  static constexpr int MAXT = 12;                              // transposed copies a network may have
+  static constexpr int MAXJ = MAXT + 2 * (PPO_MAX_LAYERS - 1);  // and two packed copies of every convolution but the first
   int njobs;
   int first[MAXJ + 1];
   int kind[MAXJ], a[MAXJ], b[MAXJ], ld[MAXJ];

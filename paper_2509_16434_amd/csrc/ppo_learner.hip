@@ -275,6 +275,9 @@ int validate_desc(const ppo_net_desc* d) {
   if (d->lstm_layers > 0 && (d->lstm_units < 8 || d->lstm_units % 8 || d->lstm_units > 4096)) return fail(nullptr, PPO_ESHAPE, "lstm_units must be a multiple of 8 in 8..4096");
   if (d->lstm_layers == 0 && d->lstm_units != 0) return fail(nullptr, PPO_ESHAPE, "lstm_units without lstm_layers");
   if (d->lstm_layers > 0 && !d->has_value_head) return fail(nullptr, PPO_ESHAPE, "recurrent layers are built for the actor-critic teacher (has_value_head = 1)");
+  // every convolution but the first, hidden layer, head, auxiliary, embedding and LSTM matrix has a transposed copy
+  if (d->n_conv - 1 + d->n_fc + 1 + (d->aux_hidden > 0 ? 2 : 0) + (d->embed_dim > 0 ? 1 : 0) + d->lstm_layers > RepackJobs::MAXT)
+    return fail(nullptr, PPO_ESHAPE, "too many layers for one re-pack launch");
   return PPO_OK;
 }
 
@@ -660,7 +663,7 @@ int launch_wgrad(Ctx* c, const DL& dl_, const AL& al_, int Nn, int Kk, int M, fl
   return PPO_OK;
 }
 
-// Re-packs of the weights into the layouts the backward kernels read, collected into one launch.
+// Re-packs of the weights into the layouts the backward kernels read, collected into one launch (validate_desc bounds their number).
 struct RepackList {
   RepackJobs jobs;
   int nblocks = 0;
@@ -699,9 +702,6 @@ int repack_weights(Ctx* c) {
   c->wver += 1;
   ProfScope ps(c, "weight_repack", 0.0, 4.0 * (double)c->total);
   RepackList r;
-  int packed = 0;
-  for (int l = 1; l < c->nconv; ++l) packed += c->wd_used[l] ? 2 : 0;
-  if (c->nconv - 1 + packed + c->nfc + 1 + (c->XH > 0 ? 2 : 0) + (c->E > 0 ? 1 : 0) + c->nl > RepackJobs::MAXJ) return fail(c, PPO_ESHAPE, "too many layers for one re-pack launch");
   for (int l = 1; l < c->nconv; ++l) {
     r.add(1, c->shadow + c->convW[l], c->wtap[l], c->cC[l + 1], c->cC[l], 0, (int64_t)9 * c->cC[l] * c->cC[l + 1]);
     if (c->wd_used[l]) r.add_packed_dgrad(c, l);

@@ -93,6 +93,9 @@ def test_static_permutation_validates_before_touching_the_gpu():
     (dict(has_value_head=0, aux_hidden=16, aux_dim=12), L.PPO_ESHAPE), (dict(has_value_head=0, aux_hidden=16, aux_dim=0), L.PPO_ESHAPE),
     (dict(layer_norm=2), L.PPO_EINVAL), (dict(embed_dim=12), L.PPO_ESHAPE), (dict(lstm_layers=5, lstm_units=16), L.PPO_ESHAPE),
     (dict(lstm_layers=1, lstm_units=12), L.PPO_ESHAPE), (dict(has_value_head=0, lstm_layers=1, lstm_units=16), L.PPO_ESHAPE),
+    # thirteen weight matrices with transposed copies (test_deepest_network_learns has twelve)
+    (dict(conv_ch=[8] * 8, fc_dim=[16] * 5), L.PPO_ESHAPE), (dict(conv_ch=[8] * 8, fc_dim=[16] * 2, embed_dim=16, lstm_layers=2, lstm_units=16), L.PPO_ESHAPE),
+    (dict(conv_ch=[8] * 8, fc_dim=[16] * 3, has_value_head=0, aux_hidden=16, aux_dim=2), L.PPO_ESHAPE), (dict(conv_ch=[8] * 4, fc_dim=[16] * 5, lstm_layers=4, lstm_units=16), L.PPO_ESHAPE),
 ])
 def test_create_rejects_bad_geometry_before_touching_the_gpu(change, code):
     net = dict(configs.get_config(0)["net"], **change)

@@ -170,3 +170,34 @@ def test_parameter_read_back(L, ci, hw):
     lrn.set_params(params)
     for _ in range(2):
         np.testing.assert_array_equal(lrn.get_params(), params)
+
+
+@pytest.mark.parametrize("h,w", [(33, 41), (130, 70)])
+def test_deepest_network_learns(L, h, w):
+    """The largest number of weight re-packs a network may have: twelve transposed copies and, from the first backward
+    pass on, two packed copies of seven convolutions.  Two updates, so that a step follows that pass."""
+    cfg = configs.get_config(0, num_envs=6, horizon=4)
+    net = cfg["net"]
+    net.update(in_h=h, in_w=w, conv_ch=[8] * 8, fc_dim=[32, 16, 24, 16])
+    import torch
+    hp = dict(cfg["hp"], epochs=2, minibatches=1, seed=3, lr=1e-4)
+    ro = synth.rollout(cfg, conditioned=True)
+    params = synth.init_params(net, 9)
+    a, b = (L.Learner(net, 6, 4, cfg["obs_dtype"]) for _ in range(2))
+    for lrn in (a, b):
+        lrn.set_params(params)
+        fill_learner(lrn, cfg, ro)
+        lrn.gae(torch.from_numpy(ro["last_value"]).cuda(), hp["gamma"], hp["lam"])
+    a.update(hp)
+    a.update(hp)
+    # the same steps with fresh copies in front of every update
+    b.update(hp)
+    m, v, step, upd = b.get_opt_state()
+    c = L.Learner(net, 6, 4, cfg["obs_dtype"])
+    c.set_params(b.get_params())
+    c.set_opt_state(m, v, step, upd)
+    fill_learner(c, cfg, ro)
+    c.gae(torch.from_numpy(ro["last_value"]).cuda(), hp["gamma"], hp["lam"])
+    c.update(hp)
+    np.testing.assert_array_equal(a.get_params(), c.get_params())
+    assert np.abs(a.get_params() - params).max() > 1e-4

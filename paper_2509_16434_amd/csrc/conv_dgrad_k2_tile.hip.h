@@ -7,8 +7,8 @@
 // What is different: 9 taps x 128 x 64 weights are twice the registers two compute waves have, so
 // there are four, and the contraction over the gradient channels is split between them: wave
 // (wn, kh) holds the taps' weights for result channels 32 wn .. + 31 and gradient channels
-// 64 kh .. + 63 (144 registers) and stages its partial sum, rounded to bf16, in a staging area of
-// its half; three finishing waves add the halves (in fp32), apply the ReLU mask of the stored
+// 64 kh .. + 63 (144 registers) and stages its partial sum in a staging area of its half; three
+// finishing waves add the halves (in fp32), apply the ReLU mask of the stored
 // activation (sign-bit words) and write (some sixty vector-ALU instructions per 16 bytes: the role
 // that needs the waves).  One loader wave copies the band's dY rows (256 bytes per
 // pixel, 1 KiB per load) into a ring of three LDS images; the 16-byte chunks of each 128-byte half
@@ -16,6 +16,11 @@
 // short rows of such a layer, so that any eight consecutive lanes read eight different chunk
 // positions.  Two barriers per tile order the three roles; the finishing waves work one tile
 // behind the compute waves (double-buffered staging) and fetch their mask words two tiles ahead.
+//
+// Partial sums are staged in fp32 (F32: networks with layer normalisation or an embedding, whose
+// gradient is one fp32 sum over all 128 channels in the implicit-GEMM form too) or rounded to bf16
+// (networks without either: half the LDS, so twice the rows per band where rows are wide; the
+// rounding of the halves adds to the rounding of their sum).
 #pragma once
 #include "conv_dgrad_tile.hip.h"
 
@@ -23,8 +28,8 @@ struct ConvDgradK2Shape {
   static constexpr int CI = 64, CO = 128, PB = CO * 2, BQ = 64, MT = 2, NBUF = 3, THREADS = 512, MAXSEG = 6;
   static constexpr int NFT = 192, MAXCH = 8;  // finishing threads, 16-byte chunks per finishing thread and tile
   static int dyimg_bytes(int Wo, int TQ) { return (TQ + 1) * (Wo + 1) * PB; }
-  static int stage_bytes(int W, int TQ) { return 2 * TQ * W * CI * 2; }
-  static int lds_bytes(int W, int Wo, int TQ) { return NBUF * dyimg_bytes(Wo, TQ) + 4 * stage_bytes(W, TQ); }
+  static int result_bytes(int W, int TQ) { return 2 * TQ * W * CI * 2; }  // a band's result
+  static int lds_bytes(int W, int Wo, int TQ, bool f32) { return NBUF * dyimg_bytes(Wo, TQ) + 4 * (f32 ? 2 : 1) * result_bytes(W, TQ); }
 };
 
 // permutation of the 16-byte chunks within each 128-byte half of a 256-byte dY pixel: `slot` in its row, `row` of the LDS image
@@ -40,7 +45,13 @@ __device__ __forceinline__ uint4 add_bf16x8(const uint4& x, const uint4& y) {
   return make_uint4(add2(x.x, y.x), add2(x.y, y.y), add2(x.z, y.z), add2(x.w, y.w));
 }
 
-template <bool MASK>  // false: as in k_conv_dgrad_tile
+// the same of two vectors of eight fp32
+__device__ __forceinline__ uint4 add_f32x8(const float4* x, const float4* y) {
+  const float4 x0 = x[0], x1 = x[1], y0 = y[0], y1 = y[1];
+  return make_uint4(pack2bf(x0.x + y0.x, x0.y + y0.y), pack2bf(x0.z + y0.z, x0.w + y0.w), pack2bf(x1.x + y1.x, x1.y + y1.y), pack2bf(x1.z + y1.z, x1.w + y1.w));
+}
+
+template <bool MASK, bool F32>  // MASK false: as in k_conv_dgrad_tile
 __global__ __launch_bounds__(512) void k_conv_dgrad_k2_tile(ConvDgradArgs a) {
   typedef ConvDgradK2Shape S;
   constexpr int CI = S::CI, CO = S::CO, PB = S::PB, CC = 4, NBUF = S::NBUF, MT = S::MT;  // CC: 16-deep steps over a wave's 64 gradient channels
@@ -49,7 +60,8 @@ __global__ __launch_bounds__(512) void k_conv_dgrad_k2_tile(ConvDgradArgs a) {
   const int W = a.W, Wo = a.Wo, TQ = a.TQ;
   const int RP = (Wo + 1) * PB;  // dY image row pitch
   const int dyimg_bytes = (TQ + 1) * RP;
-  const int stage_bytes = 2 * TQ * W * CI * 2;
+  constexpr int SB = F32 ? 2 : 1;  // staged bytes per byte of the result
+  const int result_bytes = 2 * TQ * W * CI * 2, stage_bytes = SB * result_bytes;
   char* const stage0 = lds + NBUF * dyimg_bytes;  // [tile parity][gradient-channel half][stage_bytes]
   const int vb = xcd_block((int)blockIdx.x, (int)gridDim.x);  // this block's number in the dealing of tiles
   const int nq = (a.ntiles > vb) ? (a.ntiles - 1 - vb) / (int)gridDim.x + 1 : 0;
@@ -96,7 +108,7 @@ __global__ __launch_bounds__(512) void k_conv_dgrad_k2_tile(ConvDgradArgs a) {
   if (wave >= 5) {
     // ------------------------------------------------------------------ finishing waves: thread et of 192 takes the chunks et, et + 192, ...
     const int et = tid - 320;
-    const int nchunk = stage_bytes >> 4;
+    const int nchunk = result_bytes >> 4;
     // two register sets: the mask of tile q+1 is fetched while tile q-1 is finished
     uint32_t mk[2][S::MAXCH];      // the word holding a chunk's eight mask bits
     int64_t band_off[2] = {0, 0};  // element offset of the set's band within dx
@@ -129,7 +141,9 @@ __global__ __launch_bounds__(512) void k_conv_dgrad_k2_tile(ConvDgradArgs a) {
         const int c = et + S::NFT * i;
         if (c < nchunk && c < nvalid[SET]) {
           const uint32_t L = (uint32_t)c * 16u, ph = L ^ tile_swz_bits<CI>(L);
-          uint4 v = add_bf16x8(*reinterpret_cast<const uint4*>(st + ph), *reinterpret_cast<const uint4*>(st + stage_bytes + ph));
+          uint4 v;
+          if constexpr (F32) v = add_f32x8(reinterpret_cast<const float4*>(st + 2 * ph), reinterpret_cast<const float4*>(st + stage_bytes + 2 * ph));
+          else v = add_bf16x8(*reinterpret_cast<const uint4*>(st + ph), *reinterpret_cast<const uint4*>(st + stage_bytes + ph));
           if constexpr (MASK) {
             const uint32_t b8 = mk[SET][i] >> ((c & 3) * 8);  // this chunk's eight bits
             v.x &= keep_pair(b8, 0); v.y &= keep_pair(b8, 1); v.z &= keep_pair(b8, 2); v.w &= keep_pair(b8, 3);
@@ -239,10 +253,9 @@ __global__ __launch_bounds__(512) void k_conv_dgrad_k2_tile(ConvDgradArgs a) {
           const uint32_t sp = L ^ tile_swz_bits<CI>(L);
 #pragma unroll
           for (int g = 0; g < 4; ++g) {
-            uint2 o;
-            o.x = pack2bf(acc[c][g * 4], acc[c][g * 4 + 1]);
-            o.y = pack2bf(acc[c][g * 4 + 2], acc[c][g * 4 + 3]);
-            *reinterpret_cast<uint2*>(st + (sp ^ (uint32_t)(g * 16))) = o;
+            char* const d = st + SB * (sp ^ (uint32_t)(g * 16));
+            if constexpr (F32) *reinterpret_cast<float4*>(d) = make_float4(acc[c][g * 4], acc[c][g * 4 + 1], acc[c][g * 4 + 2], acc[c][g * 4 + 3]);
+            else *reinterpret_cast<uint2*>(d) = make_uint2(pack2bf(acc[c][g * 4], acc[c][g * 4 + 1]), pack2bf(acc[c][g * 4 + 2], acc[c][g * 4 + 3]));
           }
         }
       }

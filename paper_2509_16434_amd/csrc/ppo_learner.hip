@@ -886,11 +886,11 @@ ConvDgradArgs conv_dgrad_args(Ctx* c, const ImgAddr& dy, const ImgAddr& xa, cons
   return a;
 }
 // The form for 128 gradient channels and 64 result channels (the contraction split over two pairs of compute waves).
-template <bool MASK>
+template <bool MASK, bool F32>
 int launch_conv_dgrad_k2_tile(Ctx* c, ConvDgradArgs a, int nimg, const std::string& name, double flops, double abytes) {
   typedef ConvDgradK2Shape S;
   if (a.Wo > S::BQ) return 1;
-  auto fits = [&](int tq) { return S::stage_bytes(a.W, tq) <= S::MAXCH * S::NFT * 16 && S::lds_bytes(a.W, a.Wo, tq) <= 158 * 1024; };
+  auto fits = [&](int tq) { return S::result_bytes(a.W, tq) <= S::MAXCH * S::NFT * 16 && S::lds_bytes(a.W, a.Wo, tq, F32) <= 158 * 1024; };
   int TQ = S::BQ / a.Wo < a.Ho ? S::BQ / a.Wo : a.Ho;
   while (TQ > 1 && !fits(TQ)) --TQ;
   if (!fits(TQ)) return 1;
@@ -899,20 +899,23 @@ int launch_conv_dgrad_k2_tile(Ctx* c, ConvDgradArgs a, int nimg, const std::stri
   const int segs = cdiv(a.Wo * S::PB, 1024);
   if (segs > S::MAXSEG || (a.TQ + 1) * segs > 63) return 1;
   const int gx = a.ntiles < 256 ? a.ntiles : 256;
-  auto kfn = k_conv_dgrad_k2_tile<MASK>;
+  auto kfn = k_conv_dgrad_k2_tile<MASK, F32>;
   static uint64_t attr_devs = 0;  /* bit d: set on device d */
   if (!((attr_devs >> c->dev) & 1)) { HIPCHK(c, hipFuncSetAttribute((const void*)kfn, hipFuncAttributeMaxDynamicSharedMemorySize, 160 * 1024)); attr_devs |= 1ull << c->dev; }
   ProfScope ps(c, name, flops, abytes);
-  hipLaunchKernelGGL(kfn, dim3(gx), dim3(S::THREADS), S::lds_bytes(a.W, a.Wo, a.TQ), c->stream, a);
+  hipLaunchKernelGGL(kfn, dim3(gx), dim3(S::THREADS), S::lds_bytes(a.W, a.Wo, a.TQ, F32), c->stream, a);
   LAUNCHCHK(c, "k_conv_dgrad_k2_tile");
   return PPO_OK;
 }
-// (xbits NULL: the gradient is left unmasked)
+// (xbits NULL: the gradient is left unmasked; f32: partial sums stay fp32)
 int launch_conv_dgrad_tile(Ctx* c, const ImgAddr& dy, const ImgAddr& xa, const uint32_t* xbits, bf16_t* dx, const bf16_t* wt, int Co, int Ci, int H, int W, int Ho, int Wo,
-                           int nimg, const std::string& name, double flops, double abytes) {
+                           int nimg, const std::string& name, double flops, double abytes, bool f32) {
   if (dy.idx || nimg < 1) return 1;
   const ConvDgradArgs a = conv_dgrad_args(c, dy, xa, xbits, dx, wt, H, W, Ho, Wo);
-  if (Co == 128 && Ci == 64) return xbits ? launch_conv_dgrad_k2_tile<true>(c, a, nimg, name, flops, abytes) : launch_conv_dgrad_k2_tile<false>(c, a, nimg, name, flops, abytes);
+  if (Co == 128 && Ci == 64) {
+    if (!f32) return xbits ? launch_conv_dgrad_k2_tile<true, false>(c, a, nimg, name, flops, abytes) : 1;
+    return xbits ? launch_conv_dgrad_k2_tile<true, true>(c, a, nimg, name, flops, abytes) : launch_conv_dgrad_k2_tile<false, true>(c, a, nimg, name, flops, abytes);
+  }
   if (Co != 64 || (Ci != 32 && Ci != 64)) return 1;
   if (xbits) return Ci == 32 ? launch_conv_dgrad_tile_t<32, 0>(c, a, nimg, name, flops, abytes, nullptr) : launch_conv_dgrad_tile_t<64, 0>(c, a, nimg, name, flops, abytes, nullptr);
   return Ci == 32 ? launch_conv_dgrad_tile_t<32, 0, false>(c, a, nimg, name, flops, abytes, nullptr) : launch_conv_dgrad_tile_t<64, 0, false>(c, a, nimg, name, flops, abytes, nullptr);
@@ -1366,7 +1369,7 @@ int encoder_backward_ff(Ctx* c, const int32_t* idx, int n, bool acc, int cur) {
     }
     double ab = 2.0 * ((double)nimg * Ho * Wo * Co + pix * Ci + 9.0 * Ci * Co) + (c->abits_ok[l - 1] && (Co == 64 || ep.mbits) ? pix * Ci / 8.0 : 2.0 * pix * Ci);
     const double dflops = 2.0 * (double)nimg * Ho * Wo * 9.0 * Ci * Co;
-    rc = !c->abits_ok[l - 1] ? 1 : launch_conv_dgrad_tile(c, dy, xa, c->abits[l - 1], c->gbuf[cur ^ 1], c->wtap[l], Co, Ci, H, W, Ho, Wo, nimg, "conv_dgrad." + std::to_string(l), dflops, ab);
+    rc = !c->abits_ok[l - 1] ? 1 : launch_conv_dgrad_tile(c, dy, xa, c->abits[l - 1], c->gbuf[cur ^ 1], c->wtap[l], Co, Ci, H, W, Ho, Wo, nimg, "conv_dgrad." + std::to_string(l), dflops, ab, false);
     if (rc == PPO_OK + 1) {
       rc = ensure_packed_dgrad_weights(c, l);
       if (rc) return rc;
@@ -1570,7 +1573,7 @@ int encoder_backward_seq(Ctx* c, const int32_t* idx, int n, bool acc, const bf16
     const uint32_t* const xbits = c->ln ? nullptr : c->abits[l - 1];
     if (c->ln || c->abits_ok[l - 1]) {
       rc = launch_conv_dgrad_tile(c, dconv, xa, xbits, c->gbuf[cur ^ 1], c->wtap[l], Co, Ci, H, W, Ho, Wo, nimg, "conv_dgrad." + std::to_string(l), dflops,
-                                  dab + (xbits ? pix * Ci / 8.0 : 0.0));
+                                  dab + (xbits ? pix * Ci / 8.0 : 0.0), true);
       if (rc != PPO_OK && rc != 1) return rc;
       if (rc == PPO_OK) {
         cur ^= 1;

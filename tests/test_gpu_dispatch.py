@@ -59,12 +59,15 @@ def test_gemm_plans(L, M, N, K):
     assert np.abs(L.diag_gemm(a, b) - want).max() <= 1e-4 * np.abs(want).max()
 
 
-def _check_gradients(L, cfg, N, T):
-    """One minibatch of a conditioned rollout: every tensor's gradient against the oracle's bf16-operand mode."""
+def _check_gradients(L, cfg, N, T, change=None):
+    """One minibatch of a conditioned rollout: every tensor's gradient against the oracle's bf16-operand mode (`change`:
+    edits the initial parameters in place)."""
     import torch
     net, hp = cfg["net"], dict(cfg["hp"], epochs=1, minibatches=1, seed=3)
     ro = synth.rollout(cfg, conditioned=True)
     params = synth.init_params(net, 9)
+    if change:
+        change(params)
     lrn = L.Learner(net, N, T, cfg["obs_dtype"])
     lrn.set_params(params)
     distill = cfg["kind"] == "distill"
@@ -201,3 +204,24 @@ def test_deepest_network_learns(L, h, w):
     c.update(hp)
     np.testing.assert_array_equal(a.get_params(), c.get_params())
     assert np.abs(a.get_params() - params).max() > 1e-4
+
+
+@pytest.mark.parametrize("h,w", [(40, 52), (72, 160), (120, 96)])
+def test_gradient_sum_over_128_channels_is_rounded_once(L, h, w):
+    """Transposed convolution from 128 gradient channels in a network with an embedding: channels 64 .. 127 carry the
+    negative of channels 0 .. 63 but for 1/128, so that half-sums rounded to bf16 (2^-9 each) would leave the result
+    with an error of about half of its own size, where one rounding leaves 2^-9."""
+    cfg = configs.get_config(1, num_envs=10, horizon=4)
+    net = cfg["net"]
+    net.update(in_h=h, in_w=w, conv_ch=[16, 32, 64, 128], embed_dim=32)
+
+    def opposed(params):
+        sl = synth.param_slices(net)
+        t = {n: params[a:b].reshape(s) for n, (a, b, s) in sl.items()}   # views
+        t["conv3.w"][64:] = t["conv3.w"][:64]
+        t["conv3.b"][64:] = t["conv3.b"][:64]
+        e = t["emb.w"].reshape(32, 128, -1)
+        e[:, :64] = np.sign(e[:, :64]) * 2.0 ** np.round(np.log2(np.abs(e[:, :64]) + 1e-6))   # both halves exact in bf16
+        e[:, 64:] = -127 / 128 * e[:, :64]
+
+    _check_gradients(L, cfg, 10, 4, opposed)

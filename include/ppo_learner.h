@@ -117,8 +117,8 @@ typedef struct {
   float lr;          /* learning rate this step's Adam update used */
 } ppo_mb_stats;
 
-/* Create a learner for `desc` on the current HIP device; all device memory is
- * allocated here.  `hip_stream` is a hipStream_t (may be NULL).  Parameters
+/* Create a learner for `desc` on the current HIP device; all device memory and the
+ * pinned staging of the parameter read-back are allocated here.  `hip_stream` is a hipStream_t (may be NULL).  Parameters
  * start at zero: load them with ppo_set_params. */
 int ppo_create(ppo_ctx** out, const ppo_net_desc* desc, void* hip_stream);
 int ppo_destroy(ppo_ctx* ctx);

@@ -114,7 +114,7 @@ struct Ctx {
   int CHe = 0;                              // environments per sequence chunk
   ParamMap pmap;             // internal order <-> canonical order
   float* canon = nullptr;    // device staging in canonical order for parameter / gradient / moment I/O
-  float* hstage = nullptr;   // pinned host staging of the same (slots of HSTAGE elements), allocated by the first read
+  float* hstage = nullptr;   // pinned host staging of the same (slots of HSTAGE elements)
   hipEvent_t hstage_ev[8] = {};
   // device: parameters
   float *p = nullptr, *m = nullptr, *v = nullptr, *g = nullptr;
@@ -2057,6 +2057,23 @@ int run_update(Ctx* c, const ppo_hparams* hp, ppo_mb_stats* host_stats, bool dis
   return PPO_OK;
 }
 
+// The way back ends in ordinary host memory.  Every thread of a small team takes pieces of the vector in turn through
+// two pinned staging slots of its own, so that copies into the caller's memory (whose fresh pages fault on first
+// touch) run under the transfers: 22 MB arrive in about 0.6 ms and 64 MB in 1.6 (one thread: 0.8 and 4.4; straight
+// into pageable memory: 1.25 and 6.3; reordered by the host: 8.2 and 20).  Vectors of a few pieces need no team.
+// One piece has nothing to overlap with: straight into the caller's memory (70 k parameters 44 -> 38 us, 235 k 73 -> 66).
+constexpr int64_t HSTAGE = 1 << 18;  // floats per slot (1 MiB)
+constexpr int HSTAGE_TEAM = 4;
+int64_t read_pieces(const Ctx* c) { return cdiv(c->total, HSTAGE); }
+int read_team(const Ctx* c) { return read_pieces(c) < 2 * HSTAGE_TEAM ? 1 : HSTAGE_TEAM; }
+int create_read_staging(Ctx* c) {
+  const int64_t slots = std::min(read_pieces(c), (int64_t)2 * read_team(c));
+  if (slots < 2) return PPO_OK;
+  HIPCHK(c, hipHostMalloc((void**)&c->hstage, sizeof(float) * (size_t)slots * HSTAGE, hipHostMallocDefault));
+  for (int i = 0; i < slots; ++i) HIPCHK(c, hipEventCreateWithFlags(&c->hstage_ev[i], hipEventDisableTiming));
+  return PPO_OK;
+}
+
 int create_impl(Ctx* c) {
   build_geometry(c);
   HIPCHK(c, hipGetDevice(&c->dev));
@@ -2225,6 +2242,8 @@ int create_impl(Ctx* c) {
   HIPCHK(c, hipMemsetAsync(c->shadow, 0, sizeof(bf16_t) * (size_t)(c->total + 8), c->stream));
   int rc = refresh_shadow(c);
   if (rc) return rc;
+  rc = create_read_staging(c);
+  if (rc) return rc;
   HIPCHK(c, hipStreamSynchronize(c->stream));
   c->written.assign((size_t)c->T, 0);
   c->cover.assign((size_t)c->T, {});
@@ -2247,27 +2266,15 @@ int to_internal(Ctx* c, const float* canon, float* dev) {
   HIPCHK(c, hipStreamSynchronize(c->stream));
   return PPO_OK;
 }
-// The way back ends in ordinary host memory.  Every thread of a small team takes pieces of the vector in turn through
-// two pinned staging slots of its own, so that copies into the caller's memory (whose fresh pages fault on first
-// touch) run under the transfers: 22 MB arrive in about 0.6 ms and 64 MB in 1.6 (one thread: 0.8 and 4.4; straight
-// into pageable memory: 1.25 and 6.3; reordered by the host: 8.2 and 20).  Vectors of a few pieces need no team.
-constexpr int64_t HSTAGE = 1 << 18;  // floats per slot (1 MiB)
-constexpr int HSTAGE_TEAM = 4;
 int to_canonical(Ctx* c, const float* dev, float* canon) {
   hipLaunchKernelGGL(k_param_map<false>, dim3(cdiv(c->total, 256)), dim3(256), 0, c->stream, c->pmap, dev, c->canon);
   LAUNCHCHK(c, "k_param_map");
-  const int64_t np = cdiv(c->total, HSTAGE);
-  const int team = np < 2 * HSTAGE_TEAM ? 1 : HSTAGE_TEAM;
-  // One piece has nothing to overlap with: straight into the caller's memory (70 k parameters 44 -> 38 us, 235 k 73 -> 66;
-  // a context's first read, which would allocate the staging, 72 -> 41 and 96 -> 67).
+  const int64_t np = read_pieces(c);
+  const int team = read_team(c);
   if (np == 1) {
     HIPCHK(c, hipMemcpyAsync(canon, c->canon, sizeof(float) * (size_t)c->total, hipMemcpyDeviceToHost, c->stream));
     HIPCHK(c, hipStreamSynchronize(c->stream));
     return PPO_OK;
-  }
-  if (!c->hstage) {
-    HIPCHK(c, hipHostMalloc((void**)&c->hstage, sizeof(float) * (size_t)std::min(np, (int64_t)2 * team) * HSTAGE, hipHostMallocDefault));
-    for (int i = 0; i < 2 * team; ++i) HIPCHK(c, hipEventCreateWithFlags(&c->hstage_ev[i], hipEventDisableTiming));
   }
   auto work = [c, canon, np, team](int t) -> hipError_t {
     auto count = [&](int64_t k) { return std::min(HSTAGE, c->total - k * HSTAGE); };

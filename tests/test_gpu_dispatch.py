@@ -225,3 +225,25 @@ def test_gradient_sum_over_128_channels_is_rounded_once(L, h, w):
         e[:, 64:] = -127 / 128 * e[:, :64]
 
     _check_gradients(L, cfg, 10, 4, opposed)
+
+
+def test_read_back_staging_is_allocated_at_creation(L):
+    """The first read of a context into memory in hand allocates nothing: its pinned staging (two pieces, 2 MiB, for this
+    network) is part of ppo_create."""
+    net = configs.get_config(1)["net"]
+    params = synth.init_params(net, 2)
+    out = np.zeros_like(params)
+
+    def mapped():   # address space of the process, KiB
+        with open("/proc/self/status") as f:
+            return next(int(line.split()[1]) for line in f if line.startswith("VmSize"))
+
+    grown = []
+    keep = [L.Learner(net, 4, 1, "bf16") for _ in range(4)]
+    for lrn in keep:   # the first brings in what the runtime itself keeps
+        lrn.set_params(params)
+        before = mapped()
+        assert L._lib.ppo_get_params(lrn._h, L._fp(out), out.size) == L.PPO_OK
+        grown.append(mapped() - before)
+        np.testing.assert_array_equal(out, params)
+    assert max(grown[1:]) < 1024, grown

@@ -247,3 +247,36 @@ def test_read_back_staging_is_allocated_at_creation(L):
         grown.append(mapped() - before)
         np.testing.assert_array_equal(out, params)
     assert min(grown) < 1024, grown   # (the runtime's own threads may map memory during any of them)
+
+
+def test_read_back_behind_work_on_the_per_thread_stream(L):
+    """hipStreamPerThread (handle 2) names another stream in every thread: what a read-back returns is ordered behind the
+    update before it only if the thread that launched the update queues all of the read-back's transfers."""
+    import types
+
+    import torch
+    cfg = configs.get_config(2, num_envs=64, horizon=4)
+    net, hp = cfg["net"], dict(cfg["hp"], epochs=4, minibatches=2, seed=3)
+    ro = synth.rollout(cfg, conditioned=True)
+    params = synth.init_params(net, 9)
+    dt = torch.float32 if cfg["obs_dtype"] == "fp32" else torch.bfloat16
+    steps = [[torch.from_numpy(ro["obs"][t]).to("cuda", dt).contiguous()] +
+             [torch.from_numpy(ro[k][t]).cuda().contiguous() for k in ("proprio", "action", "logp_old", "value", "reward", "done")] for t in range(4)]
+    last = torch.from_numpy(ro["last_value"]).cuda()
+    torch.cuda.synchronize()
+    got = []
+    for stream in (None, types.SimpleNamespace(cuda_stream=2, synchronize=torch.cuda.synchronize)):
+        lrn = L.Learner(net, 64, 4, cfg["obs_dtype"], stream=stream)
+        lrn.set_params(params)
+        for t, d in enumerate(steps):
+            lrn.buffer_write(t, *d)
+        lrn.gae(last, hp["gamma"], hp["lam"])
+        reads = []
+        for _ in range(2):
+            lrn.update(hp, want_stats=False)   # asynchronous
+            reads.append(lrn.get_params())
+        got.append(reads + [lrn.get_grads()] + list(lrn.get_opt_state()[:2]))
+    assert got[0][0].size >= 8 << 18           # pieces for a team
+    for x, y in zip(*got):
+        np.testing.assert_array_equal(x, y)
+    assert not np.array_equal(got[0][0], got[0][1])

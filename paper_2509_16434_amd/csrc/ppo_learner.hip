@@ -1503,6 +1503,16 @@ int encoder_forward_generic(Ctx* c, const int32_t* idx, int n, int64_t first) {
   return PPO_OK;
 }
 
+// Layer-normalisation backward in registers by the number of 16-byte chunks per thread.  A form for every number: one
+// made for more chunks than the image has spends the others' instructions and registers on zeros (two layers, 2048
+// images, the first of 4096 values per chunk, us: 1 chunk 58, in a form for three 79, read twice 63; 6 chunks 106, in a
+// form for ten 156, read twice 127; 11 chunks 180, in a form for nineteen 219, read twice 200).
+template <int... N>
+decltype(&k_ln_bwd) ln_bwd_reg(int chunks, std::integer_sequence<int, N...>) {
+  static const decltype(&k_ln_bwd) form[] = {k_ln_bwd_reg<N + 1>...};
+  return form[chunks - 1];
+}
+
 // Its backward from d(features) in `dfeat` (row stride ld_df; with an embedding its columns [v*E, (v+1)*E) are the
 // gradient of view v's embedding, without one the masked gradient of the last convolution's activation).
 int encoder_backward_seq(Ctx* c, const int32_t* idx, int n, bool acc, const bf16_t* dfeat, int64_t ld_df, int cur) {
@@ -1546,7 +1556,7 @@ int encoder_backward_seq(Ctx* c, const int32_t* idx, int n, bool acc, const bf16
         // an image whose input and gradient fit one block's registers is read once
         const int64_t pch = cdiv(e / 8, LN_THREADS);  // 16-byte chunks per thread
         const bool rows16 = dy.stride_b % 8 == 0 && dy.stride_v % 8 == 0;
-        auto kfn = !rows16 ? k_ln_bwd : pch <= 3 ? k_ln_bwd_reg<3> : pch <= 5 ? k_ln_bwd_reg<5> : pch <= 10 ? k_ln_bwd_reg<10> : pch <= 19 ? k_ln_bwd_reg<19> : k_ln_bwd;
+        auto kfn = rows16 && pch <= LN_BWD_CHUNKS ? ln_bwd_reg((int)pch, std::make_integer_sequence<int, LN_BWD_CHUNKS>()) : k_ln_bwd;
         hipLaunchKernelGGL(kfn, dim3(grid), dim3(LN_THREADS), 0, c->stream, dy, c->pre[l], c->lnstat[l], nimg, (int)e, Co, c->p + c->lnG[l], c->p + c->lnB[l], c->dpre, c->partial);
         LAUNCHCHK(c, "k_ln_bwd");
       }

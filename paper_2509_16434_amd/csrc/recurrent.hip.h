@@ -9,6 +9,7 @@
 
 #define LN_EPS 1e-5f
 #define LN_THREADS 512
+#define LN_BWD_CHUNKS 19  // largest NCH of k_ln_bwd_reg (252 of 256 registers)
 
 // idx[t*ne + j] = t*N + env[j]: the rollout samples of the chunk's environments, time-major.
 __global__ void k_seq_index(const int32_t* __restrict__ env, int ne, int T, int N, int32_t* __restrict__ idx) {

@@ -107,6 +107,14 @@ def test_gradients_with_layer_norm(L, c0, conv, h, w):
     _check_gradients(L, cfg, 10, 4)
 
 
+@pytest.mark.parametrize("chunks", range(1, 21))
+def test_layer_norm_backward_of_any_chunk_count(L, chunks):
+    """One form of the layer-normalisation backward per number of 16-byte chunks a thread holds (up to 19; 20 reads
+    twice): the first layer's 16 x (16 chunks - 0 .. 2) x 16 values fill the last chunk or part of it."""
+    cfg = configs.get_config(1, num_envs=10, horizon=2)
+    cfg["net"].update(in_h=32, in_w=32 * chunks - 2 * (chunks % 3), conv_ch=[16, 8], fc_dim=[32], layer_norm=1)
+    _check_gradients(L, cfg, 10, 2)
+
 
 @pytest.mark.parametrize("ci,dtype", [(0, "fp32"), (0, "bf16"), (3, "fp32"), (3, "bf16")])
 @pytest.mark.parametrize("h,w", [(5, 7), (6, 8), (4, 9), (3, 15), (9, 33)])

@@ -101,7 +101,7 @@ struct Ctx {
   bf16_t* embT = nullptr;                   // [flat][E]
   bf16_t* lstmWT[4] = {};                   // [lin + H][4H]
   bf16_t* xh[4] = {};                       // LSTM layer inputs [CH][lin + H]: x_t, then the h entering step t (xh[0] is the feature matrix)
-  bf16_t* dxh[4] = {};                      // their gradients
+  bf16_t* dxh[4] = {};                      // their gradients (side by side: the bottom layer's x half)
   float* gates[4] = {};                     // [CH][4H] gate activations
   float* c_enter[4] = {};                   // [CH][H] cell state entering each step
   float* lstm_pre = nullptr;                // [CHe][4H] gate pre-activations of one step
@@ -418,19 +418,21 @@ inline int class_len(int n, int par) { return (n - par + 1) / 2; }
 // ---------------------------------------------------------------- launch helpers
 inline int ilog2(int x) { int l = 0; while ((1 << l) < x) ++l; return l; }
 
-// How a product with plain rows (C [M][N] = A [M][K] B^T) is cut up.  Every form is a chain of k-steps of 64 per tile, of
+// With few tiles and short rows (<= 512 tiles of 32 x 32 at K <= 512, <= 128 at K <= 2048) the latency of an LDS ring
+// is the larger part of a product with plain rows, and k_gemm_small wins (64 x 64 x 1056: 7.9 -> 4.7 us; 1250 x 128 x 256:
+// 5.1 -> 3.4 us; beyond these lines its operand traffic, 32 x 32 per tile, loses: 4096 x 256 x 512: 7.0 against 9.6 us).
+bool gemm_small_covers(int M, int N, int K) {
+  const int64_t t32 = (int64_t)cdiv(M, 32) * cdiv(N, 32);
+  return (t32 <= 512 && K <= 512) || (t32 <= 128 && K <= 2048);
+}
+// How a product with plain rows (C [M][N] = A [M][K] B^T) and K >= 1024 is cut up otherwise.  Every form is a chain of k-steps of 64 per tile, of
 // measured length (us, operands in L2 / the last-level cache, chip full): 0.34 for a 64 x 64 tile, 0.60 for 128 x 128, 1.0
 // for 256 x 128, behind 3.5 us of launch, ring fill and epilogue; a reduction over `splits` slices of K costs another 3 us
 // and its fp32 partials at 6 TB/s.  The plan is the form with the smallest sum, blocks counted in rounds of 256 CUs: e.g.
 // 4096 x 512 x 10304 leaves two rounds of 64 x 64 tiles (107 us) for 64 tiles of 256 x 128 in four slices (53 us);
 // 16384 x 512 x 10304 stays one round of undivided 256 x 128 tiles (157 us).
-// With few tiles and short rows (<= 512 tiles of 32 x 32 at K <= 512, <= 128 at K <= 2048) the LDS ring's own
-// latency is the larger part, and k_gemm_small wins (64 x 64 x 1056: 7.9 -> 4.7 us; 1250 x 128 x 256: 5.1 -> 3.4 us;
-// beyond these lines its operand traffic, 32 x 32 per tile, loses: 4096 x 256 x 512: 7.0 against 9.6 us).
-struct GemmPlan { int bm, bn, splits, W; };  // bm = 32: k_gemm_small; splits > 1: W k-steps per slice
+struct GemmPlan { int bm, bn, splits, W; };  // splits > 1: W k-steps per slice
 GemmPlan plan_gemm(int M, int N, int K, int64_t partial_elems) {
-  const int64_t t32 = (int64_t)cdiv(M, 32) * cdiv(N, 32);
-  if ((t32 <= 512 && K <= 512) || (t32 <= 128 && K <= 2048)) return {32, 32, 1, 0};
   const int nk = cdiv(K, 64);
   GemmPlan best = {64, 64, 1, nk};
   double tbest = 1e30;
@@ -482,15 +484,20 @@ int launch_gemm(Ctx* c, const AL& al_, int M, const bf16_t* Bm, int64_t ldb, int
   const char* what = name.c_str();
   ProfScope ps(c, name, flops >= 0.0 ? flops : 2.0 * M * (double)N * K, abytes);
   dim3 blk(256);
-  if constexpr (std::is_same<AL, ARows>::value) {
-    const GemmPlan plan = plan_gemm(M, N, K, c->partial_elems > 4 ? c->partial_elems - 4 : 0);
-    if (al.plain && (plan.bm == 32 || K >= 1024)) {
+  constexpr bool rows = std::is_same<AL, ARows>::value;
+  if constexpr (rows) {
+    if (!al.plain) return fail(c, PPO_ESHAPE, "%s: rows of images have no product of their own", what);
+    if (gemm_small_covers(M, N, K)) {
+      const dim3 grid(cdiv(M, 32), cdiv(N, 32));
+      if (K <= 512) hipLaunchKernelGGL((k_gemm_small<4, EP>), grid, dim3(256), 0, c->stream, al.a.base, al.a.stride_b, M, Bm, ldb, N, K, ep);
+      else hipLaunchKernelGGL((k_gemm_small<8, EP>), grid, dim3(512), 0, c->stream, al.a.base, al.a.stride_b, M, Bm, ldb, N, K, ep);
+      LAUNCHCHK(c, what);
+      return PPO_OK;
+    }
+    if (K >= 1024) {
+      const GemmPlan plan = plan_gemm(M, N, K, c->partial_elems > 4 ? c->partial_elems - 4 : 0);
       int rc = PPO_OK;
-      if (plan.bm == 32) {
-        const dim3 grid(cdiv(M, 32), cdiv(N, 32));
-        if (K <= 512) hipLaunchKernelGGL((k_gemm_small<4, EP>), grid, dim3(256), 0, c->stream, al.a.base, al.a.stride_b, M, Bm, ldb, N, K, ep);
-        else hipLaunchKernelGGL((k_gemm_small<8, EP>), grid, dim3(512), 0, c->stream, al.a.base, al.a.stride_b, M, Bm, ldb, N, K, ep);
-      } else if (plan.bn == 32) rc = launch_gemm_ring<128, 32, 4, 1>(c, al, M, Bm, ldb, N, K, ep, plan);
+      if (plan.bn == 32) rc = launch_gemm_ring<128, 32, 4, 1>(c, al, M, Bm, ldb, N, K, ep, plan);
       else if (plan.bm == 64) rc = launch_gemm_ring<64, 64, 2, 2>(c, al, M, Bm, ldb, N, K, ep, plan);
       else if (plan.bn == 64) rc = launch_gemm_ring<128, 64, 2, 2>(c, al, M, Bm, ldb, N, K, ep, plan);
       else if (plan.bm == 128) rc = launch_gemm_ring<128, 128, 2, 2>(c, al, M, Bm, ldb, N, K, ep, plan);
@@ -500,10 +507,10 @@ int launch_gemm(Ctx* c, const AL& al_, int M, const bf16_t* Bm, int64_t ldb, int
       return PPO_OK;
     }
   }
-  // Very deep reductions stream their operands through an LDS ring of up to eight stages, filled by
-  // four loader waves while four or eight other waves compute (k_gemm_rs); medium ones take 64-wide
-  // steps through registers, where the smaller LDS footprint lets more blocks share a CU and hide
-  // the prologue and epilogue of their short loops.
+  // Very deep reductions of gathered rows stream their operands through an LDS ring of up to eight stages, filled by
+  // four loader waves while four or eight other waves compute (k_gemm_rs; plain rows took plan_gemm's forms above);
+  // medium ones take 64-wide steps through registers, where the smaller LDS footprint lets more blocks share a CU and
+  // hide the prologue and epilogue of their short loops.
 #define LAUNCH_GEMM_RS(BM_, BN_, WM_, WN_)                                                                              \
   do {                                                                                                                   \
     constexpr int ncw = WM_ * WN_;                                                                                       \
@@ -517,12 +524,11 @@ int launch_gemm(Ctx* c, const AL& al_, int M, const bf16_t* Bm, int64_t ldb, int
 #define LAUNCH_GEMM(BM_, BN_, WM_, WN_, GX, GY)                                                                        \
   do {                                                                                                                   \
     dim3 grid(GX, GY, zdim);                                                                                             \
-    if constexpr (WM_ * WN_ != 4) {                                                                                      \
-      LAUNCH_GEMM_RS(BM_, BN_, WM_, WN_);                                                                                \
-    } else if (K >= 1024) {                                                                                              \
-      LAUNCH_GEMM_RS(BM_, BN_, WM_, WN_);                                                                                \
-    } else if (K >= 128) hipLaunchKernelGGL((k_gemm<BM_, BN_, WM_, WN_, 64, AL, EP>), grid, blk, 0, c->stream, al, Bm, ldb, N, ep); \
-    else hipLaunchKernelGGL((k_gemm<BM_, BN_, WM_, WN_, 32, AL, EP>), grid, blk, 0, c->stream, al, Bm, ldb, N, ep);        \
+    if constexpr (!rows) { if (K >= 1024) { LAUNCH_GEMM_RS(BM_, BN_, WM_, WN_); break; } }                                \
+    if constexpr (WM_ * WN_ == 4) {                                                                                      \
+      if (K >= 128) hipLaunchKernelGGL((k_gemm<BM_, BN_, WM_, WN_, 64, AL, EP>), grid, blk, 0, c->stream, al, Bm, ldb, N, ep); \
+      else hipLaunchKernelGGL((k_gemm<BM_, BN_, WM_, WN_, 32, AL, EP>), grid, blk, 0, c->stream, al, Bm, ldb, N, ep);      \
+    }                                                                                                                    \
   } while (0)
   if (N > 64) {
     if (K >= 1024 && (int64_t)cdiv(M, 256) * cdiv(N, 128) * zdim >= 256) LAUNCH_GEMM(256, 128, 4, 2, cdiv(M, 256), cdiv(N, 128));
@@ -1401,8 +1407,8 @@ int backward_chunk(Ctx* c, const int32_t* idx, int n, bool acc, bool with_head =
 }
 
 // ---------------------------------------------------------------- encoder with layer normalisation and / or embedding
-// Every convolution through the implicit-GEMM kernels without the fused ReLU; with layer_norm the convolution
-// output is stored (pre), normalised per image and rectified by k_ln_fwd; without it the ReLU stays in the
+// The LDS-image kernels where they cover a layer, else the implicit-GEMM ones; with layer_norm without the ReLU: the
+// convolution's output is stored (pre), normalised per image and rectified by k_ln_fwd; without it the ReLU stays in the
 // convolution's epilogue.  The last layer's activation goes into the feature matrix, or (embed_dim > 0) into a
 // buffer of its own that the embedding GEMM reads, view by view.
 static ImgAddrW as_w(const ImgAddr& a) { ImgAddrW w; w.base = const_cast<bf16_t*>(a.base); w.stride_b = a.stride_b; w.stride_v = a.stride_v; w.V = a.V; return w; }
@@ -1773,8 +1779,9 @@ int lstm_backward_side_by_side(Ctx* c, const bf16_t* dtop, int ne) {
 }
 
 // Forward of a chunk of `ne` whole environments (device list env) x T steps, rows time-major.  Encoder on all
-// ne*T rows at once, then per LSTM layer and step one GEMM (the operand row [x_t, h_enter] against the layer's
-// [W_ih, W_hh]) and one cell kernel, then hidden layers and heads on all rows.
+// ne*T rows at once, then the LSTM (products of the operand rows [x_t, h_enter] with [W_ih, W_hh] and cell kernels: the
+// layers side by side, or, for units that are no multiple of 32, one layer and step after the other), then hidden layers
+// and heads on all rows.
 int forward_seq_chunk(Ctx* c, const int32_t* env, int ne, bool with_head) {
   const int T = c->T, n = ne * T, H = c->H;
   hipLaunchKernelGGL(k_seq_index, dim3(cdiv(n, 256)), dim3(256), 0, c->stream, env, ne, T, c->N, c->seqidx);
@@ -1814,10 +1821,10 @@ int forward_seq_chunk(Ctx* c, const int32_t* env, int ne, bool with_head) {
   return trunk_forward(c, c->nl > 0 ? c->htop : c->feat, c->nl > 0 ? (int64_t)H : c->feat_ld, n, with_head);
 }
 
-// Its backward: heads and hidden layers on all rows, then back-propagation through time per LSTM layer (top
-// first): per step the cell's backward kernel and one GEMM that turns the gate gradients into the gradient of
-// the operand row [x_t, h_enter] - its h half is what step t-1 receives -; the layer's weight gradient is one
-// contraction over all rows afterwards.  Then the encoder's backward on all rows.
+// Its backward: heads and hidden layers on all rows, then back-propagation through time: per step the cells' backward
+// and a product that turns the gate gradients into the gradient of the operand row [x_t, h_enter] - its h half is what
+// step t-1 receives -, the layers side by side or (other units) one after the other, the top one first; a layer's weight
+// gradient is one contraction over all rows afterwards.  Then the encoder's backward on all rows.
 int backward_seq_chunk(Ctx* c, int ne, bool acc, bool with_head) {
   const int T = c->T, n = ne * T, H = c->H;
   int cur = 0;
@@ -2158,7 +2165,7 @@ int create_impl(Ctx* c) {
       const int64_t K = c->lin[l] + H;
       DALLOC(c, c->lstmWT[l], K * 4 * H);
       if (l > 0) DALLOC(c, c->xh[l], (int64_t)CH * K);
-      DALLOC(c, c->dxh[l], (int64_t)CH * K);
+      if (l == 0 || !lstm_side_by_side(c)) DALLOC(c, c->dxh[l], (int64_t)CH * K);  // side by side, upper layers' stay in lstm_part
       const int64_t rows = std::max<int64_t>(CH, c->T * lstm_tiled_rows(c, c->CHe));
       DALLOC(c, c->gates[l], rows * 4 * H); DALLOC(c, c->c_enter[l], rows * H);
       DALLOC(c, c->da[l], (int64_t)CH * 4 * H); DALLOC(c, c->dc_carry[l], lstm_tiled_rows(c, c->CHe) * H);

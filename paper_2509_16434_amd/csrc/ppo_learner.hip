@@ -633,6 +633,9 @@ int launch_wgrad_rs(Ctx* c, const bf16_t* dy, int64_t ld_dy, const bf16_t* x, in
 template <class DL, class AL>
 int launch_wgrad(Ctx* c, const DL& dl_, const AL& al_, int Nn, int Kk, int M, float* gw, float* gb, bool accumulate, const std::string& name, double abytes) {
   if (M <= 0) return PPO_OK;
+  // the queued sums of one launch run side by side: one that this gradient is added to is taken first
+  for (int j = 0; accumulate && j < c->rjobs.njobs; ++j)
+    if (c->rjobs.dst[j] == gw) { const int erc = flush_reduces(c); if (erc) return erc; }
   if constexpr (std::is_same<DL, ARows>::value && std::is_same<AL, ARows>::value) {
     if (dl_.plain && al_.plain) {
       const int rc = launch_wgrad_rs(c, dl_.a.base, dl_.a.stride_b, al_.a.base, al_.a.stride_b, Nn, Kk, M, gw, gb, accumulate, name, abytes);

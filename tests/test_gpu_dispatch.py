@@ -89,6 +89,21 @@ def _check_gradients(L, cfg, N, T, change=None):
     assert not bad, bad
 
 
+def _check_forward(L, cfg, N, T):
+    """Action means and values of some stored samples, chosen by index, against the oracle."""
+    import torch
+    net, ro = cfg["net"], synth.rollout(cfg, conditioned=True)
+    params = synth.init_params(net, 9)
+    lrn = L.Learner(net, N, T, cfg["obs_dtype"])
+    lrn.set_params(params)
+    fill_learner(lrn, cfg, ro)
+    idx = np.random.default_rng(1).permutation(N * T)[: max(1, N * T // 2)].astype(np.int32)
+    mu, v = (x.cpu().numpy() for x in lrn.forward(torch.from_numpy(idx).cuda()))
+    with orc.quant(1):
+        omu, ov = orc.forward(net, params, ro["obs"].reshape((N * T,) + ro["obs"].shape[2:])[idx], ro["proprio"].reshape(N * T, -1)[idx])
+    assert rel_l2(mu, omu) <= TOL_BF16 and rel_l2(v, ov) <= TOL_BF16
+
+
 @pytest.mark.parametrize("ci,h,w", [(1, 51, 61), (1, 49, 58), (1, 89, 117), (1, 31, 33), (1, 45, 90), (3, 49, 58), (2, 62, 101)])
 def test_gradients_odd_second_layer_width(L, ci, h, w):
     """Widths whose first-layer output is odd."""
@@ -169,6 +184,16 @@ def test_small_network_convolutions(L, h, w, N, T):
     cfg = configs.get_config(0, num_envs=N, horizon=T)
     cfg["net"]["in_h"], cfg["net"]["in_w"] = h, w
     _check_gradients(L, cfg, N, T)
+
+@pytest.mark.parametrize("c0,conv,h,w,views,more", [(1, (16, 32), 33, 47, 2, {}), (1, (16, 32, 64, 128), 40, 72, 2, {}), (3, (32, 64, 64), 37, 53, 2, {}),
+                                                    (3, (16, 32), 18, 66, 3, dict(embed_dim=24)), (1, (32, 64), 16, 130, 4, dict(embed_dim=32)),
+                                                    (1, (8, 64, 128), 52, 60, 2, dict(embed_dim=16, layer_norm=0))])
+def test_gradients_of_several_views_behind_layer_norm_or_embedding(L, c0, conv, h, w, views, more):
+    """Strides between views in the unmasked transposed convolutions and the first layer's weight gradient from a stored one."""
+    cfg = configs.get_config(1, num_envs=10, horizon=4)
+    cfg["net"].update(dict(in_c=c0, in_h=h, in_w=w, n_views=views, conv_ch=list(conv), layer_norm=1), **more)
+    _check_gradients(L, cfg, 10, 4)
+    _check_forward(L, cfg, 10, 4)
 
 
 @pytest.mark.parametrize("ci,hw", [(0, 28), (0, 60), (0, 64), (1, 64), (2, 120)])

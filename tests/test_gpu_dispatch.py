@@ -185,6 +185,15 @@ def test_small_network_convolutions(L, h, w, N, T):
     cfg["net"]["in_h"], cfg["net"]["in_w"] = h, w
     _check_gradients(L, cfg, N, T)
 
+@pytest.mark.parametrize("h,w,views,P,N,T", [(32, 32, 2, 16, 9, 4), (33, 47, 3, 8, 5, 3), (60, 89, 2, 2056, 70, 4), (28, 31, 4, 2064, 3, 2), (64, 64, 2, 4096, 300, 2)])
+def test_small_network_convolutions_of_several_views(L, h, w, views, P, N, T):
+    """Views share a sample's proprioception, which is copied once, its first 2048 columns ahead of the rest."""
+    cfg = configs.get_config(0, num_envs=N, horizon=T)
+    cfg["net"].update(in_h=h, in_w=w, n_views=views, proprio_dim=P)
+    _check_gradients(L, cfg, N, T)
+    _check_forward(L, cfg, N, T)
+
+
 @pytest.mark.parametrize("c0,conv,h,w,views,more", [(1, (16, 32), 33, 47, 2, {}), (1, (16, 32, 64, 128), 40, 72, 2, {}), (3, (32, 64, 64), 37, 53, 2, {}),
                                                     (3, (16, 32), 18, 66, 3, dict(embed_dim=24)), (1, (32, 64), 16, 130, 4, dict(embed_dim=32)),
                                                     (1, (8, 64, 128), 52, 60, 2, dict(embed_dim=16, layer_norm=0))])

@@ -2800,7 +2800,8 @@ int ppo_diag_gemm(int32_t M, int32_t N, int32_t K, const float* h_a, const float
     DALLOC(c, da, (int64_t)M * K); DALLOC(c, db, (int64_t)N * K); DALLOC(c, dc, (int64_t)M * N);
     DALLOC(c, ba, (int64_t)M * K); DALLOC(c, bb, (int64_t)N * K);
     DALLOC(c, c->zpage, 32768);
-    c->partial_elems = (int64_t)8 * (M + 256) * (N + 128) + 4;  // room for the split reductions
+    // room for split reductions; what would need more fills the chip undivided (1 GiB: 32 tiles of 256 x 128 for every CU)
+    c->partial_elems = std::min<int64_t>((int64_t)8 * (M + 256) * (N + 128), 1 << 28) + 4;
     DALLOC(c, c->partial, c->partial_elems);
     HIPCHK(c, hipMemset(c->zpage, 0, 65536));
     HIPCHK(c, hipMemcpy(da, h_a, sizeof(float) * (size_t)M * K, hipMemcpyHostToDevice));

@@ -65,6 +65,8 @@ typedef struct {
   int32_t n_fc, fc_dim[PPO_MAX_LAYERS];    /* hidden widths, each a multiple of 8, n_fc >= 1 */
   int32_t has_value_head;            /* 1 actor-critic (PPO), 0 distillation student */
   int32_t max_chunk;                 /* samples per forward/backward pass inside a minibatch; 0 = default */
+  /* (n_conv - 1) + n_fc + 1 head + 2 with the auxiliary head below + 1 with an embedding + lstm_layers must be at
+   * most 12 (else PPO_ESHAPE). */
   /* The deployed student's extra MLP head (Sec. IV-C: "an extra MLP head that predicts the position of the
    * object"): with aux_hidden > 0 (a multiple of 8; students only) the last aux_dim (1 .. act_dim-1) output
    * columns are  W_a2 relu(W_a1 h + b_a1) + b_a2  on the last hidden layer h, and the linear head has

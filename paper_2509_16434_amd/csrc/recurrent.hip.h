@@ -1,7 +1,7 @@
 // Kernels of the paper's own teacher network (Sec. III-C, Fig. 3) beyond convolutions and linear layers:
 // layer normalisation after a convolution (forward with the ReLU, backward with the gain / shift gradients),
-// the LSTM cell (forward and backward of one time step for all environments of a chunk; the matrix products
-// around it are the library's GEMM kernels), and the small index / state kernels of sequence minibatches.
+// the LSTM cells (forward and backward of one time step for all environments of a chunk, of one layer or of all layers
+// side by side; the matrix products around them are the library's GEMM kernels), and the small index / state kernels of sequence minibatches.
 // Rows of a sequence chunk are time-major: row = t * ne + j for environment j of the chunk's ne environments.
 #pragma once
 #include "common.hip.h"

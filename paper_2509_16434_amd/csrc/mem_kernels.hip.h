@@ -771,7 +771,7 @@ __device__ __forceinline__ void loss_finalize_block(const LossFinalize& f) {
 // is the bias gradient (dst2).  Jobs with vec set (n a multiple of 4, partials 16-byte aligned) take
 // four outputs per lane with 16-byte loads (128 outputs per block), the others one (32 per block).
 struct ReduceJobs {
-  static constexpr int MAXJ = 16;
+  static constexpr int MAXJ = 17;  // the deepest feed-forward workload's 15, and room for the three jobs of one kernel behind 14
   int njobs;
   int first[MAXJ + 1];
   int kind[MAXJ], splits[MAXJ], N[MAXJ], K[MAXJ], accumulate[MAXJ], vec[MAXJ];
@@ -989,7 +989,7 @@ __global__ __launch_bounds__(256) void k_param_map(ParamMap pm, const float* __r
 // All per-update re-packs in one launch: job j covers blocks [first[j], first[j+1]).
 // kind 0, transpose with zero padding (a = rows, b = cols, ld = leading dimension of dst; cols and ld multiples of 8):
 //   dst[c][r] = src[r][c] for r < rows, zero for rows <= r < ld; a block takes a 64 x 64 tile through LDS, 16 bytes per
-//   access on both sides (element by element the strided side cost a line per 2 bytes: 16 M weights 109 -> 20 us);
+//   access on both sides (element by element the strided side cost a line per 2 bytes: 16 M weights 109 -> 13 us);
 // kind 1, per-tap transpose for the quad-organised transposed convolution (a = Cout, b = Cin):
 //   dst[(tap*Cin + ci)*Cout + co] = W[co][tap*Cin + ci];
 // kind 2, parity-class packing of the implicit-GEMM transposed convolution (a = Cout, b = Cin, ld = row parity py):

@@ -322,3 +322,21 @@ def test_read_back_behind_work_on_the_per_thread_stream(L):
     for x, y in zip(*got):
         np.testing.assert_array_equal(x, y)
     assert not np.array_equal(got[0][0], got[0][1])
+
+
+def test_one_reduction_launch_per_step(L):
+    """The partial sums of a backward pass of the full-size network (15 jobs at this batch) are taken by one launch."""
+    import torch
+    cfg = configs.get_config(2, num_envs=512, horizon=8)
+    net, hp = cfg["net"], dict(cfg["hp"], epochs=3, minibatches=1, seed=3)
+    lrn = L.Learner(net, 512, 8, "bf16")
+    lrn.set_params(synth.init_params(net, 9))
+    gen = torch.Generator(device="cuda")
+    gen.manual_seed(1)
+    keep = [synth.rollout_step_torch(cfg, gen) for _ in range(8)]
+    for t, d in enumerate(keep):
+        lrn.buffer_write(t, *(d[k].contiguous() for k in ("obs", "proprio", "action", "logp_old", "value", "reward", "done")))
+    lrn.gae(torch.zeros(512, device="cuda"), hp["gamma"], hp["lam"])
+    lrn.profile(True)
+    lrn.update(hp)
+    assert lrn.profile_report()["wgrad_reduce"]["launches"] == 3

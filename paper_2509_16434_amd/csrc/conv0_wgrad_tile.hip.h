@@ -12,7 +12,7 @@
 // owns one patch column; its eight values are the same half of eight consecutive dwords when C0 = 1 (four two-dword
 // reads and four byte permutes).  Accumulators stay in registers over all bands; a block leaves one partial
 // [Cout][9*C0 + 1], summed in block order by k_reduce_batch.
-// 4096 images of 60x80x16: 712 -> 160 us (0.79 GB, 4.9 TB/s).
+// 4096 images of 60x80x16: 712 -> 157 us (0.79 GB, 5.0 TB/s).
 #pragma once
 #include "conv0_tile.hip.h"
 

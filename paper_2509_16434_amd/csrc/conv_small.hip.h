@@ -14,8 +14,8 @@
 // tap reads ones: the bias column).  Its input gradient works on quads (2x2 pixels of the first layer): rows 0-7 / 8-15
 // of the product are the even / odd column's eight channels, k runs over the two gradient pixels a quad row touches.
 // The gradient then meets the image patch of its pixel in fp32 registers.
-// Against one kernel per layer: 256 images of 32x32 forward 15 -> 6.5 us, backward 22 -> 9.4; 16384 images 91 -> 38 and
-// 222 -> 62 us (60 % of the vector units' issue slots); 8000 images of 64x64 133 -> 53 and 403 -> 101 us.
+// Against one kernel per layer: 256 images of 32x32 forward 15 -> 6.5 us, backward 22 -> 9.4; 16384 images 91 -> 35 and
+// 222 -> 61 us (0.62 of the vector units' issue slots); 8000 images of 64x64 133 -> 53 and 403 -> 101 us.
 #pragma once
 #include "conv_tile.hip.h"
 

@@ -2081,8 +2081,9 @@ int run_update(Ctx* c, const ppo_hparams* hp, ppo_mb_stats* host_stats, bool dis
 // The way back ends in ordinary host memory, by way of a ring of pinned pieces.  The calling thread queues every transfer
 // (a stream handle may name another stream in another thread) and waits for each to arrive; a small team copies the pieces
 // into the caller's memory, whose fresh pages fault on first touch, under the transfers that follow: 22 MB
-// arrive in 0.79 ms, 43 MB in 1.75 (the same as with every thread queueing its own transfers; one thread takes 0.8 ms where
-// the team took 0.6, and 4.4 for 64 MB where it took 1.6).  Vectors of a few pieces need no team.
+// arrive in 0.79 ms, 43 MB in 1.64 (with every thread queueing its own transfers 0.79 and 1.61; pieces dealt to the team
+// in turn 1.72: one thread's slow page faults then hold up the ring; a lone thread took 4.4 for 64 MB where a team
+// took 1.6).  Vectors of a few pieces need no team.
 // One piece has nothing to overlap with: straight into the caller's memory (70 k parameters 44 -> 38 us, 235 k 73 -> 66).
 constexpr int64_t HSTAGE = 1 << 18;  // floats per slot (1 MiB)
 constexpr int HSTAGE_TEAM = 4;
@@ -2298,63 +2299,70 @@ int to_canonical(Ctx* c, const float* dev, float* canon) {
     HIPCHK(c, hipStreamSynchronize(c->stream));
     return PPO_OK;
   }
-  const int64_t slots = std::min(np, (int64_t)2 * team);
+  const int slots = (int)std::min(np, (int64_t)2 * team);
   auto count = [&](int64_t k) { return std::min(HSTAGE, c->total - k * HSTAGE); };
-  auto copy = [&](int64_t k) { memcpy(canon + k * HSTAGE, c->hstage + (k % slots) * HSTAGE, sizeof(float) * (size_t)count(k)); };
-  // piece k lies in slot k % slots and is copied by team member k % team, or by this thread where that one has none
+  auto copy = [&](int64_t k, int slot) { memcpy(canon + k * HSTAGE, c->hstage + slot * HSTAGE, sizeof(float) * (size_t)count(k)); };
+  // pieces arrive in order, in whichever slot was free; whoever of the team is idle copies the oldest one
+  struct Piece { int64_t k; int slot; };
   std::mutex mu;
-  std::condition_variable cv;
-  int64_t arrived = 0;              // pieces in the ring or beyond it
-  int64_t copied[2 * HSTAGE_TEAM] = {};  // pieces that have left each slot
-  bool stop = false;
-  auto member = [&](int t) {
-    for (int64_t k = t; k < np; k += team) {
+  std::condition_variable work, space;
+  Piece arrived[2 * HSTAGE_TEAM], flight[2 * HSTAGE_TEAM];  // rings of `slots`
+  int64_t n_arrived = 0, n_taken = 0, n_queued = 0, n_landed = 0;
+  int spare[2 * HSTAGE_TEAM], n_spare = slots;
+  for (int i = 0; i < slots; ++i) spare[i] = i;
+  bool last = false;  // nothing arrives any more
+  auto member = [&]() {
+    for (;;) {
+      Piece q;
       {
         std::unique_lock<std::mutex> lk(mu);
-        cv.wait(lk, [&]() { return arrived > k || stop; });
-        if (arrived <= k) return;
+        work.wait(lk, [&]() { return n_taken < n_arrived || last; });
+        if (n_taken == n_arrived) return;
+        q = arrived[n_taken++ % slots];
       }
-      copy(k);
-      { std::lock_guard<std::mutex> lk(mu); copied[k % slots] += 1; }
-      cv.notify_all();
+      copy(q.k, q.slot);
+      { std::lock_guard<std::mutex> lk(mu); spare[n_spare++] = q.slot; }
+      space.notify_one();
     }
   };
   std::thread members[HSTAGE_TEAM];
+  bool helped = false;
   for (int t = 0; t < team && team > 1; ++t) {
     try {
-      members[t] = std::thread(member, t);
-    } catch (...) {  // no thread to be had
+      members[t] = std::thread(member);
+      helped = true;
+    } catch (...) {  // no thread to be had: the others do its share, or this one
     }
   }
   hipError_t e = hipSuccess;
-  auto queue = [&](int64_t k) {
-    e = hipMemcpyAsync(c->hstage + (k % slots) * HSTAGE, c->canon + k * HSTAGE, sizeof(float) * (size_t)count(k), hipMemcpyDeviceToHost, c->stream);
-    if (e == hipSuccess) e = hipEventRecord(c->hstage_ev[k % slots], c->stream);
-  };
-  int64_t queued = 0;
-  for (int64_t k = 0; k < np && e == hipSuccess; ++k) {
-    // every transfer whose slot is free; piece k's own, whatever it takes
-    while (queued < np && e == hipSuccess) {
+  while (n_landed < np && e == hipSuccess) {
+    while (n_queued < np && e == hipSuccess) {  // every transfer there is room for; at least one in flight
+      int slot;
       {
         std::unique_lock<std::mutex> lk(mu);
-        auto free = [&]() { return copied[queued % slots] == queued / slots; };
-        if (!free()) {
-          if (queued > k) break;
-          cv.wait(lk, free);
-        }
+        if (n_spare == 0 && n_queued > n_landed) break;
+        space.wait(lk, [&]() { return n_spare > 0; });
+        slot = spare[--n_spare];
       }
-      queue(queued);
-      ++queued;
+      const int64_t k = n_queued;
+      e = hipMemcpyAsync(c->hstage + slot * HSTAGE, c->canon + k * HSTAGE, sizeof(float) * (size_t)count(k), hipMemcpyDeviceToHost, c->stream);
+      if (e == hipSuccess) e = hipEventRecord(c->hstage_ev[slot], c->stream);
+      flight[n_queued++ % slots] = Piece{k, slot};
     }
-    if (e == hipSuccess) e = hipEventSynchronize(c->hstage_ev[k % slots]);
     if (e != hipSuccess) break;
-    const bool mine = !members[k % team].joinable();
-    if (mine) copy(k);
-    { std::lock_guard<std::mutex> lk(mu); arrived = k + 1; if (mine) copied[k % slots] += 1; }
-    cv.notify_all();
+    const Piece q = flight[n_landed++ % slots];
+    e = hipEventSynchronize(c->hstage_ev[q.slot]);
+    if (e != hipSuccess) break;
+    if (helped) {
+      { std::lock_guard<std::mutex> lk(mu); arrived[n_arrived++ % slots] = q; }
+      work.notify_one();
+    } else {
+      copy(q.k, q.slot);
+      spare[n_spare++] = q.slot;
+    }
   }
-  { std::lock_guard<std::mutex> lk(mu); stop = true; }
-  cv.notify_all();
+  { std::lock_guard<std::mutex> lk(mu); last = true; }
+  work.notify_all();
   for (std::thread& m : members) if (m.joinable()) m.join();
   HIPCHK(c, e);
   return PPO_OK;

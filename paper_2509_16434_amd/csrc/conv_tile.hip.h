@@ -22,6 +22,14 @@
 //    for every tile.
 //  * Each compute wave stages its 32 output pixels in a private LDS strip and writes them as
 //    16-byte row segments; a band's outputs are one contiguous span of the output image.
+//  * Rows too long for that (COLS): a tile is TR rows of TC output COLUMNS.  Its input is 2*TR+1 rows of 2*TC+1 pixels,
+//    slot 0 being the pixel left of the tile (or padding); the rows lie back to back in LDS and are copied in 1 KiB
+//    pieces that run on across row ends, every lane looking up its own source (row pitch of the image, zeros outside
+//    it).  Bound by HBM like the narrow form: 120 of 128 pixels used at 80-pixel result rows in two parts, 1.18 times
+//    the band's bytes loaded (a whole row of 80 would use 80 of 128 and load 1.5 times).  Measured on 8400 images of
+//    240x320, against the implicit-GEMM kernels such rows took before: second and third layer together forward
+//    5.74 -> 4.25 ms (5.0 TB/s of algorithmic bytes), weight gradient 6.94 -> 3.83 ms (5.6 TB/s); and with the forward's
+//    sign bits the third and fourth layer's input gradient takes the LDS-image kernels too, 4.17 -> 3.09 ms.
 #pragma once
 #include "common.hip.h"
 #include "gemm_dma.hip.h"
@@ -38,6 +46,7 @@ struct ConvTileArgs {
   int V, H, W, Ho, Wo, Cout;
   int TR, NB, ntiles;         // output rows per band, bands per image, nimg * NB
   int nbuf;                   // ring images (3 .. MAXBUF)
+  int TC, NP;                 // COLS: output columns per tile, tiles side by side (ntiles = nimg * NB * NP); else TC = Wo, NP = 1
 };
 
 // bf16 pair of (max(lo, 0), max(hi, 0)): rounded first, then clamped as 16-bit integers (a negative bf16 is a
@@ -79,8 +88,38 @@ struct ConvTileShape {
   static constexpr int SP = NW + 8;                   // staging pitch (elements)
   static constexpr int STAGE_BYTES = 4 * 32 * SP * 2;
   static constexpr int THREADS = 512;                 // four compute waves + four loader waves
-  static int image_bytes(int W, int TR) { return (2 * TR + 1) * (W + 2) * PIX; }
-  static int lds_bytes(int W, int TR, int nbuf) { return nbuf * image_bytes(W, TR) + STAGE_BYTES + BN * 4; }
+  static constexpr int MAXLD = 13;                    // COLS: 1 KiB loads per loader wave and tile
+  static int image_bytes(int slots, int TR) { return (2 * TR + 1) * slots * PIX; }  // slots: W + 2, or 2 * TC + 1
+  static int lds_bytes(int slots, int TR, int nbuf) { return nbuf * image_bytes(slots, TR) + STAGE_BYTES + BN * 4; }
+};
+
+// The loads of a tile of columns (COLS): piece j of 1 KiB belongs to loader wave j % 4.  Lane -> source is the same for
+// every tile but for the image's edges: byte offset from the pixel (2*row0 - 1, 2*col0) of the image, and the row and slot.
+template <int MAXLD>
+struct ColsLoads {
+  int goff[MAXLD];
+  uint32_t rs[MAXLD];  // row | slot << 8, or ~0: nothing to load
+  template <class SWZ>
+  __device__ __forceinline__ void init(int lw, int lane, int image_bytes, int rp, int pix, int rowbytes, SWZ swz) {
+#pragma unroll
+    for (int i = 0; i < MAXLD; ++i) {
+      const int p = (lw + 4 * i) * 1024 + lane * 16, row = p / rp, inrow = p - row * rp;
+      const int logi = inrow ^ (int)swz((uint32_t)inrow, row);
+      goff[i] = row * rowbytes + logi - pix;
+      rs[i] = p < image_bytes ? (uint32_t)row | (uint32_t)(logi / pix) << 8 : 0xffffffffu;
+    }
+  }
+  // src: the image's pixel (iy_lo, ix0); n: this wave's loads of a tile (each has at least one lane that loads)
+  template <int AUX>
+  __device__ __forceinline__ void issue(const char* src, const char* zp, char* dst, int n, int lw, int iy_lo, int H, int ix0, int W) const {
+#pragma unroll
+    for (int i = 0; i < MAXLD; ++i)
+      if (i < n) {
+        const int iy = iy_lo + (int)(rs[i] & 255u), ix = ix0 - 1 + (int)(rs[i] >> 8);
+        const char* p = ((uint32_t)iy < (uint32_t)H && (uint32_t)ix < (uint32_t)W) ? src + goff[i] : zp;
+        if (rs[i] != 0xffffffffu) __builtin_amdgcn_global_load_lds(GLOBAL_AS(p), LDS_AS(dst + (lw + 4 * i) * 1024), 16, 0, AUX);
+      }
+  }
 };
 
 // LDS image rows hold pixel slots of CIN*2 bytes (slot 0 and slot W+1 are zero pads).  A byte at
@@ -109,7 +148,7 @@ __device__ __forceinline__ uint32_t fwd_swz_bits(uint32_t off, uint32_t rowkey) 
 
 // AUX: cache policy of the band loads (LOAD_NT where a band shares few rows with its neighbours); RELU = false: the sums
 // pass as they are (a layer normalisation follows)
-template <int CIN, int AUX, int WIDE = 0, bool RELU = true>
+template <int CIN, int AUX, int WIDE = 0, bool RELU = true, bool COLS = false>
 __global__ __launch_bounds__(512) void k_conv_fwd_tile(ConvTileArgs a) {
   typedef ConvTileShape<CIN, WIDE> S;
   constexpr int NW = S::NW, WGN = S::WGN, TN = NW / 32, TM = S::TM, PIX = S::PIX, SP = S::SP;
@@ -117,7 +156,7 @@ __global__ __launch_bounds__(512) void k_conv_fwd_tile(ConvTileArgs a) {
   constexpr int CPP = CIN / 8;  // 16-byte chunks per pixel
   extern __shared__ __attribute__((aligned(16))) char lds[];
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, l32 = lane & 31, h = lane >> 5;
-  const int W = a.W, WP = W + 2, TR = a.TR, Wo = a.Wo, NBUF = a.nbuf;
+  const int W = a.W, TR = a.TR, Wo = COLS ? a.TC : a.Wo, WP = COLS ? 2 * Wo + 1 : W + 2, NBUF = a.nbuf;  // Wo: of the tile
   const int nrows = 2 * TR + 1, rowbytes = W * PIX, segs = (rowbytes + 1023) >> 10;
   const int image_bytes = nrows * WP * PIX;
   // tiles of this block: vb, vb + gridDim.x, ...
@@ -125,14 +164,35 @@ __global__ __launch_bounds__(512) void k_conv_fwd_tile(ConvTileArgs a) {
   const int nq = (a.ntiles > vb) ? (a.ntiles - 1 - vb) / (int)gridDim.x + 1 : 0;
 
   // zero the pad pixels of all ring images once
-  for (int i = tid; i < NBUF * nrows * 2 * CPP; i += S::THREADS) {
+  if constexpr (!COLS) for (int i = tid; i < NBUF * nrows * 2 * CPP; i += S::THREADS) {
     const int chunk = i % CPP, side = (i / CPP) & 1, row = i / (2 * CPP);  // row over all images
     *reinterpret_cast<uint4*>(lds + (int64_t)row * WP * PIX + (side ? (W + 1) * PIX : 0) + chunk * 16) = make_uint4(0u, 0u, 0u, 0u);
   }
 
   if (wave >= 4) {
     // ------------------------------------------------------------------ loaders: span row r belongs to loader r % 4
-    const int lw = wave - 4;
+    const int lw = __builtin_amdgcn_readfirstlane(wave - 4);
+    if constexpr (COLS) {
+      const int ni = (((image_bytes + 1023) >> 10) - lw + 3) >> 2;  // this wave's loads per tile
+      ColsLoads<S::MAXLD> ld;
+      ld.init(lw, lane, image_bytes, WP * PIX, PIX, rowbytes, [&](uint32_t off, int row) { return fwd_swz_bits<CIN>(off, (uint32_t)(Wo * (row >> 1))); });
+      int slot = 0;
+      auto issue = [&](int q) {
+        const int t = vb + q * gridDim.x, tb = t / a.NP, part = t - tb * a.NP;
+        const int img = tb / a.NB, band = tb - img * a.NB, iy_lo = 2 * band * TR - 1, ix0 = 2 * part * Wo;
+        const char* src = reinterpret_cast<const char*>(a.in.ptr_uniform(img)) + (int64_t)iy_lo * rowbytes + ix0 * PIX;
+        ld.template issue<AUX>(src, reinterpret_cast<const char*>(a.zpage) + lane * 16, lds + slot * image_bytes, ni, lw, iy_lo, a.H, ix0, W);
+        slot = slot + 1 == NBUF ? 0 : slot + 1;
+      };
+      const int D = NBUF - 1;
+      for (int q = 0; q < D && q < nq; ++q) issue(q);
+      for (int q = 0; q < nq; ++q) {
+        vm_wait_dyn(min(D - 1, nq - 1 - q) * ni);
+        __builtin_amdgcn_s_barrier();
+        if (q + D < nq) issue(q + D);
+      }
+      return;
+    }
     const int ni = ((nrows - lw + 3) >> 2) * segs;  // this wave's loads per band
     // this lane's 16 bytes land at in-row offset PIX + sg*1024 + lane*16: it fetches what belongs there
     // (byte offset within the image row; depends on the row for 64 channels)
@@ -210,6 +270,20 @@ __global__ __launch_bounds__(512) void k_conv_fwd_tile(ConvTileArgs a) {
         hx[i][u2][v] = (uint32_t)(h * 16) ^ fwd_swz_bits<CIN>((uint32_t)((2 * ox + v) * PIX), (uint32_t)(Wo * (oyl + u2)));
   }
 
+  // COLS: row and column within the tile of the output pixels this lane writes out, row | column << 8
+  constexpr int CPRO = NW / 8;  // 16-byte chunks per staged row
+  uint32_t opix[TM][32 * CPRO / 64], bpix[TM];
+  if constexpr (COLS) {
+#pragma unroll
+    for (int i = 0; i < TM; ++i) {
+      const int p0 = (wm * TM + i) * 32;
+      auto rc = [&](int p) { const int r = p / Wo; return (uint32_t)r | (uint32_t)(p - r * Wo) << 8; };
+      bpix[i] = rc(p0 + l32);
+#pragma unroll
+      for (int e = 0; e < 32 * CPRO / 64; ++e) opix[i][e] = rc(p0 + (lane + 64 * e) / CPRO);
+    }
+  }
+
   // the first tile's barrier also orders the pad fill and the bias table before their first use
   int slot = 0;
   for (int q = 0; q < nq; ++q) {
@@ -248,11 +322,15 @@ __global__ __launch_bounds__(512) void k_conv_fwd_tile(ConvTileArgs a) {
       __builtin_amdgcn_sched_barrier(0);  // keep the read of step s + RD in front of the MFMA of step s
     }
     // ---- epilogue: bf16, ReLU; lane holds pixel l32 of the wave's pixel group i, columns j*32 + g*8 + h*4 + 0..3
-    const int img = t / a.NB, band = t - img * a.NB;
+    const int tb = COLS ? t / a.NP : t, ox0 = COLS ? (t - tb * a.NP) * Wo : 0;
+    const int img = tb / a.NB, band = tb - img * a.NB;
     const int b = img / a.V, vw = img - b * a.V;
-    const int rows_here = min(TR, a.Ho - band * TR);
+    const int rows_here = min(TR, a.Ho - band * TR), cols_here = min(Wo, a.Wo - ox0);
     const int plim = rows_here * Wo;  // pixels of the band that exist
-    bf16_t* dst = a.out + (int64_t)b * a.out_stride_b + (int64_t)vw * a.out_stride_v + (int64_t)band * TR * Wo * a.Cout;
+    bf16_t* dst = a.out + (int64_t)b * a.out_stride_b + (int64_t)vw * a.out_stride_v + ((int64_t)band * TR * a.Wo + ox0) * a.Cout;
+    // is pixel p of the tile (COLS: at row and column rc) in the image, and which pixel of the image, counted from the tile's first
+    auto exists = [&](int p, uint32_t rc) { return COLS ? (int)(rc & 255u) < rows_here && (int)(rc >> 8) < cols_here : p < plim; };
+    auto pix_of = [&](int p, uint32_t rc) { return COLS ? (int)(rc & 255u) * a.Wo + (int)(rc >> 8) : p; };
     const uint32_t negw = nonzero_weights(h);
 #pragma unroll
     for (int i = 0; i < TM; ++i) {
@@ -279,17 +357,17 @@ __global__ __launch_bounds__(512) void k_conv_fwd_tile(ConvTileArgs a) {
         for (int j = 0; j < TN; ++j) {
           const uint32_t word = or_with_lane_xor32(pw[j]);
           const int wi = (n0 >> 5) + j;
-          if (h == 0 && p < plim && wi < wpp)
-            a.bits[((int64_t)img * a.Ho * Wo + (int64_t)band * TR * Wo + p) * wpp + wi] = word;
+          if (h == 0 && exists(p, COLS ? bpix[i] : 0u) && wi < wpp)
+            a.bits[((int64_t)img * a.Ho * a.Wo + (int64_t)band * TR * a.Wo + ox0 + pix_of(p, COLS ? bpix[i] : 0u)) * wpp + wi] = word;
         }
       }
-      constexpr int CPRO = NW / 8;  // 16-byte chunks per staged row
 #pragma unroll
       for (int e = 0; e < 32 * CPRO / 64; ++e) {
         const int ch = lane + 64 * e, rl = ch / CPRO, cg = ch - rl * CPRO;
         const int p = p0 + rl, n = n0 + cg * 8;
-        if (p < plim && n < a.Cout)
-          store_stream16(dst + (int64_t)p * a.Cout + n, *reinterpret_cast<const uint4*>(stage + (rl * SP + cg * 8) * 2));
+        const uint32_t rc = COLS ? opix[i][e] : 0u;
+        if (exists(p, rc) && n < a.Cout)
+          store_stream16(dst + (int64_t)pix_of(p, rc) * a.Cout + n, *reinterpret_cast<const uint4*>(stage + (rl * SP + cg * 8) * 2));
       }
     }
   }
@@ -318,6 +396,7 @@ struct ConvWgradArgs {
   int H, W, Ho, Wo, Cout;
   int TR, NB, ntiles, nstep;  // output rows per band, bands per image, nimg * NB, ceil(TR*Wo / 16)
   int nbuf;                   // ring buffers (3 .. MAXBUF)
+  int TC, NP;                 // as in ConvTileArgs
 };
 
 template <int CIN>
@@ -327,9 +406,11 @@ struct ConvWgradShape {
   static_assert(3 + 4 * (KTW - 1) >= KT, "wave 3's last accumulator pair must be free for the bias sums");
   // rounded up to 128 bytes: the dY pixels behind the image are addressed by flipping bit 6 of the whole offset (an
   // odd number of 64-byte pixel slots, i.e. an odd W at 32 channels, would leave them half a pixel off)
-  __host__ __device__ static int image_bytes(int W, int TR) { return ((2 * TR + 1) * (W + 2) * PIX + 127) & ~127; }
-  static int buf_bytes(int W, int TR, int nstep) { return image_bytes(W, TR) + nstep * 16 * 128; }
-  static int lds_bytes(int W, int TR, int nstep, int nbuf) { return nbuf * buf_bytes(W, TR, nstep) + 4 * 64 * 4; }
+  // (slots: pixel slots per row, W + 2, or 2 * TC + 1 in a tile of columns)
+  static constexpr int MAXLD = 13;  // COLS: 1 KiB image loads per loader wave and tile
+  __host__ __device__ static int image_bytes(int slots, int TR) { return ((2 * TR + 1) * slots * PIX + 127) & ~127; }
+  static int buf_bytes(int slots, int TR, int nstep) { return image_bytes(slots, TR) + nstep * 16 * 128; }
+  static int lds_bytes(int slots, int TR, int nstep, int nbuf) { return nbuf * buf_bytes(slots, TR, nstep) + 4 * 64 * 4; }
 };
 
 __device__ __forceinline__ bf16x8_t lds_read_tr8_2(const char* p_lo, const char* p_hi) {
@@ -342,21 +423,22 @@ __device__ __forceinline__ bf16x8_t lds_read_tr8_2(const char* p_lo, const char*
 
 // NS > 0: the number of pixel steps per band is NS (known when the kernel is compiled), which lets the tile loop run
 // without a branch and its operand reads ahead of the MFMAs; NS = 0: any number of steps up to MAXSTEP.
-template <int CIN, int NS = 0>
+// COLS: tiles of columns, as in the forward kernel.
+template <int CIN, int NS = 0, bool COLS = false>
 __global__ __launch_bounds__(512) void k_conv_wgrad_tile(ConvWgradArgs a) {
   typedef ConvWgradShape<CIN> S;
   constexpr int PIX = S::PIX, KT = S::KT, KTW = S::KTW, MAXSTEP = S::MAXSTEP;
   extern __shared__ __attribute__((aligned(16))) char lds[];
   const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-  const int W = a.W, WP = W + 2, TR = a.TR, Wo = a.Wo, nstep = NS ? NS : a.nstep, NBUF = a.nbuf;
+  const int W = a.W, TR = a.TR, Wo = COLS ? a.TC : a.Wo, WP = COLS ? 2 * Wo + 1 : W + 2, nstep = NS ? NS : a.nstep, NBUF = a.nbuf;  // Wo: of the tile
   const int nrows = 2 * TR + 1, rowbytes = W * PIX, segs = (rowbytes + 1023) >> 10;
-  const int image_bytes = S::image_bytes(W, TR), dy_bytes = nstep * 16 * 128, buf_bytes = image_bytes + dy_bytes;
+  const int image_bytes = S::image_bytes(WP, TR), dy_bytes = nstep * 16 * 128, buf_bytes = image_bytes + dy_bytes;
   const int vb = xcd_block((int)blockIdx.x, (int)gridDim.x);  // this block's number in the dealing of tiles
   const int nq = (a.ntiles > vb) ? (a.ntiles - 1 - vb) / (int)gridDim.x + 1 : 0;
   const int nb0 = blockIdx.y * 64;
 
   // zero the pad pixels of all ring images once
-  for (int i = tid; i < NBUF * nrows * 2 * (PIX / 16); i += S::THREADS) {
+  if constexpr (!COLS) for (int i = tid; i < NBUF * nrows * 2 * (PIX / 16); i += S::THREADS) {
     const int chunk = i % (PIX / 16), side = (i / (PIX / 16)) & 1, row = i / (2 * (PIX / 16));
     const int b = row / nrows, rr = row - b * nrows;
     *reinterpret_cast<uint4*>(lds + b * buf_bytes + (int64_t)rr * WP * PIX + (side ? (W + 1) * PIX : 0) + chunk * 16) = make_uint4(0u, 0u, 0u, 0u);
@@ -366,6 +448,46 @@ __global__ __launch_bounds__(512) void k_conv_wgrad_tile(ConvWgradArgs a) {
     // ------------------------------------------------------------------ loaders
     // loader lw copies the image rows lw, lw+4, ... and the 1 KiB dY pieces lw, lw+4, ... of a band
     const int lw = wave - 4;
+    if constexpr (COLS) {
+      const int xbytes = nrows * WP * PIX;
+      const int nx = (((xbytes + 1023) >> 10) - lw + 3) >> 2, ni = nx + ((nstep * 2 - lw + 3) >> 2);  // this wave's loads per tile
+      ColsLoads<S::MAXLD> ld;
+      ld.init(lw, lane, xbytes, WP * PIX, PIX, rowbytes, [&](uint32_t off, int) { return tile_swz_bits<CIN>(off); });
+      constexpr int MAXDY = (S::MAXSTEP * 2 + 3) / 4;
+      int dgoff[MAXDY]; uint32_t drc[MAXDY];  // this lane's dY sources: byte offset from the tile's first pixel; row | column << 8, ~0: zeros
+#pragma unroll
+      for (int i = 0; i < MAXDY; ++i) {
+        const uint32_t phys = (lw + 4 * i) * 1024 + lane * 16, logi = phys ^ (((phys >> 8) & 1u) << 6);
+        const int p = (int)(logi >> 7), cb = (int)(logi & 127u), r = p / Wo, cl = p - r * Wo;
+        dgoff[i] = (r * a.Wo + cl) * a.Cout * 2 + cb;
+        drc[i] = (r < TR && nb0 + (cb >> 1) < a.Cout) ? (uint32_t)r | (uint32_t)cl << 8 : 0xffffffffu;
+      }
+      int slot = 0;
+      auto issue = [&](int q) {
+        const int t = vb + q * gridDim.x, tb = t / a.NP, part = t - tb * a.NP;
+        const int img = tb / a.NB, band = tb - img * a.NB, iy_lo = 2 * band * TR - 1, ox0 = part * Wo;
+        const char* zp = reinterpret_cast<const char*>(a.zpage) + lane * 16;
+        char* buf = lds + slot * buf_bytes;
+        slot = slot + 1 == NBUF ? 0 : slot + 1;
+        ld.template issue<LOAD_NT>(reinterpret_cast<const char*>(a.in.ptr_uniform(img)) + (int64_t)iy_lo * rowbytes + 2 * ox0 * PIX, zp, buf, nx, lw, iy_lo, a.H, 2 * ox0, W);
+        const char* dsrc = reinterpret_cast<const char*>(a.dy.ptr_uniform(img) + ((int64_t)band * TR * a.Wo + ox0) * a.Cout + nb0);
+#pragma unroll
+        for (int i = 0; i < MAXDY; ++i)
+          if (lw + 4 * i < nstep * 2) {
+            const bool ok = band * TR + (int)(drc[i] & 255u) < a.Ho && ox0 + (int)(drc[i] >> 8) < a.Wo;  // (~0: column 2^24 - 1)
+            __builtin_amdgcn_global_load_lds(GLOBAL_AS(ok ? dsrc + dgoff[i] : zp), LDS_AS(buf + image_bytes + (lw + 4 * i) * 1024), 16, 0, LOAD_NT);
+          }
+      };
+      const int D = NBUF - 1;
+      for (int q = 0; q < D && q < nq; ++q) issue(q);
+      for (int q = 0; q < nq; ++q) {
+        vm_wait_dyn(min(D - 1, nq - 1 - q) * ni);
+        __builtin_amdgcn_s_barrier();
+        if (q + D < nq) issue(q + D);
+      }
+      __builtin_amdgcn_s_barrier();  // pairs with the compute waves' barrier before the bias reduction
+      return;
+    }
     const int ni = ((nrows - lw + 3) >> 2) * segs + ((nstep * 2 - lw + 3) >> 2);  // this wave's loads per band
     int xgoff[S::MAXSEG];
 #pragma unroll

@@ -745,24 +745,60 @@ ImgAddr conv_out_addr(Ctx* c, int l, const bf16_t* contiguous, const bf16_t* str
   return a;
 }
 
+// Tiles of output columns for result rows that the row-wise LDS-image kernels do not cover: the numbers of tiles side by
+// side (parts) and one above the other (bands) that load the fewest pixels with their halos, among those of at most `maxpix`
+// pixels whose `fits(columns, rows)` holds.  Parts of fewer than 8 columns are not tried (their halo is a quarter of what
+// they load); false: none fits.
+struct ColsPlan { int TC, NP, TR, NB; };
+template <class FITS>
+bool plan_cols(int Ho, int Wo, int maxpix, FITS fits, ColsPlan* out) {
+  int64_t best = -1;
+  for (int np = 1; np <= cdiv(Wo, 8); ++np) {
+    const int tc = cdiv(Wo, np);
+    if (tc > maxpix || (np > 1 && cdiv(Wo, tc) != np)) continue;
+    int tr = std::min(maxpix / tc, Ho);
+    while (tr > 0 && !fits(tc, tr)) --tr;
+    if (tr == 0) continue;
+    const int nb = cdiv(Ho, tr);
+    tr = cdiv(Ho, nb);
+    const int64_t loads = (int64_t)np * nb * (2 * tr + 1) * (2 * tc + 1);
+    if (best < 0 || loads < best) { best = loads; *out = ColsPlan{tc, np, tr, nb}; }
+  }
+  return best >= 0;
+}
+
 // Forward convolution through the LDS-image kernel; returns 1 when the layer's shape is not one
 // it covers (the caller then takes the implicit-GEMM path).
 template <int CIN, int WIDE, bool RELU>
 int launch_conv_fwd_tile_t(Ctx* c, ConvTileArgs a, const std::string& name, double flops, double abytes) {
   typedef ConvTileShape<CIN, WIDE> S;
-  const int segs = cdiv(a.W * S::PIX, 1024), ni = cdiv(2 * a.TR + 1, 4) * segs;  // loads per loader wave per band
+  const int nimg = a.ntiles;  // passed in as the image count
+  int segs = cdiv(a.W * S::PIX, 1024), slots = a.W + 2, form = 2, ni = 0;
+  if (a.Wo <= S::BM) {
+    const int trmax = std::min(S::BM / a.Wo, a.Ho);
+    a.NB = cdiv(a.Ho, trmax); a.TR = cdiv(a.Ho, a.NB);  // balanced bands
+    a.TC = a.Wo; a.NP = 1;
+    ni = cdiv(2 * a.TR + 1, 4) * segs;  // loads per loader wave per band
+    // bands of four or more output rows share at most an eighth of their input rows with a neighbour: read once, non-temporal
+    form = a.TR >= 4;
+  }
+  if (a.Wo > S::BM || segs > S::MAXSEG || ni > 63 || S::lds_bytes(slots, a.TR, 3) > 160 * 1024) {
+    ColsPlan p;
+    auto fits = [&](int tc, int tr) { return S::image_bytes(2 * tc + 1, tr) <= S::MAXLD * 4096 && S::lds_bytes(2 * tc + 1, tr, 3) <= 160 * 1024; };
+    if (!plan_cols(a.Ho, a.Wo, S::BM, fits, &p)) return 1;
+    a.TC = p.TC; a.NP = p.NP; a.TR = p.TR; a.NB = p.NB;
+    slots = 2 * a.TC + 1; ni = cdiv(cdiv(S::image_bytes(slots, a.TR), 1024), 4); form = 2;
+  }
+  a.ntiles = nimg * a.NB * a.NP;
   // as many ring images as fit: a loader wave has (nbuf - 2) * ni loads outstanding behind the band it waits for
   a.nbuf = S::MAXBUF;
-  while (a.nbuf > 3 && (S::lds_bytes(a.W, a.TR, a.nbuf) > 160 * 1024 || (a.nbuf - 2) * ni > 63)) --a.nbuf;
-  const int lds = S::lds_bytes(a.W, a.TR, a.nbuf);
-  if (segs > S::MAXSEG || ni > 63 || lds > 160 * 1024) return 1;
+  while (a.nbuf > 3 && (S::lds_bytes(slots, a.TR, a.nbuf) > 160 * 1024 || (a.nbuf - 2) * ni > 63)) --a.nbuf;
+  const int lds = S::lds_bytes(slots, a.TR, a.nbuf);
   const int gy = cdiv(a.Cout, S::BN);
   int gx = 256 / gy; if (gx > a.ntiles) gx = a.ntiles; if (gx < 1) gx = 1;
-  // bands of four or more output rows share at most an eighth of their input rows with a neighbour: read once, non-temporal
-  const bool nt = a.TR >= 4;
-  auto kfn = nt ? k_conv_fwd_tile<CIN, LOAD_NT, WIDE, RELU> : k_conv_fwd_tile<CIN, 0, WIDE, RELU>;
-  static uint64_t attr_devs[2] = {0, 0};  // bit d: set on device d
-  if (!((attr_devs[nt] >> c->dev) & 1)) { HIPCHK(c, hipFuncSetAttribute((const void*)kfn, hipFuncAttributeMaxDynamicSharedMemorySize, 160 * 1024)); attr_devs[nt] |= 1ull << c->dev; }
+  auto kfn = form == 2 ? k_conv_fwd_tile<CIN, 0, WIDE, RELU, true> : form == 1 ? k_conv_fwd_tile<CIN, LOAD_NT, WIDE, RELU> : k_conv_fwd_tile<CIN, 0, WIDE, RELU>;
+  static uint64_t attr_devs[3] = {0, 0, 0};  // bit d: set on device d
+  if (!((attr_devs[form] >> c->dev) & 1)) { HIPCHK(c, hipFuncSetAttribute((const void*)kfn, hipFuncAttributeMaxDynamicSharedMemorySize, 160 * 1024)); attr_devs[form] |= 1ull << c->dev; }
   ProfScope ps(c, name, flops, abytes);
   hipLaunchKernelGGL(kfn, dim3(gx, gy), dim3(S::THREADS), lds, c->stream, a);
   LAUNCHCHK(c, "k_conv_fwd_tile");
@@ -771,15 +807,12 @@ int launch_conv_fwd_tile_t(Ctx* c, ConvTileArgs a, const std::string& name, doub
 int launch_conv_fwd_tile(Ctx* c, const AConvFwd& al, const ImgAddr& o, int Cout, const bf16_t* w, const float* bias, int nimg,
                          const std::string& name, double abytes, uint32_t* bits, bool relu = true) {
   if ((al.Cin != 32 && al.Cin != 64) || Cout % 8 || nimg < 1 || al.in.idx) return 1;
-  const int BM = al.Cin == 32 ? 128 : 64;
-  if (al.Wo > BM) return 1;
   ConvTileArgs a;
   a.in = al.in; a.in.prepare();
   a.out = const_cast<bf16_t*>(o.base); a.out_stride_b = o.stride_b; a.out_stride_v = o.stride_v;
   a.w = w; a.bias = bias; a.zpage = c->zpage; a.bits = bits; a.V = o.V; a.H = al.H; a.W = al.W; a.Ho = al.Ho; a.Wo = al.Wo; a.Cout = Cout;
-  const int trmax = BM / al.Wo < al.Ho ? BM / al.Wo : al.Ho;
-  a.NB = cdiv(al.Ho, trmax); a.TR = cdiv(al.Ho, a.NB);  // balanced bands
-  a.ntiles = nimg * a.NB; a.nbuf = 3;
+  a.TR = a.NB = a.TC = a.NP = 0; a.nbuf = 3;
+  a.ntiles = nimg;  // image count; the template turns it into tiles
   const double flops = 2.0 * (double)al.M * Cout * al.K;
   // more than 64 output channels: the 64 x 128 form reads the input once
 #define LAUNCH_FWD(R_)                                                                       \
@@ -796,17 +829,26 @@ template <int CIN>
 int launch_conv_wgrad_tile_t(Ctx* c, ConvWgradArgs a, float* gw, float* gb, bool accumulate, const std::string& name, double flops, double abytes) {
   typedef ConvWgradShape<CIN> S;
   // largest band that fits the pixel-step table and three ring buffers, then balanced over the image
-  int TR = 0;
-  for (int tr = a.Ho; tr >= 1; --tr)
-    if (tr * a.Wo <= 16 * S::MAXSTEP && S::lds_bytes(a.W, tr, cdiv(tr * a.Wo, 16), 3) <= 158 * 1024) { TR = tr; break; }
-  if (TR == 0) return 1;
-  a.NB = cdiv(a.Ho, TR); a.TR = cdiv(a.Ho, a.NB); a.nstep = cdiv(a.TR * a.Wo, 16);
   const int nimg = a.ntiles;  // passed in as the image count
-  a.ntiles = nimg * a.NB;
-  const int segs = cdiv(a.W * S::PIX, 1024), ni = cdiv(2 * a.TR + 1, 4) * segs + cdiv(a.nstep * 2, 4);  // loads per loader wave per band
-  if (segs > S::MAXSEG || ni > 63) return 1;
+  const int segs = cdiv(a.W * S::PIX, 1024);
+  int TR = 0, slots = a.W + 2, ni = 0;
+  for (int tr = a.Ho; tr >= 1; --tr)
+    if (tr * a.Wo <= 16 * S::MAXSTEP && S::lds_bytes(slots, tr, cdiv(tr * a.Wo, 16), 3) <= 158 * 1024) { TR = tr; break; }
+  if (TR > 0) {
+    a.NB = cdiv(a.Ho, TR); a.TR = cdiv(a.Ho, a.NB); a.nstep = cdiv(a.TR * a.Wo, 16); a.TC = a.Wo; a.NP = 1;
+    ni = cdiv(2 * a.TR + 1, 4) * segs + cdiv(a.nstep * 2, 4);  // loads per loader wave per band
+  }
+  const bool cols = TR == 0 || segs > S::MAXSEG || ni > 63;
+  if (cols) {
+    ColsPlan p;
+    auto fits = [&](int tc, int tr) { return S::image_bytes(2 * tc + 1, tr) <= S::MAXLD * 4096 && S::lds_bytes(2 * tc + 1, tr, cdiv(tc * tr, 16), 3) <= 158 * 1024; };
+    if (!plan_cols(a.Ho, a.Wo, 16 * S::MAXSTEP, fits, &p)) return 1;
+    a.TC = p.TC; a.NP = p.NP; a.TR = p.TR; a.NB = p.NB; a.nstep = cdiv(a.TR * a.TC, 16);
+    slots = 2 * a.TC + 1; ni = cdiv(cdiv(S::image_bytes(slots, a.TR), 1024), 4) + cdiv(a.nstep * 2, 4);
+  }
+  a.ntiles = nimg * a.NB * a.NP;
   a.nbuf = S::MAXBUF;  // as many ring buffers as fit (the balanced band may be smaller than the largest that fits three)
-  while (a.nbuf > 3 && (S::lds_bytes(a.W, a.TR, a.nstep, a.nbuf) > 158 * 1024 || (a.nbuf - 2) * ni > 63)) --a.nbuf;
+  while (a.nbuf > 3 && (S::lds_bytes(slots, a.TR, a.nstep, a.nbuf) > 158 * 1024 || (a.nbuf - 2) * ni > 63)) --a.nbuf;
   const int gy = cdiv(a.Cout, 64), K = 9 * CIN;
   int gx = 256 / gy; if (gx > a.ntiles) gx = a.ntiles; if (gx < 1) gx = 1;
   const int64_t per = (int64_t)a.Cout * K;
@@ -815,12 +857,14 @@ int launch_conv_wgrad_tile_t(Ctx* c, ConvWgradArgs a, float* gw, float* gb, bool
   if (gb && (int64_t)gx * a.Cout > c->bias_partial_elems) gx = (int)(c->bias_partial_elems / a.Cout);
   if (gx < 1) return 1;
   a.partial = c->partial; a.bias_partial = gb ? c->bias_partial : nullptr;
-  const int lds = S::lds_bytes(a.W, a.TR, a.nstep, a.nbuf);
-  // the step counts of the benchmark shapes have a form of their own (branch-free tile loop); index 0: any count
+  const int lds = S::lds_bytes(slots, a.TR, a.nstep, a.nbuf);
+  // full and nearly full tiles have a form of their own (branch-free tile loop); index 0: any number of steps
   constexpr int NS1 = S::MAXSTEP, NS2 = S::MAXSTEP - 1;
-  const int form = a.nstep == NS1 ? 1 : (a.nstep == NS2 ? 2 : 0);
-  auto kfn = form == 1 ? k_conv_wgrad_tile<CIN, NS1> : (form == 2 ? k_conv_wgrad_tile<CIN, NS2> : k_conv_wgrad_tile<CIN, 0>);
-  static uint64_t attr_devs[3] = {0, 0, 0};  /* bit d: set on device d */
+  const int form = (a.nstep == NS1 ? 1 : (a.nstep == NS2 ? 2 : 0)) + (cols ? 3 : 0);
+  static decltype(&k_conv_wgrad_tile<CIN, 0>) const forms[6] = {k_conv_wgrad_tile<CIN, 0>, k_conv_wgrad_tile<CIN, NS1>, k_conv_wgrad_tile<CIN, NS2>,
+                                                                 k_conv_wgrad_tile<CIN, 0, true>, k_conv_wgrad_tile<CIN, NS1, true>, k_conv_wgrad_tile<CIN, NS2, true>};
+  auto kfn = forms[form];
+  static uint64_t attr_devs[6] = {};  /* bit d: set on device d */
   if (!((attr_devs[form] >> c->dev) & 1)) { HIPCHK(c, hipFuncSetAttribute((const void*)kfn, hipFuncAttributeMaxDynamicSharedMemorySize, 160 * 1024)); attr_devs[form] |= 1ull << c->dev; }
   {
     ProfScope ps(c, name, flops, abytes);
@@ -835,7 +879,7 @@ int launch_conv_wgrad_tile(Ctx* c, const ImgAddr& dy, const AConvFwd& xl, int Co
   if ((xl.Cin != 32 && xl.Cin != 64) || Cout % 8 || nimg < 1 || xl.in.idx || dy.idx) return 1;
   ConvWgradArgs a;
   a.in = xl.in; a.in.prepare(); a.dy = dy; a.dy.prepare(); a.zpage = c->zpage; a.partial = nullptr; a.bias_partial = nullptr;
-  a.H = xl.H; a.W = xl.W; a.Ho = xl.Ho; a.Wo = xl.Wo; a.Cout = Cout; a.TR = 0; a.NB = 0; a.nstep = 0; a.nbuf = 3;
+  a.H = xl.H; a.W = xl.W; a.Ho = xl.Ho; a.Wo = xl.Wo; a.Cout = Cout; a.TR = a.NB = a.TC = a.NP = 0; a.nstep = 0; a.nbuf = 3;
   a.ntiles = nimg;  // image count; the template turns it into tiles
   const double flops = 2.0 * (double)xl.M * Cout * xl.K;
   return xl.Cin == 32 ? launch_conv_wgrad_tile_t<32>(c, a, gw, gb, accumulate, name, flops, abytes)

@@ -112,7 +112,16 @@ def test_gradients_odd_second_layer_width(L, ci, h, w):
     _check_gradients(L, cfg, 12, 4)
 
 
-@pytest.mark.parametrize("c0,conv,h,w", [(1, (8, 16), 33, 47), (1, (16, 32, 64, 128), 40, 64), (1, (32, 64), 16, 130), (1, (64, 64), 21, 24),
+@pytest.mark.parametrize("ci,h,w", [(1, 20, 193), (1, 18, 261), (1, 37, 390), (2, 34, 322), (2, 64, 410), (2, 33, 262)])
+def test_gradients_wide_rows(L, ci, h, w):
+    """Rows too long for a row-wise LDS image (more than 96 pixels of 32 channels, 48 of 64): tiles of columns, with a last
+    column tile that is full, ragged or ends in an odd pixel; 64 x 128 tiles of the last layer from 52-pixel rows."""
+    cfg = configs.get_config(ci, num_envs=6, horizon=4)
+    cfg["net"].update(in_h=h, in_w=w)
+    _check_gradients(L, cfg, 6, 4)
+
+
+@pytest.mark.parametrize("c0,conv,h,w", [(1, (32, 64, 32), 22, 226), (1, (8, 16), 33, 47), (1, (16, 32, 64, 128), 40, 64), (1, (32, 64), 16, 130), (1, (64, 64), 21, 24),
                                          (3, (16, 32), 18, 66), (3, (32, 64, 64), 37, 53), (1, (16, 64), 9, 16)])
 def test_gradients_with_layer_norm(L, c0, conv, h, w):
     """Convolutions that store their output before a layer normalisation: the first layer's weight gradient from a stored

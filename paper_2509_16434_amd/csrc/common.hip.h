@@ -85,6 +85,26 @@ struct ImgAddr {
     return base + s * stride_b + (int64_t)v * stride_v;
   }
 };
+// The images of a wave's tiles, tile by tile, through a gather index: the samples of 64 tiles at a time sit in one register
+// (lane i: tile q0 + i) and are read across lanes.  A scalar load per tile would cost a memory latency each (the tiles of a
+// block are far apart in the list), which the wave's LDS reads would wait for too: both count in lgkmcnt.
+struct ImgAhead {
+  int smp = 0;  // sample of tile (q & ~63) + lane
+  // the image of tile q; image_of(q): its number.  To be called for q = 0, 1, 2, ...
+  template <class F>
+  __device__ __forceinline__ const bf16_t* ptr(const ImgAddr& a, int q, F image_of) {
+    if (a.idx && (q & 63) == 0) {
+      const int img = image_of(q + (int)(threadIdx.x & 63));
+      smp = img >= 0 ? a.idx[a.V == 1 ? img : (int)a.dv.div((uint32_t)img)] : 0;
+      asm volatile("" : "+v"(smp));  // waited for here, once in 64 tiles
+    }
+    const int img = image_of(q);
+    int b = img, v = 0;
+    if (a.V != 1) { b = (int)a.dv.div((uint32_t)img); v = img - b * a.V; }
+    const int64_t s = a.idx ? __builtin_amdgcn_readlane(smp, q & 63) : b;
+    return a.base + s * a.stride_b + (int64_t)v * a.stride_v;
+  }
+};
 // Mutable twin for outputs.
 struct ImgAddrW {
   bf16_t* base;

@@ -31,8 +31,7 @@
 //    5.74 -> 4.25 ms (5.0 TB/s of algorithmic bytes), weight gradient 6.94 -> 3.83 ms (5.6 TB/s); and with the forward's
 //    sign bits the third and fourth layer's input gradient takes the LDS-image kernels too, 4.17 -> 3.09 ms.
 #pragma once
-#include "common.hip.h"
-#include "gemm_dma.hip.h"
+#include "conv0_rows.hip.h"
 
 struct ConvTileArgs {
   ImgAddr in;                 // input images [H][W][CIN], dense
@@ -46,33 +45,16 @@ struct ConvTileArgs {
   int V, H, W, Ho, Wo, Cout;
   int TR, NB, ntiles;         // output rows per band, bands per image, nimg * NB
   int nbuf;                   // ring images (3 .. MAXBUF)
+  FastDiv dv_nb, dv_np;       // division by NB, NP
   int TC, NP;                 // COLS: output columns per tile, tiles side by side (ntiles = nimg * NB * NP); else TC = Wo, NP = 1
+  // C0 > 0: the input is the first layer's output, made from the images in src0; every block also copies its share of the n0
+  // samples' proprioception (P values, a multiple of 8, gathered like the images) into their feature rows
+  Conv0Src src0;
+  int n0, P;
+  const bf16_t* proprio;
+  bf16_t* feat;               // first column that receives it
+  int64_t feat_ld;
 };
-
-// bf16 pair of (max(lo, 0), max(hi, 0)): rounded first, then clamped as 16-bit integers (a negative bf16 is a
-// negative int16, and rounding keeps the sign, so the order of rounding and clamping does not matter)
-__device__ __forceinline__ uint32_t relu_pack2bf(float lo, float hi) {
-  typedef short s16x2_t __attribute__((ext_vector_type(2)));
-  const s16x2_t z = {0, 0};
-  return __builtin_bit_cast(uint32_t, __builtin_elementwise_max(__builtin_bit_cast(s16x2_t, pack2bf(lo, hi)), z));
-}
-// Which of the four non-negative bf16 of the pairs (x, y) are non-zero, as bits 0..3 times the weight the caller's
-// negw encodes (nonzero_weights: 1, or 16 for the upper nibble of a byte), added to acc.  A half is at most 0x7fff, so
-// x + 0x7fff7fff carries "non-zero" into each half's top bit without a carry between the halves; the byte permute's
-// sign selectors spread the four top bits to bytes 0x00 / 0xff (= -1), and the signed 4-byte dot product with the
-// weights -1, -2, -4, -8 (or -16 .. -128) sums them.
-// x of this lane OR x of the lane 32 away (one half-wave swap instead of a permute through LDS): either returned half
-// holds the own value and the other the partner's, so the OR of both is independent of which is which
-__device__ __forceinline__ uint32_t or_with_lane_xor32(uint32_t x) {
-  const auto r = __builtin_amdgcn_permlane32_swap(x, x, false, false);
-  return r[0] | r[1];
-}
-__device__ __forceinline__ uint32_t nonzero_weights(int upper) { return upper ? 0x80c0e0f0u : 0xf8fcfeffu; }
-__device__ __forceinline__ uint32_t nonzero4(uint32_t x, uint32_t y, uint32_t negw) {
-  const uint32_t tx = x + 0x7fff7fffu, ty = y + 0x7fff7fffu;
-  const uint32_t s = __builtin_amdgcn_perm(ty, tx, 0x0b0a0908u);
-  return (uint32_t)__builtin_amdgcn_sdot4((int)s, (int)negw, 0, false);
-}
 
 template <int CIN, int WIDE = 0>
 struct ConvTileShape {
@@ -122,18 +104,6 @@ struct ColsLoads {
   }
 };
 
-// LDS image rows hold pixel slots of CIN*2 bytes (slot 0 and slot W+1 are zero pads).  A byte at
-// logical in-row offset `off` is stored at off ^ tile_swz_bits<CIN>(off): the 16-byte chunks of a
-// pixel are permuted by bits of the slot index (which the permutation leaves unchanged, so it is
-// its own inverse).  Reads that walk over every second slot then use all banks evenly, two lanes
-// per bank group.
-template <int CIN>
-__device__ __forceinline__ uint32_t tile_swz_bits(uint32_t off) {
-  if (CIN == 32) return ((off >> 8) & 3u) << 4;          // slot >> 2
-  const uint32_t t = (off >> 8) & 7u;                    // slot >> 1
-  return (((t & 1u) << 2) | (t >> 1)) << 4;              // rotated, so neighbours differ in the top bit
-}
-
 // The forward kernel's form for 64 channels.  A b128 operand read is served eight lanes at a time, and eight lanes
 // run at full rate when their 16-byte chunks sit at eight different positions of the 128-byte pixel.  Consecutive
 // lanes are consecutive output pixels, row after row of the band, so the key that permutes a pixel's chunks counts
@@ -148,23 +118,28 @@ __device__ __forceinline__ uint32_t fwd_swz_bits(uint32_t off, uint32_t rowkey) 
 
 // AUX: cache policy of the band loads (LOAD_NT where a band shares few rows with its neighbours); RELU = false: the sums
 // pass as they are (a layer normalisation follows)
-template <int CIN, int AUX, int WIDE = 0, bool RELU = true, bool COLS = false>
+// C0 > 0 (32 input channels): the input rows are made from C0-channel images by the four waves that otherwise load them
+// (conv0_rows.hip.h), one tile ahead of the compute waves, in two LDS buffers; BITS0: the mask bits of the rows are stored.
+template <int CIN, int AUX, int WIDE = 0, bool RELU = true, bool COLS = false, int C0 = 0, bool BITS0 = false>
 __global__ __launch_bounds__(512) void k_conv_fwd_tile(ConvTileArgs a) {
+  static_assert(C0 == 0 || (CIN == 32 && RELU), "the first layer has 32 output channels");
   typedef ConvTileShape<CIN, WIDE> S;
   constexpr int NW = S::NW, WGN = S::WGN, TN = NW / 32, TM = S::TM, PIX = S::PIX, SP = S::SP;
   constexpr int KC = CIN / 16;  // MFMA k-steps per tap
   constexpr int CPP = CIN / 8;  // 16-byte chunks per pixel
   extern __shared__ __attribute__((aligned(16))) char lds[];
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, l32 = lane & 31, h = lane >> 5;
-  const int W = a.W, TR = a.TR, Wo = COLS ? a.TC : a.Wo, WP = COLS ? 2 * Wo + 1 : W + 2, NBUF = a.nbuf;  // Wo: of the tile
+  const int W = a.W, TR = a.TR, Wo = COLS ? a.TC : a.Wo, WP = COLS || C0 ? 2 * Wo + 1 : W + 2, NBUF = C0 ? 2 : a.nbuf;  // Wo: of the tile
   const int nrows = 2 * TR + 1, rowbytes = W * PIX, segs = (rowbytes + 1023) >> 10;
-  const int image_bytes = nrows * WP * PIX;
+  const int image_bytes = C0 ? Conv0Shape1<C0>::act_bytes(Wo, TR) : nrows * WP * PIX;
   // tiles of this block: vb, vb + gridDim.x, ...
   const int vb = xcd_block((int)blockIdx.x, (int)gridDim.x);  // this block's number in the dealing of tiles
   const int nq = (a.ntiles > vb) ? (a.ntiles - 1 - vb) / (int)gridDim.x + 1 : 0;
 
   // zero the pad pixels of all ring images once
-  if constexpr (!COLS) for (int i = tid; i < NBUF * nrows * 2 * CPP; i += S::THREADS) {
+  if constexpr (C0 > 0) {
+    for (int i = tid; i < 2 * image_bytes / 16; i += S::THREADS) reinterpret_cast<uint4*>(lds)[i] = make_uint4(0u, 0u, 0u, 0u);
+  } else if constexpr (!COLS) for (int i = tid; i < NBUF * nrows * 2 * CPP; i += S::THREADS) {
     const int chunk = i % CPP, side = (i / CPP) & 1, row = i / (2 * CPP);  // row over all images
     *reinterpret_cast<uint4*>(lds + (int64_t)row * WP * PIX + (side ? (W + 1) * PIX : 0) + chunk * 16) = make_uint4(0u, 0u, 0u, 0u);
   }
@@ -172,14 +147,68 @@ __global__ __launch_bounds__(512) void k_conv_fwd_tile(ConvTileArgs a) {
   if (wave >= 4) {
     // ------------------------------------------------------------------ loaders: span row r belongs to loader r % 4
     const int lw = __builtin_amdgcn_readfirstlane(wave - 4);
+    if constexpr (C0 > 0) {
+      typedef Conv0Shape1<C0> S0;
+      char* const ring = lds + 2 * image_bytes + S::STAGE_BYTES + S::BN * 4;
+      const int ring_bytes = S0::image_bytes(Wo, TR), NI = a.src0.nimage, D = NI - 1, pieces = a.src0.rowbytes >> 4;
+      Conv0Producer<C0, COLS, BITS0> pr;
+      pr.init(a.src0, lw, lane, TR, Wo, W);
+      struct Pos { int img, band, part; };
+      auto pos = [&](int q) {
+        const int t = vb + q * gridDim.x, tb = COLS ? (int)a.dv_np.div((uint32_t)t) : t;
+        Pos p; p.part = COLS ? t - tb * a.NP : 0; p.img = (int)a.dv_nb.div((uint32_t)tb); p.band = tb - p.img * a.NB;
+        return p;
+      };
+      int islot = 0, pslot = 0;
+      typedef typename Conv0Producer<C0, COLS, BITS0>::Img Img;
+      ImgAhead ahead;
+      auto image = [&](int q) {
+        const Pos p = pos(q);
+        const int iy_lo = 4 * p.band * TR - 3, b0 = 8 * C0 * p.part * Wo;  // (Wo is even where there are several parts)
+        const bf16_t* const img = ahead.ptr(a.src0.img, q, [&](int k) __attribute__((always_inline)) { return k < nq ? pos(k).img : -1; });
+        const char* src = reinterpret_cast<const char*>(img) + (int64_t)iy_lo * a.src0.rowbytes + b0;
+        const Img m = {src, reinterpret_cast<const char*>(a.zpage) + lane * 16, ring + islot * ring_bytes, iy_lo, a.src0.H, b0 >> 4, pieces, lw};
+        islot = islot + 1 == NI ? 0 : islot + 1;
+        return m;
+      };
+      auto produce = [&](int q) {
+        const Pos p = pos(q);
+        const bool edge = p.band == 0 || p.band == a.NB - 1 || (COLS && (p.part == 0 || p.part == a.NP - 1));
+        const int row_lo = 2 * p.band * TR - 1, col_lo = 2 * p.part * Wo - 1;
+        char* bits = BITS0 ? reinterpret_cast<char*>(a.src0.bits + ((int64_t)p.img * a.H + row_lo + 1) * W + col_lo + 1) : nullptr;
+        const int st = pr.produce(ring + pslot * ring_bytes, lds + (q & 1) * image_bytes, edge, row_lo, col_lo, a.H, W, bits, [](int) {});
+        pslot = pslot + 1 == NI ? 0 : pslot + 1;
+        return st;
+      };
+      // Image q + 2 must have landed when tile q + 1 is done being made.  Behind its loads this wave has issued those of the
+      // images up to q + 1 + D and the mask stores of the last D tiles it made (st[]: at least so many).
+      for (int q = 0; q < D && q < nq; ++q) pr.load_all(image(q));
+      asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+      vm_wait_few((min(D, nq) - 1) * pr.nl);
+      __builtin_amdgcn_s_barrier();  // the first image has landed, the buffers are zeroed
+      int st0 = 0, st1 = 0, st2 = 0;
+      for (int q = -1; q < nq; ++q) {
+        if (q >= 0) __builtin_amdgcn_s_barrier();  // tile q is made, image q + 1 has landed
+        if (q + 1 < nq) {
+          if (q + 1 + D < nq) pr.load_all(image(q + 1 + D));
+          __builtin_amdgcn_sched_barrier(0);
+          st2 = D > 2 ? st1 : 0; st1 = st0;
+          st0 = produce(q + 1);
+          __builtin_amdgcn_sched_barrier(0);
+          vm_wait_few(max(0, min(q + 1 + D, nq - 1) - (q + 2)) * pr.nl + st0 + st1 + st2);
+          asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+        }
+      }
+      return;
+    }
     if constexpr (COLS) {
       const int ni = (((image_bytes + 1023) >> 10) - lw + 3) >> 2;  // this wave's loads per tile
       ColsLoads<S::MAXLD> ld;
       ld.init(lw, lane, image_bytes, WP * PIX, PIX, rowbytes, [&](uint32_t off, int row) { return fwd_swz_bits<CIN>(off, (uint32_t)(Wo * (row >> 1))); });
       int slot = 0;
       auto issue = [&](int q) {
-        const int t = vb + q * gridDim.x, tb = t / a.NP, part = t - tb * a.NP;
-        const int img = tb / a.NB, band = tb - img * a.NB, iy_lo = 2 * band * TR - 1, ix0 = 2 * part * Wo;
+        const int t = vb + q * gridDim.x, tb = (int)a.dv_np.div((uint32_t)t), part = t - tb * a.NP;
+        const int img = (int)a.dv_nb.div((uint32_t)tb), band = tb - img * a.NB, iy_lo = 2 * band * TR - 1, ix0 = 2 * part * Wo;
         const char* src = reinterpret_cast<const char*>(a.in.ptr_uniform(img)) + (int64_t)iy_lo * rowbytes + ix0 * PIX;
         ld.template issue<AUX>(src, reinterpret_cast<const char*>(a.zpage) + lane * 16, lds + slot * image_bytes, ni, lw, iy_lo, a.H, ix0, W);
         slot = slot + 1 == NBUF ? 0 : slot + 1;
@@ -206,7 +235,7 @@ __global__ __launch_bounds__(512) void k_conv_fwd_tile(ConvTileArgs a) {
     int slot = 0;  // ring image the next issued band goes to
     auto issue = [&](int q) {
       const int t = vb + q * gridDim.x;
-      const int img = t / a.NB, band = t - img * a.NB;
+      const int img = (int)a.dv_nb.div((uint32_t)t), band = t - img * a.NB;
       const int iy_lo = 2 * band * TR - 1;
       const char* src = reinterpret_cast<const char*>(a.in.ptr_uniform(img)) + (int64_t)iy_lo * rowbytes;
       char* dst = lds + slot * image_bytes + PIX;  // skip the left pad
@@ -285,6 +314,16 @@ __global__ __launch_bounds__(512) void k_conv_fwd_tile(ConvTileArgs a) {
   }
 
   // the first tile's barrier also orders the pad fill and the bias table before their first use
+  if constexpr (C0 > 0) {
+    const int cpr = a.P >> 3;
+    for (int i = (int)blockIdx.x * 256 + tid; i < a.n0 * cpr; i += (int)gridDim.x * 256) {
+      const int b = i / cpr, j = i - b * cpr;
+      const int64_t sm = a.src0.img.idx ? a.src0.img.idx[b] : b;
+      reinterpret_cast<uint4*>(a.feat + (int64_t)b * a.feat_ld)[j] = reinterpret_cast<const uint4*>(a.proprio + sm * a.P)[j];
+    }
+    asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+    __builtin_amdgcn_s_barrier();  // the producers' first image has landed
+  }
   int slot = 0;
   for (int q = 0; q < nq; ++q) {
     const int t = vb + q * gridDim.x;
@@ -322,8 +361,8 @@ __global__ __launch_bounds__(512) void k_conv_fwd_tile(ConvTileArgs a) {
       __builtin_amdgcn_sched_barrier(0);  // keep the read of step s + RD in front of the MFMA of step s
     }
     // ---- epilogue: bf16, ReLU; lane holds pixel l32 of the wave's pixel group i, columns j*32 + g*8 + h*4 + 0..3
-    const int tb = COLS ? t / a.NP : t, ox0 = COLS ? (t - tb * a.NP) * Wo : 0;
-    const int img = tb / a.NB, band = tb - img * a.NB;
+    const int tb = COLS ? (int)a.dv_np.div((uint32_t)t) : t, ox0 = COLS ? (t - tb * a.NP) * Wo : 0;
+    const int img = (int)a.dv_nb.div((uint32_t)tb), band = tb - img * a.NB;
     const int b = img / a.V, vw = img - b * a.V;
     const int rows_here = min(TR, a.Ho - band * TR), cols_here = min(Wo, a.Wo - ox0);
     const int plim = rows_here * Wo;  // pixels of the band that exist
@@ -396,7 +435,9 @@ struct ConvWgradArgs {
   int H, W, Ho, Wo, Cout;
   int TR, NB, ntiles, nstep;  // output rows per band, bands per image, nimg * NB, ceil(TR*Wo / 16)
   int nbuf;                   // ring buffers (3 .. MAXBUF)
+  FastDiv dv_nb, dv_np;       // division by NB, NP
   int TC, NP;                 // as in ConvTileArgs
+  Conv0Src src0;              // C0 > 0: where the input rows are made from
 };
 
 template <int CIN>
@@ -413,6 +454,31 @@ struct ConvWgradShape {
   static int lds_bytes(int slots, int TR, int nstep, int nbuf) { return nbuf * buf_bytes(slots, TR, nstep) + 4 * 64 * 4; }
 };
 
+// The dY pixels of a tile of columns, 64 channels each: piece j of 1 KiB belongs to loader wave j % 4.
+template <int MAXDY>
+struct ColsDy {
+  int goff[MAXDY];     // byte offset from the tile's first pixel
+  uint32_t rc[MAXDY];  // row | column << 8, ~0: zeros (such a column is in no image)
+  __device__ __forceinline__ void init(int lw, int lane, int TR, int TC, int Wo, int Cout, int nb0) {
+#pragma unroll
+    for (int i = 0; i < MAXDY; ++i) {
+      const uint32_t phys = (lw + 4 * i) * 1024 + lane * 16, logi = phys ^ (((phys >> 8) & 1u) << 6);
+      const int p = (int)(logi >> 7), cb = (int)(logi & 127u), r = p / TC, cl = p - r * TC;
+      goff[i] = (r * Wo + cl) * Cout * 2 + cb;
+      rc[i] = (r < TR && nb0 + (cb >> 1) < Cout) ? (uint32_t)r | (uint32_t)cl << 8 : 0xffffffffu;
+    }
+  }
+  __device__ __forceinline__ void load(const char* src, const char* zp, char* dst, int i, int lw, int oy0, int Ho, int ox0, int Wo) const {
+    const bool ok = oy0 + (int)(rc[i] & 255u) < Ho && ox0 + (int)(rc[i] >> 8) < Wo;
+    __builtin_amdgcn_global_load_lds(GLOBAL_AS(ok ? src + goff[i] : zp), LDS_AS(dst + (lw + 4 * i) * 1024), 16, 0, LOAD_NT);
+  }
+  __device__ __forceinline__ void issue(const char* src, const char* zp, char* dst, int n, int lw, int oy0, int Ho, int ox0, int Wo) const {
+#pragma unroll
+    for (int i = 0; i < MAXDY; ++i)
+      if (i < n) load(src, zp, dst, i, lw, oy0, Ho, ox0, Wo);
+  }
+};
+
 __device__ __forceinline__ bf16x8_t lds_read_tr8_2(const char* p_lo, const char* p_hi) {
   typedef short s16x4_t_ __attribute__((ext_vector_type(4)));
   struct { s16x4_t_ lo, hi; } v;
@@ -423,22 +489,29 @@ __device__ __forceinline__ bf16x8_t lds_read_tr8_2(const char* p_lo, const char*
 
 // NS > 0: the number of pixel steps per band is NS (known when the kernel is compiled), which lets the tile loop run
 // without a branch and its operand reads ahead of the MFMAs; NS = 0: any number of steps up to MAXSTEP.
-// COLS: tiles of columns, as in the forward kernel.
-template <int CIN, int NS = 0, bool COLS = false>
+// COLS: tiles of columns, as in the forward kernel.  C0 > 0: the input rows are made from C0-channel images, as there; the
+// ring of nbuf buffers then holds dY alone, an image travels with the dY of the tile before.
+template <int CIN, int NS = 0, bool COLS = false, int C0 = 0>
 __global__ __launch_bounds__(512) void k_conv_wgrad_tile(ConvWgradArgs a) {
+  static_assert(C0 == 0 || CIN == 32, "the first layer has 32 output channels");
   typedef ConvWgradShape<CIN> S;
   constexpr int PIX = S::PIX, KT = S::KT, KTW = S::KTW, MAXSTEP = S::MAXSTEP;
   extern __shared__ __attribute__((aligned(16))) char lds[];
   const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-  const int W = a.W, TR = a.TR, Wo = COLS ? a.TC : a.Wo, WP = COLS ? 2 * Wo + 1 : W + 2, nstep = NS ? NS : a.nstep, NBUF = a.nbuf;  // Wo: of the tile
+  const int W = a.W, TR = a.TR, Wo = COLS ? a.TC : a.Wo, WP = COLS || C0 ? 2 * Wo + 1 : W + 2, nstep = NS ? NS : a.nstep, NBUF = a.nbuf;  // Wo: of the tile
   const int nrows = 2 * TR + 1, rowbytes = W * PIX, segs = (rowbytes + 1023) >> 10;
-  const int image_bytes = S::image_bytes(WP, TR), dy_bytes = nstep * 16 * 128, buf_bytes = image_bytes + dy_bytes;
+  // (C0 > 0: two buffers of made rows, then the ring of dY buffers, then the images)
+  const int image_bytes = C0 ? Conv0Shape1<C0>::act_bytes(Wo, TR) : S::image_bytes(WP, TR), dy_bytes = nstep * 16 * 128, buf_bytes = C0 ? dy_bytes : image_bytes + dy_bytes;
+  const int dy_off = C0 ? 0 : image_bytes;  // of the dY pixels in a ring buffer
+  char* const dyring = lds + (C0 ? 2 * image_bytes : 0);
   const int vb = xcd_block((int)blockIdx.x, (int)gridDim.x);  // this block's number in the dealing of tiles
   const int nq = (a.ntiles > vb) ? (a.ntiles - 1 - vb) / (int)gridDim.x + 1 : 0;
   const int nb0 = blockIdx.y * 64;
 
   // zero the pad pixels of all ring images once
-  if constexpr (!COLS) for (int i = tid; i < NBUF * nrows * 2 * (PIX / 16); i += S::THREADS) {
+  if constexpr (C0 > 0) {
+    for (int i = tid; i < 2 * image_bytes / 16; i += S::THREADS) reinterpret_cast<uint4*>(lds)[i] = make_uint4(0u, 0u, 0u, 0u);
+  } else if constexpr (!COLS) for (int i = tid; i < NBUF * nrows * 2 * (PIX / 16); i += S::THREADS) {
     const int chunk = i % (PIX / 16), side = (i / (PIX / 16)) & 1, row = i / (2 * (PIX / 16));
     const int b = row / nrows, rr = row - b * nrows;
     *reinterpret_cast<uint4*>(lds + b * buf_bytes + (int64_t)rr * WP * PIX + (side ? (W + 1) * PIX : 0) + chunk * 16) = make_uint4(0u, 0u, 0u, 0u);
@@ -448,35 +521,106 @@ __global__ __launch_bounds__(512) void k_conv_wgrad_tile(ConvWgradArgs a) {
     // ------------------------------------------------------------------ loaders
     // loader lw copies the image rows lw, lw+4, ... and the 1 KiB dY pieces lw, lw+4, ... of a band
     const int lw = wave - 4;
+    if constexpr (C0 > 0) {
+      typedef Conv0Shape1<C0> S0;
+      char* const ring = dyring + NBUF * dy_bytes;
+      const int ring_bytes = S0::image_bytes(Wo, TR), D = NBUF - 1, pieces = a.src0.rowbytes >> 4;
+      Conv0Producer<C0, COLS, false> pr;
+      pr.init(a.src0, lw, lane, TR, Wo, W);
+      ColsDy<(S::MAXSTEP * 2 + 3) / 4> dl;
+      dl.init(lw, lane, TR, Wo, a.Wo, a.Cout, nb0);
+      const int nd = (nstep * 2 - lw + 3) >> 2;  // this wave's dY loads per tile
+      const char* const zp = reinterpret_cast<const char*>(a.zpage) + lane * 16;
+      struct Pos { int img, band, part; };
+      auto pos = [&](int q) {
+        const int t = vb + q * gridDim.x, tb = COLS ? (int)a.dv_np.div((uint32_t)t) : t;
+        Pos p; p.part = COLS ? t - tb * a.NP : 0; p.img = (int)a.dv_nb.div((uint32_t)tb); p.band = tb - p.img * a.NB;
+        return p;
+      };
+      int islot = 0, pslot = 0, dslot = 0;
+      typedef typename Conv0Producer<C0, COLS, false>::Img Img;
+      ImgAhead ahead;
+      auto image = [&](int q) {
+        const Pos p = pos(q);
+        const int iy_lo = 4 * p.band * TR - 3, b0 = 8 * C0 * p.part * Wo;
+        const bf16_t* const img = ahead.ptr(a.src0.img, q, [&](int k) __attribute__((always_inline)) { return k < nq ? pos(k).img : -1; });
+        const char* src = reinterpret_cast<const char*>(img) + (int64_t)iy_lo * a.src0.rowbytes + b0;
+        const Img m = {src, zp, ring + islot * ring_bytes, iy_lo, a.src0.H, b0 >> 4, pieces, lw};
+        islot = islot + 1 == NBUF ? 0 : islot + 1;
+        return m;
+      };
+      struct Dy { const char* src; char* dst; int oy0, ox0; };
+      auto dy_of = [&](int q) {
+        const Pos p = pos(q);
+        const Dy d = {reinterpret_cast<const char*>(a.dy.ptr_uniform(p.img) + ((int64_t)p.band * TR * a.Wo + p.part * Wo) * a.Cout + nb0), dyring + dslot * dy_bytes, p.band * TR, p.part * Wo};
+        dslot = dslot + 1 == NBUF ? 0 : dslot + 1;
+        return d;
+      };
+      // the loads of tile q: its dY and the image of tile q + 1
+      auto issue = [&](int q) {
+        const Dy d = dy_of(q);
+        dl.issue(d.src, zp, d.dst, nd, lw, d.oy0, a.Ho, d.ox0, a.Wo);
+        if (q + 1 < nq) pr.load_all(image(q + 1));
+      };
+      // Tile q from its image, the loads of tile qn (qn < nq - 1) one by one between the groups: four waves issuing all of theirs
+      // at once wait hundreds of cycles for each.
+      constexpr int MAXDY = (S::MAXSTEP * 2 + 3) / 4;
+      auto produce = [&](int q, int qn) {
+        const Pos p = pos(q);
+        const bool edge = p.band == 0 || p.band == a.NB - 1 || (COLS && (p.part == 0 || p.part == a.NP - 1));
+        const Dy d = dy_of(qn);
+        const Img m = image(qn + 1);
+        pr.produce(ring + pslot * ring_bytes, lds + (q & 1) * image_bytes, edge, 2 * p.band * TR - 1, 2 * p.part * Wo - 1, a.H, W, nullptr, [&](int g) __attribute__((always_inline)) {
+          if (g < MAXDY && g < nd) dl.load(d.src, zp, d.dst, g, lw, d.oy0, a.Ho, d.ox0, a.Wo);
+          if (g < pr.MAXL && g < pr.nl) pr.load(m, g);
+        });
+        pslot = pslot + 1 == NBUF ? 0 : pslot + 1;
+      };
+      auto produce_alone = [&](int q) {
+        const Pos p = pos(q);
+        pr.produce(ring + pslot * ring_bytes, lds + (q & 1) * image_bytes, true, 2 * p.band * TR - 1, 2 * p.part * Wo - 1, a.H, W, nullptr, [](int) {});
+        pslot = pslot + 1 == NBUF ? 0 : pslot + 1;
+      };
+      // loads issued behind those of tile q when tiles up to q + D - 1 have been issued
+      auto younger = [&](int q) { const int last = min(q + D - 1, nq - 1); return max(0, last - q) * (nd + pr.nl) - (last == nq - 1 && last > q ? pr.nl : 0); };
+      // (every block has a tile)
+      pr.load_all(image(0));
+      for (int q = 0; q < D && q < nq; ++q) issue(q);
+      asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+      vm_wait_few(younger(0) + nd + (nq > 1 ? pr.nl : 0));
+      __builtin_amdgcn_s_barrier();  // the first image has landed, the buffers are zeroed
+      produce_alone(0);
+      const bool interleave = pr.ng > 3 ? max(nd, pr.nl) <= pr.GPW : max(nd, pr.nl) <= 3;  // as many loads of a kind as groups at most
+      for (int q = 0; q < nq; ++q) {
+        vm_wait_few(younger(q));       // dY of tile q and the image of tile q + 1 have landed
+        asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+        __builtin_amdgcn_s_barrier();  // and tile q is made
+        if (interleave && q + D + 1 < nq) produce(q + 1, q + D);
+        else {
+          if (q + D < nq) issue(q + D);
+          if (q + 1 < nq) produce_alone(q + 1);
+        }
+      }
+      __builtin_amdgcn_s_barrier();  // pairs with the compute waves' barrier before the bias reduction
+      return;
+    }
     if constexpr (COLS) {
       const int xbytes = nrows * WP * PIX;
       const int nx = (((xbytes + 1023) >> 10) - lw + 3) >> 2, ni = nx + ((nstep * 2 - lw + 3) >> 2);  // this wave's loads per tile
       ColsLoads<S::MAXLD> ld;
       ld.init(lw, lane, xbytes, WP * PIX, PIX, rowbytes, [&](uint32_t off, int) { return tile_swz_bits<CIN>(off); });
-      constexpr int MAXDY = (S::MAXSTEP * 2 + 3) / 4;
-      int dgoff[MAXDY]; uint32_t drc[MAXDY];  // this lane's dY sources: byte offset from the tile's first pixel; row | column << 8, ~0: zeros
-#pragma unroll
-      for (int i = 0; i < MAXDY; ++i) {
-        const uint32_t phys = (lw + 4 * i) * 1024 + lane * 16, logi = phys ^ (((phys >> 8) & 1u) << 6);
-        const int p = (int)(logi >> 7), cb = (int)(logi & 127u), r = p / Wo, cl = p - r * Wo;
-        dgoff[i] = (r * a.Wo + cl) * a.Cout * 2 + cb;
-        drc[i] = (r < TR && nb0 + (cb >> 1) < a.Cout) ? (uint32_t)r | (uint32_t)cl << 8 : 0xffffffffu;
-      }
+      ColsDy<(S::MAXSTEP * 2 + 3) / 4> dl;
+      dl.init(lw, lane, TR, Wo, a.Wo, a.Cout, nb0);
       int slot = 0;
       auto issue = [&](int q) {
-        const int t = vb + q * gridDim.x, tb = t / a.NP, part = t - tb * a.NP;
-        const int img = tb / a.NB, band = tb - img * a.NB, iy_lo = 2 * band * TR - 1, ox0 = part * Wo;
+        const int t = vb + q * gridDim.x, tb = (int)a.dv_np.div((uint32_t)t), part = t - tb * a.NP;
+        const int img = (int)a.dv_nb.div((uint32_t)tb), band = tb - img * a.NB, iy_lo = 2 * band * TR - 1, ox0 = part * Wo;
         const char* zp = reinterpret_cast<const char*>(a.zpage) + lane * 16;
         char* buf = lds + slot * buf_bytes;
         slot = slot + 1 == NBUF ? 0 : slot + 1;
         ld.template issue<LOAD_NT>(reinterpret_cast<const char*>(a.in.ptr_uniform(img)) + (int64_t)iy_lo * rowbytes + 2 * ox0 * PIX, zp, buf, nx, lw, iy_lo, a.H, 2 * ox0, W);
         const char* dsrc = reinterpret_cast<const char*>(a.dy.ptr_uniform(img) + ((int64_t)band * TR * a.Wo + ox0) * a.Cout + nb0);
-#pragma unroll
-        for (int i = 0; i < MAXDY; ++i)
-          if (lw + 4 * i < nstep * 2) {
-            const bool ok = band * TR + (int)(drc[i] & 255u) < a.Ho && ox0 + (int)(drc[i] >> 8) < a.Wo;  // (~0: column 2^24 - 1)
-            __builtin_amdgcn_global_load_lds(GLOBAL_AS(ok ? dsrc + dgoff[i] : zp), LDS_AS(buf + image_bytes + (lw + 4 * i) * 1024), 16, 0, LOAD_NT);
-          }
+        dl.issue(dsrc, zp, buf + image_bytes, ni - nx, lw, band * TR, a.Ho, ox0, a.Wo);
       };
       const int D = NBUF - 1;
       for (int q = 0; q < D && q < nq; ++q) issue(q);
@@ -498,7 +642,7 @@ __global__ __launch_bounds__(512) void k_conv_wgrad_tile(ConvWgradArgs a) {
     int slot = 0;  // ring buffer the next issued band goes to
     auto issue = [&](int q) {
       const int t = vb + q * gridDim.x;
-      const int img = t / a.NB, band = t - img * a.NB;
+      const int img = (int)a.dv_nb.div((uint32_t)t), band = t - img * a.NB;
       const int iy_lo = 2 * band * TR - 1;
       const char* xsrc = reinterpret_cast<const char*>(a.in.ptr_uniform(img)) + (int64_t)iy_lo * rowbytes;
       const int plim = min(TR, a.Ho - band * TR) * Wo;  // pixels of the band that exist
@@ -547,7 +691,7 @@ __global__ __launch_bounds__(512) void k_conv_wgrad_tile(ConvWgradArgs a) {
     for (int hf = 0; hf < 2; ++hf) {
       int p = s * 16 + 8 * (g >> 1) + (r16 >> 2) + 4 * hf;
       const uint32_t dl = (uint32_t)(p * 128 + scolb);
-      db[s][hf] = (uint32_t)image_bytes + (dl ^ (((dl >> 8) & 1u) << 6));
+      db[s][hf] = (uint32_t)dy_off + (dl ^ (((dl >> 8) & 1u) << 6));
       if (p >= TR * Wo) p = 0;  // its dY is zero; any finite pixel will do
       const int oyl = p / Wo, ox = p - oyl * Wo;
       const uint32_t inrow = (uint32_t)(2 * ox * PIX + scolb), rowb = (uint32_t)(2 * oyl * WP * PIX);
@@ -573,10 +717,15 @@ __global__ __launch_bounds__(512) void k_conv_wgrad_tile(ConvWgradArgs a) {
     tapc[t] = (uint32_t)((u * WP + v) * PIX); tapv2[t] = v == 2; taphi[t] = (CIN == 64) && (kt & 1);
   }
 
+  if constexpr (C0 > 0) {
+    asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+    __builtin_amdgcn_s_barrier();  // the producers' first image has landed
+  }
   int slot = 0;
   for (int q = 0; q < nq; ++q) {
     __builtin_amdgcn_s_barrier();  // band q is in LDS (the first one also orders the pad fill)
-    const char* buf = lds + slot * buf_bytes;
+    const char* dbuf = dyring + slot * buf_bytes;
+    const char* buf = C0 ? lds + (q & 1) * image_bytes : dbuf;
     slot = slot + 1 == NBUF ? 0 : slot + 1;
     if constexpr (NS > 0) {
       // The operand reads run ahead of the MFMAs (the window operand RD k-tiles, the dY operand a whole pixel
@@ -586,8 +735,8 @@ __global__ __launch_bounds__(512) void k_conv_wgrad_tile(ConvWgradArgs a) {
       bf16x8_t aq[2][2], bq[RD + 1];
       const uint32_t bias_sel = (wave == 3) ? 0xffffffffu : 0u;  // wave 3's last k-tile is the bias column
       auto read_a = [&](int s_) __attribute__((always_inline)) {
-        aq[s_ & 1][0] = lds_read_tr8_2(buf + db[s_][0], buf + db[s_][1]);
-        aq[s_ & 1][1] = lds_read_tr8_2(buf + (db[s_][0] ^ 64u), buf + (db[s_][1] ^ 64u));
+        aq[s_ & 1][0] = lds_read_tr8_2(dbuf + db[s_][0], dbuf + db[s_][1]);
+        aq[s_ & 1][1] = lds_read_tr8_2(dbuf + (db[s_][0] ^ 64u), dbuf + (db[s_][1] ^ 64u));
       };
       auto read_b = [&](int u) __attribute__((always_inline)) {
         const int s_ = u / KTW, t_ = u % KTW;
@@ -618,8 +767,8 @@ __global__ __launch_bounds__(512) void k_conv_wgrad_tile(ConvWgradArgs a) {
 #pragma unroll
     for (int s = 0; s < MAXSTEP; ++s) {
       if (s < nstep) {
-        const bf16x8_t a0 = lds_read_tr8_2(buf + db[s][0], buf + db[s][1]);
-        const bf16x8_t a1 = lds_read_tr8_2(buf + (db[s][0] ^ 64u), buf + (db[s][1] ^ 64u));
+        const bf16x8_t a0 = lds_read_tr8_2(dbuf + db[s][0], dbuf + db[s][1]);
+        const bf16x8_t a1 = lds_read_tr8_2(dbuf + (db[s][0] ^ 64u), dbuf + (db[s][1] ^ 64u));
 #pragma unroll
         for (int t = 0; t < KTW; ++t) {
           if (wave + 4 * t < KT) {

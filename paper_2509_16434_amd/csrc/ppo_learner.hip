@@ -124,6 +124,8 @@ struct Ctx {
   bf16_t* wtap[PPO_MAX_LAYERS];   // the same weights transposed per tap: [9][Cin][Cout]
   uint32_t* abits[PPO_MAX_LAYERS] = {};  // sign bits of conv layer l's stored output for the current chunk (ReLU mask of the backward pass)
   bool abits_ok[PPO_MAX_LAYERS] = {};    // written by the forward kernel that ran for this chunk
+  bool dry = false;                      // the launchers of the first two convolutions only say whether they cover the shapes
+  bool f01_fwd = false, f01_train = false;  // those two run in one kernel: forward only / forward and backward (act[0] then stays unused)
   int64_t wver = 0;                      // bumped whenever the weights change (every repack_weights call)
   int64_t wd_ver[PPO_MAX_LAYERS] = {};   // weight version that wd[l] holds (0: none): packed on demand the first time,
   bool wd_used[PPO_MAX_LAYERS] = {};     // with every other re-pack from then on
@@ -140,7 +142,7 @@ struct Ctx {
   int nb = 1, shift = 64;
   // device: workspaces for one chunk of CH samples
   int CH = 0;
-  bf16_t* act[PPO_MAX_LAYERS];    // conv outputs of layers 0..nconv-2, [CH*V][H][W][C]
+  bf16_t* act[PPO_MAX_LAYERS] = {};  // conv outputs of layers 0..nconv-2, [CH*V][H][W][C]
   bf16_t* feat = nullptr;         // [CH][feat_ld]: last conv output per view, then proprio
   bf16_t* fcact[PPO_MAX_LAYERS];  // [CH][fout]
   float* headout = nullptr;       // [CH][32]
@@ -751,10 +753,10 @@ ImgAddr conv_out_addr(Ctx* c, int l, const bf16_t* contiguous, const bf16_t* str
 // they load); false: none fits.
 struct ColsPlan { int TC, NP, TR, NB; };
 template <class FITS>
-bool plan_cols(int Ho, int Wo, int maxpix, FITS fits, ColsPlan* out) {
+bool plan_cols(int Ho, int Wo, int maxpix, FITS fits, ColsPlan* out, int multiple = 1) {
   int64_t best = -1;
   for (int np = 1; np <= cdiv(Wo, 8); ++np) {
-    const int tc = cdiv(Wo, np);
+    const int tc = cdiv(cdiv(Wo, np), multiple) * multiple;
     if (tc > maxpix || (np > 1 && cdiv(Wo, tc) != np)) continue;
     int tr = std::min(maxpix / tc, Ho);
     while (tr > 0 && !fits(tc, tr)) --tr;
@@ -789,7 +791,7 @@ int launch_conv_fwd_tile_t(Ctx* c, ConvTileArgs a, const std::string& name, doub
     a.TC = p.TC; a.NP = p.NP; a.TR = p.TR; a.NB = p.NB;
     slots = 2 * a.TC + 1; ni = cdiv(cdiv(S::image_bytes(slots, a.TR), 1024), 4); form = 2;
   }
-  a.ntiles = nimg * a.NB * a.NP;
+  a.ntiles = nimg * a.NB * a.NP; a.dv_nb = make_fastdiv(a.NB); a.dv_np = make_fastdiv(a.NP);
   // as many ring images as fit: a loader wave has (nbuf - 2) * ni loads outstanding behind the band it waits for
   a.nbuf = S::MAXBUF;
   while (a.nbuf > 3 && (S::lds_bytes(slots, a.TR, a.nbuf) > 160 * 1024 || (a.nbuf - 2) * ni > 63)) --a.nbuf;
@@ -823,6 +825,118 @@ int launch_conv_fwd_tile(Ctx* c, const AConvFwd& al, const ImgAddr& o, int Cout,
 #undef LAUNCH_FWD
 }
 
+// Tiles of the second layer's kernels that make its input from the images (conv0_rows.hip.h): whole result rows where the
+// tile's input fits the producer waves, else columns (an even number: a tile's image rows then start at a multiple of 16
+// bytes).  Whole rows also where columns would save less than a tenth of the pixels to make: their tiles test for missing
+// pixels only in the first and last band.  `lds(TC, TR)`: bytes of a tile's LDS with the shortest rings.
+template <int C0, class LDS>
+bool plan_conv01(int W1, int Ho, int Wo, int maxpix, LDS lds, ColsPlan* out, bool* cols) {
+  typedef Conv0Shape1<C0> S0;
+  auto fits = [&](int tc, int tr, int ncol) { return (2 * tr + 1) * ncol <= S0::MAXPIX && S0::fits(tc, tr) && lds(tc, tr) <= 160 * 1024; };
+  ColsPlan pc;
+  bool havec = plan_cols(Ho, Wo, maxpix, [&](int tc, int tr) { return fits(tc, tr, 2 * tc + 1); }, &pc, 2);
+  int tr = Wo <= maxpix ? std::min(maxpix / Wo, Ho) : 0;
+  while (tr > 0 && !fits(Wo, tr, W1)) --tr;
+  if (tr > 0) {
+    const int nb = cdiv(Ho, tr);
+    tr = cdiv(Ho, nb);
+    const double made = (double)nb * (2 * tr + 1) * W1;
+    if (!havec || made <= 1.1 * pc.NB * pc.NP * (2.0 * pc.TR + 1) * (2 * pc.TC + 1)) { *out = ColsPlan{Wo, 1, tr, nb}; *cols = false; return true; }
+  }
+  *out = pc; *cols = true;
+  return havec;
+}
+// The two first convolutions' forward in one kernel; returns 1 when the shapes are not covered.  bits0, bits1: the layers' mask
+// bits (both or neither).
+template <int C0, bool BITS>
+int launch_conv01_fwd_t(Ctx* c, ConvTileArgs a, const std::string& name, double flops, double abytes) {
+  typedef ConvTileShape<32> S;
+  typedef Conv0Shape1<C0> S0;
+  const int nimg = a.ntiles;  // passed in as the image count
+  auto lds_of = [&](int tc, int tr, int ni) { return 2 * S0::act_bytes(tc, tr) + S::STAGE_BYTES + S::BN * 4 + ni * S0::image_bytes(tc, tr); };
+  ColsPlan p;
+  bool cols;
+  if (!plan_conv01<C0>(a.W, a.Ho, a.Wo, S::BM, [&](int tc, int tr) { return lds_of(tc, tr, 3); }, &p, &cols)) return 1;
+  if (c->dry) return PPO_OK;
+  a.TC = p.TC; a.NP = p.NP; a.TR = p.TR; a.NB = p.NB; a.ntiles = nimg * p.NB * p.NP; a.dv_nb = make_fastdiv(p.NB); a.dv_np = make_fastdiv(p.NP); a.nbuf = 2;
+  a.src0.nimage = lds_of(p.TC, p.TR, S0::AHEAD + 1) <= 160 * 1024 ? S0::AHEAD + 1 : 3;
+  const int gx = std::min(256, a.ntiles);
+  auto kfn = cols ? k_conv_fwd_tile<32, 0, 0, true, true, C0, BITS> : k_conv_fwd_tile<32, 0, 0, true, false, C0, BITS>;
+  static uint64_t attr_devs[2] = {0, 0};  // bit d: set on device d
+  if (!((attr_devs[cols] >> c->dev) & 1)) { HIPCHK(c, hipFuncSetAttribute((const void*)kfn, hipFuncAttributeMaxDynamicSharedMemorySize, 160 * 1024)); attr_devs[cols] |= 1ull << c->dev; }
+  ProfScope ps(c, name, flops, abytes);
+  hipLaunchKernelGGL(kfn, dim3(gx), dim3(S::THREADS), lds_of(p.TC, p.TR, a.src0.nimage), c->stream, a);
+  LAUNCHCHK(c, "k_conv_fwd_tile");
+  return PPO_OK;
+}
+Conv0Src conv0_src(Ctx* c, const ImgAddr& in, uint32_t* bits) {
+  Conv0Src s;
+  s.img = in; s.img.prepare(); s.w = c->shadow + c->convW[0]; s.bias = c->p + c->convB[0]; s.bits = bits;
+  s.H = c->cH[0]; s.rowbytes = c->cW[0] * c->cC[0] * 2; s.nimage = 0;
+  return s;
+}
+int launch_conv01_fwd(Ctx* c, const ImgAddr& in, const ImgAddr& o, const bf16_t* proprio, int n, bool train) {
+  const int C0 = c->cC[0], Co = c->cC[2];
+  if (c->nconv < 2 || (C0 != 1 && C0 != 3) || c->cC[1] != 32 || Co % 8 || Co > 64 || c->P % 8 || c->feat_ld % 8 || c->flat % 8) return 1;
+  ConvTileArgs a = {};
+  const int nimg = n * c->V;
+  const bool bits1 = train && c->nconv > 2;  // the last layer's mask is applied by the first linear layer's input gradient
+  a.out = const_cast<bf16_t*>(o.base); a.out_stride_b = o.stride_b; a.out_stride_v = o.stride_v;
+  a.w = c->shadow + c->convW[1]; a.bias = c->p + c->convB[1]; a.zpage = c->zpage; a.bits = bits1 ? c->abits[1] : nullptr; a.V = c->V;
+  a.H = c->cH[1]; a.W = c->cW[1]; a.Ho = c->cH[2]; a.Wo = c->cW[2]; a.Cout = Co; a.ntiles = nimg;
+  a.src0 = conv0_src(c, in, train ? c->abits[0] : nullptr);
+  a.n0 = n; a.P = c->P; a.proprio = proprio; a.feat = c->feat + c->V * c->flat; a.feat_ld = c->feat_ld;
+  const double m0 = (double)nimg * a.H * a.W, m1 = (double)nimg * a.Ho * a.Wo;
+  const double flops = 2.0 * (m0 * 32 * 9 * C0 + m1 * Co * 288), bytes = 2.0 * ((double)nimg * c->img_elems + m1 * Co + 288.0 * Co) + (train ? m0 * 4 : 0.0) + (bits1 ? m1 * Co / 8 : 0.0);
+  if (train) return C0 == 1 ? launch_conv01_fwd_t<1, true>(c, a, "conv_fwd.0+1", flops, bytes) : launch_conv01_fwd_t<3, true>(c, a, "conv_fwd.0+1", flops, bytes);
+  return C0 == 1 ? launch_conv01_fwd_t<1, false>(c, a, "conv_fwd.0+1", flops, bytes) : launch_conv01_fwd_t<3, false>(c, a, "conv_fwd.0+1", flops, bytes);
+}
+// The second convolution's weight gradient with its input made again from the images; returns 1 when the shapes are not covered.
+template <int C0>
+int launch_conv01_wgrad_t(Ctx* c, ConvWgradArgs a, float* gw, float* gb, bool accumulate, const std::string& name, double flops, double abytes) {
+  typedef ConvWgradShape<32> S;
+  typedef Conv0Shape1<C0> S0;
+  const int nimg = a.ntiles;  // passed in as the image count
+  auto lds_of = [&](int tc, int tr, int nb) { return 2 * S0::act_bytes(tc, tr) + nb * (cdiv(tc * tr, 16) * 16 * 128 + S0::image_bytes(tc, tr)); };
+  ColsPlan p;
+  bool cols;
+  if (!plan_conv01<C0>(a.W, a.Ho, a.Wo, 16 * S::MAXSTEP, [&](int tc, int tr) { return lds_of(tc, tr, 3); }, &p, &cols)) return 1;
+  if (c->dry) return PPO_OK;
+  a.TC = p.TC; a.NP = p.NP; a.TR = p.TR; a.NB = p.NB; a.ntiles = nimg * p.NB * p.NP; a.dv_nb = make_fastdiv(p.NB); a.dv_np = make_fastdiv(p.NP); a.nstep = cdiv(p.TR * p.TC, 16);
+  a.nbuf = a.src0.nimage = lds_of(p.TC, p.TR, 4) <= 160 * 1024 ? 4 : 3;
+  const int K = 288;
+  int gx = std::min(256, a.ntiles);
+  const int64_t per = (int64_t)a.Cout * K;
+  { const int erc = ensure_partial(c, (int64_t)gx * per, (int64_t)gx * a.Cout); if (erc) return erc; }
+  gx = (int)std::min<int64_t>(gx, std::min(c->partial_elems / per, c->bias_partial_elems / a.Cout));
+  if (gx < 1) return fail(c, PPO_ENOMEM, "weight-gradient workspace too small for the second convolution");
+  a.partial = c->partial; a.bias_partial = c->bias_partial;
+  constexpr int NS1 = S::MAXSTEP, NS2 = S::MAXSTEP - 1;
+  const int form = (a.nstep == NS1 ? 1 : (a.nstep == NS2 ? 2 : 0)) + (cols ? 3 : 0);
+  static decltype(&k_conv_wgrad_tile<32, 0>) const forms[6] = {
+      k_conv_wgrad_tile<32, 0, false, C0>, k_conv_wgrad_tile<32, NS1, false, C0>, k_conv_wgrad_tile<32, NS2, false, C0>,
+      k_conv_wgrad_tile<32, 0, true, C0>, k_conv_wgrad_tile<32, NS1, true, C0>, k_conv_wgrad_tile<32, NS2, true, C0>};
+  static uint64_t attr_devs[6] = {};  /* bit d: set on device d */
+  if (!((attr_devs[form] >> c->dev) & 1)) { HIPCHK(c, hipFuncSetAttribute((const void*)forms[form], hipFuncAttributeMaxDynamicSharedMemorySize, 160 * 1024)); attr_devs[form] |= 1ull << c->dev; }
+  {
+    ProfScope ps(c, name, flops, abytes);
+    hipLaunchKernelGGL(forms[form], dim3(gx), dim3(S::THREADS), lds_of(p.TC, p.TR, a.nbuf), c->stream, a);
+    LAUNCHCHK(c, "k_conv_wgrad_tile");
+  }
+  defer_reduce(c, 1, gx, per, a.Cout, K, gw, nullptr, accumulate, true, a.Cout, gb);
+  return PPO_OK;
+}
+int launch_conv01_wgrad(Ctx* c, const ImgAddr& in, const ImgAddr& dy, int nimg, bool accumulate) {
+  if (c->cC[2] > 64) return 1;
+  ConvWgradArgs a = {};
+  a.dy = dy; a.dy.prepare(); a.zpage = c->zpage; a.src0 = conv0_src(c, in, nullptr);
+  a.H = c->cH[1]; a.W = c->cW[1]; a.Ho = c->cH[2]; a.Wo = c->cW[2]; a.Cout = c->cC[2]; a.ntiles = nimg;
+  const double m0 = (double)nimg * a.H * a.W, m1 = (double)nimg * a.Ho * a.Wo;
+  const double flops = 2.0 * (m1 * a.Cout * 288 + m0 * 32 * 9 * c->cC[0]), bytes = 2.0 * (m1 * a.Cout + (double)nimg * c->img_elems) + 4.0 * 288 * a.Cout;
+  float *gw = c->g + c->convW[1], *gb = c->g + c->convB[1];
+  return c->cC[0] == 1 ? launch_conv01_wgrad_t<1>(c, a, gw, gb, accumulate, "conv_wgrad.1", flops, bytes) : launch_conv01_wgrad_t<3>(c, a, gw, gb, accumulate, "conv_wgrad.1", flops, bytes);
+}
+
 // Weight (and bias) gradient of conv layer with 32 or 64 input channels through the LDS-image
 // kernel; returns 1 when the shape is not covered (the caller then takes the implicit-GEMM path).
 template <int CIN>
@@ -846,7 +960,7 @@ int launch_conv_wgrad_tile_t(Ctx* c, ConvWgradArgs a, float* gw, float* gb, bool
     a.TC = p.TC; a.NP = p.NP; a.TR = p.TR; a.NB = p.NB; a.nstep = cdiv(a.TR * a.TC, 16);
     slots = 2 * a.TC + 1; ni = cdiv(cdiv(S::image_bytes(slots, a.TR), 1024), 4) + cdiv(a.nstep * 2, 4);
   }
-  a.ntiles = nimg * a.NB * a.NP;
+  a.ntiles = nimg * a.NB * a.NP; a.dv_nb = make_fastdiv(a.NB); a.dv_np = make_fastdiv(a.NP);
   a.nbuf = S::MAXBUF;  // as many ring buffers as fit (the balanced band may be smaller than the largest that fits three)
   while (a.nbuf > 3 && (S::lds_bytes(slots, a.TR, a.nstep, a.nbuf) > 158 * 1024 || (a.nbuf - 2) * ni > 63)) --a.nbuf;
   const int gy = cdiv(a.Cout, 64), K = 9 * CIN;
@@ -914,6 +1028,7 @@ int launch_conv_dgrad_tile_t(Ctx* c, ConvDgradArgs a, int nimg, const std::strin
     ni += cdiv(cdiv((4 * a.TQ + 1) * rb0, 1024), 2);
   }
   if (segs > S::MAXSEG || ni > 63) return 1;
+  if (c->dry) return PPO_OK;
   int gx = a.ntiles < 256 ? a.ntiles : 256;
   if (C0 > 0) {
     const int64_t npair = (int64_t)CI * (9 * C0 + 1);
@@ -991,6 +1106,7 @@ int launch_conv_dgrad_wgrad0_reg_t(Ctx* c, ConvDgradArgs a, int nimg, const std:
   if (TQ < 1 || !fits(TQ)) return 1;
   a.NB = cdiv(a.Ho, TQ); a.TQ = cdiv(a.Ho, a.NB); a.NB = cdiv(a.Ho, a.TQ); a.ntiles = nimg * a.NB;
   a.dv_rb0 = make_fastdiv(rb0); a.dv_mrow = make_fastdiv(a.W * 4); a.seg_split = S::seg_split(a.Wo, a.TQ);
+  if (c->dry) return PPO_OK;
   int gx = a.ntiles < 256 ? a.ntiles : 256;
   const int64_t npair = (int64_t)S::CI * (9 * C0 + 1);
   { const int erc = ensure_partial(c, gx * npair, 0); if (erc) return erc; }
@@ -1220,14 +1336,21 @@ int conv_small_backward(Ctx* c, const int32_t* idx, int n, bool acc, int cur) {
 // Encoder of the feed-forward configurations: convolutions with fused bias + ReLU, the last one writing into the
 // feature matrix, whose tail columns receive the proprioception.  `n` samples selected by device indices idx
 // (NULL: samples first .. first + n - 1 of the buffer).
-int encoder_forward_ff(Ctx* c, const int32_t* idx, int n, int64_t first) {
+// train: a backward pass follows and wants the mask bits.
+int encoder_forward_ff(Ctx* c, const int32_t* idx, int n, int64_t first, bool train) {
   const int V = c->V, nimg = n * V;
   bool proprio_done = false;
   if (idx) first = 0;
   if (conv_small_covers(c)) return conv_small_forward(c, idx, n, first);
   const bf16_t* const proprio = c->proprio + first * c->P;
-  {  // first convolution straight from the rollout buffer
-    ImgAddr in; in.base = c->obs + first * c->img_elems * V; in.idx = idx; in.stride_b = c->img_elems * V; in.stride_v = c->img_elems; in.V = V;
+  ImgAddr in; in.base = c->obs + first * c->img_elems * V; in.idx = idx; in.stride_b = c->img_elems * V; in.stride_v = c->img_elems; in.V = V;
+  const bool both = train ? c->f01_train : c->f01_fwd;
+  if (both) {
+    const int rc = launch_conv01_fwd(c, in, conv_out_addr(c, 1, c->act[1], c->feat), proprio, n, train);
+    if (rc) return rc == 1 ? fail(c, PPO_ESHAPE, "the first two convolutions' kernel does not cover the shapes it was chosen for") : rc;
+    c->abits_ok[0] = train; c->abits_ok[1] = train && c->nconv > 2;
+    proprio_done = true;
+  } else {  // first convolution straight from the rollout buffer
     int Co = c->cC[1], Ho = c->cH[1], Wo = c->cW[1];
     int64_t M = (int64_t)nimg * Ho * Wo;
     ProfScope ps(c, "conv_fwd.0", 2.0 * (double)M * Co * 9 * c->cC[0], 2.0 * ((double)nimg * c->img_elems + (double)M * Co));
@@ -1235,12 +1358,12 @@ int encoder_forward_ff(Ctx* c, const int32_t* idx, int n, int64_t first) {
     const int grid = cdiv(M, 32 * 4 * TPW);
     Conv0Args ca;
     ca.in = in; ca.in.prepare(); ca.out = c->act[0]; ca.w = c->shadow + c->convW[0]; ca.bias = c->p + c->convB[0]; ca.zpage = c->zpage;
-    ca.bits = c->nconv > 1 ? c->abits[0] : nullptr;
+    ca.bits = train && c->nconv > 1 ? c->abits[0] : nullptr;
     ca.H = c->cH[0]; ca.W = c->cW[0]; ca.Ho = Ho; ca.Wo = Wo; ca.Cout = Co; ca.TR = 0; ca.NB = 0; ca.ntiles = 0;
     ca.tile_blocks = 0; ca.gather_blocks = 1; ca.pB = n; ca.P = c->P; ca.pcol0 = V * c->flat; ca.proprio = proprio; ca.feat = c->feat; ca.feat_ld = c->feat_ld;
     int trc = c->cC[0] == 1 ? launch_conv0_fwd_tile_t<1>(c, ca, nimg) : (c->cC[0] == 3 ? launch_conv0_fwd_tile_t<3>(c, ca, nimg) : 1);
     if (trc != PPO_OK && trc != 1) return trc;
-    c->abits_ok[0] = trc == PPO_OK && c->nconv > 1;
+    c->abits_ok[0] = trc == PPO_OK && ca.bits;
     proprio_done = trc == PPO_OK;
     if (trc != PPO_OK) {  // shapes the LDS-ring kernel does not cover
       if (c->cC[0] == 1)
@@ -1250,7 +1373,7 @@ int encoder_forward_ff(Ctx* c, const int32_t* idx, int n, int64_t first) {
       LAUNCHCHK(c, "k_conv1_fwd");
     }
   }
-  for (int l = 1; l < c->nconv; ++l) {
+  for (int l = both ? 2 : 1; l < c->nconv; ++l) {
     AConvFwd al;
     al.in = conv_out_addr(c, l - 1, c->act[l - 1], nullptr);
     al.H = c->cH[l]; al.W = c->cW[l]; al.Cin = c->cC[l]; al.lc = ilog2(al.Cin); al.Ho = c->cH[l + 1]; al.Wo = c->cW[l + 1];
@@ -1260,7 +1383,7 @@ int encoder_forward_ff(Ctx* c, const int32_t* idx, int n, int64_t first) {
     ep.map.stride_b = o.stride_b; ep.map.stride_v = o.stride_v; ep.map.V = V; ep.map.HW = al.Ho * al.Wo; ep.map.C = c->cC[l + 1]; ep.map.M = al.M;
     ep.out = const_cast<bf16_t*>(o.base); ep.bias = c->p + c->convB[l]; ep.mask = nullptr; ep.N = c->cC[l + 1];
     double ab = 2.0 * ((double)nimg * al.H * al.W * al.Cin + (double)al.M * c->cC[l + 1] + (double)al.K * c->cC[l + 1]);
-    const bool want_bits = l < c->nconv - 1;  // the last layer's mask is applied by the first linear layer's input gradient
+    const bool want_bits = train && l < c->nconv - 1;  // the last layer's mask is applied by the first linear layer's input gradient
     int rc = launch_conv_fwd_tile(c, al, o, c->cC[l + 1], c->shadow + c->convW[l], c->p + c->convB[l], nimg, "conv_fwd." + std::to_string(l), ab,
                                   want_bits ? c->abits[l] : nullptr);
     c->abits_ok[l] = want_bits && rc == PPO_OK;
@@ -1301,8 +1424,8 @@ int encoder_forward_generic(Ctx* c, const int32_t* idx, int n, int64_t first);
 
 // Forward of `n` samples of a feed-forward network selected by device indices idx (NULL: samples first ..
 // first + n - 1 of the buffer).
-int forward_chunk(Ctx* c, const int32_t* idx, int n, bool with_head = true, int64_t first = 0) {
-  const int rc = (c->ln || c->E > 0) ? encoder_forward_generic(c, idx, n, first) : encoder_forward_ff(c, idx, n, first);
+int forward_chunk(Ctx* c, const int32_t* idx, int n, bool train, bool with_head, int64_t first = 0) {
+  const int rc = (c->ln || c->E > 0) ? encoder_forward_generic(c, idx, n, first) : encoder_forward_ff(c, idx, n, first, train);
   if (rc) return rc;
   return trunk_forward(c, c->feat, c->feat_ld, n, with_head);
 }
@@ -1366,9 +1489,16 @@ int encoder_backward_ff(Ctx* c, const int32_t* idx, int n, bool acc, int cur) {
     AConvFwd xl; xl.in = conv_out_addr(c, l - 1, c->act[l - 1], nullptr);
     xl.H = H; xl.W = W; xl.Cin = Ci; xl.lc = ilog2(Ci); xl.Ho = Ho; xl.Wo = Wo; xl.M = dl.M; xl.K = 9 * Ci;
     const double wab = 2.0 * ((double)dl.M * Co + (double)nimg * H * W * Ci) + 4.0 * 9.0 * Ci * Co;
-    int rc = launch_conv_wgrad_tile(c, dy, xl, Co, nimg, c->g + c->convW[l], c->g + c->convB[l], acc, "conv_wgrad." + std::to_string(l), wab);
-    if (rc == PPO_OK + 1)
-      rc = launch_wgrad(c, dl, xl, Co, 9 * Ci, dl.M, c->g + c->convW[l], c->g + c->convB[l], acc, "conv_wgrad." + std::to_string(l), wab);
+    ImgAddr in; in.base = c->obs; in.idx = idx; in.stride_b = c->img_elems * V; in.stride_v = c->img_elems; in.V = V;
+    int rc;
+    if (l == 1 && c->f01_train) {
+      rc = launch_conv01_wgrad(c, in, dy, nimg, acc);
+      if (rc == 1) return fail(c, PPO_ESHAPE, "the second convolution's weight-gradient kernel does not cover the shapes it was chosen for");
+    } else {
+      rc = launch_conv_wgrad_tile(c, dy, xl, Co, nimg, c->g + c->convW[l], c->g + c->convB[l], acc, "conv_wgrad." + std::to_string(l), wab);
+      if (rc == PPO_OK + 1)
+        rc = launch_wgrad(c, dl, xl, Co, 9 * Ci, dl.M, c->g + c->convW[l], c->g + c->convB[l], acc, "conv_wgrad." + std::to_string(l), wab);
+    }
     if (rc) return rc;
     // transposed convolution over horizontal pixel pairs, both row parities in one launch (grid.z)
     AConvDgrad al; al.dy = dy; al.Ho = Ho; al.Wo = Wo; al.Cout = Co; al.lco = ilog2(Co); al.H = H; al.W = W; al.dy_imgs = nimg;
@@ -1385,7 +1515,6 @@ int encoder_backward_ff(Ctx* c, const int32_t* idx, int n, bool acc, int cur) {
     const size_t wlds = (size_t)6 * Co * BNf * sizeof(bf16_t);  // both parities' packed weights, resident in LDS
     if (l == 1 && wlds <= 56 * 1024) {
       // fused with the first layer's weight gradient: its input gradient never leaves the chip
-      ImgAddr in; in.base = c->obs; in.idx = idx; in.stride_b = c->img_elems * V; in.stride_v = c->img_elems; in.V = V;
       in.prepare(); al.prepare(); ep.map.prepare();
       const int K0 = 9 * c->cC[0], npair = Ci * (K0 + 1), tpp = cdiv(M0, 128);
       int grid = 2 * tpp < 512 ? 2 * tpp : 512;
@@ -1833,7 +1962,7 @@ int forward_seq_chunk(Ctx* c, const int32_t* env, int ne, bool with_head) {
   const int T = c->T, n = ne * T, H = c->H;
   hipLaunchKernelGGL(k_seq_index, dim3(cdiv(n, 256)), dim3(256), 0, c->stream, env, ne, T, c->N, c->seqidx);
   LAUNCHCHK(c, "k_seq_index");
-  int rc = (c->ln || c->E > 0) ? encoder_forward_generic(c, c->seqidx, n, 0) : encoder_forward_ff(c, c->seqidx, n, 0);
+  int rc = (c->ln || c->E > 0) ? encoder_forward_generic(c, c->seqidx, n, 0) : encoder_forward_ff(c, c->seqidx, n, 0, true);
   if (rc) return rc;
   const bool side = lstm_side_by_side(c);
   for (int l = 0; l < c->nl; ++l) {
@@ -2044,7 +2173,7 @@ int run_update(Ctx* c, const ppo_hparams* hp, ppo_mb_stats* host_stats, bool dis
         // the rollout samples of the chunk's rows: the permutation's entries themselves, or the index list that
         // forward_seq_chunk builds from the chunk's environments
         const int32_t* rows = recurrent ? c->seqidx : units + c0;
-        rc = recurrent ? forward_seq_chunk(c, units + c0, nu, !fused_head) : forward_chunk(c, rows, n, !fused_head);
+        rc = recurrent ? forward_seq_chunk(c, units + c0, nu, !fused_head) : forward_chunk(c, rows, n, true, !fused_head);
         if (rc) return rc;
         float* sp = c->stat_part + (int64_t)ci * blocks_per_chunk * LOSS_NSTAT;
         float* dp = c->dls_part + (int64_t)ci * blocks_per_chunk * 32;
@@ -2141,6 +2270,21 @@ int create_read_staging(Ctx* c) {
   return PPO_OK;
 }
 
+// Which passes run the first two convolutions in one kernel per direction: the forward where its kernel covers the shapes; in
+// training the weight gradient and the input gradient must as well (nothing then reads the first layer's output from memory).
+void choose_conv01(Ctx* c) {
+  c->f01_fwd = c->f01_train = false;
+  if (c->ln || c->E > 0 || c->nl > 0 || c->nconv < 2 || conv_small_covers(c)) return;
+  ImgAddr none; none.base = nullptr; none.idx = nullptr; none.stride_b = none.stride_v = 0; none.V = c->V;
+  static const uint32_t some_bits = 0;
+  int grid = 0;
+  c->dry = true;
+  c->f01_fwd = launch_conv01_fwd(c, none, none, nullptr, 1, false) == PPO_OK;
+  c->f01_train = c->f01_fwd && launch_conv01_wgrad(c, none, none, 1, false) == PPO_OK &&
+                 launch_conv_dgrad_wgrad0_tile(c, none, none, &some_bits, nullptr, c->cC[2], c->cC[1], c->cH[1], c->cW[1], c->cH[2], c->cW[2], none, c->cC[0], c->cH[0], c->cW[0], 1,
+                                               "", 0.0, 0.0, &grid) == PPO_OK;
+  c->dry = false;
+}
 int create_impl(Ctx* c) {
   build_geometry(c);
   HIPCHK(c, hipGetDevice(&c->dev));
@@ -2151,6 +2295,7 @@ int create_impl(Ctx* c) {
   if (CH > c->S) CH = c->S;
   if (CH < 1) CH = 1;
   c->CH = CH;
+  choose_conv01(c);
   // the kernels index rows with 32-bit integers
   if ((int64_t)CH * V * c->cH[1] * c->cW[1] >= (1LL << 31) || (int64_t)CH * c->feat_ld >= (1LL << 40))
     return fail(c, PPO_ESHAPE, "chunk of %d samples is too large for 32-bit row indices; lower max_chunk", CH);
@@ -2184,9 +2329,10 @@ int create_impl(Ctx* c) {
   int64_t gmax = (int64_t)CH * c->feat_ld;
   for (int l = 0; l < c->nconv - 1; ++l) {
     int64_t e = (int64_t)CH * V * c->cC[l + 1] * c->cH[l + 1] * c->cW[l + 1];
-    DALLOC(c, c->act[l], e);
+    const bool in_memory = l > 0 || !c->f01_train;  // else neither the first layer's output nor its gradient is
+    if (in_memory) DALLOC(c, c->act[l], e);
     DALLOC(c, c->abits[l], (int64_t)CH * V * c->cH[l + 1] * c->cW[l + 1] * ((c->cC[l + 1] + 31) / 32));
-    if (e > gmax) gmax = e;
+    if (in_memory && e > gmax) gmax = e;
   }
   DALLOC(c, c->feat, (int64_t)CH * c->feat_ld);
   if ((int64_t)CH * c->fin[0] > gmax) gmax = (int64_t)CH * c->fin[0];
@@ -2744,7 +2890,7 @@ int ppo_forward(ppo_ctx* c, const int32_t* d_idx, int64_t count, float* d_mu, fl
     int n = (int)((count - c0 < c->CH) ? count - c0 : c->CH);
     const int32_t* idx = d_idx ? d_idx + c0 : nullptr;
     const bool fused = head_act_covers(c);
-    int rc = forward_chunk(c, idx, n, !fused, c0);  // without indices: samples c0 .. c0 + n - 1
+    int rc = forward_chunk(c, idx, n, false, !fused, c0);  // without indices: samples c0 .. c0 + n - 1
     if (rc) return rc;
     if (fused) {
       HeadActArgs a = {};
@@ -2777,7 +2923,7 @@ int ppo_act(ppo_ctx* c, int32_t t, const void* d_obs, const float* d_proprio, co
   for (int64_t c0 = 0; c0 < c->N; c0 += c->CH) {
     const int n = (int)((c->N - c0 < c->CH) ? c->N - c0 : c->CH);
     const bool fused = head_act_covers(c);
-    rc = forward_chunk(c, nullptr, n, !fused, first + c0);
+    rc = forward_chunk(c, nullptr, n, false, !fused, first + c0);
     if (rc) return rc;
     const int64_t s0 = first + c0;
     if (fused) {

@@ -121,6 +121,39 @@ def test_gradients_wide_rows(L, ci, h, w):
     _check_gradients(L, cfg, 6, 4)
 
 
+@pytest.mark.parametrize("c0,views,conv,h,w", [(1, 1, (32, 64), 9, 10), (1, 1, (32, 64, 16), 16, 8), (1, 1, (32, 64, 64), 21, 67),
+                                               (1, 2, (32, 64, 64), 45, 90), (1, 1, (32, 64, 64), 13, 333), (1, 1, (32, 64, 64), 35, 280),
+                                               (3, 1, (32, 64), 11, 14), (3, 2, (32, 64, 32), 30, 71), (3, 1, (32, 64, 64), 14, 200)])
+def test_first_two_convolutions_in_one_kernel(L, c0, views, conv, h, w):
+    """The second layer's kernels that make the first layer's output in LDS: tiles of few and of many pixel groups, one and several
+    bands, tiles of columns, a last band or column that ends inside a tile, the result in the feature matrix (two layers)."""
+    cfg = configs.get_config(1, num_envs=10, horizon=4)
+    cfg["net"].update(in_c=c0, n_views=views, in_h=h, in_w=w, conv_ch=list(conv))
+    _check_gradients(L, cfg, 10, 4)
+
+
+@pytest.mark.parametrize("c0", [1, 3])
+def test_non_finite_pixels_stay_in_their_sample(L, c0):
+    """Values beside a window are read with it and must not reach its sum: NaN and infinity in one sample's image leave every
+    other sample's outputs as they were, bit for bit."""
+    import torch
+    cfg = configs.get_config(1, num_envs=12, horizon=1)
+    cfg["net"].update(in_c=c0, in_h=37, in_w=50)
+    ro = synth.rollout(cfg)
+    outs = []
+    for bad in (False, True):
+        if bad:
+            ro["obs"][0, 5, 0, :, 20, 30] = np.nan
+            ro["obs"][0, 7, 0, :, :, 49] = np.inf
+        lrn = L.Learner(cfg["net"], 12, 1, "fp32")
+        lrn.set_params(synth.init_params(cfg["net"], 4))
+        fill_learner(lrn, dict(cfg, obs_dtype="fp32"), ro)
+        outs.append([x.cpu().numpy() for x in lrn.forward()])
+    keep = [i for i in range(12) if i not in (5, 7)]
+    for a, b in zip(*outs):
+        np.testing.assert_array_equal(a[keep], b[keep])
+
+
 @pytest.mark.parametrize("c0,conv,h,w", [(1, (32, 64, 32), 22, 226), (1, (8, 16), 33, 47), (1, (16, 32, 64, 128), 40, 64), (1, (32, 64), 16, 130), (1, (64, 64), 21, 24),
                                          (3, (16, 32), 18, 66), (3, (32, 64, 64), 37, 53), (1, (16, 64), 9, 16)])
 def test_gradients_with_layer_norm(L, c0, conv, h, w):

@@ -50,6 +50,7 @@ struct Conv0Src {
   const float* bias;     // [32]
   uint32_t* bits;        // BITS: one word per pixel of the first layer's output, bit c = channel c is positive
   int H, rowbytes;       // rows of rowbytes = 2 * C0 * W bytes, a multiple of 16
+  int bpitch;            // BITS: words per row
   int nimage;            // LDS slots of the image ring (bands in flight + 1)
 };
 
@@ -103,7 +104,7 @@ struct Conv0Producer {
       wa[g] = live ? (uint32_t)(row * WP * 64) + ((uint32_t)(sl * 64 + h * 32) ^ tile_swz_bits<32>((uint32_t)(sl * 64)))
                    : (uint32_t)((2 * TR + 1) * WP * 64 + h * 32);
       rc[g] = (uint32_t)row | (uint32_t)sl << 16;
-      boff[g] = (uint32_t)(((row - 1) * W1 + sl - 1) * 4 + h * 2);
+      boff[g] = (uint32_t)(((row - 1) * s.bpitch + sl - 1) * 4 + h * 2);
     }
 #pragma unroll
     for (int i = 0; i < NOFF; ++i) dlt[i] = C0 == 1 ? 2 * LB + 4 * h : i == 0 ? h * LB + 4 : h ? (i - 1) % 3 * LB : 2 * LB + 4 * i;

@@ -54,9 +54,11 @@ struct ConvDgradW0Shape {
   static int dyimg_bytes(int Wo, int TQ) { return (TQ + 1) * (Wo + 1) * 128; }
   static int img0_bytes(int W0, int C0, int TQ) { return (4 * TQ + 1) * W0 * C0 * 2; }
   static int mask_bytes(int W, int TQ) { return 2 * TQ * W * 4; }
+  // zeros behind the image rows: the windows of the columns that were added to a row reach past its end
+  __host__ __device__ static int slack_bytes(int W, int W0, int C0) { return 16 + (2 * W > W0 ? (2 * W - W0) * C0 * 2 : 0); }
   // ones: the slot ends with the block of bf16 ones of the forms whose width is known at compile time (one-channel images)
   static int slot_bytes(int W, int Wo, int W0, int C0, int TQ, bool ones) {
-    return dyimg_bytes(Wo, TQ) + img0_bytes(W0, C0, TQ) + 16 + mask_bytes(W, TQ) + W * 4 + 32 + (ones ? 4 * W0 * C0 + 32 : 0);
+    return dyimg_bytes(Wo, TQ) + img0_bytes(W0, C0, TQ) + slack_bytes(W, W0, C0) + mask_bytes(W, TQ) + W * 4 + 32 + (ones ? 4 * W0 * C0 + 32 : 0);
   }
   static int ring_bytes(int W, int Wo, int W0, int C0, int TQ, bool ones) {
     const int r = NBUF * slot_bytes(W, Wo, W0, C0, TQ, ones);
@@ -77,6 +79,9 @@ struct ConvDgradW0Shape {
 };
 
 // Requires (checked by the host): W % 8 == 0 (Wo % 4 == 0), (W0 * C0 * 2) % 16 == 0, Wo == W / 2 <= BQ, TQ * Wo <= BQ.
+// Other widths are rounded up: the added columns' dY pixels are zeros in LDS, their mask words (the forward kernel stores rows
+// of W words, the added ones zero) drop whatever comes out.  38-wide results (1250 images of 52x76) took the LDS-fused form,
+// 46 us; here 38 (600 images of 3x52x100: 135 and 108 us).
 // WC: the width W of the result known at compile time (row pitches become instruction offsets), or 0: taken from a.W.
 template <int C0, int NCW, int WC>
 __global__ __launch_bounds__((NCW + 4) * 64) void k_conv_dgrad_wgrad0_tile(ConvDgradArgs a) {
@@ -89,23 +94,25 @@ __global__ __launch_bounds__((NCW + 4) * 64) void k_conv_dgrad_wgrad0_tile(ConvD
   const int RP = (Wo + 1) * 128, dyimg_bytes = (TQ + 1) * RP;  // dY image: row pitch, bytes
   const int RB0 = (WC ? 2 * WC : a.W0) * C0 * 2, img0_bytes = (4 * TQ + 1) * RB0;
   const int MRB = W * 4, mask_bytes = 2 * TQ * MRB;
-  // slot: dY image | image rows | 16 zero bytes | mask words | one row of mask words + 32 bytes of zeros |
+  // slot: dY image | image rows | 16 zero bytes or more | mask words | one row of mask words + 32 bytes of zeros |
   // one-channel images: 32 bytes of bf16 ones, and 32 more two image rows further (the window of the bias column)
-  const int OFF_IMG = dyimg_bytes, OFF_MSK = OFF_IMG + img0_bytes + 16, OFF_Z = OFF_MSK + mask_bytes, OFF_ONES = OFF_Z + MRB + 32;
+  const int slack = WC ? 16 : S::slack_bytes(W, a.W0, C0);
+  const int OFF_IMG = dyimg_bytes, OFF_MSK = OFF_IMG + img0_bytes + slack, OFF_Z = OFF_MSK + mask_bytes, OFF_ONES = OFF_Z + MRB + 32;
   constexpr bool ONES = C0 == 1 && WC != 0;  // the bias column reads a block of ones (costs 2 image rows of LDS per slot) instead of being ORed in
   const int SLOT = OFF_ONES + (ONES ? 2 * RB0 + 32 : 0);
   const int vb = xcd_block((int)blockIdx.x, (int)gridDim.x);  // this block's number in the dealing of tiles
   const int nq = (a.ntiles > vb) ? (a.ntiles - 1 - vb) / (int)gridDim.x + 1 : 0;
 
   // ---- once: the zero pads no load ever writes
-  for (int i = tid; i < NBUF * (TQ + 1) * 8; i += S::THREADS) {
-    const int chunk = i & 7, row = i >> 3, s = row / (TQ + 1), rr = row - s * (TQ + 1);
-    *reinterpret_cast<uint4*>(lds + s * SLOT + rr * RP + Wo * 128 + chunk * 16) = make_uint4(0u, 0u, 0u, 0u);
-  }
+  for (int px = a.WoR; px <= Wo; ++px)
+    for (int i = tid; i < NBUF * (TQ + 1) * 8; i += S::THREADS) {
+      const int chunk = i & 7, row = i >> 3, s = row / (TQ + 1), rr = row - s * (TQ + 1);
+      *reinterpret_cast<uint4*>(lds + s * SLOT + rr * RP + px * 128 + chunk * 16) = make_uint4(0u, 0u, 0u, 0u);
+    }
   {
-    const int nz = 1 + (MRB + 32) / 16;  // 16-byte pieces of zeros per slot: one behind the image rows, the tail behind the mask words
+    const int ns = slack / 16, nz = ns + (MRB + 32) / 16;  // 16-byte pieces of zeros per slot: behind the image rows, the tail behind the mask words
     for (int i = tid; i < NBUF * nz; i += S::THREADS) {
-      const int s = i / nz, k = i - nz * s, off = k == 0 ? OFF_IMG + img0_bytes : OFF_Z + (k - 1) * 16;
+      const int s = i / nz, k = i - nz * s, off = k < ns ? OFF_IMG + img0_bytes + k * 16 : OFF_Z + (k - ns) * 16;
       *reinterpret_cast<uint4*>(lds + s * SLOT + off) = make_uint4(0u, 0u, 0u, 0u);
     }
     if (ONES && tid < NBUF * 4) {
@@ -117,7 +124,7 @@ __global__ __launch_bounds__((NCW + 4) * 64) void k_conv_dgrad_wgrad0_tile(ConvD
   if (wave >= NCW) {
     // ------------------------------------------------------------------ loaders: piece i of a band belongs to loader i % 4
     const int lw = wave - NCW;
-    const int rowbytes = Wo * 128, segs = (rowbytes + 1023) >> 10;
+    const int rowbytes = a.WoR * 128, segs = (rowbytes + 1023) >> 10;
     const int n_im = (img0_bytes + 1023) >> 10, n_mk = (mask_bytes + 1023) >> 10;
     // piece j of a kind (rows of the dY image, 1 KiB pieces of the image rows, of the mask words) belongs to loader j % 4
     auto mine = [&](int n) { return n > lw ? (n - lw + S::NLW - 1) / S::NLW : 0; };

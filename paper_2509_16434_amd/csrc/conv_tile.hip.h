@@ -175,7 +175,7 @@ __global__ __launch_bounds__(512) void k_conv_fwd_tile(ConvTileArgs a) {
         const Pos p = pos(q);
         const bool edge = p.band == 0 || p.band == a.NB - 1 || (COLS && (p.part == 0 || p.part == a.NP - 1));
         const int row_lo = 2 * p.band * TR - 1, col_lo = 2 * p.part * Wo - 1;
-        char* bits = BITS0 ? reinterpret_cast<char*>(a.src0.bits + ((int64_t)p.img * a.H + row_lo + 1) * W + col_lo + 1) : nullptr;
+        char* bits = BITS0 ? reinterpret_cast<char*>(a.src0.bits + ((int64_t)p.img * a.H + row_lo + 1) * a.src0.bpitch + col_lo + 1) : nullptr;
         const int st = pr.produce(ring + pslot * ring_bytes, lds + (q & 1) * image_bytes, edge, row_lo, col_lo, a.H, W, bits, [](int) {});
         pslot = pslot + 1 == NI ? 0 : pslot + 1;
         return st;

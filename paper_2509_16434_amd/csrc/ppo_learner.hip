@@ -125,6 +125,7 @@ struct Ctx {
   uint32_t* abits[PPO_MAX_LAYERS] = {};  // sign bits of conv layer l's stored output for the current chunk (ReLU mask of the backward pass)
   bool abits_ok[PPO_MAX_LAYERS] = {};    // written by the forward kernel that ran for this chunk
   bool dry = false;                      // the launchers of the first two convolutions only say whether they cover the shapes
+  int b0pitch = 0;                       // words per row of abits[0] when f01_train
   bool f01_fwd = false, f01_train = false;  // those two run in one kernel: forward only / forward and backward (act[0] then stays unused)
   int64_t wver = 0;                      // bumped whenever the weights change (every repack_weights call)
   int64_t wd_ver[PPO_MAX_LAYERS] = {};   // weight version that wd[l] holds (0: none): packed on demand the first time,
@@ -872,7 +873,7 @@ int launch_conv01_fwd_t(Ctx* c, ConvTileArgs a, const std::string& name, double 
 Conv0Src conv0_src(Ctx* c, const ImgAddr& in, uint32_t* bits) {
   Conv0Src s;
   s.img = in; s.img.prepare(); s.w = c->shadow + c->convW[0]; s.bias = c->p + c->convB[0]; s.bits = bits;
-  s.H = c->cH[0]; s.rowbytes = c->cW[0] * c->cC[0] * 2; s.nimage = 0;
+  s.H = c->cH[0]; s.rowbytes = c->cW[0] * c->cC[0] * 2; s.bpitch = c->b0pitch; s.nimage = 0;
   return s;
 }
 int launch_conv01_fwd(Ctx* c, const ImgAddr& in, const ImgAddr& o, const bf16_t* proprio, int n, bool train) {
@@ -1049,7 +1050,7 @@ int launch_conv_dgrad_tile_t(Ctx* c, ConvDgradArgs a, int nimg, const std::strin
 ConvDgradArgs conv_dgrad_args(Ctx* c, const ImgAddr& dy, const ImgAddr& xa, const uint32_t* xbits, bf16_t* dx, const bf16_t* wt, int H, int W, int Ho, int Wo) {
   ConvDgradArgs a;
   a.dy = dy; a.dy.prepare(); a.dx = dx; a.xbits = xbits; a.x_stride_b = xa.stride_b; a.x_stride_v = xa.stride_v;
-  a.wt = wt; a.zpage = c->zpage; a.V = xa.V; a.H = H; a.W = W; a.Ho = Ho; a.Wo = Wo; a.TQ = 0; a.NB = 0; a.ntiles = 0; a.seg_split = 0;
+  a.wt = wt; a.zpage = c->zpage; a.V = xa.V; a.H = H; a.W = W; a.Ho = Ho; a.Wo = a.WoR = Wo; a.TQ = 0; a.NB = 0; a.ntiles = 0; a.seg_split = 0;
   a.img0 = ImgAddr(); a.img0.base = nullptr; a.img0.idx = nullptr; a.img0.stride_b = 0; a.img0.stride_v = 0; a.img0.V = 1;
   a.H0 = 0; a.W0 = 0; a.partial0 = nullptr;
   return a;
@@ -1093,10 +1094,13 @@ int launch_conv_dgrad_tile(Ctx* c, const ImgAddr& dy, const ImgAddr& xa, const u
 template <int C0, int NCW, int WC = 0>
 int launch_conv_dgrad_wgrad0_reg_t(Ctx* c, ConvDgradArgs a, int nimg, const std::string& name, double flops, double abytes, int* grid_out) {
   typedef ConvDgradW0Shape<NCW> S;
-  if (WC && a.W != WC) return 1;
+  const bool exact = a.W % 8 == 0 && a.Wo * 2 == a.W && a.W * 2 == a.W0;
+  if (!exact && !c->dry && !c->f01_train) return 1;  // only the two layers' forward kernel stores mask rows of a rounded-up width
+  a.WoR = a.Wo; a.W = cdiv(a.W, 8) * 8; a.Wo = a.W / 2;
+  if (WC && (a.W != WC || a.W0 != 2 * WC)) return 1;
   constexpr bool ones = C0 == 1 && WC != 0;  // the kernel's ONES
   const int rb0 = a.W0 * C0 * 2;
-  if (a.W % 8 || rb0 % 16 || a.Wo * 2 != a.W || a.Wo > S::BQ || a.H != (a.H0 + 1) / 2 || a.W * 2 != a.W0) return 1;
+  if (rb0 % 16 || a.Wo > S::BQ || a.H != (a.H0 + 1) / 2) return 1;
   auto fits = [&](int tq) {
     return tq * a.Wo <= S::BQ && S::lds_bytes(a.W, a.Wo, a.W0, C0, tq, ones) <= 160 * 1024 && S::loads_fit(a.W, a.Wo, a.W0, C0, tq) &&
            S::dyimg_bytes(a.Wo, tq) <= 65536;  // offsets into the page of zeros
@@ -1106,7 +1110,7 @@ int launch_conv_dgrad_wgrad0_reg_t(Ctx* c, ConvDgradArgs a, int nimg, const std:
   if (TQ < 1 || !fits(TQ)) return 1;
   a.NB = cdiv(a.Ho, TQ); a.TQ = cdiv(a.Ho, a.NB); a.NB = cdiv(a.Ho, a.TQ); a.ntiles = nimg * a.NB;
   a.dv_rb0 = make_fastdiv(rb0); a.dv_mrow = make_fastdiv(a.W * 4); a.seg_split = S::seg_split(a.Wo, a.TQ);
-  if (c->dry) return PPO_OK;
+  if (c->dry) { c->b0pitch = a.W; return PPO_OK; }
   int gx = a.ntiles < 256 ? a.ntiles : 256;
   const int64_t npair = (int64_t)S::CI * (9 * C0 + 1);
   { const int erc = ensure_partial(c, gx * npair, 0); if (erc) return erc; }
@@ -1128,6 +1132,7 @@ int launch_conv_dgrad_wgrad0_tile(Ctx* c, const ImgAddr& dy, const ImgAddr& xa, 
   if (Co != 64 || Ci != 32 || (C0 != 1 && C0 != 3) || dy.idx || nimg < 1 || !xbits) return 1;
   ConvDgradArgs a = conv_dgrad_args(c, dy, xa, xbits, nullptr, wt, H, W, Ho, Wo);
   a.img0 = img0; a.img0.prepare(); a.H0 = H0; a.W0 = W0;
+  if (c->dry) c->b0pitch = W;  // words per mask row, unless a form below rounds it up
   // eight compute waves (two per SIMD) when the larger tile fits, else four
   // (the 80-wide result of 120x160 depth images has a form of its own with the row pitches known at compile time)
   int rrc = C0 == 1 ? launch_conv_dgrad_wgrad0_reg_t<1, 8, 80>(c, a, nimg, name, flops, abytes, grid_out) : 1;
@@ -1138,6 +1143,7 @@ int launch_conv_dgrad_wgrad0_tile(Ctx* c, const ImgAddr& dy, const ImgAddr& xa, 
     rrc = C0 == 1 ? launch_conv_dgrad_wgrad0_reg_t<1, 4>(c, a, nimg, name, flops, abytes, grid_out)
                   : launch_conv_dgrad_wgrad0_reg_t<3, 4>(c, a, nimg, name, flops, abytes, grid_out);
   if (rrc != 1) return rrc;
+  if (!c->dry && c->f01_train && c->b0pitch != W) return fail(c, PPO_ENOMEM, "the input-gradient kernel does not fit the workspace it was chosen for");
   return C0 == 1 ? launch_conv_dgrad_tile_t<32, 1>(c, a, nimg, name, flops, abytes, grid_out)
                  : launch_conv_dgrad_tile_t<32, 3>(c, a, nimg, name, flops, abytes, grid_out);
 }
@@ -2331,7 +2337,9 @@ int create_impl(Ctx* c) {
     int64_t e = (int64_t)CH * V * c->cC[l + 1] * c->cH[l + 1] * c->cW[l + 1];
     const bool in_memory = l > 0 || !c->f01_train;  // else neither the first layer's output nor its gradient is
     if (in_memory) DALLOC(c, c->act[l], e);
-    DALLOC(c, c->abits[l], (int64_t)CH * V * c->cH[l + 1] * c->cW[l + 1] * ((c->cC[l + 1] + 31) / 32));
+    const int64_t words = (int64_t)CH * V * c->cH[l + 1] * (l == 0 && c->f01_train ? c->b0pitch : c->cW[l + 1]) * ((c->cC[l + 1] + 31) / 32);
+    DALLOC(c, c->abits[l], words);
+    if (l == 0 && c->f01_train) HIPCHK(c, hipMemsetAsync(c->abits[0], 0, (size_t)words * 4, c->stream));  // the words behind a row's last pixel stay zero
     if (in_memory && e > gmax) gmax = e;
   }
   DALLOC(c, c->feat, (int64_t)CH * c->feat_ld);

@@ -132,6 +132,14 @@ def test_first_two_convolutions_in_one_kernel(L, c0, views, conv, h, w):
     _check_gradients(L, cfg, 10, 4)
 
 
+@pytest.mark.parametrize("ci,h,w", [(1, 12, 34), (1, 27, 50), (1, 40, 61), (1, 21, 147), (3, 20, 35), (3, 33, 106)])
+def test_input_gradient_of_a_rounded_up_width(L, ci, h, w):
+    """First-layer outputs whose width is no multiple of 8: 17, 25, 31, 74; 18 and 53 (RGB)."""
+    cfg = configs.get_config(ci, num_envs=10, horizon=4)
+    cfg["net"].update(in_h=h, in_w=w)
+    _check_gradients(L, cfg, 10, 4)
+
+
 @pytest.mark.parametrize("c0", [1, 3])
 def test_non_finite_pixels_stay_in_their_sample(L, c0):
     """Values beside a window are read with it and must not reach its sum: NaN and infinity in one sample's image leave every

@@ -132,6 +132,15 @@ def test_first_two_convolutions_in_one_kernel(L, c0, views, conv, h, w):
     _check_gradients(L, cfg, 10, 4)
 
 
+@pytest.mark.parametrize("conv,ln,h,w", [((32, 16), 0, 24, 33), ((32, 32, 64), 1, 40, 66), ((32, 128), 0, 29, 80), ((32, 128, 64), 1, 35, 42)])
+def test_weight_gradient_dealt_by_halves(L, conv, ln, h, w):
+    """32 input channels: the last k-tile and the bias column go to the waves by halves of 64 output channels; fewer than 32 of them,
+    one half, two blocks of 64, behind made rows and behind stored ones (layer normalisation)."""
+    cfg = configs.get_config(1, num_envs=10, horizon=4)
+    cfg["net"].update(in_h=h, in_w=w, conv_ch=list(conv), layer_norm=ln)
+    _check_gradients(L, cfg, 10, 4)
+
+
 @pytest.mark.parametrize("ci,h,w", [(1, 12, 34), (1, 27, 50), (1, 40, 61), (1, 21, 147), (3, 20, 35), (3, 33, 106)])
 def test_input_gradient_of_a_rounded_up_width(L, ci, h, w):
     """First-layer outputs whose width is no multiple of 8: 17, 25, 31, 74; 18 and 53 (RGB)."""

@@ -1534,6 +1534,7 @@ int encoder_backward_ff(Ctx* c, const int32_t* idx, int n, bool acc, int cur) {
                                          "conv_dgrad.1+wgrad.0", fflops, fbytes, &tgrid);
       if (rc == PPO_OK) grid = tgrid;
       else if (rc != PPO_OK + 1) return rc;
+      else if (c->f01_train) return fail(c, PPO_ESHAPE, "the second convolution's input-gradient kernel does not cover the shapes it was chosen for");  // (its mask is nowhere else)
       else {
         rc = ensure_packed_dgrad_weights(c, l);
         if (rc) return rc;

@@ -20,7 +20,7 @@
 // Measured (16384 images of 120x160, the layers' own kernels before -> this): forward 1206 + 1420 -> 1204 us (mask bits of both
 // layers stored), weight gradient of the second layer 1124 -> 1271 us (1180 with the later changes to its waves); forward alone, 4096 images, 279 + 367 -> 279 us.  The
 // rows are made at the expense of the compute waves' issue slots: matrix and vector instructions together fill 0.79 of a
-// SIMD's cycles forward, 0.75 in the weight gradient; memory would allow some 860 and 650 us.
+// SIMD's cycles forward, 0.76 in the weight gradient; memory would allow some 860 and 650 us.
 #pragma once
 #include "conv_bits.hip.h"
 

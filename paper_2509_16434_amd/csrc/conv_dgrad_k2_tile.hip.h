@@ -17,10 +17,12 @@
 // positions.  Two barriers per tile order the three roles; the finishing waves work one tile
 // behind the compute waves (double-buffered staging) and fetch their mask words two tiles ahead.
 //
-// Partial sums are staged in fp32 (F32: networks with layer normalisation or an embedding, whose
-// gradient is one fp32 sum over all 128 channels in the implicit-GEMM form too) or rounded to bf16
-// (networks without either: half the LDS, so twice the rows per band where rows are wide; the
-// rounding of the halves adds to the rounding of their sum).
+// Partial sums are staged in fp32 (F32: networks with layer normalisation or an embedding, and wide
+// images, on which the layer below cuts its rows into columns: their gradient is one fp32 sum over all
+// 128 channels in the implicit-GEMM form too, and where the halves cancel, halves rounded to bf16 left
+// a gradient with an error of 0.1 to 0.26 of its norm) or rounded to bf16 (the others: half the LDS, so
+// twice the rows per band where rows are wide; the rounding of the halves adds to the rounding of their
+// sum).
 #pragma once
 #include "conv_dgrad_tile.hip.h"
 

@@ -770,22 +770,29 @@ bool plan_cols(int Ho, int Wo, int maxpix, FITS fits, ColsPlan* out, int multipl
   return best >= 0;
 }
 
+// Bands of whole result rows for the forward kernel: *TR rows each, balanced, *NB of them; false where they do not fit (tiles
+// of columns then).
+template <int CIN, int WIDE>
+bool plan_fwd_rows(int W, int Ho, int Wo, int* TR, int* NB) {
+  typedef ConvTileShape<CIN, WIDE> S;
+  if (Wo > S::BM) return false;
+  *NB = cdiv(Ho, std::min(S::BM / Wo, Ho)); *TR = cdiv(Ho, *NB);
+  const int segs = cdiv(W * S::PIX, 1024), ni = cdiv(2 * *TR + 1, 4) * segs;  // loads per loader wave per band
+  return segs <= S::MAXSEG && ni <= 63 && S::lds_bytes(W + 2, *TR, 3) <= 160 * 1024;
+}
 // Forward convolution through the LDS-image kernel; returns 1 when the layer's shape is not one
 // it covers (the caller then takes the implicit-GEMM path).
 template <int CIN, int WIDE, bool RELU>
 int launch_conv_fwd_tile_t(Ctx* c, ConvTileArgs a, const std::string& name, double flops, double abytes) {
   typedef ConvTileShape<CIN, WIDE> S;
   const int nimg = a.ntiles;  // passed in as the image count
-  int segs = cdiv(a.W * S::PIX, 1024), slots = a.W + 2, form = 2, ni = 0;
-  if (a.Wo <= S::BM) {
-    const int trmax = std::min(S::BM / a.Wo, a.Ho);
-    a.NB = cdiv(a.Ho, trmax); a.TR = cdiv(a.Ho, a.NB);  // balanced bands
+  int slots = a.W + 2, form, ni;
+  if (plan_fwd_rows<CIN, WIDE>(a.W, a.Ho, a.Wo, &a.TR, &a.NB)) {
     a.TC = a.Wo; a.NP = 1;
-    ni = cdiv(2 * a.TR + 1, 4) * segs;  // loads per loader wave per band
+    ni = cdiv(2 * a.TR + 1, 4) * cdiv(a.W * S::PIX, 1024);
     // bands of four or more output rows share at most an eighth of their input rows with a neighbour: read once, non-temporal
     form = a.TR >= 4;
-  }
-  if (a.Wo > S::BM || segs > S::MAXSEG || ni > 63 || S::lds_bytes(slots, a.TR, 3) > 160 * 1024) {
+  } else {
     ColsPlan p;
     auto fits = [&](int tc, int tr) { return S::image_bytes(2 * tc + 1, tr) <= S::MAXLD * 4096 && S::lds_bytes(2 * tc + 1, tr, 3) <= 160 * 1024; };
     if (!plan_cols(a.Ho, a.Wo, S::BM, fits, &p)) return 1;
@@ -1559,7 +1566,11 @@ int encoder_backward_ff(Ctx* c, const int32_t* idx, int n, bool acc, int cur) {
     }
     double ab = 2.0 * ((double)nimg * Ho * Wo * Co + pix * Ci + 9.0 * Ci * Co) + (c->abits_ok[l - 1] && (Co == 64 || ep.mbits) ? pix * Ci / 8.0 : 2.0 * pix * Ci);
     const double dflops = 2.0 * (double)nimg * Ho * Wo * 9.0 * Ci * Co;
-    rc = !c->abits_ok[l - 1] ? 1 : launch_conv_dgrad_tile(c, dy, xa, c->abits[l - 1], c->gbuf[cur ^ 1], c->wtap[l], Co, Ci, H, W, Ho, Wo, nimg, "conv_dgrad." + std::to_string(l), dflops, ab, false);
+    // From 128 channels: fp32 halves where the layer below reads rows that its forward cuts into columns (they hold the sum that
+    // the implicit-GEMM form takes at once), else bf16 halves.
+    int tr, nb;
+    const bool f32 = l > 1 && !(c->cC[l - 1] == 32 ? plan_fwd_rows<32, 0>(c->cW[l - 1], H, W, &tr, &nb) : plan_fwd_rows<64, 0>(c->cW[l - 1], H, W, &tr, &nb));
+    rc = !c->abits_ok[l - 1] ? 1 : launch_conv_dgrad_tile(c, dy, xa, c->abits[l - 1], c->gbuf[cur ^ 1], c->wtap[l], Co, Ci, H, W, Ho, Wo, nimg, "conv_dgrad." + std::to_string(l), dflops, ab, f32);
     if (rc == PPO_OK + 1) {
       rc = ensure_packed_dgrad_weights(c, l);
       if (rc) return rc;

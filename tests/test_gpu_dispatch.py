@@ -328,6 +328,27 @@ def test_gradient_sum_over_128_channels_is_rounded_once(L, h, w):
     _check_gradients(L, cfg, 10, 4, opposed)
 
 
+@pytest.mark.parametrize("conv,h,w", [((32, 64, 64, 128), 24, 200), ((32, 64, 64, 128), 61, 322), ((32, 64, 64, 128), 20, 380), ((64, 64, 128), 43, 170), ((32, 64, 64, 128), 20, 450)])
+def test_gradient_sum_over_128_channels_of_wide_rows_is_rounded_once(L, conv, h, w):
+    """The same sum in a feed-forward network whose layer before the last reads rows of more than 48 pixels of 64 channels: bands
+    of fp32 halves up to the widest rows of the kernel (24 pixels of dY), and wider ones."""
+    cfg = configs.get_config(1, num_envs=10, horizon=2)
+    net, last = cfg["net"], f"conv{len(conv) - 1}"
+    net.update(in_h=h, in_w=w, conv_ch=list(conv), fc_dim=[32])
+
+    def opposed(params):
+        sl = synth.param_slices(net)
+        t = {n: params[a:b].reshape(s) for n, (a, b, s) in sl.items()}   # views
+        t[last + ".w"][64:] = t[last + ".w"][:64]
+        t[last + ".b"][64:] = t[last + ".b"][:64]
+        f = t["fc0.w"][:, :-net["proprio_dim"]].reshape(32, 128, -1)     # a copy
+        f[:, :64] = np.sign(f[:, :64]) * 2.0 ** np.round(np.log2(np.abs(f[:, :64]) + 1e-6))   # both halves exact in bf16
+        f[:, 64:] = -127 / 128 * f[:, :64]
+        t["fc0.w"][:, :-net["proprio_dim"]] = f.reshape(32, -1)
+
+    _check_gradients(L, cfg, 10, 2, opposed)
+
+
 def test_read_back_staging_is_allocated_at_creation(L):
     """The first read of a context into memory in hand allocates nothing: its pinned staging (two pieces, 2 MiB, for this
     network) is part of ppo_create."""

@@ -5,13 +5,14 @@
 // A wave makes 32 pixels x 32 channels ("a group") with one (C0 = 1) or two (C0 = 3) 32x32x16 MFMAs; what bounds it is
 // the vector work around them, so the operands are laid out to need almost none:
 //  * The window rows of a pixel lie in LDS as dwords (a row starts 16 or 32 bytes left of the tile's first window), and the
-//    weights are permuted to the order in which they are read.  C0 = 1: two dwords per row, (2x-2, 2x-1) and (2x, 2x+1), packed
-//    so that lane half 0 has eight taps and half 1 the ninth: two permutes, four masks.  C0 = 3: five dwords per row, the
-//    value in front of the window and its nine; rows 0, 1 and 2 without their first values fill three of the four groups of
-//    eight as they are, the first values of the three rows the last: two permutes, two masks.  The matrix core rounds after
-//    each group of eight, and a result near zero is the more exact the less the last groups change: with the values spread
-//    evenly (six and three taps, no permutes) 101 instead of 71 of 4.2 M outputs were rounded to another bf16 than the
-//    exact sum's.  Values outside the window have zero weights and are masked off as well: a NaN there must not reach the sum.
+//    weights are permuted to the order in which they are read.  The matrix core rounds after each group of eight (a lane half's
+//    operand), in which the order does not matter: the groups are those of k_conv0_fwd_tile, elements 0..7, 8..15, .. of the
+//    9*C0 window values row after row, and the sums its sums, bit for bit.  (A network may have its policy step here and its
+//    update there: the update's first step must see the policy that acted.)  C0 = 1: two dwords per row, (2x-2, 2x-1) and
+//    (2x, 2x+1), packed so that lane half 0 has eight taps and half 1 the ninth: two permutes, four masks.  C0 = 3: five
+//    dwords per row, the value in front of the window and its nine (x 0)(1 2)(3 4)(5 6)(7 8); each group is three dwords as
+//    they are and a pair from two others: two permutes, two masks.  Values outside the window have zero weights and are masked
+//    off as well: a NaN there must not reach the sum.
 //  * The weights' rows are permuted so that a lane ends up with 16 consecutive channels of its pixel: 8 conversions, 8
 //    clamps, two 16-byte LDS writes, and (BITS) its 16 mask bits are a half-word of the pixel's mask word.
 //  * Pixel -> address is the same for every tile; only tiles at an image's edge test which pixels exist (the others are
@@ -72,7 +73,7 @@ template <int C0, bool COLS, bool BITS>
 struct Conv0Producer {
   typedef Conv0Shape1<C0> S;
   static constexpr int KS = C0 == 1 ? 1 : 2, GPW = S::GPW, MAXL = S::MAXL;
-  static constexpr int NOFF = C0 == 1 ? 1 : 5;
+  static constexpr int NOFF = C0 == 1 ? 1 : 2;
   int b1[GPW], dlt[NOFF], pitch, ng, nl;
   uint32_t wa[GPW], rc[GPW], boff[GPW];
   int goff[MAXL];
@@ -107,7 +108,7 @@ struct Conv0Producer {
       boff[g] = (uint32_t)(((row - 1) * s.bpitch + sl - 1) * 4 + h * 2);
     }
 #pragma unroll
-    for (int i = 0; i < NOFF; ++i) dlt[i] = C0 == 1 ? 2 * LB + 4 * h : i == 0 ? h * LB + 4 : h ? (i - 1) % 3 * LB : 2 * LB + 4 * i;
+    for (int i = 0; i < NOFF; ++i) dlt[i] = C0 == 1 ? 2 * LB + 4 * h : (h + i) * LB;
     // row i of the product is channel ch: a lane's accumulators are then the channels h*16 .. h*16 + 15
     const int ch = ((l32 >> 2) & 1) * 16 + (l32 >> 3) * 4 + (l32 & 3);
     const bf16_t* wp = s.w + ch * 9 * C0;
@@ -117,8 +118,9 @@ struct Conv0Producer {
       // k-th value of this lane half: element t of window row u, or none
       int u, t;
       if (C0 == 1) { constexpr int order[8] = {0, 3, 1, 2, 4, 5, 6, 7}; u = 0; t = h ? (k == 6 ? 8 : -1) : order[k & 7]; }
-      else if (k < 8 || !h) { u = k < 8 ? h : 2; t = (k & 7) + 1; }
-      else { u = k == 11 ? 2 : k - 8; t = k == 10 || k > 11 ? -1 : 0; }
+      else if (k < 8) { u = k == 7 ? 0 : h; t = k == 7 ? 7 + h : k == 6 ? 0 : k + 1; }
+      else if (k < 10) { u = 1 + h; t = k - 1; }
+      else { u = 2; t = k == 15 ? 5 + h : h ? -1 : k == 14 ? 0 : k - 9; }
       v[k] = t >= 0 ? (uint32_t)wp[t >= 0 ? u * 3 * C0 + t : 0] : 0u;
     }
 #pragma unroll
@@ -126,10 +128,11 @@ struct Conv0Producer {
       w[m] = __builtin_bit_cast(bf16x8_t, make_uint4(v[8 * m] | v[8 * m + 1] << 16, v[8 * m + 2] | v[8 * m + 3] << 16, v[8 * m + 4] | v[8 * m + 5] << 16, v[8 * m + 6] | v[8 * m + 7] << 16));
 #pragma unroll
     for (int e = 0; e < 16; ++e) bias[e] = s.bias[h * 16 + e];
-    // C0 = 1: half 1 has but the first value of its shifted row; C0 = 3: half 1 packs the first values of the three rows
+    // C0 = 1: half 1 has but the first value of its shifted row; C0 = 3: the pairs (0 of row h, 7 or 8 of row 0) and (0 and 5 of
+    // row 2, or 6 of row 2)
     m2 = h ? 0u : 0xffffffffu;
-    m3 = C0 == 1 ? (h ? 0x0000ffffu : 0xffffffffu) : (h ? 0x07060302u : 0x03020100u);
-    m4 = h ? 0x07060c0cu : 0x03020100u;
+    m3 = C0 == 1 ? (h ? 0x0000ffffu : 0xffffffffu) : (h ? 0x07060302u : 0x05040302u);
+    m4 = h ? 0x07060c0cu : 0x05040302u;
     negw[0] = nonzero_weights(0); negw[1] = nonzero_weights(1);
   }
 
@@ -152,14 +155,16 @@ struct Conv0Producer {
   // work on them: the compute wave on the same SIMD leaves a lone dependent chain little.  Returns the stores surely issued.
   template <int NG, bool EDGE, class F>
   __device__ __forceinline__ int groups(const char* im, char* act, int row_lo, int col_lo, int H1, int W1, char* bits, F after) const {
-    constexpr int ND = C0 == 1 ? 6 : 8;
+    constexpr int ND = C0 == 1 ? 6 : 10;
     uint32_t d[NG][ND];
 #pragma unroll
     for (int g = 0; g < NG; ++g) {
       const char* const p1 = im + b1[g];
 #pragma unroll
       for (int i = 0; i < ND; ++i) {
-        const char* p = C0 == 1 ? (i < 2 ? p1 : i < 4 ? p1 + pitch : p1 + dlt[0]) + 4 * (i & 1) : i < 4 ? p1 + dlt[0] + 4 * i : p1 + dlt[(i - 3) % NOFF];
+        // C0 = 3: 0..3 = row h, 4 = the last of row 0, 5 = the last of row 1 + h, 6..9 = row 2
+        const char* p = C0 == 1 ? (i < 2 ? p1 : i < 4 ? p1 + pitch : p1 + dlt[0]) + 4 * (i & 1)
+                                : i < 4 ? p1 + dlt[0] + 4 * i : i == 4 ? p1 + 16 : i == 5 ? p1 + dlt[NOFF - 1] + 16 : p1 + 2 * pitch + 4 * (i - 6);
         d[g][i] = *reinterpret_cast<const uint32_t*>(p);
       }
     }
@@ -169,8 +174,9 @@ struct Conv0Producer {
         const uint4 v = make_uint4(__builtin_amdgcn_perm(x[2], x[0], 0x07060302u) & m2, x[1] & m2, x[3] & m2, __builtin_amdgcn_alignbit(x[5], x[4], 16) & m3);
         return __builtin_amdgcn_mfma_f32_32x32x16_bf16(w[0], __builtin_bit_cast(bf16x8_t, v), bias, 0, 0, 0);
       } else {
-        const f32x16_t acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(w[0], __builtin_bit_cast(bf16x8_t, make_uint4(x[0], x[1], x[2], x[3])), bias, 0, 0, 0);
-        const uint4 v = make_uint4(__builtin_amdgcn_perm(x[5], x[4], m3), __builtin_amdgcn_perm(x[6], x[5], m4), x[6] & m2, x[7] & m2);
+        const uint4 u = make_uint4(x[1], x[2], x[3], __builtin_amdgcn_perm(x[4], x[0], m3));
+        const f32x16_t acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(w[0], __builtin_bit_cast(bf16x8_t, u), bias, 0, 0, 0);
+        const uint4 v = make_uint4(x[5], x[7] & m2, x[8] & m2, __builtin_amdgcn_perm(x[9], x[6], m4));
         return __builtin_amdgcn_mfma_f32_32x32x16_bf16(w[KS - 1], __builtin_bit_cast(bf16x8_t, v), acc, 0, 0, 0);
       }
     };

@@ -349,6 +349,33 @@ def test_gradient_sum_over_128_channels_of_wide_rows_is_rounded_once(L, conv, h,
     _check_gradients(L, cfg, 10, 2, opposed)
 
 
+@pytest.mark.parametrize("c0,conv,h,w", [(1, (32, 32), 60, 81), (1, (32, 64, 64), 64, 64), (3, (32, 64), 60, 80), (3, (32, 32), 60, 80),
+                                         (3, (32, 16, 32), 45, 67), (3, (32, 32), 20, 270)])
+def test_the_update_sees_the_policy_that_acted(L, c0, conv, h, w):
+    """The first optimiser step on a fresh rollout evaluates the network as the policy step did, to the last bit (ratio 1 exactly),
+    whichever kernels the two take: the first two layers in one kernel for both, or for the policy step alone (second layers of
+    other than 64 channels)."""
+    import torch
+    N, T = 128, 2
+    cfg = configs.get_config(1, num_envs=N, horizon=T)
+    net = cfg["net"]
+    net.update(in_c=c0, in_h=h, in_w=w, conv_ch=list(conv), fc_dim=[64])
+    params = synth.init_params(net, 9)
+    a0, a1, _ = synth.param_slices(net)["logstd"]
+    params[a0:a1] = -8.0   # the log-probability moves by 3000 times a change of the mean
+    lrn = L.Learner(net, N, T, "bf16")
+    lrn.set_params(params)
+    gen = torch.Generator(device="cuda")
+    gen.manual_seed(3)
+    for t in range(T):
+        d = synth.rollout_step_torch(cfg, gen)
+        lrn.act(t, d["obs"].to(torch.bfloat16).contiguous(), d["proprio"].contiguous(), torch.randn(N, net["act_dim"], generator=gen, device="cuda"))
+        lrn.buffer_write_outcome(t, d["reward"].contiguous(), d["done"].contiguous())
+    lrn.gae(torch.zeros(N, device="cuda"), 0.99, 0.95)
+    st = lrn.update(dict(cfg["hp"], epochs=1, minibatches=1))
+    assert st[0]["approx_kl"] == 0.0 and st[0]["clip_frac"] == 0.0
+
+
 def test_read_back_staging_is_allocated_at_creation(L):
     """The first read of a context into memory in hand allocates nothing: its pinned staging (two pieces, 2 MiB, for this
     network) is part of ppo_create."""

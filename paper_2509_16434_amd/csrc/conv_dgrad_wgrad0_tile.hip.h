@@ -82,7 +82,9 @@ struct ConvDgradW0Shape {
 // Other widths are rounded up: the added columns' dY pixels are zeros in LDS, their mask words (the forward kernel stores rows
 // of W words, the added ones zero) drop whatever comes out.  38-wide results (1250 images of 52x76) took the LDS-fused form,
 // 46 us; here 38 (600 images of 3x52x100: 135 and 108 us).
-// WC: the width W of the result known at compile time (row pitches become instruction offsets), or 0: taken from a.W.
+// WC: the width W of the result known at compile time, of WC / 2 columns of dY in memory (row pitches become instruction offsets,
+// the loaders' parts of a row constants: as run-time values they cost 174 instead of 27 spilled scalars; 16384 images of 120x160
+// 808 -> 785 us), or 0: taken from a.
 template <int C0, int NCW, int WC>
 __global__ __launch_bounds__((NCW + 4) * 64) void k_conv_dgrad_wgrad0_tile(ConvDgradArgs a) {
   typedef ConvDgradW0Shape<NCW> S;
@@ -90,7 +92,7 @@ __global__ __launch_bounds__((NCW + 4) * 64) void k_conv_dgrad_wgrad0_tile(ConvD
   constexpr int NBUF = S::NBUF, K0 = 9 * C0, NV = K0 + 1, NT = (NV + 15) / 16;
   extern __shared__ __attribute__((aligned(16))) char lds[];
   const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-  const int W = WC ? WC : a.W, Wo = WC ? WC / 2 : a.Wo, TQ = a.TQ;
+  const int W = WC ? WC : a.W, Wo = WC ? WC / 2 : a.Wo, WoR = WC ? WC / 2 : a.WoR, TQ = a.TQ;
   const int RP = (Wo + 1) * 128, dyimg_bytes = (TQ + 1) * RP;  // dY image: row pitch, bytes
   const int RB0 = (WC ? 2 * WC : a.W0) * C0 * 2, img0_bytes = (4 * TQ + 1) * RB0;
   const int MRB = W * 4, mask_bytes = 2 * TQ * MRB;
@@ -104,7 +106,7 @@ __global__ __launch_bounds__((NCW + 4) * 64) void k_conv_dgrad_wgrad0_tile(ConvD
   const int nq = (a.ntiles > vb) ? (a.ntiles - 1 - vb) / (int)gridDim.x + 1 : 0;
 
   // ---- once: the zero pads no load ever writes
-  for (int px = a.WoR; px <= Wo; ++px)
+  for (int px = WoR; px <= Wo; ++px)
     for (int i = tid; i < NBUF * (TQ + 1) * 8; i += S::THREADS) {
       const int chunk = i & 7, row = i >> 3, s = row / (TQ + 1), rr = row - s * (TQ + 1);
       *reinterpret_cast<uint4*>(lds + s * SLOT + rr * RP + px * 128 + chunk * 16) = make_uint4(0u, 0u, 0u, 0u);
@@ -128,7 +130,7 @@ __global__ __launch_bounds__((NCW + 4) * 64) void k_conv_dgrad_wgrad0_tile(ConvD
     // 240x320: 1954 -> 1990, 8192 stereo pairs: 1717 -> 1998).
     if (WC) __builtin_amdgcn_s_setprio(2);
     const int lw = wave - NCW;
-    const int rowbytes = a.WoR * 128, segs = (rowbytes + 1023) >> 10;
+    const int rowbytes = WoR * 128, segs = (rowbytes + 1023) >> 10;
     const int n_im = (img0_bytes + 1023) >> 10, n_mk = (mask_bytes + 1023) >> 10;
     // piece j of a kind (rows of the dY image, 1 KiB pieces of the image rows, of the mask words) belongs to loader j % 4
     auto mine = [&](int n) { return n > lw ? (n - lw + S::NLW - 1) / S::NLW : 0; };

@@ -1104,7 +1104,7 @@ int launch_conv_dgrad_wgrad0_reg_t(Ctx* c, ConvDgradArgs a, int nimg, const std:
   const bool exact = a.W % 8 == 0 && a.Wo * 2 == a.W && a.W * 2 == a.W0;
   if (!exact && !c->dry && !c->f01_train) return 1;  // only the two layers' forward kernel stores mask rows of a rounded-up width
   a.WoR = a.Wo; a.W = cdiv(a.W, 8) * 8; a.Wo = a.W / 2;
-  if (WC && (a.W != WC || a.W0 != 2 * WC)) return 1;
+  if (WC && (a.W != WC || a.W0 != 2 * WC || a.WoR * 2 != WC)) return 1;
   constexpr bool ones = C0 == 1 && WC != 0;  // the kernel's ONES
   const int rb0 = a.W0 * C0 * 2;
   if (rb0 % 16 || a.Wo > S::BQ || a.H != (a.H0 + 1) / 2) return 1;

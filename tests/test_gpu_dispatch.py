@@ -149,6 +149,15 @@ def test_input_gradient_of_a_rounded_up_width(L, ci, h, w):
     _check_gradients(L, cfg, 10, 4)
 
 
+@pytest.mark.parametrize("h,w", [(13, 152), (13, 154), (20, 156), (20, 157), (13, 159), (30, 160), (13, 162)])
+def test_input_gradient_beside_the_width_known_at_compile_time(L, h, w):
+    """First-layer outputs of 76 to 81 columns: 77 to 80 are stored 80 wide, with 39 or 40 columns of the gradient behind them, of
+    which the form with the width known at compile time takes 40."""
+    cfg = configs.get_config(1, num_envs=10, horizon=4)
+    cfg["net"].update(in_h=h, in_w=w)
+    _check_gradients(L, cfg, 10, 4)
+
+
 @pytest.mark.parametrize("c0", [1, 3])
 def test_non_finite_pixels_stay_in_their_sample(L, c0):
     """Values beside a window are read with it and must not reach its sum: NaN and infinity in one sample's image leave every

@@ -125,10 +125,9 @@ __global__ __launch_bounds__((NCW + 4) * 64) void k_conv_dgrad_wgrad0_tile(ConvD
 
   if (wave >= NCW) {
     // ------------------------------------------------------------------ loaders: piece i of a band belongs to loader i % 4
-    // A loader shares its SIMD with two compute waves.  Its few scalar-addressed loads of the WC form go first (16384 images
-    // of 120x160: 947 -> 850 us); the longer address work of the other forms would cost more than it gives (8400 images of
-    // 240x320: 1954 -> 1990, 8192 stereo pairs: 1717 -> 1998).
-    if (WC) __builtin_amdgcn_s_setprio(2);
+    // A loader shares its SIMD with two compute waves, and goes before them nowhere (s_setprio): the WC form is as fast either way
+    // (16384 images of 120x160: 778 and 792 us raised, 803 and 787 not), the longer address work of the others costs more than it
+    // gives (8400 images of 240x320: 1954 -> 1990, 8192 stereo pairs: 1717 -> 1998).
     const int lw = wave - NCW;
     const int rowbytes = WoR * 128, segs = (rowbytes + 1023) >> 10;
     const int n_im = (img0_bytes + 1023) >> 10, n_mk = (mask_bytes + 1023) >> 10;

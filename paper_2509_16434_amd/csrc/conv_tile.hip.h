@@ -400,15 +400,18 @@ __global__ __launch_bounds__(512) void k_conv_fwd_tile(ConvTileArgs a) {
         for (int j = 0; j < TN; ++j) {
           const uint32_t word = or_with_lane_xor32(pw[j]);
           const int wi = (n0 >> 5) + j;
-          if (h == 0 && exists(p, COLS ? bpix[i] : 0u) && wi < wpp)
-            a.bits[((int64_t)img * a.Ho * a.Wo + (int64_t)band * TR * a.Wo + ox0 + pix_of(p, COLS ? bpix[i] : 0u)) * wpp + wi] = word;
+          uint32_t rc = COLS ? bpix[i] : 0u;
+          if (COLS) asm volatile("" : "+v"(rc));  // (its parts are not to be kept from tile to tile: the wide form has no register to spare)
+          if (h == 0 && exists(p, rc) && wi < wpp)
+            a.bits[((int64_t)img * a.Ho * a.Wo + (int64_t)band * TR * a.Wo + ox0 + pix_of(p, rc)) * wpp + wi] = word;
         }
       }
 #pragma unroll
       for (int e = 0; e < 32 * CPRO / 64; ++e) {
         const int ch = lane + 64 * e, rl = ch / CPRO, cg = ch - rl * CPRO;
         const int p = p0 + rl, n = n0 + cg * 8;
-        const uint32_t rc = COLS ? opix[i][e] : 0u;
+        uint32_t rc = COLS ? opix[i][e] : 0u;
+        if (COLS) asm volatile("" : "+v"(rc));
         if (exists(p, rc) && n < a.Cout)
           store_stream16(dst + (int64_t)pix_of(p, rc) * a.Cout + n, *reinterpret_cast<const uint4*>(stage + (rl * SP + cg * 8) * 2));
       }

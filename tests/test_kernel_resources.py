@@ -46,3 +46,10 @@ def test_row_length_of_the_known_width_stays_a_constant(kernels):
     """The register-fused input gradient of 80-wide rows: 27 spilled scalars, 174 where the loaders' row length is read at run time."""
     for n, m in _of(kernels, "_Z24k_conv_dgrad_wgrad0_tileILi1ELi8ELi80EE").items():
         assert m[".sgpr_spill_count"] <= 40 and m[".private_segment_fixed_size"] == 0, n
+
+
+def test_forward_kernels_use_no_scratch(kernels):
+    """64 channels to more than 64 in tiles of columns has the fewest registers left: the places of its results, kept apart from
+    tile to tile, cost four of them spilled."""
+    for n, m in _of(kernels, "_Z15k_conv_fwd_tile").items():
+        assert m[".vgpr_spill_count"] == 0 and m[".private_segment_fixed_size"] == 0, n

@@ -114,10 +114,21 @@ def test_gradients_odd_second_layer_width(L, ci, h, w):
 
 @pytest.mark.parametrize("ci,h,w", [(1, 20, 193), (1, 18, 261), (1, 37, 390), (2, 34, 322), (2, 64, 410), (2, 33, 262)])
 def test_gradients_wide_rows(L, ci, h, w):
-    """Rows too long for a row-wise LDS image (more than 96 pixels of 32 channels, 48 of 64): tiles of columns, with a last
-    column tile that is full, ragged or ends in an odd pixel; 64 x 128 tiles of the last layer from 52-pixel rows."""
+    """Rows too long for a row-wise LDS image (more than 48 pixels of 64 channels): tiles of columns, with a last column tile that
+    is full, ragged or ends in an odd pixel; 64 x 128 tiles of the last layer from 52-pixel rows.  (The second layer, of 32
+    channels, makes its rows from the images here.)"""
     cfg = configs.get_config(ci, num_envs=6, horizon=4)
     cfg["net"].update(in_h=h, in_w=w)
+    _check_gradients(L, cfg, 6, 4)
+
+
+@pytest.mark.parametrize("conv,more,h,w", [((16, 32, 64, 32), {}, 18, 404), ((32, 128, 64), {}, 20, 200), ((32, 64, 64), dict(embed_dim=32), 18, 261),
+                                           ((16, 32, 32, 16), {}, 33, 437)])
+def test_gradients_wide_rows_of_a_stored_layer(L, conv, more, h, w):
+    """Rows of more than 96 pixels of 32 channels that come from memory, with the sign bits of their results: a deeper layer, a second
+    layer of more than 64 channels, a network with an embedding."""
+    cfg = configs.get_config(1, num_envs=6, horizon=4)
+    cfg["net"].update(dict(in_h=h, in_w=w, conv_ch=list(conv)), **more)
     _check_gradients(L, cfg, 6, 4)
 
 
@@ -130,6 +141,19 @@ def test_first_two_convolutions_in_one_kernel(L, c0, views, conv, h, w):
     cfg = configs.get_config(1, num_envs=10, horizon=4)
     cfg["net"].update(in_c=c0, n_views=views, in_h=h, in_w=w, conv_ch=list(conv))
     _check_gradients(L, cfg, 10, 4)
+
+
+@pytest.mark.parametrize("c0,views,conv,h,w,N", [(1, 1, (32, 64, 64), 28, 31, 425), (1, 1, (32, 64), 21, 67, 410), (1, 1, (32, 64, 64), 13, 333, 130),
+                                                 (1, 1, (32, 64), 45, 90, 150), (1, 1, (32, 64, 32), 12, 34, 450), (3, 2, (32, 64, 32), 30, 71, 100),
+                                                 (3, 1, (32, 64), 30, 270, 90), (3, 1, (32, 64, 64), 52, 100, 130)])
+def test_first_two_convolutions_over_many_tiles(L, c0, views, conv, h, w, N):
+    """The same kernels with six to nine tiles per block (a tile is a whole small image, one of two to four bands, one of three or five
+    columns): the rings of images and gradients and the two row buffers turn over, mask stores lie between the loads that are
+    waited for, the weight gradient deals its loads between the groups.  All producing waves with three groups or fewer (28x31,
+    12x34, RGB 30x71), or four and five; odd widths, rounded-up mask rows (12x34, 45x90)."""
+    cfg = configs.get_config(1, num_envs=N, horizon=4)
+    cfg["net"].update(in_c=c0, n_views=views, in_h=h, in_w=w, conv_ch=list(conv), fc_dim=[64])
+    _check_gradients(L, cfg, N, 4)
 
 
 @pytest.mark.parametrize("conv,ln,h,w", [((32, 16), 0, 24, 33), ((32, 32, 64), 1, 40, 66), ((32, 128), 0, 29, 80), ((32, 128, 64), 1, 35, 42)])
@@ -158,26 +182,58 @@ def test_input_gradient_beside_the_width_known_at_compile_time(L, h, w):
     _check_gradients(L, cfg, 10, 4)
 
 
-@pytest.mark.parametrize("c0", [1, 3])
-def test_non_finite_pixels_stay_in_their_sample(L, c0):
-    """Values beside a window are read with it and must not reach its sum: NaN and infinity in one sample's image leave every
-    other sample's outputs as they were, bit for bit."""
+@pytest.mark.parametrize("c0,h,w,N", [(1, 37, 50, 700), (3, 37, 50, 700), (1, 60, 97, 500), (3, 52, 100, 480), (1, 24, 390, 260), (3, 30, 270, 300)])
+def test_non_finite_pixels_stay_in_their_sample(L, c0, h, w, N):
+    """Values beside a window are read with it, LDS keeps those of earlier tiles, and neither must reach a sum: NaN and infinity in
+    some samples' images leave every other sample's outputs as they were, bit for bit.  A block makes five tiles or more, of
+    good and bad samples in turn; whole rows in two and in three bands, and tiles of columns."""
     import torch
-    cfg = configs.get_config(1, num_envs=12, horizon=1)
-    cfg["net"].update(in_c=c0, in_h=37, in_w=50)
+    cfg = configs.get_config(1, num_envs=N, horizon=1)
+    cfg["net"].update(in_c=c0, in_h=h, in_w=w)
     ro = synth.rollout(cfg)
+    rng = np.random.default_rng(5)
+    bad = np.flatnonzero(rng.random(N) < 0.3)
     outs = []
-    for bad in (False, True):
-        if bad:
-            ro["obs"][0, 5, 0, :, 20, 30] = np.nan
-            ro["obs"][0, 7, 0, :, :, 49] = np.inf
-        lrn = L.Learner(cfg["net"], 12, 1, "fp32")
+    for spoil in (False, True):
+        if spoil:
+            for i in bad:
+                ro["obs"][0, i, 0, :, rng.integers(h), rng.integers(w)] = np.nan
+                ro["obs"][0, i, 0, :, rng.integers(h), 0] = np.inf
+                ro["obs"][0, i, 0, :, :, w - 1] = -np.inf
+        lrn = L.Learner(cfg["net"], N, 1, "fp32")
         lrn.set_params(synth.init_params(cfg["net"], 4))
         fill_learner(lrn, dict(cfg, obs_dtype="fp32"), ro)
         outs.append([x.cpu().numpy() for x in lrn.forward()])
-    keep = [i for i in range(12) if i not in (5, 7)]
+    keep = np.setdiff1d(np.arange(N), bad)
+    assert len(bad) > N // 5
     for a, b in zip(*outs):
         np.testing.assert_array_equal(a[keep], b[keep])
+        assert np.isfinite(a).all() and (a[bad] != b[bad]).any()
+
+
+@pytest.mark.parametrize("c0,conv,h,w,N", [(1, (32, 64, 64), 37, 50, 100), (1, (32, 64, 64), 12, 34, 100), (1, (32, 64, 64, 128), 60, 97, 40), (1, (32, 64, 64), 24, 390, 40),
+                                           (3, (32, 64, 64), 37, 50, 100), (3, (32, 64, 32), 30, 270, 40), (1, (32, 64, 64), 20, 157, 60)])
+def test_gradients_after_a_non_finite_update(L, c0, conv, h, w, N):
+    """An update of another learner whose images are all NaN leaves NaN in LDS and in the memory it gives back; the gradients of the
+    next learner are those of before, bit for bit (slots, pads and slack that a kernel reads are ones that it has written)."""
+    import torch
+    cfg = configs.get_config(1, num_envs=N, horizon=2)
+    net, hp = cfg["net"], dict(cfg["hp"], epochs=1, minibatches=1, seed=3)
+    net.update(in_c=c0, in_h=h, in_w=w, conv_ch=list(conv), fc_dim=[64])
+    ro = synth.rollout(cfg, conditioned=True)
+    params = synth.init_params(net, 9)
+
+    def gradients(rollout):
+        lrn = L.Learner(net, N, 2, cfg["obs_dtype"])
+        lrn.set_params(params)
+        fill_learner(lrn, cfg, rollout)
+        lrn.gae(torch.from_numpy(rollout["last_value"]).cuda(), hp["gamma"], hp["lam"])
+        lrn.update(hp)
+        return lrn.get_grads()
+
+    before = gradients(ro)
+    assert not np.array_equal(before, gradients(dict(ro, obs=np.full_like(ro["obs"], np.nan))), equal_nan=True)
+    np.testing.assert_array_equal(before, gradients(ro))
 
 
 @pytest.mark.parametrize("c0,conv,h,w", [(1, (32, 64, 32), 22, 226), (1, (8, 16), 33, 47), (1, (16, 32, 64, 128), 40, 64), (1, (32, 64), 16, 130), (1, (64, 64), 21, 24),
@@ -359,11 +415,13 @@ def test_gradient_sum_over_128_channels_of_wide_rows_is_rounded_once(L, conv, h,
 
 
 @pytest.mark.parametrize("c0,conv,h,w", [(1, (32, 32), 60, 81), (1, (32, 64, 64), 64, 64), (3, (32, 64), 60, 80), (3, (32, 32), 60, 80),
-                                         (3, (32, 16, 32), 45, 67), (3, (32, 32), 20, 270)])
-def test_the_update_sees_the_policy_that_acted(L, c0, conv, h, w):
+                                         (3, (32, 16, 32), 45, 67), (3, (32, 32), 20, 270), (1, (32, 16), 24, 390)])
+@pytest.mark.parametrize("spoil", [False, True])
+def test_the_update_sees_the_policy_that_acted(L, c0, conv, h, w, spoil):
     """The first optimiser step on a fresh rollout evaluates the network as the policy step did, to the last bit (ratio 1 exactly),
     whichever kernels the two take: the first two layers in one kernel for both, or for the policy step alone (second layers of
-    other than 64 channels)."""
+    other than 64 channels).  With NaN in images too (spoil): the first layer rectifies its sums to 0, and they are those of the
+    windows that hold it and no others."""
     import torch
     N, T = 128, 2
     cfg = configs.get_config(1, num_envs=N, horizon=T)
@@ -378,7 +436,12 @@ def test_the_update_sees_the_policy_that_acted(L, c0, conv, h, w):
     gen.manual_seed(3)
     for t in range(T):
         d = synth.rollout_step_torch(cfg, gen)
-        lrn.act(t, d["obs"].to(torch.bfloat16).contiguous(), d["proprio"].contiguous(), torch.randn(N, net["act_dim"], generator=gen, device="cuda"))
+        obs = d["obs"].to(torch.bfloat16).contiguous()
+        if spoil:
+            obs[1::3, ..., h // 2, w // 3] = float("nan")
+            obs[2::5, ..., 0, w - 1] = float("nan")
+            obs[2::7, ..., h - 1, 0] = float("nan")
+        lrn.act(t, obs, d["proprio"].contiguous(), torch.randn(N, net["act_dim"], generator=gen, device="cuda"))
         lrn.buffer_write_outcome(t, d["reward"].contiguous(), d["done"].contiguous())
     lrn.gae(torch.zeros(N, device="cuda"), 0.99, 0.95)
     st = lrn.update(dict(cfg["hp"], epochs=1, minibatches=1))

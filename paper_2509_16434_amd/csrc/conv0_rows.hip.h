@@ -1,6 +1,6 @@
 // The first convolution (one or three input channels, 32 output channels, 3x3 stride 2 pad 1, bias, ReLU) produced row by row
-// in LDS for the second layer's kernels, so that its output - the largest tensor of the network, 16 times the image of one
-// channel - is neither written nor read back.
+// in LDS for the second layer's kernels, so that its output - the largest tensor of the network, 8 times the image of one
+// channel, 8/3 times that of three - is neither written nor read back.
 //
 // A wave makes 32 pixels x 32 channels ("a group") with one (C0 = 1) or two (C0 = 3) 32x32x16 MFMAs; what bounds it is
 // the vector work around them, so the operands are laid out to need almost none:

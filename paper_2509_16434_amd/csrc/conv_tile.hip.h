@@ -421,16 +421,19 @@ __global__ __launch_bounds__(512) void k_conv_fwd_tile(ConvTileArgs a) {
 
 // ------------------------------------------------------------------------------------------------
 // Weight gradient of the same convolution: G[n][k] = sum over pixels p of dY[p][n] * X[win(p)][k],
-// k = (u*3+v)*CIN + ci, with the same organisation.  A tile is (image, band of TR output rows); the
-// loader waves copy the band's input rows (LDS image as above) and the band's dY pixels (64 output
-// channels of this block, 128 bytes per pixel, NSTEP*16 pixels with zeros beyond the band) into a
-// ring of nbuf buffers (three, or more where they fit: small bands need more of them in flight).  The contraction runs over pixels, 16 per MFMA step; both operands are
+// k = (u*3+v)*CIN + ci, with the same organisation.  A tile is (image, band of TR output rows), or TR rows of TC columns; the
+// loader waves copy the tile's input rows (LDS image as above) and its dY pixels (64 output
+// channels of this block, 128 bytes per pixel, NSTEP*16 pixels with zeros beyond the tile) into a
+// ring of nbuf buffers (three, or more where they fit: small bands need more of them in flight).  With C0 > 0 they load the
+// first layer's images and dY alone and make the input rows, as in the forward kernel.  The contraction runs over pixels, 16
+// per MFMA step; both operands are
 // read through ds_read_b64_tr_b16 (lane r of a 16-lane group supplies 4 consecutive channels of
 // pixel r/4, lane i receives channel i of 4 pixels), the im2col being the per-lane pixel address.
-// Compute wave w owns the 32-wide k-tiles w, w+4, ... of both 32-row n-tiles; the accumulators live
-// in registers across all tiles of the block and leave once, as this block's fp32 partial
-// [9*CIN][Cout] (partials are summed in a fixed order by the caller).  Waves without a last k-tile also
-// accumulate the column sums of dY (the bias gradient) with an all-ones operand.
+// 64 channels (18 k-tiles of 32): compute wave w owns the k-tiles w, w+4, ... of both 32-row n-tiles; waves 2 and 3
+// have no fifth, and wave 3 sums the columns of dY (the bias gradient) with an all-ones operand instead.  32 channels (nine k-tiles): two whole
+// k-tiles per wave; the two n-tiles of the ninth go to waves 0 and 1, those of the bias column to waves 2 and 3.
+// The accumulators live in registers across all tiles of the block and leave once, as this block's fp32 partial
+// [9*CIN][Cout] (partials are summed in a fixed order by the caller).
 // dY pixels are 128 bytes apart; bit 6 of the offset is flipped for every second pixel pair so that
 // the four pixels of one transposing read fall into different banks.
 struct ConvWgradArgs {

@@ -10,8 +10,9 @@
 //    9*C0 window values row after row, and the sums its sums, bit for bit.  (A network may have its policy step here and its
 //    update there: the update's first step must see the policy that acted.)  C0 = 1: two dwords per row, (2x-2, 2x-1) and
 //    (2x, 2x+1), packed so that lane half 0 has eight taps and half 1 the ninth: two permutes, four masks.  C0 = 3: five
-//    dwords per row, the value in front of the window and its nine (x 0)(1 2)(3 4)(5 6)(7 8); each group is three dwords as
-//    they are and a pair from two others: two permutes, two masks.  Values outside the window have zero weights and are masked
+//    dwords per row, the value in front of the window and its nine (x 0)(1 2)(3 4)(5 6)(7 8); a group is whole dwords and a pair
+//    from two others.  The last dwords of rows 0 and 1, which the other lane half's groups take too, change halves in one swap:
+//    nine dwords read, one swap, two permutes, two masks.  Values outside the window have zero weights and are masked
 //    off as well: a NaN there must not reach the sum.
 //  * The weights' rows are permuted so that a lane ends up with 16 consecutive channels of its pixel: 8 conversions, 8
 //    clamps, two 16-byte LDS writes, and (BITS) its 16 mask bits are a half-word of the pixel's mask word.
@@ -62,7 +63,7 @@ struct Conv0Shape1 {
   static constexpr int MAXPIX = 4 * GPW * 32;
   static constexpr int AHEAD = 3;                          // images in flight, if the LDS holds one more than that
   __host__ __device__ static int row_pitch(int TC) { return (LEAD * 16 + 8 * C0 * TC + 15) & ~15; }
-  __host__ __device__ static int image_bytes(int TC, int TR) { return (4 * TR + 3) * row_pitch(TC) + 16; }  // (the last window row's reads may run 4 bytes over)
+  __host__ __device__ static int image_bytes(int TC, int TR) { return (4 * TR + 3) * row_pitch(TC) + 16; }  // (the last window row's reads may run 4 bytes over, 8 with three channels)
   __host__ __device__ static int act_bytes(int TC, int TR) { return ((2 * TR + 1) * (2 * TC + 1) * 64 + 64 + 127) & ~127; }  // ends in a pixel that takes what no pixel wants
   static bool fits(int TC, int TR) { return (4 * TR + 3) * row_pitch(TC) <= MAXL * 4096 && 4 * TR + 3 <= 255; }
 };
@@ -108,7 +109,7 @@ struct Conv0Producer {
       boff[g] = (uint32_t)(((row - 1) * s.bpitch + sl - 1) * 4 + h * 2);
     }
 #pragma unroll
-    for (int i = 0; i < NOFF; ++i) dlt[i] = C0 == 1 ? 2 * LB + 4 * h : (h + i) * LB;
+    for (int i = 0; i < NOFF; ++i) dlt[i] = C0 == 1 ? 2 * LB + 4 * h : i == 0 ? h * LB : 2 * LB + 12 * h;
     // row i of the product is channel ch: a lane's accumulators are then the channels h*16 .. h*16 + 15
     const int ch = ((l32 >> 2) & 1) * 16 + (l32 >> 3) * 4 + (l32 & 3);
     const bf16_t* wp = s.w + ch * 9 * C0;
@@ -118,8 +119,9 @@ struct Conv0Producer {
       // k-th value of this lane half: element t of window row u, or none
       int u, t;
       if (C0 == 1) { constexpr int order[8] = {0, 3, 1, 2, 4, 5, 6, 7}; u = 0; t = h ? (k == 6 ? 8 : -1) : order[k & 7]; }
-      else if (k < 8) { u = k == 7 ? 0 : h; t = k == 7 ? 7 + h : k == 6 ? 0 : k + 1; }
-      else if (k < 10) { u = 1 + h; t = k - 1; }
+      else if (k < 8) { u = k == 1 ? 0 : h; t = k == 1 ? 7 + h : k == 0 ? 0 : k - 1; }
+      else if (k < 10) { u = 1; t = h ? -1 : k - 1; }
+      else if (k < 12) { u = 2; t = h ? k - 3 : k - 9; }
       else { u = 2; t = k == 15 ? 5 + h : h ? -1 : k == 14 ? 0 : k - 9; }
       v[k] = t >= 0 ? (uint32_t)wp[t >= 0 ? u * 3 * C0 + t : 0] : 0u;
     }
@@ -132,7 +134,7 @@ struct Conv0Producer {
     // row 2, or 6 of row 2)
     m2 = h ? 0u : 0xffffffffu;
     m3 = C0 == 1 ? (h ? 0x0000ffffu : 0xffffffffu) : (h ? 0x07060302u : 0x05040302u);
-    m4 = h ? 0x07060c0cu : 0x05040302u;
+    m4 = h ? 0x03020c0cu : 0x05040302u;
     negw[0] = nonzero_weights(0); negw[1] = nonzero_weights(1);
   }
 
@@ -155,18 +157,20 @@ struct Conv0Producer {
   // work on them: the compute wave on the same SIMD leaves a lone dependent chain little.  Returns the stores surely issued.
   template <int NG, bool EDGE, class F>
   __device__ __forceinline__ int groups(const char* im, char* act, int row_lo, int col_lo, int H1, int W1, char* bits, F after) const {
-    constexpr int ND = C0 == 1 ? 6 : 10;
+    constexpr int ND = C0 == 1 ? 6 : 9;
     uint32_t d[NG][ND];
 #pragma unroll
     for (int g = 0; g < NG; ++g) {
       const char* const p1 = im + b1[g];
 #pragma unroll
       for (int i = 0; i < ND; ++i) {
-        // C0 = 3: 0..3 = row h, 4 = the last of row 0, 5 = the last of row 1 + h, 6..9 = row 2
-        const char* p = C0 == 1 ? (i < 2 ? p1 : i < 4 ? p1 + pitch : p1 + dlt[0]) + 4 * (i & 1)
-                                : i < 4 ? p1 + dlt[0] + 4 * i : i == 4 ? p1 + 16 : i == 5 ? p1 + dlt[NOFF - 1] + 16 : p1 + 2 * pitch + 4 * (i - 6);
+        // C0 = 3: 0..4 = row h, 5..8 = row 2 from its first dword, or from (5 6) on in half 1 (whose last two are nobody's)
+        const char* p = C0 == 1 ? (i < 2 ? p1 : i < 4 ? p1 + pitch : p1 + dlt[0]) + 4 * (i & 1) : i < 5 ? p1 + dlt[0] + 4 * i : p1 + dlt[NOFF - 1] + 4 * (i - 5);
         d[g][i] = *reinterpret_cast<const uint32_t*>(p);
       }
+      // three channels: group after group, so that the first sums wait for few of the 45 reads (8192 stereo pairs: weight gradient
+      // 1667 -> 1624 us, forward 1381 -> 1298)
+      if (C0 > 1) __builtin_amdgcn_sched_barrier(0);
     }
     auto sums = [&](int g) __attribute__((always_inline)) {
       const uint32_t* const x = d[g];
@@ -174,9 +178,11 @@ struct Conv0Producer {
         const uint4 v = make_uint4(__builtin_amdgcn_perm(x[2], x[0], 0x07060302u) & m2, x[1] & m2, x[3] & m2, __builtin_amdgcn_alignbit(x[5], x[4], 16) & m3);
         return __builtin_amdgcn_mfma_f32_32x32x16_bf16(w[0], __builtin_bit_cast(bf16x8_t, v), bias, 0, 0, 0);
       } else {
-        const uint4 u = make_uint4(x[1], x[2], x[3], __builtin_amdgcn_perm(x[4], x[0], m3));
+        // (dwords stand where the pairs of reads put them: no moves)
+        const auto last = __builtin_amdgcn_permlane32_swap(x[4], x[4], false, false);  // of row 0, of row 1, in both halves
+        const uint4 u = make_uint4(__builtin_amdgcn_perm(last[0], x[0], m3), x[1], x[2], x[3]);
         const f32x16_t acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(w[0], __builtin_bit_cast(bf16x8_t, u), bias, 0, 0, 0);
-        const uint4 v = make_uint4(x[5], x[7] & m2, x[8] & m2, __builtin_amdgcn_perm(x[9], x[6], m4));
+        const uint4 v = make_uint4(last[1] & m2, x[6], x[7] & m2, __builtin_amdgcn_perm(x[8], x[5], m4));
         return __builtin_amdgcn_mfma_f32_32x32x16_bf16(w[KS - 1], __builtin_bit_cast(bf16x8_t, v), acc, 0, 0, 0);
       }
     };

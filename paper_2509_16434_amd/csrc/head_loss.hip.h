@@ -6,14 +6,18 @@
 // A block of 256 threads takes 64 samples:
 //   1. the samples' last hidden activations H (64 x HID bf16) and the head weights W (NH x HID) go to LDS;
 //   2. O = H W^T + b (fp32) with 32x32x16 MFMAs (waves 0 and 1, 32 samples each);
-//   3. wave 0, one lane per sample, evaluates the loss: the gradient row dO (bf16, 32 columns) stays in
-//      LDS, the loss statistics leave as one partial per block;
+//   3. four lanes per sample, eight columns each, evaluate the loss: the gradient row dO (bf16, 32
+//      columns) stays in LDS; the sums over the samples (statistics, log-std gradient, column sums of
+//      dO) are taken by eight lanes per column and leave as one partial per block;
 //   4. dH = dO W, masked by H > 0 (ReLU), rounded to bf16, staged and written out as full rows
 //      (wave w: hidden units 32w .. 32w+31);
 //   5. this block's term of dW = dO^T H (contraction over the 64 samples; both operands are row-major
-//      over samples and are read with transposing LDS reads, as in k_wgrad) and of db = column sums
-//      of dO leave as fp32 partials, summed afterwards in block order.
+//      over samples and are read with transposing LDS reads, as in k_wgrad) leaves as an fp32 partial,
+//      summed afterwards in block order.
 // Operand rounding is that of the separate kernels: bf16 H, W, dO and dH, fp32 accumulation.
+// Bound by latency (a block is alone on its CU; its 64 samples' gathers, then one dependent chain): with one lane per
+// sample and 36 block sums by butterfly in every wave it took 18.0 us for 4096 samples and 128 hidden units
+// (13.4 for 256 and 64), with the columns dealt to four lanes 10.5 (8.3).
 #pragma once
 #include "gemm.hip.h"
 #include "mem_kernels.hip.h"
@@ -38,7 +42,7 @@ struct HeadLossShape {
   static constexpr int DPA = 40, DPB = 96;
   static constexpr int OFF_HA = 0, OFF_HB = OFF_HA + 64 * HPA * 2, OFF_W = OFF_HB + 64 * HPB * 2, OFF_O = OFF_W + 32 * HPA * 2;
   static constexpr int OFF_DA = OFF_O + 64 * 33 * 4, OFF_DB = OFF_DA + 64 * DPA * 2, OFF_DH = OFF_DB + 64 * DPB * 2, OFF_RED = OFF_DH + 64 * HPA * 2;
-  static constexpr int LDS_BYTES = OFF_RED + (4 * 36 + 64) * 4;
+  static constexpr int LDS_BYTES = OFF_RED + (64 * 4 + 64) * 4;
 };
 
 template <int HID, bool DISTILL>
@@ -54,14 +58,16 @@ __global__ __launch_bounds__(256) void k_head_loss(HeadLossArgs a, LossData L) {
   bf16_t* const Da = reinterpret_cast<bf16_t*>(lds + S::OFF_DA);
   bf16_t* const Db = reinterpret_cast<bf16_t*>(lds + S::OFF_DB);
   bf16_t* const DHs = reinterpret_cast<bf16_t*>(lds + S::OFF_DH);
-  float (*wred)[36] = reinterpret_cast<float (*)[36]>(lds + S::OFF_RED);
-  float* const sgl = reinterpret_cast<float*>(lds + S::OFF_RED) + 4 * 36;  // sig_inv[32], ls[32]
+  float* const stt = reinterpret_cast<float*>(lds + S::OFF_RED);  // [64][4] statistics
+  float* const sgl = stt + 64 * 4;                               // sig_inv[32], ls[32]
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, l32 = lane & 31, h = lane >> 5;
   const int s0 = blockIdx.x * 64, ns = min(64, a.n - s0);  // this block's samples
 
-  // the loss's gathers from the rollout start now: their latency passes during steps 1 and 2
-  LossSample smp;
-  if (wave == 0 && lane < ns) smp = loss_gather(L, (int64_t)L.idx[s0 + lane], !DISTILL);
+  // step 3's sample and first column of this thread; the gathers from the rollout start now: their latency passes during
+  // steps 1 and 2
+  const int sl = tid >> 2, c0 = (tid & 3) * 8;
+  LossColumns smp = {};
+  if (sl < ns) smp = loss_gather_columns(L, (int64_t)L.idx[s0 + sl], c0, !DISTILL);
 
   // ---- 1. H rows (zeros beyond the chunk) in both pitches, W rows (zeros beyond NH)
   constexpr int CPR = HID / 8;  // 16-byte chunks per row
@@ -98,30 +104,49 @@ __global__ __launch_bounds__(256) void k_head_loss(HeadLossArgs a, LossData L) {
   }
   __syncthreads();
 
-  // ---- 3. the loss, one lane of wave 0 per sample
-  float st[4] = {0.f, 0.f, 0.f, 0.f}, dls[32];
+  // ---- 3. the loss: columns c0 .. c0 + 7 of sample sl (a sample beyond the chunk has zeros everywhere)
+  {
+    float o[8], g[8], dls[8], st[4] = {0.f, 0.f, 0.f, 0.f};
 #pragma unroll
-  for (int j = 0; j < 32; ++j) dls[j] = 0.f;
-  if (wave == 0) {
-    uint32_t pk[16];
+    for (int j = 0; j < 8; ++j) { o[j] = Os[sl * 33 + c0 + j]; g[j] = 0.f; dls[j] = 0.f; }
+    if (DISTILL) mse_loss_columns(L, smp, c0, o, g, st);
+    else ppo_loss_columns(L, sgl, sgl + 32, smp, c0, o, g, st, dls);
+    uint4 v = make_uint4(pack2bf(g[0], g[1]), pack2bf(g[2], g[3]), pack2bf(g[4], g[5]), pack2bf(g[6], g[7]));
+    if (sl >= ns) {
+      v = make_uint4(0u, 0u, 0u, 0u);
 #pragma unroll
-    for (int q = 0; q < 16; ++q) pk[q] = 0u;
-    if (lane < ns) {
-      float o[HEAD_LD];
+      for (int j = 0; j < 8; ++j) dls[j] = 0.f;
 #pragma unroll
-      for (int j = 0; j < HEAD_LD; ++j) o[j] = Os[lane * 33 + j];
-      if (DISTILL) mse_loss_sample(L, smp, o, pk, st);
-      else ppo_loss_sample(L, sgl, sgl + 32, smp, o, pk, st, dls);
+      for (int k = 0; k < 4; ++k) st[k] = 0.f;
     }
-    // the gradient row (zeros for lanes beyond the chunk) in both pitches
+    // the gradient row in both pitches; the terms of the sums, the log-std gradient's in the place of the outputs just read
+    *reinterpret_cast<uint4*>(Da + sl * DPA + c0) = v;
+    *reinterpret_cast<uint4*>(Db + sl * DPB + c0) = v;
+    if (!DISTILL) {
 #pragma unroll
-    for (int q = 0; q < 4; ++q) {
-      const uint4 v = make_uint4(pk[4 * q], pk[4 * q + 1], pk[4 * q + 2], pk[4 * q + 3]);
-      *reinterpret_cast<uint4*>(Da + lane * DPA + q * 8) = v;
-      *reinterpret_cast<uint4*>(Db + lane * DPB + q * 8) = v;
+      for (int j = 0; j < 8; ++j) Os[sl * 33 + c0 + j] = dls[j];
+    }
+    if ((tid & 3) == 0) *reinterpret_cast<float4*>(stt + sl * 4) = make_float4(st[0], st[1], st[2], st[3]);
+  }
+  __syncthreads();
+  // column sums over the samples: eight lanes per column, eight samples each, in a fixed order
+  {
+    const int col = tid >> 3, r0 = (tid & 7) * 8;
+    float sd = 0.f, sb = 0.f, ss = 0.f;
+#pragma unroll
+    for (int i = 0; i < 8; ++i) {
+      if (!DISTILL) sd += Os[(r0 + i) * 33 + col];
+      sb += bf2f(Da[(r0 + i) * DPA + col]);
+      ss += stt[(r0 + i) * 4 + (col & 3)];
+    }
+#pragma unroll
+    for (int off = 1; off < 8; off <<= 1) { sd += __shfl_xor(sd, off); sb += __shfl_xor(sb, off); ss += __shfl_xor(ss, off); }
+    if ((tid & 7) == 0) {
+      if (col < a.NH) a.bpart[(int64_t)blockIdx.x * a.NH + col] = sb;
+      if (!DISTILL && col < L.A) a.dls_part[(int64_t)blockIdx.x * 32 + col] = sd;
+      if (col < 4) a.stat_part[(int64_t)blockIdx.x * LOSS_NSTAT + col] = ss;
     }
   }
-  loss_block_sums(st, dls, DISTILL ? 0 : L.A, wred, a.stat_part, DISTILL ? nullptr : a.dls_part);  // holds the barriers after step 3
 
   // ---- 4. dH[s][n] = sum_j dO[s][j] W[j][n], hidden units 32*wave .. +31 (waves beyond HID/32 idle)
   if (wave < NT) {
@@ -173,12 +198,6 @@ __global__ __launch_bounds__(256) void k_head_loss(HeadLossArgs a, LossData L) {
       const int j = (e >> 2) * 8 + h * 4 + (e & 3);
       if (j < a.NH) P[j * HID + wave * 32 + l32] = acc[e];
     }
-  }
-  if (tid >= 192 && tid - 192 < a.NH) {  // db: column sums of dO in sample order
-    const int j = tid - 192;
-    float sum = 0.f;
-    for (int s = 0; s < 64; ++s) sum += bf2f(Da[s * DPA + j]);
-    a.bpart[(int64_t)blockIdx.x * a.NH + j] = sum;
   }
   __syncthreads();
   // ---- dH rows leave as 16-byte segments

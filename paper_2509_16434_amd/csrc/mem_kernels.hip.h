@@ -631,6 +631,66 @@ __device__ __forceinline__ void mse_loss_sample(const LossData& L, const LossSam
   st[0] = la; st[1] = lx; st[2] = 0.f; st[3] = 0.f;
 }
 
+// The same losses by four lanes per sample (consecutive lanes of a wave), columns c0 .. c0 + 7 each: g = the gradient of these
+// columns, st = the sample's statistics, alike in all four lanes.
+struct LossColumns { float act[8], lpo, adv, ret, vo; };
+__device__ __forceinline__ LossColumns loss_gather_columns(const LossData& L, int64_t s, int c0, bool ppo) {
+  LossColumns g;
+  const int A = L.A;
+#pragma unroll
+  for (int j = 0; j < 8; ++j) g.act[j] = L.action[s * A + (c0 + j < A ? c0 + j : A - 1)];
+  g.lpo = ppo ? L.logp_old[s] : 0.f; g.adv = ppo ? L.adv[s] : 0.f; g.ret = ppo ? L.ret[s] : 0.f; g.vo = ppo ? L.v_old[s] : 0.f;
+  return g;
+}
+__device__ __forceinline__ float sum4lanes(float x) { x += __shfl_xor(x, 1); x += __shfl_xor(x, 2); return x; }
+__device__ __forceinline__ void ppo_loss_columns(const LossData& L, const float* sig_inv, const float* ls, const LossColumns& smp, int c0, const float (&o)[8],
+                                                 float (&g)[8], float (&st)[4], float (&dls)[8]) {
+  const int A = L.A;
+  const float invB = 1.f / (float)L.Bfull, a = smp.adv, r = smp.ret, vo = smp.vo;
+  float z[8], si[8], lp = 0.f, vc = 0.f;
+#pragma unroll
+  for (int j = 0; j < 8; ++j) {
+    const bool on = c0 + j < A;
+    si[j] = on ? sig_inv[c0 + j] : 0.f;
+    z[j] = on ? (smp.act[j] - o[j]) * si[j] : 0.f;
+    lp += on ? -0.5f * z[j] * z[j] - ls[c0 + j] - 0.91893853320467274178f : 0.f;
+    vc = c0 + j == A ? o[j] : vc;  // the value head's column
+  }
+  const float logp = sum4lanes(lp), v = sum4lanes(vc);
+  const float lr = logp - smp.lpo, rho = expf(lr);
+  const float rc = fminf(fmaxf(rho, 1.f - L.clip_eps), 1.f + L.clip_eps);
+  const float s1 = rho * a, s2 = rc * a;
+  st[0] = -fminf(s1, s2);
+  const float dlogp = (s1 <= s2) ? -invB * a * rho : 0.f;
+  st[2] = (rho - 1.f) - lr;
+  st[3] = fabsf(rho - 1.f) > L.clip_eps ? 1.f : 0.f;
+  const float err = v - r;
+  st[1] = err * err;
+  float dv = 2.f * err;
+  if (L.vclip_eps > 0.f) {
+    const float d = v - vo, dc = fminf(fmaxf(d, -L.vclip_eps), L.vclip_eps), errc = vo + dc - r;
+    if (errc * errc > err * err) { st[1] = errc * errc; dv = (d >= -L.vclip_eps && d <= L.vclip_eps) ? 2.f * errc : 0.f; }
+  }
+#pragma unroll
+  for (int j = 0; j < 8; ++j) {
+    g[j] = c0 + j < A ? dlogp * z[j] * si[j] : c0 + j == A ? L.vf_coef * invB * dv : 0.f;
+    dls[j] = c0 + j < A ? dlogp * (z[j] * z[j] - 1.f) : 0.f;
+  }
+}
+__device__ __forceinline__ void mse_loss_columns(const LossData& L, const LossColumns& smp, int c0, const float (&o)[8], float (&g)[8], float (&st)[4]) {
+  const int A = L.A, Aa = A - L.aux_dim;
+  const float sa = 1.f / ((float)L.Bfull * (float)Aa), sx = L.aux_dim > 0 ? L.aux_coef / ((float)L.Bfull * (float)L.aux_dim) : 0.f;
+  float la = 0.f, lx = 0.f;
+#pragma unroll
+  for (int j = 0; j < 8; ++j) {
+    const float e = o[j] - smp.act[j];
+    la += c0 + j < Aa ? e * e : 0.f;
+    lx += (c0 + j >= Aa && c0 + j < A) ? e * e : 0.f;
+    g[j] = c0 + j < Aa ? 2.f * sa * e : (c0 + j < A ? 2.f * sx * e : 0.f);
+  }
+  st[0] = sum4lanes(la); st[1] = sum4lanes(lx); st[2] = 0.f; st[3] = 0.f;
+}
+
 // Sums of the four statistics and (if dls_part) of the A log-std terms over the block, in a fixed
 // order: xor-butterfly inside each wave (all sums side by side, so that their steps overlap), then
 // the wave sums.  Every thread of the block calls this (threads without a sample pass zeros);
@@ -768,8 +828,12 @@ __device__ __forceinline__ void loss_finalize_block(const LossFinalize& f) {
 // Every pending reduction of a backward pass in one launch: job j covers blocks [first[j], first[j+1]).
 // kind 0: dst[i] (+)= sum_s partial[s][i]; kind 1: partials stored transposed, dst[n*K + k] (+)=
 // sum_s partial[s][k*N + n]; kind 2: partial[s][co][K+1] of the first convolution, whose last column
-// is the bias gradient (dst2).  Jobs with vec set (n a multiple of 4, partials 16-byte aligned) take
-// four outputs per lane with 16-byte loads (128 outputs per block), the others one (32 per block).
+// is the bias gradient (dst2).  vec 1 (n a multiple of 4, partials 16-byte aligned): four outputs per
+// lane with 16-byte loads, 128 outputs per block; vec 2 (the same with at most 8 partials): a lane takes
+// all partials of its four outputs, 1024 outputs per block, in the same order of sums; vec 0: one
+// output per lane, 32 per block.  The wide linear layers have two or three partials of millions of
+// outputs: by 128 outputs per block they were 41 000 blocks of mostly idle lanes (10304 x 512 outputs
+// and the convolutions' partials 83.4 us, now 54.4; 4496 x 256 20.8 and 15.1).
 struct ReduceJobs {
   static constexpr int MAXJ = 17;  // the deepest feed-forward workload's 15, and room for the three jobs of one kernel behind 14
   int njobs;
@@ -794,7 +858,20 @@ __global__ __launch_bounds__(256) void k_reduce_batch(ReduceJobs jobs, LossFinal
     else { const int KP = jobs.K[j] + 1, co = (int)(i / KP), k = (int)(i - (int64_t)co * KP); d = k == jobs.K[j] ? jobs.dst2[j] + co : jobs.dst[j] + (int64_t)co * jobs.K[j] + k; }
     *d = jobs.accumulate[j] ? *d + s : s;
   };
-  if (jobs.vec[j]) {
+  if (jobs.vec[j] == 2) {
+    const int64_t i = ((int64_t)blk * 256 + threadIdx.x) * 4;
+    if (i >= nn) return;
+    const float* const p = jobs.partial[j] + i;
+    const int splits = jobs.splits[j];
+    float4 v[8];
+#pragma unroll
+    for (int q = 0; q < 8; ++q) v[q] = q < splits ? *reinterpret_cast<const float4*>(p + (int64_t)q * nn) : make_float4(0.f, 0.f, 0.f, 0.f);
+    auto sum = [](float a, float b, float c, float d, float e, float f, float g, float h) { return ((a + b) + (c + d)) + ((e + f) + (g + h)); };
+    put(i, sum(v[0].x, v[1].x, v[2].x, v[3].x, v[4].x, v[5].x, v[6].x, v[7].x));
+    put(i + 1, sum(v[0].y, v[1].y, v[2].y, v[3].y, v[4].y, v[5].y, v[6].y, v[7].y));
+    put(i + 2, sum(v[0].z, v[1].z, v[2].z, v[3].z, v[4].z, v[5].z, v[6].z, v[7].z));
+    put(i + 3, sum(v[0].w, v[1].w, v[2].w, v[3].w, v[4].w, v[5].w, v[6].w, v[7].w));
+  } else if (jobs.vec[j]) {
     const int64_t i = ((int64_t)blk * 32 + (threadIdx.x & 31)) * 4;
     float s[4];
     reduce_partials_block<4>(jobs.partial[j], jobs.splits[j], nn, i, red, s);

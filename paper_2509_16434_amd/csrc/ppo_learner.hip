@@ -585,8 +585,8 @@ void defer_reduce(Ctx* c, int kind, int splits, int64_t n, int N, int K, float* 
     const int j = J.njobs++;
     J.first[j] = c->rjob_blocks; J.kind[j] = kd; J.splits[j] = splits; J.N[j] = N; J.K[j] = K; J.accumulate[j] = accumulate ? 1 : 0;
     J.n[j] = nn; J.partial[j] = part; J.dst[j] = d; J.dst2[j] = d2;
-    J.vec[j] = (nn % 4 == 0 && (reinterpret_cast<uintptr_t>(part) & 15) == 0) ? 1 : 0;
-    c->rjob_blocks += cdiv(nn, J.vec[j] ? 128 : 32);
+    J.vec[j] = (nn % 4 != 0 || (reinterpret_cast<uintptr_t>(part) & 15) != 0) ? 0 : splits <= 8 ? 2 : 1;
+    c->rjob_blocks += cdiv(nn, J.vec[j] == 2 ? 1024 : J.vec[j] ? 128 : 32);
   };
   add(kind, c->partial, n, dst, dst2);
   c->partial += (int64_t)splits * n; c->partial_elems -= (int64_t)splits * n;

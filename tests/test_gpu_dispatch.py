@@ -104,6 +104,17 @@ def _check_forward(L, cfg, N, T):
     assert rel_l2(mu, omu) <= TOL_BF16 and rel_l2(v, ov) <= TOL_BF16
 
 
+@pytest.mark.parametrize("hid,A,N,T,kind", [(64, 1, 9, 7, "ppo"), (32, 7, 8, 8, "ppo"), (128, 8, 5, 13, "ppo"), (64, 9, 16, 16, "ppo"), (128, 23, 31, 5, "ppo"),
+                                            (64, 31, 11, 6, "ppo"), (64, 1, 9, 7, "distill"), (128, 16, 5, 13, "distill"), (32, 25, 3, 43, "distill")])
+def test_output_layer_and_loss(L, hid, A, N, T, kind):
+    """Output layer, loss and their backward in one kernel: eight columns per lane, 64 samples per block, with remainders of both."""
+    cfg = configs.get_config(0, num_envs=N, horizon=T)
+    cfg["net"].update(fc_dim=[hid], act_dim=A)
+    if kind == "distill":
+        cfg["kind"], cfg["net"]["has_value_head"] = "distill", 0
+    _check_gradients(L, cfg, N, T)
+
+
 @pytest.mark.parametrize("ci,h,w", [(1, 51, 61), (1, 49, 58), (1, 89, 117), (1, 31, 33), (1, 45, 90), (3, 49, 58), (2, 62, 101)])
 def test_gradients_odd_second_layer_width(L, ci, h, w):
     """Widths whose first-layer output is odd."""

@@ -56,6 +56,38 @@ inline FastDiv make_fastdiv(int32_t d) {
 // by CUs behind the same L2.  A permutation when nb is a multiple of 8, else the identity.
 __device__ __forceinline__ int xcd_block(int b, int nb) { return (nb & 7) == 0 ? (b & 7) * (nb >> 3) + (b >> 3) : b; }
 
+// The images of a batch seen as one tall image ("stacked"): image i's Ho result rows are the rows i*Ho .. of the stack, and its
+// 2*Ho input rows (the last one missing, zeros, when the height is odd) the rows 2*i*Ho ..  A tile of the stack may then span
+// images, so that bands are full whatever the height: result row R reads the input rows 2R-1, 2R, 2R+1 as ever.  Only the row
+// above an image's first (of an even height: the one before has no missing row) is not the stack's: it is zeros.
+struct Stack {
+  int on = 0, rows = 0;      // result rows of the whole batch
+  int odd = 0;               // the height is odd
+  int dense = 0;             // the images of the strided side follow each other without a gap
+  FastDiv ho, hv, hw, v;     // division by Ho, 2*Ho, Ho*Wo, V
+  // input row g of the stack: false if missing; else *mem = its number among the rows in memory (dense images)
+  __device__ __forceinline__ bool in_row(int g, int H, int* mem) const {
+    bool ok = g >= 0 && g < 2 * rows;
+    *mem = g;
+    if (odd) { const int gg = ok ? g : 0, i = (int)hv.div((uint32_t)gg); *mem = gg - i; ok = ok && gg - i * (int)hv.d < H; }
+    return ok;
+  }
+  // first input row in memory of result row R (2R, less the missing rows above it)
+  __device__ __forceinline__ int row_of(int R) const { return odd ? 2 * R - (int)ho.div((uint32_t)R) : 2 * R; }
+  // row of the tile at R0, counted modulo Ho, that is an image's first (or, shift = 1, last) one; none: -1
+  __device__ __forceinline__ int edge_row(int R0, int shift) const {
+    if (odd) return -1;
+    const int Ho = (int)ho.d, rm = R0 - (int)ho.div((uint32_t)R0) * Ho;
+    return shift ? Ho - 1 - rm : rm ? Ho - rm : 0;
+  }
+  __device__ __forceinline__ int mod_ho(int r) const { return r - (int)ho.div((uint32_t)r) * (int)ho.d; }
+};
+inline Stack make_stack(int nimg, int Ho, int Wo, int H, int V) {
+  Stack s;
+  s.on = 1; s.rows = nimg * Ho; s.odd = H & 1; s.ho = make_fastdiv(Ho); s.hv = make_fastdiv(2 * Ho); s.hw = make_fastdiv(Ho * Wo); s.v = make_fastdiv(V);
+  return s;
+}
+
 // Address of image `img` (= sample*V + view) inside a tensor whose samples may be gathered
 // through an index list and whose views sit at a fixed stride inside a sample row.
 struct ImgAddr {

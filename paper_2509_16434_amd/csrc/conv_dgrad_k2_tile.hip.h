@@ -201,7 +201,7 @@ __global__ __launch_bounds__(512) void k_conv_dgrad_k2_tile(ConvDgradArgs a) {
       // this lane's quad of the group (lanes beyond the band work on quad 0 and store nothing)
       const int qi = mt * 32 + l32;
       const bool in_band = qi < TQ * Wo;
-      const int al = in_band ? qi / Wo : 0, b = in_band ? qi - al * Wo : 0;
+      const int al = in_band ? (int)a.dv_wo.div((uint32_t)qi) : 0, b = in_band ? qi - al * Wo : 0;
       const char* img_s = lds + (q % NBUF) * dyimg_bytes + al * RP + b * PB + kh * 128;
       uint32_t hx[2][2];  // [row offset][column offset] of the quad's four dY pixels
 #pragma unroll

@@ -49,6 +49,8 @@ struct ConvDgradArgs {
   float* partial0;            // [gridDim.x][CI][9*C0 + 1]
   int WoR;                    // register-fused form: dY's columns in memory (W and Wo are rounded up, xbits' rows with them)
   int seg_split;              // register-fused form: the loader waves share the parts of every dY row (1) or take whole rows in turn (0)
+  Stack stk;                  // STACK: the batch as one tall image
+  FastDiv dv_wo;              // division by Wo
   FastDiv dv_rb0, dv_mrow;    // division by the bytes of an input-image row / of a row of mask words (register-fused form)
 };
 
@@ -56,6 +58,7 @@ template <int CI>
 struct ConvDgradShape {
   static constexpr int CO = 64, WGN = CI / 32, MT = 2, WGM = 2 / WGN, BQ = WGM * MT * 32;  // quads per tile
   static constexpr int NBUF = 3, THREADS = 512, MAXSEG = 6, MAXCH = 8, NFW = 4;  // chunks per finishing thread, finishing waves
+  static constexpr int ZERO_BYTES = 256;  // STACK
   static int dyimg_bytes(int Wo, int TQ) { return (TQ + 1) * (Wo + 1) * 128; }
   static int stage_bytes(int W, int TQ) { return 2 * TQ * W * CI * 2; }
   static int lds_bytes(int W, int Wo, int TQ) { return NBUF * dyimg_bytes(Wo, TQ) + 2 * stage_bytes(W, TQ); }
@@ -78,8 +81,11 @@ __device__ __forceinline__ uint32_t keep_pair(uint32_t b, int d) {
 }
 
 // MASK = false: the gradient leaves unmasked (a layer normalisation's backward applies the ReLU behind it itself)
-template <int CI, int C0, bool MASK = true>
+// STACK: bands of quad rows of the batch's stacked images (common.hip.h); the row below an image's last reads zeros behind the
+// staging areas instead of the next image's first row.
+template <int CI, int C0, bool MASK = true, bool STACK = false>
 __global__ __launch_bounds__(512) void k_conv_dgrad_tile(ConvDgradArgs a) {
+  static_assert(!STACK || C0 == 0, "the fused form's image rows are those of one image");
   static_assert(C0 == 0 || (CI == 32 && MASK), "the fused form is written for 32 input channels");
   typedef ConvDgradShape<CI> S;
   constexpr int CO = S::CO, CC = CO / 16, WGN = S::WGN, NBUF = S::NBUF;
@@ -111,6 +117,11 @@ __global__ __launch_bounds__(512) void k_conv_dgrad_tile(ConvDgradArgs a) {
   const int vb = xcd_block((int)blockIdx.x, (int)gridDim.x);  // this block's number in the dealing of tiles
   const int nq = (a.ntiles > vb) ? (a.ntiles - 1 - vb) / (int)gridDim.x + 1 : 0;
 
+  char* const zdy = stage0 + 2 * stage_bytes;  // STACK: two pixels of zeros
+  if constexpr (STACK) {
+    if (tid < 16) *reinterpret_cast<uint4*>(zdy + tid * 16) = make_uint4(0u, 0u, 0u, 0u);
+    asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");  // before this wave's first barrier
+  }
   // zero the right pad slot of every dY image row once
   for (int i = tid; i < NBUF * (TQ + 1) * 8; i += S::THREADS) {
     const int chunk = i & 7, row = i >> 3;
@@ -131,16 +142,21 @@ __global__ __launch_bounds__(512) void k_conv_dgrad_tile(ConvDgradArgs a) {
     }
     auto issue = [&](int q) __attribute__((always_inline)) {
       const int t = vb + q * gridDim.x;
-      const int img = t / a.NB, band = t - img * a.NB;
+      const int img = STACK ? 0 : t / a.NB, band = t - img * a.NB;
       const int oy_lo = band * TQ;
-      const char* src = reinterpret_cast<const char*>(a.dy.ptr_uniform(img)) + (int64_t)oy_lo * rowbytes;
+      const char* src = reinterpret_cast<const char*>(STACK ? a.dy.base : a.dy.ptr_uniform(img)) + (int64_t)oy_lo * rowbytes;
       char* dst = lds + (q % NBUF) * dyimg_bytes;
       for (int row = lw; row <= TQ; row += 2) {
-        const bool inside = oy_lo + row < a.Ho;
+        const bool inside = oy_lo + row < (STACK ? a.stk.rows : a.Ho);
+        const char* rsrc = src + (int64_t)row * rowbytes;
+        if (STACK && !a.stk.dense) {
+          const int R = inside ? oy_lo + row : 0, im = (int)a.stk.ho.div((uint32_t)R);
+          rsrc = reinterpret_cast<const char*>(a.dy.ptr_uniform(im)) + (int64_t)(R - im * (int)a.stk.ho.d) * rowbytes;
+        }
 #pragma unroll
         for (int sg = 0; sg < S::MAXSEG; ++sg)
           if (sg < segs) {
-            const char* p = inside ? src + (int64_t)row * rowbytes + goff[sg] : reinterpret_cast<const char*>(a.zpage) + lane * 16;
+            const char* p = inside ? rsrc + goff[sg] : reinterpret_cast<const char*>(a.zpage) + lane * 16;
             if (goff[sg] >= 0) __builtin_amdgcn_global_load_lds(GLOBAL_AS(p), LDS_AS(dst + row * RP + sg * 1024), 16, 0, 0);
           }
       }
@@ -190,14 +206,16 @@ __global__ __launch_bounds__(512) void k_conv_dgrad_tile(ConvDgradArgs a) {
     auto load_mask = [&](int q, auto setc) __attribute__((always_inline)) {
       constexpr int SET = decltype(setc)::value;
       const int t = vb + q * gridDim.x;
-      const int img = t / a.NB, band = t - img * a.NB;
-      const int b = img / a.V, vw = img - b * a.V;
-      const int rows = min(2 * TQ, a.H - 2 * band * TQ);
-      band_off[SET] = (int64_t)b * a.x_stride_b + (int64_t)vw * a.x_stride_v + (int64_t)(2 * band * TQ) * W * CI;
+      const int img = STACK ? 0 : t / a.NB, band = t - img * a.NB;
+      const int b = STACK ? 0 : img / a.V, vw = img - b * a.V;
+      // the band's first row (STACK: of all images' rows in memory) and its rows that exist
+      const int row0 = STACK ? a.stk.row_of(band * TQ) : 2 * band * TQ;
+      const int rows = STACK ? a.stk.row_of(min(band * TQ + TQ, a.stk.rows)) - row0 : min(2 * TQ, a.H - 2 * band * TQ);
+      band_off[SET] = (int64_t)b * a.x_stride_b + (int64_t)vw * a.x_stride_v + (int64_t)row0 * W * CI;
       nvalid[SET] = rows * W * CI / 8;
       // mask words of the band: pixel (band-linear) c / (CI/8), word (c % (CI/8)) / 4
       if constexpr (!MASK) return;
-      const uint32_t* wb = a.xbits + ((int64_t)img * a.H + 2 * band * TQ) * W * (CI / 32);
+      const uint32_t* wb = a.xbits + ((int64_t)img * a.H + row0) * W * (CI / 32);
 #pragma unroll
       for (int i = 0; i < S::MAXCH; ++i) {
         const int c = chunk_of(i);
@@ -378,18 +396,27 @@ __global__ __launch_bounds__(512) void k_conv_dgrad_tile(ConvDgradArgs a) {
 
   for (int q = 0; q < nq; ++q) {
     const int t = vb + q * gridDim.x;
-    const int band = t % a.NB;
+    const int band = STACK ? t : t % a.NB;
     __builtin_amdgcn_s_barrier();  // A(q): band q is in LDS, staging buffer q&1 is free
     char* st = stage0 + (q & 1) * stage_bytes;
-    const int rows_here = a.H - 2 * band * TQ;  // image rows left from the band's first row
+    const int rows_here = STACK ? 2 * (a.stk.rows - band * TQ) : a.H - 2 * band * TQ;  // image rows left from the band's first row
+    const int er = STACK ? a.stk.edge_row(band * TQ, 1) : 0;                          // STACK: quad row (modulo Ho) with no dY row below
+    const int rm = STACK ? a.stk.mod_ho(band * TQ) : 0;
 #pragma unroll 1
     for (int mt = 0; mt < MT; ++mt) {
       // this lane's quad of the group (lanes beyond the band work on quad 0 and store nothing);
       // recomputed per tile: registers are scarcer here than ALU cycles
       const int qi = (wm * MT + mt) * 32 + l32;
       const bool in_band = qi < TQ * Wo;
-      const int al = in_band ? qi / Wo : 0, b = in_band ? qi - al * Wo : 0;
+      const int al = in_band ? (int)a.dv_wo.div((uint32_t)qi) : 0, b = in_band ? qi - al * Wo : 0;
       const char* img_s = lds + (q % NBUF) * dyimg_bytes + al * RP + b * 128;
+      const char* below = img_s + RP;  // the dY row below the quad's own
+      int skip = 0;                    // STACK, odd heights: missing rows between the band's first row and the quad's
+      if constexpr (STACK) {
+        const int d = (int)a.stk.ho.div((uint32_t)al);
+        if (al - d * (int)a.stk.ho.d == er) below = zdy;
+        if (a.stk.odd) skip = (int)a.stk.ho.div((uint32_t)(rm + al));
+      }
       uint32_t hx[2];
 #pragma unroll
       for (int dxo = 0; dxo < 2; ++dxo) hx[dxo] = (uint32_t)(h * 16) ^ dy_swz_bits((uint32_t)((b + dxo) * 128));
@@ -405,7 +432,7 @@ __global__ __launch_bounds__(512) void k_conv_dgrad_tile(ConvDgradArgs a) {
         const int dyo = pi >> 1, dxo = pi & 1;
 #pragma unroll
         for (int cc = 0; cc < CC; ++cc)
-          dst[cc] = *reinterpret_cast<const bf16x8_t*>(img_s + dyo * RP + dxo * 128 + ((uint32_t)(cc * 32) ^ hx[dxo]));
+          dst[cc] = *reinterpret_cast<const bf16x8_t*>((dyo ? below : img_s) + dxo * 128 + ((uint32_t)(cc * 32) ^ hx[dxo]));
       };
       fetch(0, av[0]);
 #pragma unroll
@@ -435,9 +462,10 @@ __global__ __launch_bounds__(512) void k_conv_dgrad_tile(ConvDgradArgs a) {
 #pragma unroll
       for (int c = 0; c < 4; ++c) {
         const bool col_ok = in_band && ((c & 1) == 0 || 2 * b + 1 < W);
-        if (col_ok && 2 * al + (c >> 1) < rows_here) {
+        const bool row_ok = 2 * al + (c >> 1) < rows_here && !(STACK && (c >> 1) && a.stk.odd && a.stk.mod_ho(rm + al) == (int)a.stk.ho.d - 1);
+        if (col_ok && row_ok) {
           // staged position of pixel class c = py*2 + px, columns wn*32 + h*4 + g*8
-          const uint32_t L = (uint32_t)((((2 * al + (c >> 1)) * W + 2 * b + (c & 1)) * CI + wn * 32 + h * 4) * 2);
+          const uint32_t L = (uint32_t)((((2 * al + (c >> 1) - skip) * W + 2 * b + (c & 1)) * CI + wn * 32 + h * 4) * 2);
           const uint32_t sp = L ^ tile_swz_bits<CI>(L);
 #pragma unroll
           for (int g = 0; g < 4; ++g) {

@@ -50,6 +50,7 @@ struct ConvTileArgs {
   // C0 > 0: the input is the first layer's output, made from the images in src0; every block also copies its share of the n0
   // samples' proprioception (P values, a multiple of 8, gathered like the images) into their feature rows
   Conv0Src src0;
+  Stack stk;                  // STACK: the batch as one tall image
   int n0, P;
   const bf16_t* proprio;
   bf16_t* feat;               // first column that receives it
@@ -68,6 +69,7 @@ struct ConvTileShape {
   static constexpr int MAXSEG = 6;                    // 1 KiB load instructions per image row
   static constexpr int MAXBUF = 6;
   static constexpr int SP = NW + 8;                   // staging pitch (elements)
+  static constexpr int ZERO_BYTES = 3 * PIX;          // STACK
   static constexpr int STAGE_BYTES = 4 * 32 * SP * 2;
   static constexpr int THREADS = 512;                 // four compute waves + four loader waves
   static constexpr int MAXLD = 13;                    // COLS: 1 KiB loads per loader wave and tile
@@ -120,9 +122,12 @@ __device__ __forceinline__ uint32_t fwd_swz_bits(uint32_t off, uint32_t rowkey) 
 // pass as they are (a layer normalisation follows)
 // C0 > 0 (32 input channels): the input rows are made from C0-channel images by the four waves that otherwise load them
 // (conv0_rows.hip.h), one tile ahead of the compute waves, in two LDS buffers; BITS0: the mask bits of the rows are stored.
-template <int CIN, int AUX, int WIDE = 0, bool RELU = true, bool COLS = false, int C0 = 0, bool BITS0 = false>
+// STACK: tiles of TR rows of the batch's stacked images (common.hip.h), whole rows each.  The taps of the row above an image's
+// first read zeros behind the bias table instead.
+template <int CIN, int AUX, int WIDE = 0, bool RELU = true, bool COLS = false, int C0 = 0, bool BITS0 = false, bool STACK = false>
 __global__ __launch_bounds__(512) void k_conv_fwd_tile(ConvTileArgs a) {
   static_assert(C0 == 0 || (CIN == 32 && RELU), "the first layer has 32 output channels");
+  static_assert(!STACK || (!COLS && C0 == 0), "stacked rows are whole rows of a stored tensor");
   typedef ConvTileShape<CIN, WIDE> S;
   constexpr int NW = S::NW, WGN = S::WGN, TN = NW / 32, TM = S::TM, PIX = S::PIX, SP = S::SP;
   constexpr int KC = CIN / 16;  // MFMA k-steps per tap
@@ -142,6 +147,11 @@ __global__ __launch_bounds__(512) void k_conv_fwd_tile(ConvTileArgs a) {
   } else if constexpr (!COLS) for (int i = tid; i < NBUF * nrows * 2 * CPP; i += S::THREADS) {
     const int chunk = i % CPP, side = (i / CPP) & 1, row = i / (2 * CPP);  // row over all images
     *reinterpret_cast<uint4*>(lds + (int64_t)row * WP * PIX + (side ? (W + 1) * PIX : 0) + chunk * 16) = make_uint4(0u, 0u, 0u, 0u);
+  }
+  char* const zrow = lds + NBUF * image_bytes + S::STAGE_BYTES + S::BN * 4;  // STACK: three pixels of zeros
+  if constexpr (STACK) {
+    if (tid < 3 * CPP) *reinterpret_cast<uint4*>(zrow + tid * 16) = make_uint4(0u, 0u, 0u, 0u);
+    asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");  // before this wave's first barrier
   }
 
   if (wave >= 4) {
@@ -239,19 +249,20 @@ __global__ __launch_bounds__(512) void k_conv_fwd_tile(ConvTileArgs a) {
     int slot = 0;  // ring image the next issued band goes to
     auto issue = [&](int q) {
       const int t = vb + q * gridDim.x;
-      const int img = (int)a.dv_nb.div((uint32_t)t), band = t - img * a.NB;
-      const int iy_lo = 2 * band * TR - 1;
-      const char* src = reinterpret_cast<const char*>(a.in.ptr_uniform(img)) + (int64_t)iy_lo * rowbytes;
+      const int img = STACK ? 0 : (int)a.dv_nb.div((uint32_t)t), band = t - img * a.NB;
+      const int iy_lo = 2 * (STACK ? t : band) * TR - 1;
+      const char* src = STACK ? reinterpret_cast<const char*>(a.in.base) : reinterpret_cast<const char*>(a.in.ptr_uniform(img)) + (int64_t)iy_lo * rowbytes;
       char* dst = lds + slot * image_bytes + PIX;  // skip the left pad
       slot = slot + 1 == NBUF ? 0 : slot + 1;
       for (int row = lw; row < nrows; row += 4) {
         const int iy = iy_lo + row;
-        const bool inside = iy >= 0 && iy < a.H;
+        int mem = row;
+        const bool inside = STACK ? a.stk.in_row(iy, a.H, &mem) : iy >= 0 && iy < a.H;
 #pragma unroll
         for (int sg = 0; sg < S::MAXSEG; ++sg)
           if (sg < segs) {
             const int go = (CIN == 32) ? goff[sg] : src_off(sg, row);
-            const char* p = inside ? src + (int64_t)row * rowbytes + go : reinterpret_cast<const char*>(a.zpage) + lane * 16;
+            const char* p = inside ? src + (int64_t)mem * rowbytes + go : reinterpret_cast<const char*>(a.zpage) + lane * 16;
             if (go >= 0) __builtin_amdgcn_global_load_lds(GLOBAL_AS(p), LDS_AS(dst + row * WP * PIX + sg * 1024), 16, 0, AUX);
           }
       }
@@ -290,11 +301,13 @@ __global__ __launch_bounds__(512) void k_conv_fwd_tile(ConvTileArgs a) {
   // u < 2, row 2*oyl + 2 for u = 2)
   constexpr int NU = (CIN == 32) ? 1 : 2;
   uint32_t abase[TM], hx[TM][NU][3];
+  uint32_t rmod = 0u;  // STACK: the pixels' rows modulo Ho, 16 bits each
 #pragma unroll
   for (int i = 0; i < TM; ++i) {
     const int r = (wm * TM + i) * 32 + l32;
     const bool in_band = r < TR * Wo;  // lanes beyond the band compute on pixel 0; never stored
     const int oyl = in_band ? r / Wo : 0, ox = in_band ? r - oyl * Wo : 0;
+    if constexpr (STACK) rmod |= (uint32_t)a.stk.mod_ho(oyl) << (16 * i);
     abase[i] = (uint32_t)(((2 * oyl) * WP + 2 * ox) * PIX);
 #pragma unroll
     for (int u2 = 0; u2 < NU; ++u2)
@@ -349,8 +362,17 @@ __global__ __launch_bounds__(512) void k_conv_fwd_tile(ConvTileArgs a) {
     // itself the compiler keeps a single read in flight.  Logical chunk 2*cc + h of a slot sits at position
     // (2*cc + h) ^ f(slot, row) = (32*cc) ^ hx in bytes.
     constexpr int NS = 9 * KC * TM, RD = 3;
+    const char* top[TM];  // of the window's first row
+    if constexpr (STACK) {
+      const int er = a.stk.edge_row(t * TR, 0);
+      uint32_t rm = rmod;
+      asm volatile("" : "+v"(rm));  // (not to be unpacked ahead of the loop: the wide form has no register to spare)
+#pragma unroll
+      for (int i = 0; i < TM; ++i) top[i] = (int)(rm >> (16 * i) & 0xffffu) == er ? zrow : img_s + abase[i];
+    }
     auto operand = [&](int s) {
       const int i = s % TM, cc = (s / TM) % KC, tap = s / (TM * KC), u = tap / 3, v = tap - 3 * u;
+      if (STACK && u == 0) return *reinterpret_cast<const bf16x8_t*>(top[i] + v * PIX + ((uint32_t)(cc * 32) ^ hx[i][0][v]));
       return *reinterpret_cast<const bf16x8_t*>(img_s + abase[i] + (u * WP + v) * PIX + ((uint32_t)(cc * 32) ^ hx[i][(NU == 2 && u == 2) ? 1 : 0][v]));
     };
     bf16x8_t av[RD + 1];
@@ -365,10 +387,11 @@ __global__ __launch_bounds__(512) void k_conv_fwd_tile(ConvTileArgs a) {
       __builtin_amdgcn_sched_barrier(0);  // keep the read of step s + RD in front of the MFMA of step s
     }
     // ---- epilogue: bf16, ReLU; lane holds pixel l32 of the wave's pixel group i, columns j*32 + g*8 + h*4 + 0..3
+    // (STACK: img = 0, the band's rows are the stack's)
     const int tb = COLS ? (int)a.dv_np.div((uint32_t)t) : t, ox0 = COLS ? (t - tb * a.NP) * Wo : 0;
-    const int img = (int)a.dv_nb.div((uint32_t)tb), band = tb - img * a.NB;
-    const int b = img / a.V, vw = img - b * a.V;
-    const int rows_here = min(TR, a.Ho - band * TR), cols_here = min(Wo, a.Wo - ox0);
+    const int img = STACK ? 0 : (int)a.dv_nb.div((uint32_t)tb), band = tb - img * a.NB;
+    const int b = STACK ? 0 : img / a.V, vw = img - b * a.V;
+    const int rows_here = min(TR, (STACK ? a.stk.rows : a.Ho) - band * TR), cols_here = min(Wo, a.Wo - ox0);
     const int plim = rows_here * Wo;  // pixels of the band that exist
     bf16_t* dst = a.out + (int64_t)b * a.out_stride_b + (int64_t)vw * a.out_stride_v + ((int64_t)band * TR * a.Wo + ox0) * a.Cout;
     // is pixel p of the tile (COLS: at row and column rc) in the image, and which pixel of the image, counted from the tile's first
@@ -412,8 +435,14 @@ __global__ __launch_bounds__(512) void k_conv_fwd_tile(ConvTileArgs a) {
         const int p = p0 + rl, n = n0 + cg * 8;
         uint32_t rc = COLS ? opix[i][e] : 0u;
         if (COLS) asm volatile("" : "+v"(rc));
-        if (exists(p, rc) && n < a.Cout)
-          store_stream16(dst + (int64_t)pix_of(p, rc) * a.Cout + n, *reinterpret_cast<const uint4*>(stage + (rl * SP + cg * 8) * 2));
+        if (exists(p, rc) && n < a.Cout) {
+          const uint4 v = *reinterpret_cast<const uint4*>(stage + (rl * SP + cg * 8) * 2);
+          if (STACK && !a.stk.dense) {
+            const int P = t * TR * Wo + p, im = (int)a.stk.hw.div((uint32_t)P), bi = (int)a.stk.v.div((uint32_t)im);
+            store_stream16(a.out + (int64_t)bi * a.out_stride_b + (int64_t)(im - bi * a.V) * a.out_stride_v + (int64_t)(P - im * (int)a.stk.hw.d) * a.Cout + n, v);
+          } else
+            store_stream16(dst + (int64_t)pix_of(p, rc) * a.Cout + n, v);
+        }
       }
     }
   }
@@ -448,6 +477,7 @@ struct ConvWgradArgs {
   FastDiv dv_nb, dv_np;       // division by NB, NP
   int TC, NP;                 // as in ConvTileArgs
   Conv0Src src0;              // C0 > 0: where the input rows are made from
+  Stack stk;                  // STACK: the batch as one tall image
 };
 
 template <int CIN>
@@ -461,7 +491,7 @@ struct ConvWgradShape {
   static constexpr int MAXLD = 13;  // COLS: 1 KiB image loads per loader wave and tile
   __host__ __device__ static int image_bytes(int slots, int TR) { return ((2 * TR + 1) * slots * PIX + 127) & ~127; }
   static int buf_bytes(int slots, int TR, int nstep) { return image_bytes(slots, TR) + nstep * 16 * 128; }
-  static int lds_bytes(int slots, int TR, int nstep, int nbuf) { return nbuf * buf_bytes(slots, TR, nstep) + 4 * 64 * 4; }
+  static int lds_bytes(int slots, int TR, int nstep, int nbuf) { return nbuf * buf_bytes(slots, TR, nstep) + 4 * 64 * 4; }  // (the end: STACK's zeros)
 };
 
 // The dY pixels of a tile of columns, 64 channels each: piece j of 1 KiB belongs to loader wave j % 4.
@@ -501,8 +531,10 @@ __device__ __forceinline__ bf16x8_t lds_read_tr8_2(const char* p_lo, const char*
 // without a branch and its operand reads ahead of the MFMAs; NS = 0: any number of steps up to MAXSTEP.
 // COLS: tiles of columns, as in the forward kernel.  C0 > 0: the input rows are made from C0-channel images, as there; the
 // ring of nbuf buffers then holds dY alone, an image travels with the dY of the tile before.
-template <int CIN, int NS = 0, bool COLS = false, int C0 = 0>
+// STACK: bands of the batch's stacked images, as in the forward kernel.
+template <int CIN, int NS = 0, bool COLS = false, int C0 = 0, bool STACK = false>
 __global__ __launch_bounds__(512) void k_conv_wgrad_tile(ConvWgradArgs a) {
+  static_assert(!STACK || (!COLS && C0 == 0), "stacked rows are whole rows of a stored tensor");
   static_assert(C0 == 0 || CIN == 32, "the first layer has 32 output channels");
   typedef ConvWgradShape<CIN> S;
   constexpr int PIX = S::PIX, KT = S::KT, KTW = S::KTW, MAXSTEP = S::MAXSTEP;
@@ -525,6 +557,11 @@ __global__ __launch_bounds__(512) void k_conv_wgrad_tile(ConvWgradArgs a) {
     const int chunk = i % (PIX / 16), side = (i / (PIX / 16)) & 1, row = i / (2 * (PIX / 16));
     const int b = row / nrows, rr = row - b * nrows;
     *reinterpret_cast<uint4*>(lds + b * buf_bytes + (int64_t)rr * WP * PIX + (side ? (W + 1) * PIX : 0) + chunk * 16) = make_uint4(0u, 0u, 0u, 0u);
+  }
+  char* const zpix = lds + NBUF * buf_bytes;  // STACK: eight bytes of zeros
+  if constexpr (STACK) {
+    if (tid < 4) reinterpret_cast<uint32_t*>(zpix)[tid] = 0u;
+    asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");  // before this wave's first barrier
   }
 
   if (wave >= 4) {
@@ -655,21 +692,22 @@ __global__ __launch_bounds__(512) void k_conv_wgrad_tile(ConvWgradArgs a) {
     int slot = 0;  // ring buffer the next issued band goes to
     auto issue = [&](int q) {
       const int t = vb + q * gridDim.x;
-      const int img = (int)a.dv_nb.div((uint32_t)t), band = t - img * a.NB;
+      const int img = STACK ? 0 : (int)a.dv_nb.div((uint32_t)t), band = STACK ? t : t - img * a.NB;
       const int iy_lo = 2 * band * TR - 1;
-      const char* xsrc = reinterpret_cast<const char*>(a.in.ptr_uniform(img)) + (int64_t)iy_lo * rowbytes;
-      const int plim = min(TR, a.Ho - band * TR) * Wo;  // pixels of the band that exist
-      const bf16_t* dsrc = a.dy.ptr_uniform(img) + (int64_t)band * TR * Wo * a.Cout + nb0;
+      const char* xsrc = STACK ? reinterpret_cast<const char*>(a.in.base) : reinterpret_cast<const char*>(a.in.ptr_uniform(img)) + (int64_t)iy_lo * rowbytes;
+      const int plim = min(TR, (STACK ? a.stk.rows : a.Ho) - band * TR) * Wo;  // pixels of the band that exist
+      const bf16_t* dsrc = (STACK ? a.dy.base : a.dy.ptr_uniform(img)) + (int64_t)band * TR * Wo * a.Cout + nb0;
       char* buf = lds + slot * buf_bytes;
       slot = slot + 1 == NBUF ? 0 : slot + 1;
       const char* zp = reinterpret_cast<const char*>(a.zpage) + lane * 16;
       for (int row = lw; row < nrows; row += 4) {
         const int iy = iy_lo + row;
-        const bool inside = iy >= 0 && iy < a.H;
+        int mem = row;
+        const bool inside = STACK ? a.stk.in_row(iy, a.H, &mem) : iy >= 0 && iy < a.H;
 #pragma unroll
         for (int sg = 0; sg < S::MAXSEG; ++sg)
           if (sg < segs) {
-            const char* p = inside ? xsrc + (int64_t)row * rowbytes + xgoff[sg] : zp;
+            const char* p = inside ? xsrc + (int64_t)mem * rowbytes + xgoff[sg] : zp;
             if (xgoff[sg] >= 0) __builtin_amdgcn_global_load_lds(GLOBAL_AS(p), LDS_AS(buf + row * WP * PIX + PIX + sg * 1024), 16, 0, LOAD_NT);
           }
       }
@@ -678,6 +716,11 @@ __global__ __launch_bounds__(512) void k_conv_wgrad_tile(ConvWgradArgs a) {
         const int p_ = (int)(logi >> 7), cb = (int)(logi & 127u);
         const bool ok = p_ < plim && nb0 + (cb >> 1) < a.Cout;
         const char* p = ok ? reinterpret_cast<const char*>(dsrc + (int64_t)p_ * a.Cout) + cb : zp;
+        if (STACK && !a.stk.dense) {
+          const int P = ok ? band * TR * Wo + p_ : 0, im = (int)a.stk.hw.div((uint32_t)P), bi = (int)a.stk.v.div((uint32_t)im);
+          const bf16_t* const d = a.dy.base + (int64_t)bi * a.dy.stride_b + (int64_t)(im - bi * a.dy.V) * a.dy.stride_v + (int64_t)(P - im * (int)a.stk.hw.d) * a.Cout + nb0;
+          p = ok ? reinterpret_cast<const char*>(d) + cb : zp;
+        }
         __builtin_amdgcn_global_load_lds(GLOBAL_AS(p), LDS_AS(buf + image_bytes + j * 1024), 16, 0, LOAD_NT);
       }
     };
@@ -706,6 +749,9 @@ __global__ __launch_bounds__(512) void k_conv_wgrad_tile(ConvWgradArgs a) {
   // per step and half (pixels +0..3 / +4..7 of the lane's group): source addresses within a ring buffer
   uint32_t xb[MAXSTEP][2][2];  // image: pixel (2*oyl, 2*ox) with the chunk permutation of tap columns v < 2 / v = 2
   uint32_t db[MAXSTEP][2];     // dY: pixel p, n-tile nsw
+  uint32_t rmod[MAXSTEP / 2];  // STACK: the pixels' rows modulo Ho, eight bits each
+#pragma unroll
+  for (int i = 0; i < MAXSTEP / 2; ++i) rmod[i] = 0u;
 #pragma unroll
   for (int s = 0; s < MAXSTEP; ++s)
 #pragma unroll
@@ -715,6 +761,7 @@ __global__ __launch_bounds__(512) void k_conv_wgrad_tile(ConvWgradArgs a) {
       db[s][hf] = (uint32_t)dy_off + (dl ^ (((dl >> 8) & 1u) << 6) ^ nsw * 64u);
       if (p >= TR * Wo) p = 0;  // its dY is zero; any finite pixel will do
       const int oyl = p / Wo, ox = p - oyl * Wo;
+      if constexpr (STACK) rmod[s / 2] |= (uint32_t)a.stk.mod_ho(oyl) << (16 * (s & 1) + 8 * hf);
       const uint32_t inrow = (uint32_t)(2 * ox * PIX + scolb), rowb = (uint32_t)(2 * oyl * WP * PIX);
       xb[s][hf][0] = rowb + (inrow ^ tile_swz_bits<CIN>(inrow));
       xb[s][hf][1] = rowb + (inrow ^ tile_swz_bits<CIN>(inrow + 2 * PIX));
@@ -730,12 +777,14 @@ __global__ __launch_bounds__(512) void k_conv_wgrad_tile(ConvWgradArgs a) {
   const bf16x8_t ones = __builtin_bit_cast(bf16x8_t, make_uint4(0x3F803F80u, 0x3F803F80u, 0x3F803F80u, 0x3F803F80u));
   // byte offset of k-tile kt within the window: tap (u, v) and, for 64 channels, the pixel half
   uint32_t tapc[KTW]; bool tapv2[KTW], taphi[KTW];
+  int tapu0[KTW];  // STACK: 0 where the tap reads the window's first row, else a number that no row has
 #pragma unroll
   for (int t = 0; t < KTW; ++t) {
     // (a wave without a k-tile for t = KTW-1 reads its first one again where the loop has no branch: the product
     // lands in an accumulator that is never stored, or is replaced by the bias operand)
     const int kt = HALF && t == KTW - 1 ? KT - 1 : (wave + 4 * t < KT) ? wave + 4 * t : wave, tap = kt / (CIN / 32), u = tap / 3, v = tap - 3 * u;
     tapc[t] = (uint32_t)((u * WP + v) * PIX); tapv2[t] = v == 2; taphi[t] = (CIN == 64) && (kt & 1);
+    tapu0[t] = u == 0 ? 0 : -(1 << 20);
   }
 
   if constexpr (C0 > 0) {
@@ -748,6 +797,15 @@ __global__ __launch_bounds__(512) void k_conv_wgrad_tile(ConvWgradArgs a) {
     const char* dbuf = dyring + slot * buf_bytes;
     const char* buf = C0 ? lds + (q & 1) * image_bytes : dbuf;
     slot = slot + 1 == NBUF ? 0 : slot + 1;
+    const int er = STACK ? a.stk.edge_row((vb + q * (int)gridDim.x) * TR, 0) : 0;  // a pixel of that row (modulo Ho) has no row above
+    uint32_t rm[MAXSTEP / 2];
+#pragma unroll
+    for (int i = 0; i < MAXSTEP / 2; ++i) {
+      rm[i] = rmod[i];
+      if (STACK) asm volatile("" : "+v"(rm[i]));  // (not to be unpacked ahead of the loop: there is no register to spare)
+    }
+    // does half hf of step s lie in row e?
+    auto in_row = [&](int s, int hf, int e) __attribute__((always_inline)) { return (int)(rm[s / 2] >> (16 * (s & 1) + 8 * hf) & 255u) == e; };
     if constexpr (NS > 0) {
       // The operand reads run ahead of the MFMAs (the window operand RD k-tiles, the dY operand a whole pixel
       // step): with one compute wave per SIMD nothing else hides the LDS latency, and left to itself the compiler
@@ -764,7 +822,9 @@ __global__ __launch_bounds__(512) void k_conv_wgrad_tile(ConvWgradArgs a) {
         uint32_t o0 = tapv2[t_] ? xb[s_][0][1] : xb[s_][0][0], o1 = tapv2[t_] ? xb[s_][1][1] : xb[s_][1][0];
         const uint32_t hi = taphi[t_] ? 64u : 0u;
         o0 ^= hi; o1 ^= hi;
-        bq[u % (RD + 1)] = lds_read_tr8_2(buf + o0 + tapc[t_], buf + o1 + tapc[t_]);
+        const char *p0 = buf + o0 + tapc[t_], *p1 = buf + o1 + tapc[t_];
+        if (STACK) { const int e = er + tapu0[t_]; p0 = in_row(s_, 0, e) ? zpix : p0; p1 = in_row(s_, 1, e) ? zpix : p1; }
+        bq[u % (RD + 1)] = lds_read_tr8_2(p0, p1);
       };
       read_a(0);
 #pragma unroll
@@ -795,7 +855,9 @@ __global__ __launch_bounds__(512) void k_conv_wgrad_tile(ConvWgradArgs a) {
           if (HALF && t == KTW - 1 ? !bias_wave : wave + 4 * t < KT) {
             uint32_t o0 = tapv2[t] ? xb[s][0][1] : xb[s][0][0], o1 = tapv2[t] ? xb[s][1][1] : xb[s][1][0];
             if (taphi[t]) { o0 ^= 64u; o1 ^= 64u; }
-            const bf16x8_t b = lds_read_tr8_2(buf + o0 + tapc[t], buf + o1 + tapc[t]);
+            const char *p0 = buf + o0 + tapc[t], *p1 = buf + o1 + tapc[t];
+            if (STACK) { const int e = er + tapu0[t]; p0 = in_row(s, 0, e) ? zpix : p0; p1 = in_row(s, 1, e) ? zpix : p1; }
+            const bf16x8_t b = lds_read_tr8_2(p0, p1);
             acc[t][0] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a0, b, acc[t][0], 0, 0, 0);
             if (!HALF || t < KTW - 1) acc[t][1] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a1, b, acc[t][1], 0, 0, 0);
           }

@@ -143,6 +143,21 @@ def test_gradients_wide_rows_of_a_stored_layer(L, conv, more, h, w):
     _check_gradients(L, cfg, 6, 4)
 
 
+@pytest.mark.parametrize("ci,conv,more,h,w,N,T", [
+    (1, (32, 64, 64), {}, 52, 76, 20, 7),                              # 7 x 10 results: bands of up to six rows over the images' borders
+    (1, (32, 64, 64), {}, 28, 28, 150, 2), (1, (32, 64, 64), {}, 32, 29, 60, 5),  # 4 x 4: several images per band (of even and odd heights)
+    (1, (32, 64, 64, 64), {}, 36, 44, 75, 4),                          # odd heights 9 and 5
+    (1, (32, 64, 64, 128), {}, 60, 50, 100, 3),                        # to 128 channels
+    (3, (32, 64, 64, 128), {}, 52, 40, 50, 3), (3, (32, 64, 64, 64), {}, 64, 44, 30, 5),   # two views: strided features
+    (1, (32, 64, 64), dict(embed_dim=32), 44, 52, 45, 4),              # dense features
+    (1, (16, 32, 64), dict(layer_norm=1), 28, 28, 150, 2), (1, (16, 32, 64, 64), dict(layer_norm=1), 32, 36, 75, 4)])  # unmasked, 32 channels from memory
+def test_stacked_bands(L, ci, conv, more, h, w, N, T):
+    """Bands of rows that run on over the images' borders: even and odd heights, a band of several images, strided features."""
+    cfg = configs.get_config(ci, num_envs=N, horizon=T)
+    cfg["net"].update(dict(in_h=h, in_w=w, conv_ch=list(conv)), **more)
+    _check_gradients(L, cfg, N, T)
+
+
 @pytest.mark.parametrize("c0,views,conv,h,w", [(1, 1, (32, 64), 9, 10), (1, 1, (32, 64, 16), 16, 8), (1, 1, (32, 64, 64), 21, 67),
                                                (1, 2, (32, 64, 64), 45, 90), (1, 1, (32, 64, 64), 13, 333), (1, 1, (32, 64, 64), 35, 280),
                                                (3, 1, (32, 64), 11, 14), (3, 2, (32, 64, 32), 30, 71), (3, 1, (32, 64, 64), 14, 200)])

@@ -115,10 +115,11 @@ __device__ __forceinline__ void cs_weights0(const ConvSmallArgs& a, CsW0& q) {
     }
   }
 }
-// first layer of the image in `im` into `act`
+// first layer of the image in `im` into `act`, by NT threads
+template <int NT = 256>
 __device__ __forceinline__ void cs_conv0(const ConvSmallArgs& a, const char* im, char* act, const CsW0& q, int tid) {
   const int ip = ConvSmallShape::ip(a.W), ap = ConvSmallShape::ap(a.Wo1), n = a.Ho0 * a.Wo0;
-  for (int p = tid; p < n; p += 256) {
+  for (int p = tid; p < n; p += NT) {
     const int y = (int)a.dv0.div((uint32_t)p), x = p - y * a.Wo0;
     float v[9];
     cs_window(im, ip, y, x, v);
@@ -181,7 +182,7 @@ __global__ __launch_bounds__(256) void k_conv_small_fwd(ConvSmallArgs a) {
     cur = nxt;
     if (img + gridDim.x < a.nimg) fetch(cur);
     nxt = cs_row(a, img + 2 * gridDim.x);
-    cs_conv0(a, im, act, w0, tid);
+    cs_conv0<>(a, im, act, w0, tid);
     __syncthreads();
     for (int q = wave * 16; q < n1; q += 64) {
       const int p = q + r16, pc = p < n1 ? p : 0, y = (int)a.dv1.div((uint32_t)pc), x = pc - y * a.Wo1;
@@ -255,7 +256,7 @@ __global__ __launch_bounds__(256) void k_conv_small_bwd(ConvSmallArgs a) {
     __syncthreads();
     if (img + gridDim.x < a.nimg) fetch(nxt);
     nxt = cs_row(a, img + 2 * gridDim.x);
-    cs_conv0(a, im, act, w0, tid);
+    cs_conv0<>(a, im, act, w0, tid);
     __syncthreads();
     // dW1[co][tap*8 + ci] += sum over pixels dY[p][co] act[window(p)][ci], 32 pixels per step
     for (int q = (3 - wave) * 32; q < n1; q += 128) {

@@ -222,49 +222,64 @@ struct HeadActArgs {
   float *o_action, *o_logp, *o_value;     // SAMPLE: the rollout slab's rows
   float *c_action, *c_logp, *c_value;     // the caller's rows, each optional: actions (SAMPLE) or means, log-probs, values
 };
+// A wave's operands but the hidden activations, and what follows them.  s: sample l32 of the wave (live: it exists).
+template <int HID, bool SAMPLE>
+struct HeadActRegs {
+  static constexpr int KS = HID / 16;
+  bf16x8_t bw[KS];
+  float xi[16], ls[16];
+  f32x16_t acc;  // starts at the bias
+  __device__ __forceinline__ void load(const HeadActArgs& a, int s, bool live, int l32, int h) {
+    const bf16_t* const wr = a.w + (int64_t)(l32 < a.NH ? l32 : 0) * HID + h * 8;
+#pragma unroll
+    for (int ks = 0; ks < KS; ++ks) bw[ks] = *reinterpret_cast<const bf16x8_t*>(wr + ks * 16);
+#pragma unroll
+    for (int e = 0; e < 16; ++e) {
+      const int j = (e >> 2) * 8 + h * 4 + (e & 3);
+      acc[e] = a.bias[j < a.NH ? j : 0];
+      if (SAMPLE) { const int ja = j < a.A ? j : 0; xi[e] = a.noise[(int64_t)(live ? s : 0) * a.A + ja]; ls[e] = a.logstd[ja]; }
+    }
+  }
+  __device__ __forceinline__ void finish(const HeadActArgs& a, const bf16x8_t (&ah)[KS], int s, bool live, int h) {
+#pragma unroll
+    for (int ks = 0; ks < KS; ++ks) acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(bw[ks], ah[ks], acc, 0, 0, 0);
+    // (rows of W beyond NH repeated row 0; their columns are not used)
+    float logp = 0.f;
+#pragma unroll
+    for (int e = 0; e < 16; ++e) {
+      const int j = (e >> 2) * 8 + h * 4 + (e & 3);
+      if (j < a.A) {
+        float x = acc[e];
+        if (SAMPLE) {  // the arithmetic of k_act_sample
+          const float mu = x, sg = expf(ls[e]), sig_inv = __expf(-ls[e]);
+          x = mu + sg * xi[e];
+          const float zz = (x - mu) * sig_inv;
+          logp += -0.5f * zz * zz - ls[e] - 0.91893853320467274178f;
+          if (live) a.o_action[(int64_t)s * a.A + j] = x;
+        }
+        if (live && a.c_action) a.c_action[(int64_t)s * a.A + j] = x;
+      } else if (j == a.A && j < a.NH) {
+        if (SAMPLE && live) a.o_value[s] = acc[e];
+        if (live && a.c_value) a.c_value[s] = acc[e];
+      }
+    }
+    if (SAMPLE) {
+      const float other = __shfl_xor(logp, 32);
+      const float lp = h ? other + logp : logp + other;
+      if (live && h == 0) { a.o_logp[s] = lp; if (a.c_logp) a.c_logp[s] = lp; }
+    }
+  }
+};
 template <int HID, bool SAMPLE>
 __global__ __launch_bounds__(64) void k_head_act(HeadActArgs a) {
   constexpr int KS = HID / 16;
   const int lane = threadIdx.x, l32 = lane & 31, h = lane >> 5, s = blockIdx.x * 32 + l32;
   const bool live = s < a.n;
   const bf16_t* const hr = a.h + (int64_t)(live ? s : 0) * HID + h * 8;
-  const bf16_t* const wr = a.w + (int64_t)(l32 < a.NH ? l32 : 0) * HID + h * 8;
-  bf16x8_t ah[KS], bw[KS];
+  bf16x8_t ah[KS];
 #pragma unroll
-  for (int ks = 0; ks < KS; ++ks) { ah[ks] = *reinterpret_cast<const bf16x8_t*>(hr + ks * 16); bw[ks] = *reinterpret_cast<const bf16x8_t*>(wr + ks * 16); }
-  float xi[16], ls[16];
-  f32x16_t acc;  // starts at the bias
-#pragma unroll
-  for (int e = 0; e < 16; ++e) {
-    const int j = (e >> 2) * 8 + h * 4 + (e & 3);
-    acc[e] = a.bias[j < a.NH ? j : 0];
-    if (SAMPLE) { const int ja = j < a.A ? j : 0; xi[e] = a.noise[(int64_t)(live ? s : 0) * a.A + ja]; ls[e] = a.logstd[ja]; }
-  }
-#pragma unroll
-  for (int ks = 0; ks < KS; ++ks) acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(bw[ks], ah[ks], acc, 0, 0, 0);
-  // (rows of W beyond NH repeated row 0; their columns are not used)
-  float logp = 0.f;
-#pragma unroll
-  for (int e = 0; e < 16; ++e) {
-    const int j = (e >> 2) * 8 + h * 4 + (e & 3);
-    if (j < a.A) {
-      float x = acc[e];
-      if (SAMPLE) {  // the arithmetic of k_act_sample
-        const float mu = x, sg = expf(ls[e]), sig_inv = __expf(-ls[e]);
-        x = mu + sg * xi[e];
-        const float zz = (x - mu) * sig_inv;
-        logp += -0.5f * zz * zz - ls[e] - 0.91893853320467274178f;
-        if (live) a.o_action[(int64_t)s * a.A + j] = x;
-      }
-      if (live && a.c_action) a.c_action[(int64_t)s * a.A + j] = x;
-    } else if (j == a.A && j < a.NH) {
-      if (SAMPLE && live) a.o_value[s] = acc[e];
-      if (live && a.c_value) a.c_value[s] = acc[e];
-    }
-  }
-  if (SAMPLE) {
-    const float other = __shfl_xor(logp, 32);
-    const float lp = h ? other + logp : logp + other;
-    if (live && h == 0) { a.o_logp[s] = lp; if (a.c_logp) a.c_logp[s] = lp; }
-  }
+  for (int ks = 0; ks < KS; ++ks) ah[ks] = *reinterpret_cast<const bf16x8_t*>(hr + ks * 16);
+  HeadActRegs<HID, SAMPLE> r;
+  r.load(a, s, live, l32, h);
+  r.finish(a, ah, s, live, h);
 }

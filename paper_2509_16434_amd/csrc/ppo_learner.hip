@@ -29,6 +29,7 @@
 #include "conv0_tile.hip.h"
 #include "conv0_wgrad_tile.hip.h"
 #include "conv_small.hip.h"
+#include "small_net.hip.h"
 #include "head_loss.hip.h"
 #include "wgrad_rs.hip.h"
 #include "peaks.hip.h"
@@ -1375,6 +1376,42 @@ int conv_small_forward(Ctx* c, const int32_t* idx, int n, int64_t first) {
   c->abits_ok[0] = false;
   return PPO_OK;
 }
+// The forward of n samples in one kernel (small_net.hip.h): one hidden layer of 32 or 64 units behind one view, a product that the
+// separate launch would give to k_gemm_small, and few samples (four of a
+// block: 1024 environments 20.1 -> 14.8 us a policy step; with eight of a block it would take as long as the separate launches).
+bool small_net_covers(const Ctx* c, int n) {
+  return conv_small_covers(c) && c->V == 1 && c->nfc == 1 && (c->fout[0] == 32 || c->fout[0] == 64) && c->fin[0] <= 2048 && c->P % 8 == 0 && c->P > 0 &&
+         c->fin[0] == c->flat + c->P && n <= 256 * SmallNetShape::MAXS && gemm_small_covers(n, c->fout[0], c->fin[0]);
+}
+template <typename InT, bool ACT>
+int launch_small_net(Ctx* c, SmallNetArgs a) {
+  a.K = c->fin[0]; a.S = cdiv(a.n, 256); a.w = c->shadow + c->fcW[0]; a.b = c->p + c->fcB[0];
+  const int nw = a.K <= 512 ? 4 : 8, nk = cdiv(cdiv(a.K, 16), nw);  // k_gemm_small's slices
+  a.per = nk * 16;
+  const int lds = SmallNetShape::lds_bytes(a.cs, a.K, a.S, c->fout[0]);
+#define LAUNCH_SMALL(HID_, NK_)                                                                                                           \
+  do {                                                                                                                                      \
+    static uint64_t attr_devs = 0;  /* bit d: set on device d */                                                                            \
+    if (!((attr_devs >> c->dev) & 1)) { HIPCHK(c, hipFuncSetAttribute((const void*)k_small_net<InT, HID_, NK_, ACT>, hipFuncAttributeMaxDynamicSharedMemorySize, 128 * 1024)); attr_devs |= 1ull << c->dev; } \
+    hipLaunchKernelGGL((k_small_net<InT, HID_, NK_, ACT>), dim3(cdiv(a.n, a.S)), dim3(512), lds, c->stream, a);                              \
+  } while (0)
+  if (c->fout[0] == 32) { if (nk <= 9) LAUNCH_SMALL(32, 9); else LAUNCH_SMALL(32, 16); }
+  else { if (nk <= 9) LAUNCH_SMALL(64, 9); else LAUNCH_SMALL(64, 16); }
+#undef LAUNCH_SMALL
+  LAUNCHCHK(c, "k_small_net");
+  return PPO_OK;
+}
+// features and hidden activations of n samples of the buffer, chosen by idx (NULL: first ..)
+int small_net_forward(Ctx* c, const int32_t* idx, int n, int64_t first) {
+  SmallNetArgs a = {};
+  if (idx) first = 0;
+  a.cs = conv_small_args(c, idx, n, first); a.cs.feat = c->feat; a.cs.proprio = c->proprio + first * c->P; a.cs.P = c->P;
+  a.n = n; a.hout = c->fcact[0];
+  ProfScope ps(c, "small_net_fwd", 2.0 * n * ((double)a.cs.Ho0 * a.cs.Wo0 * 72 + (double)a.cs.Ho1 * a.cs.Wo1 * 1152 + (double)c->fin[0] * c->fout[0]),
+               2.0 * n * ((double)c->img_elems + c->fin[0] + c->fout[0]));
+  c->abits_ok[0] = false;
+  return launch_small_net<bf16_t, false>(c, a);
+}
 // from the masked gradient of the feature matrix in gbuf[cur]
 int conv_small_backward(Ctx* c, const int32_t* idx, int n, bool acc, int cur) {
   const int nimg = n * c->V;
@@ -1491,6 +1528,7 @@ int encoder_forward_generic(Ctx* c, const int32_t* idx, int n, int64_t first);
 // Forward of `n` samples of a feed-forward network selected by device indices idx (NULL: samples first ..
 // first + n - 1 of the buffer).
 int forward_chunk(Ctx* c, const int32_t* idx, int n, bool train, bool with_head, int64_t first = 0) {
+  if (!with_head && small_net_covers(c, n)) return small_net_forward(c, idx, n, first);
   const int rc = (c->ln || c->E > 0) ? encoder_forward_generic(c, idx, n, first) : encoder_forward_ff(c, idx, n, first, train);
   if (rc) return rc;
   return trunk_forward(c, c->feat, c->feat_ld, n, with_head);
@@ -2986,14 +3024,26 @@ int ppo_act(ppo_ctx* c, int32_t t, const void* d_obs, const float* d_proprio, co
   if (c->nl > 0) return fail(c, PPO_ESTATE, "ppo_act keeps no recurrent state between calls: not available for a recurrent net");
   if (t < 0 || t >= c->T) return fail(c, PPO_EINVAL, "t = %d outside [0, %d)", t, c->T);
   if (!d_obs || !d_proprio || !d_noise) return fail(c, PPO_EINVAL, "d_obs, d_proprio and d_noise must not be NULL");
-  int rc = write_slab(c, t, 0, c->N, d_obs, d_proprio, nullptr, nullptr, nullptr, nullptr, nullptr);
+  const int64_t first = (int64_t)t * c->N;
+  const bool one = head_act_covers(c) && c->N <= c->CH && small_net_covers(c, c->N);
+  int rc = PPO_OK;
+  if (one) {
+    SmallNetArgs a = {};
+    a.cs = conv_small_args(c, nullptr, c->N, first); a.cs.P = c->P;
+    a.src = d_obs; a.psrc = d_proprio; a.slab = c->obs + first * c->img_elems; a.pslab = c->proprio + first * c->P; a.W0 = c->d.in_w; a.n = c->N;
+    HeadActArgs& h = a.head;
+    h.w = c->shadow + c->headW; h.bias = c->p + c->headB; h.n = c->N; h.A = c->A; h.NH = c->NH; h.logstd = c->p + c->logstd; h.noise = d_noise;
+    h.o_action = c->action + first * c->A; h.o_logp = c->logp + first; h.o_value = c->value + first; h.c_action = d_action; h.c_logp = d_logp; h.c_value = d_value;
+    ProfScope ps(c, "small_net_act", 2.0 * c->N * ((double)a.cs.Ho0 * a.cs.Wo0 * 72 + (double)a.cs.Ho1 * a.cs.Wo1 * 1152 + (double)c->fin[0] * c->fout[0]),
+                 (double)c->N * (c->img_elems * (c->d.obs_dtype == 0 ? 6.0 : 4.0) + 6.0 * c->P + 12.0 * c->A + 16.0));
+    rc = c->d.obs_dtype == 0 ? launch_small_net<float, true>(c, a) : launch_small_net<bf16_t, true>(c, a);
+  } else rc = write_slab(c, t, 0, c->N, d_obs, d_proprio, nullptr, nullptr, nullptr, nullptr, nullptr);
   if (rc) return rc;
   if (t == 0) { c->written.assign((size_t)c->T, 0); c->cover.assign((size_t)c->T, {}); }
   c->written[(size_t)t] = 2;
   c->cover[(size_t)t].clear();
   c->gae_done = false;
-  const int64_t first = (int64_t)t * c->N;
-  for (int64_t c0 = 0; c0 < c->N; c0 += c->CH) {
+  for (int64_t c0 = 0; !one && c0 < c->N; c0 += c->CH) {
     const int n = (int)((c->N - c0 < c->CH) ? c->N - c0 : c->CH);
     const bool fused = head_act_covers(c);
     rc = forward_chunk(c, nullptr, n, false, !fused, first + c0);

@@ -474,6 +474,44 @@ def test_the_update_sees_the_policy_that_acted(L, c0, conv, h, w, spoil):
     assert st[0]["approx_kl"] == 0.0 and st[0]["clip_frac"] == 0.0
 
 
+@pytest.mark.parametrize("h,w,hid,P,N,dtype", [(32, 32, 64, 32, 64, "fp32"), (16, 20, 32, 8, 3, "bf16"), (21, 27, 64, 16, 257, "fp32"), (40, 44, 64, 24, 130, "bf16"),
+                                               (28, 33, 32, 40, 1024, "fp32"), (28, 28, 64, 32, 1025, "fp32"), (48, 48, 64, 32, 40, "fp32")])
+def test_small_network_in_one_kernel(L, h, w, hid, P, N, dtype):
+    """The small network's policy step and forward in one kernel (one to four samples per block, two depths of the hidden layer's slices,
+    rows of any width and element offset) and, beyond its range, the separate launches: the sampled action against the oracle, the
+    stored images and proprioception, and ratio 1 exactly in the update's first step."""
+    import torch
+    cfg = dict(configs.get_config(0, num_envs=N, horizon=2), obs_dtype=dtype)
+    net = cfg["net"]
+    net.update(in_h=h, in_w=w, fc_dim=[hid], proprio_dim=P)
+    params = synth.init_params(net, 9)
+    a0, a1, _ = synth.param_slices(net)["logstd"]
+    params[a0:a1] = -8.0
+    lrn = L.Learner(net, N, 2, dtype)
+    lrn.set_params(params)
+    gen = torch.Generator(device="cuda")
+    gen.manual_seed(3)
+    odt = torch.float32 if dtype == "fp32" else torch.bfloat16
+    for t in range(2):
+        d = synth.rollout_step_torch(cfg, gen)
+        room = torch.empty(d["obs"].numel() + 1, dtype=odt, device="cuda")   # the second step's images start at an odd element
+        obs = room[t:t + d["obs"].numel()].view(d["obs"].shape)
+        obs.copy_(d["obs"])
+        pro, noise = d["proprio"].contiguous(), torch.randn(N, net["act_dim"], generator=gen, device="cuda")
+        a, lp, v = lrn.act(t, obs, pro, noise)
+        with orc.quant(1):
+            oa, olp, ov = orc.act(net, params, obs.float().cpu().numpy(), pro.cpu().numpy(), noise.cpu().numpy())
+        omu = oa - np.exp(-8.0) * noise.cpu().numpy()
+        assert np.linalg.norm(a.cpu().numpy() - oa) <= TOL_BF16 * np.linalg.norm(omu) and rel_l2(v.cpu().numpy(), ov) <= TOL_BF16
+        np.testing.assert_array_equal(lrn.buffer_read_obs(t).float().cpu().numpy(), obs.to(torch.bfloat16).float().cpu().numpy())
+        lrn.buffer_write_outcome(t, d["reward"].contiguous(), d["done"].contiguous())
+    mu, v2 = lrn.forward(torch.arange(N, 2 * N, device="cuda", dtype=torch.int32))   # the second step's
+    assert rel_l2(mu.cpu().numpy(), omu) <= TOL_BF16 and torch.equal(v2, v)
+    lrn.gae(torch.zeros(N, device="cuda"), 0.99, 0.95)
+    st = lrn.update(dict(cfg["hp"], epochs=1, minibatches=2))
+    assert st[0]["approx_kl"] == 0.0 and st[0]["clip_frac"] == 0.0
+
+
 def test_read_back_staging_is_allocated_at_creation(L):
     """The first read of a context into memory in hand allocates nothing: its pinned staging (two pieces, 2 MiB, for this
     network) is part of ppo_create."""

@@ -37,6 +37,7 @@ __device__ __forceinline__ void store_stream16(bf16_t* p, const uint4& v) {
 struct FastDiv {
   uint32_t mul = 0, sh = 0, d = 0;
   __device__ __forceinline__ uint32_t div(uint32_t n) const { return d == 1u ? n : (__umulhi(n, mul) >> sh); }
+  __device__ __forceinline__ uint32_t div2(uint32_t n) const { return __umulhi(n, mul) >> sh; }  // d >= 2: no branch in unrolled code
 };
 inline FastDiv make_fastdiv(int32_t d) {
   FastDiv f;

@@ -34,6 +34,7 @@
 #include "wgrad_rs.hip.h"
 #include "peaks.hip.h"
 #include "recurrent.hip.h"
+#include "ln0_tile.hip.h"
 
 static_assert(sizeof(DevStats) == sizeof(ppo_mb_stats), "device and host statistics records must match");
 
@@ -1705,6 +1706,31 @@ static ImgAddr act_addr(Ctx* c, int l) {
   return contiguous_imgs(c->act[l], e, c->V);
 }
 
+// First layer and its normalisation in one kernel per direction (ln0_tile.hip.h): 16 channels behind a one-channel image that a
+// block's registers hold (4864 output pixels).
+bool ln0_covers(const Ctx* c) { return c->ln && c->cC[0] == 1 && c->cC[1] == 16 && c->P <= 8192 && Ln0Shape::covers(c->cH[0], c->cW[0], c->cH[1]); }
+Ln0Args ln0_args(Ctx* c, const ImgAddr& in, int nimg) {
+  Ln0Args a = {};
+  a.in = in; a.in.prepare(); a.w = c->shadow + c->convW[0]; a.bias = c->p + c->convB[0]; a.gain = c->p + c->lnG[0]; a.shift = c->p + c->lnB[0]; a.nimg = nimg;
+  a.H = c->cH[0]; a.W = c->cW[0]; a.Ho = c->cH[1]; a.Wo = c->cW[1]; a.w4 = make_fastdiv(a.W / 8); a.stats = c->lnstat[0];
+  return a;
+}
+template <bool BWD>
+int launch_ln0(Ctx* c, const Ln0Args& a, int grid) {
+  const int lds = Ln0Shape::lds_bytes(a.Ho, a.W, BWD), nt = cdiv(Ln0Shape::tiles(a.Ho, a.W), Ln0Shape::NW);
+  const int f = (nt <= 10 ? 0 : nt <= 20 ? 1 : 2) + (2 * a.Wo == a.W ? 0 : 3);
+  static decltype(&k_conv0_ln_fwd<10, false>) const fwd[6] = {k_conv0_ln_fwd<10, false>, k_conv0_ln_fwd<20, false>, k_conv0_ln_fwd<38, false>,
+                                                              k_conv0_ln_fwd<10, true>, k_conv0_ln_fwd<20, true>, k_conv0_ln_fwd<38, true>};
+  static decltype(&k_conv0_ln_fwd<10, false>) const bwd[6] = {k_conv0_ln_bwd<10, false>, k_conv0_ln_bwd<20, false>, k_conv0_ln_bwd<38, false>,
+                                                              k_conv0_ln_bwd<10, true>, k_conv0_ln_bwd<20, true>, k_conv0_ln_bwd<38, true>};
+  auto kfn = BWD ? bwd[f] : fwd[f];
+  static uint64_t attr_devs[6] = {};  /* bit d: set on device d */
+  if (!((attr_devs[f] >> c->dev) & 1)) { HIPCHK(c, hipFuncSetAttribute((const void*)kfn, hipFuncAttributeMaxDynamicSharedMemorySize, 160 * 1024)); attr_devs[f] |= 1ull << c->dev; }
+  hipLaunchKernelGGL(kfn, dim3(grid), dim3(Ln0Shape::THREADS), lds, c->stream, a);
+  LAUNCHCHK(c, BWD ? "k_conv0_ln_bwd" : "k_conv0_ln_fwd");
+  return PPO_OK;
+}
+
 int encoder_forward_generic(Ctx* c, const int32_t* idx, int n, int64_t first) {
   const int V = c->V, nimg = n * V;
   bool proprio_done = false;
@@ -1716,6 +1742,17 @@ int encoder_forward_generic(Ctx* c, const int32_t* idx, int n, int64_t first) {
     const ImgAddr oa = act_addr(c, l);
     const ImgAddr conv_to = c->ln ? contiguous_imgs(c->pre[l], e, V) : oa;
     const std::string name = "conv_fwd." + std::to_string(l);
+    if (l == 0 && ln0_covers(c)) {
+      ImgAddr in; in.base = c->obs + first * c->img_elems * V; in.idx = idx; in.stride_b = c->img_elems * V; in.stride_v = c->img_elems; in.V = V;
+      Ln0Args a = ln0_args(c, in, nimg);
+      a.out = as_w(oa); a.P = c->P; a.proprio = c->proprio + first * c->P; a.feat = c->feat + V * c->enc; a.feat_ld = c->feat_ld;
+      ProfScope ps(c, "conv_fwd.0+layer_norm", 2.0 * (double)M * Co * 9 + 8.0 * (double)nimg * e, 2.0 * ((double)nimg * c->img_elems + (double)M * Co));
+      const int rc = launch_ln0<false>(c, a, std::min(nimg, 256));
+      if (rc) return rc;
+      proprio_done = true;
+      c->abits_ok[0] = false;
+      continue;
+    }
     if (l == 0) {
       ImgAddr in; in.base = c->obs + first * c->img_elems * V; in.idx = idx; in.stride_b = c->img_elems * V; in.stride_v = c->img_elems; in.V = V;
       in.prepare();
@@ -1836,6 +1873,24 @@ int encoder_backward_seq(Ctx* c, const int32_t* idx, int n, bool acc, const bf16
     const int Co = c->cC[l + 1], Ci = c->cC[l], Ho = c->cH[l + 1], Wo = c->cW[l + 1], H = c->cH[l], W = c->cW[l];
     const int64_t e = (int64_t)Co * Ho * Wo;
     ImgAddr dconv = dy;  // gradient w.r.t. the convolution's output
+    if (l == 0 && ln0_covers(c)) {
+      ImgAddr in; in.base = c->obs; in.idx = idx; in.stride_b = c->img_elems * V; in.stride_v = c->img_elems; in.V = V;
+      Ln0Args a = ln0_args(c, in, nimg);
+      a.dy = dy; a.dy.prepare();
+      int grid = std::min(nimg, 256);
+      { const int erc = ensure_partial(c, (int64_t)grid * 192, 0); if (erc) return erc; }
+      grid = (int)std::min<int64_t>(grid, c->partial_elems / 192);
+      if (grid < 1) return fail(c, PPO_ENOMEM, "weight-gradient workspace too small for the first convolution");
+      a.part_ln = c->partial; a.part_w = c->partial + (int64_t)grid * 32;
+      {
+        ProfScope ps(c, "layer_norm_bwd+conv_wgrad.0", 2.0 * (double)nimg * Ho * Wo * 16 * 19 + 14.0 * (double)nimg * e, 2.0 * ((double)nimg * c->img_elems + (double)nimg * e));
+        const int rc = launch_ln0<true>(c, a, grid);
+        if (rc) return rc;
+      }
+      defer_reduce(c, 0, grid, 32, 0, 0, c->g + c->lnG[0], nullptr, acc, false, 0, nullptr);
+      defer_reduce(c, 2, grid, 160, 16, 9, c->g + c->convW[0], c->g + c->convB[0], acc, false, 0, nullptr);
+      break;
+    }
     if (c->ln) {
       int grid = nimg < 1024 ? nimg : 1024;
       { const int erc = ensure_partial(c, (int64_t)grid * 2 * Co, 0); if (erc) return erc; }

@@ -272,6 +272,17 @@ def test_gradients_with_layer_norm(L, c0, conv, h, w):
     _check_gradients(L, cfg, 10, 4)
 
 
+@pytest.mark.parametrize("ci,conv,h,w,N,T", [(1, (16, 32), 16, 16, 3, 1), (1, (16, 16), 20, 24, 100, 3), (1, (16, 32), 33, 30, 7, 2), (1, (16, 32, 32), 41, 69, 90, 3),
+                                              (1, (16, 32), 64, 80, 5, 3), (1, (16, 32, 64), 84, 90, 4, 2), (1, (16, 32, 64), 120, 160, 3, 2),
+                                              (1, (16, 32, 64), 122, 160, 3, 2), (1, (16, 32), 2, 64, 5, 3)])
+def test_first_layer_and_its_normalisation(L, ci, conv, h, w, N, T):
+    """First convolution, normalisation and ReLU in one kernel per direction: ten, twenty or 38 tiles per wave at most, rows that are no
+    multiple of four pixels, several images per block, and one row more than the registers hold (the separate kernels)."""
+    cfg = configs.get_config(ci, num_envs=N, horizon=T)
+    cfg["net"].update(in_h=h, in_w=w, conv_ch=list(conv), layer_norm=1)
+    _check_gradients(L, cfg, N, T)
+
+
 @pytest.mark.parametrize("chunks", range(1, 21))
 def test_layer_norm_backward_of_any_chunk_count(L, chunks):
     """One form of the layer-normalisation backward per number of 16-byte chunks a thread holds (up to 19; 20 reads

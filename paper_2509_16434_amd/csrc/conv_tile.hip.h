@@ -1,4 +1,4 @@
-// 3x3 stride-2 pad-1 convolution forward for 32 or 64 input channels, organised around what is
+// 3x3 stride-2 pad-1 convolution forward for 16, 32 or 64 input channels, organised around what is
 // scarce on the CU for this shape: bytes in flight per CU and vector-ALU issue slots, not MFMA
 // cycles.
 //
@@ -63,8 +63,8 @@ struct ConvTileShape {
   static constexpr int NW = (CIN == 32) ? 64 : 32;   // output columns per wave (18432 weights per wave)
   // WIDE: the four waves stand side by side (128 columns) and each takes both 32-pixel halves of the band, so that a
   // layer with more than 64 output channels loads its input once instead of once per 64 columns
-  static constexpr int WGM = WIDE ? 1 : (CIN == 32) ? 4 : 2, WGN = 4 / WGM, TM = WIDE ? 2 : 1;
-  static constexpr int BM = WGM * TM * 32, BN = WGN * NW;  // 128 x 64, 64 x 64 or 64 x 128
+  static constexpr int WGM = WIDE ? 1 : (CIN == 64) ? 2 : 4, WGN = 4 / WGM, TM = WIDE || CIN == 16 ? 2 : 1;
+  static constexpr int BM = WGM * TM * 32, BN = WGN * NW;  // 128 x 64, 64 x 64 or 64 x 128; 256 x 32
   static constexpr int PIX = CIN * 2;                 // bytes per pixel
   static constexpr int MAXSEG = 6;                    // 1 KiB load instructions per image row
   static constexpr int MAXBUF = 6;
@@ -115,6 +115,7 @@ struct ColsLoads {
 template <int CIN>
 __device__ __forceinline__ uint32_t fwd_swz_bits(uint32_t off, uint32_t rowkey) {
   if (CIN == 32) return tile_swz_bits<32>(off);
+  if (CIN == 16) return ((off >> 8) & 1u) << 4;  // slot >> 3
   return (((off >> 8) + rowkey) & 7u) << 4;
 }
 
@@ -261,7 +262,7 @@ __global__ __launch_bounds__(512) void k_conv_fwd_tile(ConvTileArgs a) {
 #pragma unroll
         for (int sg = 0; sg < S::MAXSEG; ++sg)
           if (sg < segs) {
-            const int go = (CIN == 32) ? goff[sg] : src_off(sg, row);
+            const int go = (CIN != 64) ? goff[sg] : src_off(sg, row);
             const char* p = inside ? src + (int64_t)mem * rowbytes + go : reinterpret_cast<const char*>(a.zpage) + lane * 16;
             if (go >= 0) __builtin_amdgcn_global_load_lds(GLOBAL_AS(p), LDS_AS(dst + row * WP * PIX + sg * 1024), 16, 0, AUX);
           }
@@ -299,7 +300,7 @@ __global__ __launch_bounds__(512) void k_conv_fwd_tile(ConvTileArgs a) {
   // 2*oyl) and, per tap column v, the chunk permutation of slot 2*ox + v folded with the lane's k half
   // (for 64 channels the permutation also depends on the image row pair: rows 2*oyl, 2*oyl + 1 for the taps
   // u < 2, row 2*oyl + 2 for u = 2)
-  constexpr int NU = (CIN == 32) ? 1 : 2;
+  constexpr int NU = (CIN == 64) ? 2 : 1;
   uint32_t abase[TM], hx[TM][NU][3];
   uint32_t rmod = 0u;  // STACK: the pixels' rows modulo Ho, 16 bits each
 #pragma unroll
@@ -640,7 +641,7 @@ __global__ __launch_bounds__(512) void k_conv_wgrad_tile(ConvWgradArgs a) {
       vm_wait_few(younger(0) + nd + (nq > 1 ? pr.nl : 0));
       __builtin_amdgcn_s_barrier();  // the first image has landed, the buffers are zeroed
       produce_alone(0);
-      const bool interleave = pr.ng > 3 ? max(nd, pr.nl) <= pr.GPW : max(nd, pr.nl) <= 3;  // as many loads of a kind as groups at most
+      const bool interleave = pr.ng > 3 ? max(nd, pr.nl) <= pr.GPW : max(nd, pr.nl) <= 3;  // as many loads of a kind as groups at most  // as many loads of a kind as groups at most
       for (int q = 0; q < nq; ++q) {
         vm_wait_few(younger(q));       // dY of tile q and the image of tile q + 1 have landed
         asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");

@@ -26,6 +26,7 @@
 #include "conv_dgrad_tile.hip.h"
 #include "conv_dgrad_wgrad0_tile.hip.h"
 #include "conv_dgrad_k2_tile.hip.h"
+#include "conv16_tile.hip.h"
 #include "conv0_tile.hip.h"
 #include "conv0_wgrad_tile.hip.h"
 #include "conv_small.hip.h"
@@ -818,8 +819,9 @@ int launch_conv_fwd_tile_t(Ctx* c, ConvTileArgs a, const std::string& name, doub
     // bands of four or more output rows share at most an eighth of their input rows with a neighbour: read once, non-temporal
     form = a.TR >= 4;
     int tr;
+    if (CIN == 16 && form != 1) return 1;
     auto fits = [&](int r) { return S::lds_bytes(slots, r, 3) + S::ZERO_BYTES <= 160 * 1024 && cdiv(2 * r + 1, 4) * cdiv(a.W * S::PIX, 1024) <= 63; };
-    if (dense_images(a.in.stride_b, a.in.stride_v, a.V, (int64_t)a.H * a.W * CIN) && plan_stack(nimg, a.Ho, a.Wo, S::BM, a.NB, 256 / cdiv(a.Cout, S::BN), CIN == 32 ? 80 : 95, fits, &tr)) {
+    if (CIN != 16 && dense_images(a.in.stride_b, a.in.stride_v, a.V, (int64_t)a.H * a.W * CIN) && plan_stack(nimg, a.Ho, a.Wo, S::BM, a.NB, 256 / cdiv(a.Cout, S::BN), CIN == 32 ? 80 : 95, fits, &tr)) {
       a.stk = make_stack(nimg, a.Ho, a.Wo, a.H, a.V);
       a.stk.dense = dense_images(a.out_stride_b, a.out_stride_v, a.V, (int64_t)a.Ho * a.Wo * a.Cout);
       a.TR = tr; ni = cdiv(2 * tr + 1, 4) * cdiv(a.W * S::PIX, 1024); form = 3;
@@ -827,7 +829,7 @@ int launch_conv_fwd_tile_t(Ctx* c, ConvTileArgs a, const std::string& name, doub
   } else {
     ColsPlan p;
     auto fits = [&](int tc, int tr) { return S::image_bytes(2 * tc + 1, tr) <= S::MAXLD * 4096 && S::lds_bytes(2 * tc + 1, tr, 3) <= 160 * 1024; };
-    if (!plan_cols(a.Ho, a.Wo, S::BM, fits, &p)) return 1;
+    if (CIN == 16 || !plan_cols(a.Ho, a.Wo, S::BM, fits, &p)) return 1;
     a.TC = p.TC; a.NP = p.NP; a.TR = p.TR; a.NB = p.NB;
     slots = 2 * a.TC + 1; ni = cdiv(cdiv(S::image_bytes(slots, a.TR), 1024), 4); form = 2;
   }
@@ -839,7 +841,8 @@ int launch_conv_fwd_tile_t(Ctx* c, ConvTileArgs a, const std::string& name, doub
   const int lds = S::lds_bytes(slots, a.TR, a.nbuf) + extra;
   const int gy = cdiv(a.Cout, S::BN);
   int gx = 256 / gy; if (gx > a.ntiles) gx = a.ntiles; if (gx < 1) gx = 1;
-  auto kfn = form == 3 ? k_conv_fwd_tile<CIN, LOAD_NT, WIDE, RELU, false, 0, false, true> : form == 2 ? k_conv_fwd_tile<CIN, 0, WIDE, RELU, true> : form == 1 ? k_conv_fwd_tile<CIN, LOAD_NT, WIDE, RELU> : k_conv_fwd_tile<CIN, 0, WIDE, RELU>;
+  auto kfn = k_conv_fwd_tile<CIN, LOAD_NT, WIDE, RELU>;  // (16 channels: bands of four or more rows only)
+  if constexpr (CIN != 16) kfn = form == 3 ? k_conv_fwd_tile<CIN, LOAD_NT, WIDE, RELU, false, 0, false, true> : form == 2 ? k_conv_fwd_tile<CIN, 0, WIDE, RELU, true> : form == 1 ? k_conv_fwd_tile<CIN, LOAD_NT, WIDE, RELU> : k_conv_fwd_tile<CIN, 0, WIDE, RELU>;
   static uint64_t attr_devs[4] = {0, 0, 0, 0};  // bit d: set on device d
   if (!((attr_devs[form] >> c->dev) & 1)) { HIPCHK(c, hipFuncSetAttribute((const void*)kfn, hipFuncAttributeMaxDynamicSharedMemorySize, 160 * 1024)); attr_devs[form] |= 1ull << c->dev; }
   ProfScope ps(c, name, flops, abytes);
@@ -849,7 +852,7 @@ int launch_conv_fwd_tile_t(Ctx* c, ConvTileArgs a, const std::string& name, doub
 }
 int launch_conv_fwd_tile(Ctx* c, const AConvFwd& al, const ImgAddr& o, int Cout, const bf16_t* w, const float* bias, int nimg,
                          const std::string& name, double abytes, uint32_t* bits, bool relu = true) {
-  if ((al.Cin != 32 && al.Cin != 64) || Cout % 8 || nimg < 1 || al.in.idx) return 1;
+  if ((al.Cin != 16 && al.Cin != 32 && al.Cin != 64) || (al.Cin == 16 && Cout > 32) || Cout % 8 || nimg < 1 || al.in.idx) return 1;
   ConvTileArgs a;
   a.in = al.in; a.in.prepare();
   a.out = const_cast<bf16_t*>(o.base); a.out_stride_b = o.stride_b; a.out_stride_v = o.stride_v;
@@ -859,7 +862,8 @@ int launch_conv_fwd_tile(Ctx* c, const AConvFwd& al, const ImgAddr& o, int Cout,
   const double flops = 2.0 * (double)al.M * Cout * al.K;
   // more than 64 output channels: the 64 x 128 form reads the input once
 #define LAUNCH_FWD(R_)                                                                       \
-  (al.Cin == 32 ? launch_conv_fwd_tile_t<32, 0, R_>(c, a, name, flops, abytes)                \
+  (al.Cin == 16 ? launch_conv_fwd_tile_t<16, 0, R_>(c, a, name, flops, abytes)                \
+   : al.Cin == 32 ? launch_conv_fwd_tile_t<32, 0, R_>(c, a, name, flops, abytes)              \
    : Cout > 64  ? launch_conv_fwd_tile_t<64, 1, R_>(c, a, name, flops, abytes)                \
                 : launch_conv_fwd_tile_t<64, 0, R_>(c, a, name, flops, abytes))
   return relu ? LAUNCH_FWD(true) : LAUNCH_FWD(false);
@@ -1040,14 +1044,45 @@ int launch_conv_wgrad_tile_t(Ctx* c, ConvWgradArgs a, float* gw, float* gb, bool
   defer_reduce(c, 1, gx, per, a.Cout, K, gw, nullptr, accumulate, gb != nullptr, a.Cout, gb);
   return PPO_OK;
 }
+// The same for 16 input and up to 32 output channels (conv16_tile.hip.h).
+int launch_conv16_wgrad_tile(Ctx* c, ConvWgradArgs a, float* gw, float* gb, bool accumulate, const std::string& name, double flops, double abytes) {
+  typedef Conv16WgradShape S;
+  const int nimg = a.ntiles, segs = cdiv(a.W * S::PIX, 1024);  // passed in as the image count
+  if (segs > S::MAXSEG || a.Wo > 16 * S::MAXSTEP || a.Cout > 32) return 1;
+  auto lds_of = [&](int tr, int nb) { return S::lds_bytes(a.W, tr, cdiv(tr * a.Wo, 16), nb); };
+  auto loads = [&](int tr) { return cdiv(2 * tr + 1, 4) * segs + cdiv(cdiv(tr * a.Wo, 16), 4); };  // per loader wave and band
+  int tr = std::min(16 * S::MAXSTEP / a.Wo, a.Ho);
+  while (tr > 0 && (lds_of(tr, 3) > 160 * 1024 || loads(tr) > 63)) --tr;
+  if (tr < 1) return 1;
+  a.NB = cdiv(a.Ho, tr); a.TR = cdiv(a.Ho, a.NB); a.nstep = cdiv(a.TR * a.Wo, 16); a.ntiles = nimg * a.NB; a.dv_nb = make_fastdiv(a.NB);
+  a.nbuf = S::MAXBUF;
+  while (a.nbuf > 3 && (lds_of(a.TR, a.nbuf) > 160 * 1024 || (a.nbuf - 2) * loads(a.TR) > 63)) --a.nbuf;
+  int gx = std::min(256, a.ntiles);
+  const int64_t per = (int64_t)a.Cout * 144;
+  { const int erc = ensure_partial(c, (int64_t)gx * per, gb ? (int64_t)gx * a.Cout : 0); if (erc) return erc; }
+  gx = (int)std::min<int64_t>(gx, c->partial_elems / per);
+  if (gb) gx = (int)std::min<int64_t>(gx, c->bias_partial_elems / a.Cout);
+  if (gx < 1) return 1;
+  a.partial = c->partial; a.bias_partial = gb ? c->bias_partial : nullptr;
+  static uint64_t attr_devs = 0;  /* bit d: set on device d */
+  if (!((attr_devs >> c->dev) & 1)) { HIPCHK(c, hipFuncSetAttribute((const void*)k_conv16_wgrad_tile, hipFuncAttributeMaxDynamicSharedMemorySize, 160 * 1024)); attr_devs |= 1ull << c->dev; }
+  {
+    ProfScope ps(c, name, flops, abytes);
+    hipLaunchKernelGGL(k_conv16_wgrad_tile, dim3(gx), dim3(S::THREADS), lds_of(a.TR, a.nbuf), c->stream, a);
+    LAUNCHCHK(c, "k_conv16_wgrad_tile");
+  }
+  defer_reduce(c, 1, gx, per, a.Cout, 144, gw, nullptr, accumulate, gb != nullptr, a.Cout, gb);
+  return PPO_OK;
+}
 int launch_conv_wgrad_tile(Ctx* c, const ImgAddr& dy, const AConvFwd& xl, int Cout, int nimg, float* gw, float* gb, bool accumulate,
                            const std::string& name, double abytes) {
-  if ((xl.Cin != 32 && xl.Cin != 64) || Cout % 8 || nimg < 1 || xl.in.idx || dy.idx) return 1;
+  if ((xl.Cin != 16 && xl.Cin != 32 && xl.Cin != 64) || Cout % 8 || nimg < 1 || xl.in.idx || dy.idx) return 1;
   ConvWgradArgs a;
   a.in = xl.in; a.in.prepare(); a.dy = dy; a.dy.prepare(); a.zpage = c->zpage; a.partial = nullptr; a.bias_partial = nullptr;
   a.H = xl.H; a.W = xl.W; a.Ho = xl.Ho; a.Wo = xl.Wo; a.Cout = Cout; a.TR = a.NB = a.TC = a.NP = 0; a.nstep = 0; a.nbuf = 3;
   a.ntiles = nimg;  // image count; the template turns it into tiles
   const double flops = 2.0 * (double)xl.M * Cout * xl.K;
+  if (xl.Cin == 16) return launch_conv16_wgrad_tile(c, a, gw, gb, accumulate, name, flops, abytes);
   return xl.Cin == 32 ? launch_conv_wgrad_tile_t<32>(c, a, gw, gb, accumulate, name, flops, abytes)
                       : launch_conv_wgrad_tile_t<64>(c, a, gw, gb, accumulate, name, flops, abytes);
 }
@@ -1139,6 +1174,22 @@ int launch_conv_dgrad_k2_tile(Ctx* c, ConvDgradArgs a, int nimg, const std::stri
   LAUNCHCHK(c, "k_conv_dgrad_k2_tile");
   return PPO_OK;
 }
+// The form for 32 gradient channels and 16 result channels, unmasked (conv16_tile.hip.h).
+int launch_conv16_dgrad_tile(Ctx* c, ConvDgradArgs a, int nimg, const std::string& name, double flops, double abytes) {
+  typedef Conv16DgradShape S;
+  if (a.Wo > S::BQ || cdiv(a.Wo * 64, 1024) > S::MAXSEG) return 1;
+  int tq = std::min(S::BQ / a.Wo, a.Ho);
+  while (tq > 1 && S::lds_bytes(a.W, a.Wo, tq) > 40 * 1024) --tq;  // four blocks to a CU
+  if (S::lds_bytes(a.W, a.Wo, tq) > 80 * 1024) return 1;
+  a.NB = cdiv(a.Ho, tq); a.TQ = cdiv(a.Ho, a.NB); a.ntiles = nimg * a.NB; a.dv_rb0 = make_fastdiv(a.NB);
+  const int lds = S::lds_bytes(a.W, a.Wo, a.TQ), gx = std::min(a.ntiles, 256 * std::min(4, 160 * 1024 / lds));
+  static uint64_t attr_devs = 0;  /* bit d: set on device d */
+  if (!((attr_devs >> c->dev) & 1)) { HIPCHK(c, hipFuncSetAttribute((const void*)k_conv16_dgrad_tile, hipFuncAttributeMaxDynamicSharedMemorySize, 80 * 1024)); attr_devs |= 1ull << c->dev; }
+  ProfScope ps(c, name, flops, abytes);
+  hipLaunchKernelGGL(k_conv16_dgrad_tile, dim3(gx), dim3(S::THREADS), lds, c->stream, a);
+  LAUNCHCHK(c, "k_conv16_dgrad_tile");
+  return PPO_OK;
+}
 // (xbits NULL: the gradient is left unmasked; f32: partial sums stay fp32)
 int launch_conv_dgrad_tile(Ctx* c, const ImgAddr& dy, const ImgAddr& xa, const uint32_t* xbits, bf16_t* dx, const bf16_t* wt, int Co, int Ci, int H, int W, int Ho, int Wo,
                            int nimg, const std::string& name, double flops, double abytes, bool f32) {
@@ -1148,6 +1199,7 @@ int launch_conv_dgrad_tile(Ctx* c, const ImgAddr& dy, const ImgAddr& xa, const u
     if (!f32) return xbits ? launch_conv_dgrad_k2_tile<true, false>(c, a, nimg, name, flops, abytes) : 1;
     return xbits ? launch_conv_dgrad_k2_tile<true, true>(c, a, nimg, name, flops, abytes) : launch_conv_dgrad_k2_tile<false, true>(c, a, nimg, name, flops, abytes);
   }
+  if (Co == 32 && Ci == 16 && !xbits) return launch_conv16_dgrad_tile(c, a, nimg, name, flops, abytes);
   if (Co != 64 || (Ci != 32 && Ci != 64)) return 1;
   if (xbits) return Ci == 32 ? launch_conv_dgrad_tile_t<32, 0>(c, a, nimg, name, flops, abytes, nullptr) : launch_conv_dgrad_tile_t<64, 0>(c, a, nimg, name, flops, abytes, nullptr);
   return Ci == 32 ? launch_conv_dgrad_tile_t<32, 0, false>(c, a, nimg, name, flops, abytes, nullptr) : launch_conv_dgrad_tile_t<64, 0, false>(c, a, nimg, name, flops, abytes, nullptr);

@@ -283,6 +283,16 @@ def test_first_layer_and_its_normalisation(L, ci, conv, h, w, N, T):
     _check_gradients(L, cfg, N, T)
 
 
+@pytest.mark.parametrize("conv,ln,h,w,N,T", [((16, 32, 64, 128), 1, 60, 80, 16, 4), ((16, 32, 32), 1, 37, 53, 20, 7), ((16, 16, 32), 1, 30, 62, 5, 3), ((16, 8, 32), 1, 40, 34, 5, 2),
+                                              ((16, 32, 64), 0, 44, 60, 6, 3), ((16, 32), 1, 18, 380, 3, 2), ((16, 32), 1, 18, 390, 3, 2), ((16, 32, 32), 1, 12, 20, 40, 8)])
+def test_second_layer_of_sixteen_channels(L, conv, ln, h, w, N, T):
+    """16 -> 32 channels from memory: odd heights and widths, last bands of fewer rows, rows up to and beyond the kernels' longest, fewer
+    than 32 channels (input gradient: the implicit form), bands of fewer than four rows (forward: the same)."""
+    cfg = configs.get_config(1, num_envs=N, horizon=T)
+    cfg["net"].update(in_h=h, in_w=w, conv_ch=list(conv), layer_norm=ln)
+    _check_gradients(L, cfg, N, T)
+
+
 @pytest.mark.parametrize("chunks", range(1, 21))
 def test_layer_norm_backward_of_any_chunk_count(L, chunks):
     """One form of the layer-normalisation backward per number of 16-byte chunks a thread holds (up to 19; 20 reads

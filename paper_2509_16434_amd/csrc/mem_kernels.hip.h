@@ -888,22 +888,50 @@ __global__ __launch_bounds__(256) void k_reduce_batch(ReduceJobs jobs, LossFinal
 }
 
 
+// Gradient norm from the per-block sums: the sum of their squares, the same in every thread of a block of 256, and, by one block,
+// the norm's entry in the step's statistics.
+struct GnormFinalize { int on, nb; const float* sq_part; DevStats* st; float max_norm; };
+__device__ __forceinline__ float gnorm_sum(const GnormFinalize& f, float* red) {
+  const int tid = threadIdx.x;
+  float s = 0.f;
+  for (int b = tid; b < f.nb; b += 256) s += f.sq_part[b];
+  red[tid] = s;
+  __syncthreads();
+  for (int w = 128; w > 0; w >>= 1) { if (tid < w) red[tid] += red[tid + w]; __syncthreads(); }
+  return red[0];
+}
+__device__ __forceinline__ void gnorm_record(const GnormFinalize& f, float sum) {
+  f.st->grad_norm = sqrtf(sum);
+  if (!isfinite(sum)) f.st->nonfinite = 1;
+}
+__device__ __forceinline__ void gnorm_finalize_block(const GnormFinalize& f) {
+  __shared__ float red[256];
+  const float sum = gnorm_sum(f, red);
+  if (threadIdx.x == 0) gnorm_record(f, sum);
+}
+
 // ---------------------------------------------------------------- Adam
 // m = b1 m + (1-b1) g; v = b2 v + (1-b2) g^2; p -= lr (m/c1) / (sqrt(v/c2) + eps), c1 = 1-b1^k,
 // c2 = 1-b2^k passed in.  Also refreshes the bf16 copy of the parameters and leaves per-block sums
-// of g^2 for the gradient-norm statistic.  With gradient-norm clipping the gradient enters as
-// g * *clip_coef (the coefficient min(1, c / (||g|| + 1e-6)) left by k_gnorm_finalize); the sums
-// of g^2 are of the gradient before clipping either way.  lr_dev (if not null) holds the rate
+// of g^2 for the gradient-norm statistic.  With gradient-norm clipping (gn.on) the gradient enters as
+// g * min(1, c / (||g|| + 1e-6)): every block adds up the norm's per-block sums, left by
+// k_gnorm_partial, itself (a launch of one block for it cost 4.9 us, some 300 sums in every block
+// less than 1); the sums of g^2 are of the gradient before clipping either way.  lr_dev (if not null) holds the rate
 // instead of the argument: the KL-adaptive schedule keeps it on the device.
 __global__ __launch_bounds__(256) void k_adam(int64_t n, float* __restrict__ p, float* __restrict__ m,
                                               float* __restrict__ v, const float* __restrict__ g,
                                               bf16_t* __restrict__ shadow, float lr, float b1, float b2, float eps,
                                               float inv_c1, float inv_c2, float* __restrict__ sq_part,
-                                              const float* __restrict__ clip_coef, const float* __restrict__ lr_dev) {
+                                              GnormFinalize gn, const float* __restrict__ lr_dev) {
   __shared__ float red[256];
   const int tid = threadIdx.x;
   if (lr_dev) lr = *lr_dev;
-  const float coef = clip_coef ? *clip_coef : 1.f;
+  float coef = 1.f;
+  if (gn.on) {
+    const float sum = gnorm_sum(gn, red);
+    coef = fminf(1.f, gn.max_norm / (sqrtf(sum) + 1e-6f));
+    if (blockIdx.x == 0 && tid == 0) gnorm_record(gn, sum);
+  }
   float sq = 0.f;
   for (int64_t i = ((int64_t)blockIdx.x * 256 + tid) * 4; i < n; i += (int64_t)gridDim.x * 1024) {
     if (i + 4 <= n) {
@@ -930,6 +958,7 @@ __global__ __launch_bounds__(256) void k_adam(int64_t n, float* __restrict__ p, 
       }
     }
   }
+  if (gn.on) return;  // (the sums are being read)
   red[tid] = sq;
   __syncthreads();
   for (int s = 128; s > 0; s >>= 1) { if (tid < s) red[tid] += red[tid + s]; __syncthreads(); }
@@ -954,26 +983,6 @@ __global__ __launch_bounds__(256) void k_gnorm_partial(int64_t n, const float* _
   for (int s = 128; s > 0; s >>= 1) { if (tid < s) red[tid] += red[tid + s]; __syncthreads(); }
   if (tid == 0) sq_part[blockIdx.x] = red[0];
 }
-// Gradient norm from the per-block sums; with max_norm > 0 also the clipping coefficient
-// min(1, max_norm / (norm + 1e-6)) for k_adam.  The work of one block of 256 threads.
-struct GnormFinalize { int on, nb; const float* sq_part; DevStats* st; float max_norm; float* clip_coef; };
-__device__ __forceinline__ void gnorm_finalize_block(const GnormFinalize& f) {
-  __shared__ float red[256];
-  const int tid = threadIdx.x;
-  float s = 0.f;
-  for (int b = tid; b < f.nb; b += 256) s += f.sq_part[b];
-  red[tid] = s;
-  __syncthreads();
-  for (int w = 128; w > 0; w >>= 1) { if (tid < w) red[tid] += red[tid + w]; __syncthreads(); }
-  if (tid == 0) {
-    const float norm = sqrtf(red[0]);
-    f.st->grad_norm = norm;
-    if (!isfinite(red[0])) f.st->nonfinite = 1;
-    if (f.clip_coef) *f.clip_coef = f.max_norm > 0.f ? fminf(1.f, f.max_norm / (norm + 1e-6f)) : 1.f;
-  }
-}
-__global__ __launch_bounds__(256) void k_gnorm_finalize(GnormFinalize f) { gnorm_finalize_block(f); }
-
 // ---------------------------------------------------------------- advantage normalisation
 // out = (adv - mean) / (std + 1e-8) over all S samples of the rollout, std the population standard deviation.
 // Two launches of ADVN_BLOCKS-or-fewer blocks.  k_adv_stats: block b takes the contiguous slice b of the samples and

@@ -164,7 +164,7 @@ struct Ctx {
   LossFinalize lossfin = {};    // pending: rides as the last block of the next reduction launch
   GnormFinalize gnfin = {}; // pending: rides as the last block of the next re-pack launch
   int rjob_blocks = 0;
-  float *stat_part = nullptr, *dls_part = nullptr, *sq_part = nullptr, *clip_coef = nullptr;
+  float *stat_part = nullptr, *dls_part = nullptr, *sq_part = nullptr;
   float* lr_dev = nullptr;  // the KL-adaptive learning rate (desired_kl > 0); lr_live: an adaptive update has left a rate there
   bool lr_live = false;
   float* adv_n = nullptr;  // advantages normalised over the rollout (norm_adv)
@@ -656,7 +656,8 @@ int launch_wgrad(Ctx* c, const DL& dl_, const AL& al_, int Nn, int Kk, int M, fl
   const int ktw = Kk <= 128 ? 1 : (Kk <= 256 ? 2 : (Kk >= 1024 ? 1 : 3));
   const int tiles = cdiv(Kk, 128 * ktw) * cdiv(Nn, 64);
   int splits = cdiv(Kk >= 1024 ? 512 : 768, tiles);
-  const int max_by_rows = cdiv(M, 128);
+  int max_by_rows = cdiv(M, 128);
+  if ((int64_t)tiles * max_by_rows < 64) max_by_rows = cdiv(M, 64);  // few blocks: shorter chains (256 rows of 64 x 1056 7.1 -> 5.3 us, 1250 of 128 x 256 8.3 -> 7.4; 4096 rows, 64 blocks: 0)
   if (splits > max_by_rows) splits = max_by_rows;
   const int64_t per = (int64_t)Nn * Kk;
   { const int erc = ensure_partial(c, (int64_t)splits * per, (int64_t)splits * Nn); if (erc) return erc; }
@@ -2441,17 +2442,16 @@ int run_update(Ctx* c, const ppo_hparams* hp, ppo_mb_stats* host_stats, bool dis
       if (clip) {  // the norm has to be known before the step: one more pass over the gradient
         hipLaunchKernelGGL(k_gnorm_partial, dim3(c->adam_blocks), dim3(256), 0, c->stream, c->total, c->g, c->sq_part);
         LAUNCHCHK(c, "k_gnorm_partial");
-        GnormFinalize gf; gf.on = 1; gf.nb = c->adam_blocks; gf.sq_part = c->sq_part; gf.st = c->dstats + k; gf.max_norm = hp->max_grad_norm; gf.clip_coef = c->clip_coef;
-        hipLaunchKernelGGL(k_gnorm_finalize, dim3(1), dim3(256), 0, c->stream, gf);
-        LAUNCHCHK(c, "k_gnorm_finalize");
       }
+      GnormFinalize norm;
+      norm.on = clip ? 1 : 0; norm.nb = c->adam_blocks; norm.sq_part = c->sq_part; norm.st = c->dstats + k; norm.max_norm = hp->max_grad_norm;
       hipLaunchKernelGGL(k_adam, dim3(c->adam_blocks), dim3(256), 0, c->stream, c->total, c->p, c->m, c->v, c->g, c->shadow, hp->lr, hp->beta1, hp->beta2,
-                         hp->adam_eps, (float)(1.0 / c1), (float)(1.0 / c2), c->sq_part, clip ? c->clip_coef : nullptr,
+                         hp->adam_eps, (float)(1.0 / c1), (float)(1.0 / c2), c->sq_part, norm,
                          adaptive ? c->lr_dev : nullptr);
       LAUNCHCHK(c, "k_adam");
       if (!clip) {  // the step's gradient norm: one more block of the re-pack launch that follows
-        GnormFinalize& gf = c->gnfin;
-        gf.on = 1; gf.nb = c->adam_blocks; gf.sq_part = c->sq_part; gf.st = c->dstats + k; gf.max_norm = 0.f; gf.clip_coef = nullptr;
+        c->gnfin = norm;
+        c->gnfin.on = 1;
       }
       }
       rc = repack_weights(c);
@@ -2664,7 +2664,7 @@ int create_impl(Ctx* c) {
   DALLOC(c, c->stat_part, (int64_t)c->max_loss_blocks * LOSS_NSTAT); DALLOC(c, c->dls_part, (int64_t)c->max_loss_blocks * 32);
   c->adam_blocks = cdiv(c->total, 1024); if (c->adam_blocks > 2048) c->adam_blocks = 2048;
   DALLOC(c, c->sq_part, c->adam_blocks);
-  DALLOC(c, c->clip_coef, 1); DALLOC(c, c->lr_dev, 1); DALLOC(c, c->advn_part, 3 * ADVN_BLOCKS);
+  DALLOC(c, c->lr_dev, 1); DALLOC(c, c->advn_part, 3 * ADVN_BLOCKS);
   DALLOC(c, c->dstats, c->max_steps);
   HIPCHK(c, hipMemsetAsync(c->p, 0, sizeof(float) * (size_t)c->total, c->stream));
   HIPCHK(c, hipMemsetAsync(c->m, 0, sizeof(float) * (size_t)c->total, c->stream));

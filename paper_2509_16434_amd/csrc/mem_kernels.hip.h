@@ -42,7 +42,8 @@ __global__ __launch_bounds__(256) void k_write_obs(const InT* __restrict__ src, 
   }
   const uint32_t gid = blockIdx.x * 256u + threadIdx.x;  // (the host keeps the slab's group count below 2^31)
   const uint32_t row = groups.div(gid);
-  if ((int64_t)row >= n_row) return;
+  if (C == 1 && (int64_t)row >= n_row) return;
+  const bool exists = (int64_t)row < n_row;
   const int x0 = (int)(gid - row * groups.d) * 8, live = W - x0;  // pixels of this group that exist (8 or more: all)
   const uint32_t img = dvh.div(row);
   const InT* s = src + ((int64_t)img * (C - 1) * dvh.d + row) * W + x0;  // plane 0; plane c is H*W further on
@@ -51,7 +52,10 @@ __global__ __launch_bounds__(256) void k_write_obs(const InT* __restrict__ src, 
 #pragma unroll
   for (int c = 0; c < C; ++c) {
     InT v[8];
-    if (live >= 8) {
+    if (C > 1 && !exists) {
+#pragma unroll
+      for (int j = 0; j < 8; ++j) v[j] = (InT)0;
+    } else if (live >= 8) {
       __builtin_memcpy(v, __builtin_assume_aligned(s + c * plane, sizeof(InT)), sizeof v);  // 16-byte loads at any element offset
     } else {
 #pragma unroll
@@ -67,9 +71,27 @@ __global__ __launch_bounds__(256) void k_write_obs(const InT* __restrict__ src, 
   for (int j = 0; j < 8; ++j)
 #pragma unroll
     for (int c = 0; c < C; ++c) o[j * C + c] = in[c][j];
-  uint4* d4 = reinterpret_cast<uint4*>(dst + (int64_t)gid * 8 * C);
+  if constexpr (C == 1) {
+    *reinterpret_cast<uint4*>(dst + (int64_t)gid * 8) = *reinterpret_cast<const uint4*>(o);
+  } else {
+    // A lane has C pieces of 16 bytes in a row: through LDS (a wave's own part, so no barrier) they leave as C stores of 64
+    // neighbouring pieces per wave instead of C stores that each touch all of the wave's lines.  Two views of three channels,
+    // bf16: 300 environments of 52 x 100 13.4 -> 10.4 us, 4096 of 120 x 160 357 -> 341 us (5.6 TB/s read and written).
+    __shared__ __attribute__((aligned(16))) uint4 stage[4][64 * C];
+    uint4* const st = stage[threadIdx.x >> 6];
+    const int lane = threadIdx.x & 63;
 #pragma unroll
-  for (int q = 0; q < C; ++q) d4[q] = reinterpret_cast<const uint4*>(o)[q];
+    for (int q = 0; q < C; ++q) st[lane * C + q] = reinterpret_cast<const uint4*>(o)[q];
+    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+    const int64_t first = (int64_t)(gid - lane) * C, end = n_row * (int64_t)groups.d * C;
+    uint4* const d4 = reinterpret_cast<uint4*>(dst);
+#pragma unroll
+    for (int q = 0; q < C; ++q) {
+      const uint4 v = st[q * 64 + lane];
+      if (first + q * 64 + lane < end) d4[first + q * 64 + lane] = v;
+    }
+  }
 }
 
 // Inverse layout change of k_write_obs (no conversion): [img][H][WP][C] -> [img][C][H][W].

@@ -320,6 +320,27 @@ def test_stored_images_bit_exact_at_any_width(L, ci, dtype, h, w):
         assert torch.equal(lrn.buffer_read_obs(t), obs.to(torch.bfloat16))
 
 
+@pytest.mark.parametrize("ci", [0, 3])
+@pytest.mark.parametrize("h,w,off,cnt", [(5, 7, 3, 1), (4, 9, 1, 11), (6, 8, 5, 2), (9, 33, 0, 12), (16, 16, 4, 8)])
+def test_a_range_of_environments_leaves_the_others(L, ci, h, w, off, cnt):
+    """Images of a range end inside a wave's staged pieces: nothing before or behind them changes, in the step or the next."""
+    import torch
+    cfg = configs.get_config(ci, num_envs=13, horizon=2)
+    cfg["net"].update(in_h=h, in_w=w)
+    net = cfg["net"]
+    lrn = L.Learner(net, 13, 2, "bf16")
+    gen = torch.Generator(device="cuda")
+    gen.manual_seed(w + cnt)
+    obs = torch.randn(2, 13, net["n_views"], net["in_c"], h, w, generator=gen, device="cuda").to(torch.bfloat16)
+    for t in (0, 1):
+        for lo, hi in ((0, off), (off + cnt, 13), (off, off + cnt)):  # the range last, between environments that are there
+            z = torch.zeros(hi - lo, device="cuda")
+            if hi > lo:
+                lrn.buffer_write_range(t, lo, obs[t, lo:hi].contiguous(), torch.zeros(hi - lo, net["proprio_dim"], device="cuda"),
+                                       torch.zeros(hi - lo, net["act_dim"], device="cuda"), z, z, z, z.to(torch.uint8))
+    assert torch.equal(lrn.buffer_read_obs(0), obs[0]) and torch.equal(lrn.buffer_read_obs(1), obs[1])
+
+
 @pytest.mark.parametrize("layers,units,N,T,P", [(2, 64, 33, 5, 8), (1, 96, 70, 3, 40), (3, 32, 9, 4, 16), (2, 24, 40, 4, 8), (4, 32, 130, 2, 8), (2, 160, 65, 1, 8), (2, 64, 200, 6, 8)])
 def test_gradients_recurrent(L, layers, units, N, T, P):
     """LSTM layers side by side (units in multiples of 32; up to 64 environments: 64 x 64 tiles, more: 128 x 128) and one

@@ -635,9 +635,17 @@ int launch_wgrad_rs(Ctx* c, const bf16_t* dy, int64_t ld_dy, const bf16_t* x, in
   return PPO_OK;
 }
 
+// A hidden layer's input gradient that may be taken beside its weight gradient (k_fc_backward).
+struct DgradBeside {
+  const bf16_t* wT;  // [Kk][Nn]
+  Ep<MapRows, bf16_t, false, false, true> ep;
+  double abytes;
+  bool taken;        // set by launch_wgrad
+};
 // G[Nn][Kk] (+)= Dy^T * A over M rows, plus optional bias gradient gb[Nn].
 template <class DL, class AL>
-int launch_wgrad(Ctx* c, const DL& dl_, const AL& al_, int Nn, int Kk, int M, float* gw, float* gb, bool accumulate, const std::string& name, double abytes) {
+int launch_wgrad(Ctx* c, const DL& dl_, const AL& al_, int Nn, int Kk, int M, float* gw, float* gb, bool accumulate, const std::string& name, double abytes,
+                 DgradBeside* beside = nullptr) {
   if (M <= 0) return PPO_OK;
   // the queued sums of one launch run side by side: one that this gradient is added to is taken first
   for (int j = 0; accumulate && j < c->rjobs.njobs; ++j)
@@ -668,9 +676,27 @@ int launch_wgrad(Ctx* c, const DL& dl_, const AL& al_, int Nn, int Kk, int M, fl
   rows = (rows + 31) / 32 * 32;
   splits = cdiv(M, rows);
   dim3 grid(cdiv(Kk, 128 * ktw), cdiv(Nn, 64), splits);
-  {
+  float* bp = gb ? c->bias_partial : nullptr;
+  if constexpr (std::is_same<DL, ARows>::value && std::is_same<AL, ARows>::value) {
+    // One launch with the input gradient where that is k_gemm_small's on four waves and the blocks of both (two to a CU by their
+    // LDS) are resident at once: each then hides behind the other.  Beyond that line nothing is hidden: the blocks queue.
+    const int nw = (int)(grid.x * grid.y * grid.z), gm = cdiv(M, 32), ng = gm * cdiv(Kk, 32);
+    if (beside && dl.plain && al.plain && Nn <= 512 && gemm_small_covers(M, Kk, Nn) && nw + ng <= 512) {
+      ProfScope ps(c, name + "+dgrad", 4.0 * M * (double)Nn * Kk, abytes + beside->abytes);
+      beside->ep.map.prepare();
+      FcBackward a;
+      a.dl = dl; a.al = al; a.Nn = Nn; a.Kk = Kk; a.M = M; a.rows = rows; a.nw = nw; a.gx = make_fastdiv(grid.x); a.gy = make_fastdiv(grid.y); a.gm = make_fastdiv(gm);
+      a.partial = c->partial; a.bias_partial = bp; a.wT = beside->wT;
+      using EP = Ep<MapRows, bf16_t, false, false, true>;
+      if (ktw == 1) hipLaunchKernelGGL((k_fc_backward<1, EP>), dim3(nw + ng), dim3(256), 0, c->stream, a, beside->ep);
+      else if (ktw == 2) hipLaunchKernelGGL((k_fc_backward<2, EP>), dim3(nw + ng), dim3(256), 0, c->stream, a, beside->ep);
+      else hipLaunchKernelGGL((k_fc_backward<3, EP>), dim3(nw + ng), dim3(256), 0, c->stream, a, beside->ep);
+      LAUNCHCHK(c, what);
+      beside->taken = true;
+    }
+  }
+  if (!beside || !beside->taken) {
     ProfScope ps(c, name, 2.0 * M * (double)Nn * Kk, abytes);
-    float* bp = gb ? c->bias_partial : nullptr;
     if (ktw == 1) hipLaunchKernelGGL((k_wgrad<1, DL, AL>), grid, dim3(256), 0, c->stream, dl, al, Nn, Kk, M, rows, c->partial, bp);
     else if (ktw == 2) hipLaunchKernelGGL((k_wgrad<2, DL, AL>), grid, dim3(256), 0, c->stream, dl, al, Nn, Kk, M, rows, c->partial, bp);
     else hipLaunchKernelGGL((k_wgrad<3, DL, AL>), grid, dim3(256), 0, c->stream, dl, al, Nn, Kk, M, rows, c->partial, bp);
@@ -1612,14 +1638,17 @@ int trunk_backward(Ctx* c, const bf16_t* xin, int64_t ldin, bool mask_in, int n,
     const int64_t ldx = l ? c->fin[l] : ldin;
     ARows dl = plain_arows(c->gbuf[cur], c->fout[l], n, c->fout[l]);
     ARows xl = plain_arows(x, ldx, n, c->fin[l]);
-    int rc = launch_wgrad(c, dl, xl, c->fout[l], c->fin[l], n, c->g + c->fcW[l], c->g + c->fcB[l], acc, "fc_wgrad." + std::to_string(l),
-                          2.0 * n * ((double)c->fin[l] + c->fout[l]) + 4.0 * (double)c->fin[l] * c->fout[l]);
-    if (rc) return rc;
     const double ab = 2.0 * ((double)n * c->fout[l] + 2.0 * n * c->fin[l] + (double)c->fin[l] * c->fout[l]);
-    if (l > 0 || mask_in) {
-      Ep<MapRows, bf16_t, false, false, true> ep;
-      ep.map = plain_map(c->fin[l], n); ep.out = c->gbuf[cur ^ 1]; ep.bias = nullptr; ep.mask = x; ep.N = c->fin[l];
-      rc = launch_gemm(c, dl, n, c->fcT[l], c->fout[l], c->fin[l], c->fout[l], ep, "fc_dgrad." + std::to_string(l), ab);
+    const bool masked = l > 0 || mask_in;
+    DgradBeside beside = {};
+    beside.wT = c->fcT[l]; beside.abytes = ab;
+    Ep<MapRows, bf16_t, false, false, true>& ep = beside.ep;
+    ep.map = plain_map(c->fin[l], n); ep.out = c->gbuf[cur ^ 1]; ep.bias = nullptr; ep.mask = x; ep.N = c->fin[l];
+    int rc = launch_wgrad(c, dl, xl, c->fout[l], c->fin[l], n, c->g + c->fcW[l], c->g + c->fcB[l], acc, "fc_wgrad." + std::to_string(l),
+                          2.0 * n * ((double)c->fin[l] + c->fout[l]) + 4.0 * (double)c->fin[l] * c->fout[l], masked ? &beside : nullptr);
+    if (rc) return rc;
+    if (masked) {
+      if (!beside.taken) rc = launch_gemm(c, dl, n, c->fcT[l], c->fout[l], c->fin[l], c->fout[l], ep, "fc_dgrad." + std::to_string(l), ab);
     } else {  // the trunk's input is not a ReLU output (an embedding, an LSTM's h): nothing to mask
       Ep<MapRows, bf16_t, false, false, false> ep;
       ep.map = plain_map(c->fin[l], n); ep.out = c->gbuf[cur ^ 1]; ep.bias = nullptr; ep.mask = nullptr; ep.N = c->fin[l];

@@ -341,6 +341,15 @@ def test_a_range_of_environments_leaves_the_others(L, ci, h, w, off, cnt):
     assert torch.equal(lrn.buffer_read_obs(0), obs[0]) and torch.equal(lrn.buffer_read_obs(1), obs[1])
 
 
+@pytest.mark.parametrize("fc,P,N,T", [([96, 40], 8, 50, 4), ([200, 72], 40, 33, 3), ([520, 136, 24], 16, 70, 3), ([264, 512], 8, 31, 1), ([512, 520], 24, 40, 4)])
+def test_hidden_layers_weight_and_input_gradient_together(L, fc, P, N, T):
+    """Blocks of 128, 256 and 384 columns of the weight gradient beside 32 x 32 tiles of the input gradient: ragged rows, columns
+    and depths, one row tile, the deepest (512 outputs) and the first depth that takes two launches (520)."""
+    cfg = configs.get_config(1, num_envs=N, horizon=T)
+    cfg["net"].update(in_h=32, in_w=32, fc_dim=fc, proprio_dim=P)
+    _check_gradients(L, cfg, N, T)
+
+
 @pytest.mark.parametrize("layers,units,N,T,P", [(2, 64, 33, 5, 8), (1, 96, 70, 3, 40), (3, 32, 9, 4, 16), (2, 24, 40, 4, 8), (4, 32, 130, 2, 8), (2, 160, 65, 1, 8), (2, 64, 200, 6, 8)])
 def test_gradients_recurrent(L, layers, units, N, T, P):
     """LSTM layers side by side (units in multiples of 32; up to 64 environments: 64 x 64 tiles, more: 128 x 128) and one

@@ -174,10 +174,10 @@ __global__ __launch_bounds__(512) void k_conv0_ln_fwd(Ln0Args a) {
     asm volatile("" : "+s"(wave));  // (the tiles' addresses are not to be kept from image to image: they are more than the registers)
     const int next = img + (int)gridDim.x < a.nimg ? img + (int)gridDim.x : img;  // (the last one is fetched again: no branch)
     im.fetch(a, next);
-    if (img % a.in.V == 0 && im.tid < a.P >> 3) {
+    if (img % a.in.V == 0) {
       const int b = img / a.in.V;
       const int64_t sm = a.in.idx ? a.in.idx[b] : b;
-      reinterpret_cast<uint4*>(a.feat + (int64_t)b * a.feat_ld)[im.tid] = reinterpret_cast<const uint4*>(a.proprio + sm * a.P)[im.tid];
+      for (int i = im.tid; i < a.P >> 3; i += S::THREADS) reinterpret_cast<uint4*>(a.feat + (int64_t)b * a.feat_ld)[i] = reinterpret_cast<const uint4*>(a.proprio + sm * a.P)[i];
     }
     uint2 x[NT];
     float s = 0.f;

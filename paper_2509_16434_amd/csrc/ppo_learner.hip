@@ -1790,7 +1790,7 @@ static ImgAddr act_addr(Ctx* c, int l) {
 
 // First layer and its normalisation in one kernel per direction (ln0_tile.hip.h): 16 channels behind a one-channel image that a
 // block's registers hold (4864 output pixels).
-bool ln0_covers(const Ctx* c) { return c->ln && c->cC[0] == 1 && c->cC[1] == 16 && c->P <= 8192 && Ln0Shape::covers(c->cH[0], c->cW[0], c->cH[1]); }
+bool ln0_covers(const Ctx* c) { return c->ln && c->cC[0] == 1 && c->cC[1] == 16 && Ln0Shape::covers(c->cH[0], c->cW[0], c->cH[1]); }
 Ln0Args ln0_args(Ctx* c, const ImgAddr& in, int nimg) {
   Ln0Args a = {};
   a.in = in; a.in.prepare(); a.w = c->shadow + c->convW[0]; a.bias = c->p + c->convB[0]; a.gain = c->p + c->lnG[0]; a.shift = c->p + c->lnB[0]; a.nimg = nimg;

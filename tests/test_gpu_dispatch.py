@@ -283,6 +283,17 @@ def test_first_layer_and_its_normalisation(L, ci, conv, h, w, N, T):
     _check_gradients(L, cfg, N, T)
 
 
+@pytest.mark.parametrize("P", [4096, 4104, 8200])
+@pytest.mark.parametrize("views,more", [(1, {}), (2, {}), (2, dict(embed_dim=16))])
+def test_wide_proprioception_behind_the_first_layer_and_its_normalisation(L, views, more, P):
+    """That kernel copies the proprioception too: as many 16-byte pieces as a block has threads, one more, and some twice as many,
+    in the forward of the update and in that by index."""
+    cfg = configs.get_config(1, num_envs=9, horizon=3)
+    cfg["net"].update(dict(in_h=16, in_w=24, conv_ch=[16, 32], layer_norm=1, n_views=views, proprio_dim=P, fc_dim=[32]), **more)
+    _check_gradients(L, cfg, 9, 3)
+    _check_forward(L, cfg, 9, 3)
+
+
 @pytest.mark.parametrize("conv,ln,h,w,N,T", [((16, 32, 64, 128), 1, 60, 80, 16, 4), ((16, 32, 32), 1, 37, 53, 20, 7), ((16, 16, 32), 1, 30, 62, 5, 3), ((16, 8, 32), 1, 40, 34, 5, 2),
                                               ((16, 32, 64), 0, 44, 60, 6, 3), ((16, 32), 1, 18, 380, 3, 2), ((16, 32), 1, 18, 390, 3, 2), ((16, 32, 32), 1, 12, 20, 40, 8)])
 def test_second_layer_of_sixteen_channels(L, conv, ln, h, w, N, T):

@@ -220,7 +220,10 @@ __global__ __launch_bounds__(512) void k_conv0_ln_fwd(Ln0Args a) {
       im.exists(a, wave + 8 * j, &off);  // (the hardware drops stores beyond the image)
       float f[4];
       unpack4(x[j], f);
-      const u32x2_buf_t o = {relu_pack2bf(f[0] * g[0] + b[0], f[1] * g[1] + b[1]), relu_pack2bf(f[2] * g[2] + b[2], f[3] * g[3] + b[3])};
+      float y[4];  // (of a non-finite image: zeros, as k_ln_fwd leaves them)
+#pragma unroll
+      for (int i = 0; i < 4; ++i) y[i] = fmaxf(f[i] * g[i] + b[i], 0.f);
+      const u32x2_buf_t o = {pack2bf(y[0], y[1]), pack2bf(y[2], y[3])};
       __builtin_amdgcn_raw_buffer_store_b64(o, ro, off, 0, 0);
     }
     im.put(a, lds + (par ^ 1) * pb);

@@ -304,6 +304,38 @@ def test_second_layer_of_sixteen_channels(L, conv, ln, h, w, N, T):
     _check_gradients(L, cfg, N, T)
 
 
+@pytest.mark.parametrize("value", [np.nan, np.inf, -np.inf])
+@pytest.mark.parametrize("conv,h,w,views,more", [((16, 32), 40, 48, 1, {}), ((16, 32), 40, 50, 2, dict(embed_dim=32)), ((16, 32, 64), 118, 157, 1, {}),  # fused
+                                                 ((32, 64), 40, 48, 1, {}), ((16, 32), 122, 160, 1, {})])                             # kernels of their own
+def test_non_finite_images_before_a_normalisation(L, conv, h, w, views, more, value):
+    """One such pixel makes the normalised layer of its image zero, in both forms of that layer: the outputs of every sample are
+    the oracle's, and so are the gradients of the layers behind it."""
+    import torch
+    N = 12
+    cfg = configs.get_config(1, num_envs=N, horizon=1)
+    net = cfg["net"]
+    net.update(dict(in_h=h, in_w=w, conv_ch=list(conv), layer_norm=1, n_views=views, fc_dim=[64]), **more)
+    hp = dict(cfg["hp"], epochs=1, minibatches=1, seed=3)
+    ro = synth.rollout(cfg, conditioned=True)
+    ro["obs"][0, 1::4, -1, 0, h // 2, w // 3] = value
+    params = synth.init_params(net, 9)
+    lrn = L.Learner(net, N, 1, cfg["obs_dtype"])
+    lrn.set_params(params)
+    fill_learner(lrn, cfg, ro)
+    mu, v = (x.cpu().numpy() for x in lrn.forward())
+    lrn.gae(torch.from_numpy(ro["last_value"]).cuda(), hp["gamma"], hp["lam"])
+    adv, ret = (x.cpu().numpy().reshape(-1) for x in lrn.get_adv_ret())
+    lrn.update(hp)
+    g = lrn.get_grads()
+    with orc.quant(1):
+        omu, ov = orc.forward(net, params, ro["obs"][0], ro["proprio"][0])
+        _, qg = orc.ppo_loss_grad(net, params, *(ro[k][0] for k in ("obs", "proprio", "action", "logp_old", "value")), adv, ret,
+                                  clip_eps=hp["clip_eps"], vclip_eps=hp["vclip_eps"], vf_coef=hp["vf_coef"], ent_coef=hp["ent_coef"])
+    assert rel_l2(mu, omu) <= TOL_BF16 and rel_l2(v, ov) <= TOL_BF16
+    behind = {n: rel_l2(g[a:b], qg[a:b]) for n, (a, b, _) in synth.param_slices(net).items() if not n.startswith(("conv0", "ln0"))}
+    assert all(e <= TOL_BF16 for e in behind.values()), behind
+
+
 @pytest.mark.parametrize("chunks", range(1, 21))
 def test_layer_norm_backward_of_any_chunk_count(L, chunks):
     """One form of the layer-normalisation backward per number of 16-byte chunks a thread holds (up to 19; 20 reads

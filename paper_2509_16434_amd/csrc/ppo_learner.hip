@@ -642,6 +642,21 @@ struct DgradBeside {
   double abytes;
   bool taken;        // set by launch_wgrad
 };
+// How k_wgrad's work on Nn x Kk outputs is cut: blocks of 64 x 128*ktw outputs, and slices of the rows.  Wide outputs (the first
+// hidden layer) have enough tiles with narrow blocks and few slices: the fp32 partials, not the operands, are then the larger part
+// of the traffic.  Slices of 128 rows or more, of 64 or more where those would make fewer than 64 blocks: shorter chains (256 rows
+// of 64 x 1056 7.1 -> 5.3 us, 1250 of 128 x 256 8.3 -> 7.4; 4096 rows, 64 blocks: 0).
+struct WgradCut {
+  int ktw, tiles, most;
+  WgradCut(int Nn, int Kk) {
+    ktw = Kk <= 128 ? 1 : (Kk <= 256 ? 2 : (Kk >= 1024 ? 1 : 3));
+    tiles = cdiv(Kk, 128 * ktw) * cdiv(Nn, 64);
+    most = cdiv(Kk >= 1024 ? 512 : 768, tiles);
+  }
+  int splits(int64_t M) const { return std::min(most, (int64_t)tiles * cdiv(M, 128) < 64 ? cdiv(M, 64) : cdiv(M, 128)); }
+  // the most slices of up to M rows: those of M, or of the most rows that are cut by 64
+  int splits_up_to(int64_t M) const { return tiles > 63 ? splits(M) : std::max(splits(M), splits(std::min<int64_t>(M, 63 / tiles * 128))); }
+};
 // G[Nn][Kk] (+)= Dy^T * A over M rows, plus optional bias gradient gb[Nn].
 template <class DL, class AL>
 int launch_wgrad(Ctx* c, const DL& dl_, const AL& al_, int Nn, int Kk, int M, float* gw, float* gb, bool accumulate, const std::string& name, double abytes,
@@ -659,14 +674,9 @@ int launch_wgrad(Ctx* c, const DL& dl_, const AL& al_, int Nn, int Kk, int M, fl
   DL dl = dl_; AL al = al_;
   dl.prepare(); al.prepare();
   const char* what = name.c_str();
-  // wide outputs (the first hidden layer) have enough tiles with narrow blocks and few splits: the fp32 partials,
-  // not the operands, are then the larger part of the traffic
-  const int ktw = Kk <= 128 ? 1 : (Kk <= 256 ? 2 : (Kk >= 1024 ? 1 : 3));
-  const int tiles = cdiv(Kk, 128 * ktw) * cdiv(Nn, 64);
-  int splits = cdiv(Kk >= 1024 ? 512 : 768, tiles);
-  int max_by_rows = cdiv(M, 128);
-  if ((int64_t)tiles * max_by_rows < 64) max_by_rows = cdiv(M, 64);  // few blocks: shorter chains (256 rows of 64 x 1056 7.1 -> 5.3 us, 1250 of 128 x 256 8.3 -> 7.4; 4096 rows, 64 blocks: 0)
-  if (splits > max_by_rows) splits = max_by_rows;
+  const WgradCut cut(Nn, Kk);
+  const int ktw = cut.ktw;
+  int splits = cut.splits(M);
   const int64_t per = (int64_t)Nn * Kk;
   { const int erc = ensure_partial(c, (int64_t)splits * per, (int64_t)splits * Nn); if (erc) return erc; }
   if ((int64_t)splits * per > c->partial_elems) splits = (int)(c->partial_elems / per);
@@ -2629,12 +2639,11 @@ int create_impl(Ctx* c) {
   // weight-gradient partials: room for every layer at its preferred split count, all layers of a backward
   // pass side by side (their sums are taken in one launch at the end of the pass)
   int64_t pe_sum = 2048LL * c->cC[1] * (9 * c->cC[0] + 1), bpe_sum = 0;
-  auto want = [&](int Nn, int Kk, int64_t M, int64_t& need, int64_t& bneed) {  // k_wgrad
-    int ktw = Kk <= 128 ? 1 : (Kk <= 256 ? 2 : 3);
-    int tiles = cdiv(Kk, 128 * ktw) * cdiv(Nn, 64);
-    int splits = cdiv(768, tiles), mr = cdiv(M, 128);
-    if (splits > mr) splits = mr;
-    if (splits < 1) splits = 1;
+  // k_wgrad, of a chunk's rows or fewer.  (Of more than 256 columns also as many slices as blocks of 384 columns would take: the
+  // products of wide layers that are cut into slices leave their partial sums here as well.)
+  auto want = [&](int Nn, int Kk, int64_t M, int64_t& need, int64_t& bneed) {
+    int splits = WgradCut(Nn, Kk).splits_up_to(M);
+    if (Kk > 256) splits = std::max(splits, std::min(cdiv(768, cdiv(Kk, 384) * cdiv(Nn, 64)), cdiv(M, 128)));
     need = (int64_t)splits * Nn * Kk; bneed = (int64_t)splits * Nn;
   };
   for (int l = 1; l < c->nconv; ++l) {

@@ -677,3 +677,25 @@ def test_one_reduction_launch_per_step(L):
     lrn.profile(True)
     lrn.update(hp)
     assert lrn.profile_report()["wgrad_reduce"]["launches"] == 3
+
+
+@pytest.mark.parametrize("minibatches", [1, 2, 4])
+@pytest.mark.parametrize("more", [{}, dict(layer_norm=1), dict(lstm_layers=1, lstm_units=64)])
+def test_one_reduction_launch_per_step_of_a_small_network(L, more, minibatches):
+    """The same for a network whose weight gradients are all cut into slices of 64 rows, at the largest chunk (1024 rows) and at
+    fewer rows than the workspace was made for."""
+    import torch
+    cfg = configs.get_config(1, num_envs=256, horizon=4)
+    net, hp = cfg["net"], dict(cfg["hp"], epochs=2, minibatches=minibatches, seed=3)
+    net.update(dict(conv_ch=[8, 8], in_h=32, in_w=56, embed_dim=64, fc_dim=[64, 64], proprio_dim=8), **more)
+    lrn = L.Learner(net, 256, 4, "bf16")
+    lrn.set_params(synth.init_params(net, 9))
+    gen = torch.Generator(device="cuda")
+    gen.manual_seed(1)
+    keep = [synth.rollout_step_torch(cfg, gen) for _ in range(4)]
+    for t, d in enumerate(keep):
+        lrn.buffer_write(t, *(d[k].contiguous() for k in ("obs", "proprio", "action", "logp_old", "value", "reward", "done")))
+    lrn.gae(torch.zeros(256, device="cuda"), hp["gamma"], hp["lam"])
+    lrn.profile(True)
+    lrn.update(hp)
+    assert lrn.profile_report()["wgrad_reduce"]["launches"] == 2 * minibatches

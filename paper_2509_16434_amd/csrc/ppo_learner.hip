@@ -2603,11 +2603,13 @@ int create_impl(Ctx* c) {
     int64_t emax = 0;
     for (int l = 0; l < c->nconv; ++l) {
       const int64_t e = (int64_t)CH * V * c->cC[l + 1] * c->cH[l + 1] * c->cW[l + 1];
-      DALLOC(c, c->pre[l], e); DALLOC(c, c->lnstat[l], (int64_t)CH * V);
+      DALLOC(c, c->lnstat[l], (int64_t)CH * V);
+      if (e > gmax) gmax = e;
+      if (l == 0 && ln0_covers(c)) continue;  // the convolution's output and its gradient stay in registers
+      DALLOC(c, c->pre[l], e);
       if (e > emax) emax = e;
     }
     DALLOC(c, c->dpre, emax);
-    if (emax > gmax) gmax = emax;
   }
   if (c->nl > 0) {
     const int H = c->H;

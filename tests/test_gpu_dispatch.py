@@ -699,3 +699,22 @@ def test_one_reduction_launch_per_step_of_a_small_network(L, more, minibatches):
     lrn.profile(True)
     lrn.update(hp)
     assert lrn.profile_report()["wgrad_reduce"]["launches"] == 2 * minibatches
+
+
+def test_memory_of_the_fused_first_layer(L):
+    """The convolution in front of the first normalisation and its gradient stay in registers: a sample of a chunk takes the layer's
+    rectified output, a gradient in either of two buffers and, of the second layer, three tensors, but not two more of the first's
+    size."""
+    import torch
+    net = configs.get_config(1)["net"]
+    net.update(in_h=120, in_w=160, conv_ch=[16, 32], layer_norm=1, fc_dim=[32])
+    free = []
+    for chunk in (256, 1280):
+        torch.cuda.synchronize()
+        before = torch.cuda.mem_get_info()[0]
+        lrn = L.Learner(net, 1280, 1, "bf16", max_chunk=chunk)
+        free.append(before - torch.cuda.mem_get_info()[0])
+        lrn.close()
+    first, second = 2 * 16 * 60 * 80, 2 * 32 * 30 * 40
+    per_sample = (free[1] - free[0]) / 1024
+    assert 3 * first + 3 * second <= per_sample <= 3.5 * first + 3 * second, per_sample / first

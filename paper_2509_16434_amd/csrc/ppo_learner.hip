@@ -3172,7 +3172,15 @@ int ppo_act(ppo_ctx* c, int32_t t, const void* d_obs, const float* d_proprio, co
   if (t < 0 || t >= c->T) return fail(c, PPO_EINVAL, "t = %d outside [0, %d)", t, c->T);
   if (!d_obs || !d_proprio || !d_noise) return fail(c, PPO_EINVAL, "d_obs, d_proprio and d_noise must not be NULL");
   const int64_t first = (int64_t)t * c->N;
-  const bool one = head_act_covers(c) && c->N <= c->CH && small_net_covers(c, c->N);
+  // One kernel reads a sample's observations while another sample's outputs are already written: a caller who takes the outputs
+  // into the memory of the observations gets the separate launches.
+  auto overlap = [&](const void* out, int64_t n) {
+    const uintptr_t o = reinterpret_cast<uintptr_t>(out), b = reinterpret_cast<uintptr_t>(d_obs), p = reinterpret_cast<uintptr_t>(d_proprio);
+    const uintptr_t on = (uintptr_t)(n * 4), bn = (uintptr_t)((int64_t)c->N * c->V * c->d.in_c * c->d.in_h * c->d.in_w * (c->d.obs_dtype == 0 ? 4 : 2)), pn = (uintptr_t)((int64_t)c->N * c->P * 4);
+    return out && ((o < b + bn && b < o + on) || (o < p + pn && p < o + on));
+  };
+  const bool one = head_act_covers(c) && c->N <= c->CH && small_net_covers(c, c->N) && !overlap(d_action, (int64_t)c->N * c->A) && !overlap(d_logp, c->N) &&
+                   !overlap(d_value, c->N);
   int rc = PPO_OK;
   if (one) {
     SmallNetArgs a = {};

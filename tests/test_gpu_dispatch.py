@@ -606,6 +606,41 @@ def test_small_network_in_one_kernel(L, h, w, hid, P, N, dtype):
     assert st[0]["approx_kl"] == 0.0 and st[0]["clip_frac"] == 0.0
 
 
+@pytest.mark.parametrize("where", ["proprio", "obs"])
+def test_policy_step_into_the_memory_of_its_observations(L, where):
+    """The C entry point takes the caller's output arrays, which may lie where the observations did: the small network's one kernel,
+    in which a block may still read what another has written, is not the one that runs then."""
+    import ctypes as C
+
+    import torch
+    N = 300
+    cfg = configs.get_config(0, num_envs=N, horizon=1)
+    net = cfg["net"]
+    lrn = L.Learner(net, N, 1, "fp32")
+    lrn.set_params(synth.init_params(net, 5))
+    gen = torch.Generator(device="cuda")
+    gen.manual_seed(3)
+    d = {k: v.contiguous() for k, v in synth.rollout_step_torch(cfg, gen).items()}
+    noise = torch.randn(N, net["act_dim"], generator=gen, device="cuda")
+    want = [x.clone() for x in lrn.act(0, d["obs"], d["proprio"], noise)]
+    lrn.profile(True)
+    lrn.act(0, d["obs"], d["proprio"], noise)
+    assert "small_net_act" in lrn.profile_report()
+    at = [1, 1 + noise.numel(), 1 + noise.numel() + N]   # the action from the second element on, log-probability and value behind it
+    for use in ((0, 1, 2), (0,), (1,), (2,)):
+        p = d["proprio"].clone() if where == "proprio" else d["proprio"]
+        o = d["obs"].clone() if where == "obs" else d["obs"]
+        room = (p if where == "proprio" else o).view(-1)
+        out = [room[a:a + w.numel()] for a, w in zip(at, want)]
+        ptr = [C.c_void_p(x.data_ptr()) if i in use else None for i, x in enumerate(out)]
+        lrn.profile(True)
+        lrn._chk(L._lib.ppo_act(lrn._h, 0, C.c_void_p(o.data_ptr()), C.c_void_p(p.data_ptr()), C.c_void_p(noise.data_ptr()), *ptr))
+        torch.cuda.synchronize()
+        assert "small_net_act" not in lrn.profile_report()
+        for i in use:
+            assert torch.equal(out[i].view(want[i].shape), want[i])
+
+
 def test_read_back_staging_is_allocated_at_creation(L):
     """The first read of a context into memory in hand allocates nothing: its pinned staging (two pieces, 2 MiB, for this
     network) is part of ppo_create."""

@@ -158,6 +158,16 @@ def test_stacked_bands(L, ci, conv, more, h, w, N, T):
     _check_gradients(L, cfg, N, T)
 
 
+@pytest.mark.parametrize("ci,conv,h,w,N,T", [
+    (1, (32, 64, 64), 28, 28, 1500, 4), (1, (32, 64, 64, 64), 36, 44, 600, 4),   # 4 x 4; odd heights 9 and 5
+    (1, (32, 64, 64, 128), 60, 50, 1200, 2), (3, (32, 64, 64, 128), 28, 36, 1100, 2)])   # to 128 channels; two views
+def test_stacked_bands_many_per_block(L, ci, conv, h, w, N, T):
+    """The same with several tiles for each block, more than its ring has buffers in the narrow layers."""
+    cfg = configs.get_config(ci, num_envs=N, horizon=T)
+    cfg["net"].update(in_h=h, in_w=w, conv_ch=list(conv), fc_dim=[32])
+    _check_gradients(L, cfg, N, T)
+
+
 @pytest.mark.parametrize("c0,views,conv,h,w", [(1, 1, (32, 64), 9, 10), (1, 1, (32, 64, 16), 16, 8), (1, 1, (32, 64, 64), 21, 67),
                                                (1, 2, (32, 64, 64), 45, 90), (1, 1, (32, 64, 64), 13, 333), (1, 1, (32, 64, 64), 35, 280),
                                                (3, 1, (32, 64), 11, 14), (3, 2, (32, 64, 32), 30, 71), (3, 1, (32, 64, 64), 14, 200)])
@@ -262,6 +272,49 @@ def test_gradients_after_a_non_finite_update(L, c0, conv, h, w, N):
     np.testing.assert_array_equal(before, gradients(ro))
 
 
+@pytest.mark.parametrize("conv,h,w,N,more", [((16, 32, 64), 40, 48, 300, dict(layer_norm=1)), ((16, 32, 64), 84, 90, 260, dict(layer_norm=1)), ((16, 32), 118, 157, 130, dict(layer_norm=1)),
+                                             ((16, 32), 20, 28, 700, {}), ((16, 32, 64), 37, 53, 300, {}), ((32, 64, 64), 28, 28, 900, {}), ((32, 64, 64, 64), 36, 44, 600, {}),
+                                             ((8, 16), 32, 32, 600, dict(fc_dim=[64])), ((8, 16), 28, 33, 1000, dict(fc_dim=[32]))])
+def test_non_finite_images_in_the_fused_and_stacked_kernels(L, conv, h, w, N, more):
+    """First layer with its normalisation, 16 -> 32 channels, bands over the images' borders, the small network in one kernel: images
+    that are NaN or hold infinities leave the other samples' outputs as they were, bit for bit, by index and in the policy step,
+    and a learner whose images are all NaN leaves the next learner's gradients as they were."""
+    import torch
+    cfg = configs.get_config(1, num_envs=N, horizon=1)
+    net, hp = cfg["net"], dict(cfg["hp"], epochs=1, minibatches=1, seed=3)
+    net.update(dict(in_h=h, in_w=w, conv_ch=list(conv)), **more)
+    ro = synth.rollout(cfg, conditioned=True)
+    params = synth.init_params(net, 4)
+    bad = np.arange(1, N, 3)
+    spoiled = ro["obs"].copy()
+    spoiled[0, bad] = np.nan
+    spoiled[0, bad[::2], ..., : h // 2, :] = 1.0
+    spoiled[0, bad[::3], ..., h - 1, w // 2] = -np.inf
+    dev = lambda x: torch.from_numpy(np.ascontiguousarray(x)).cuda()
+    noise = torch.zeros(N, net["act_dim"], device="cuda")
+
+    def run(obs):
+        lrn = L.Learner(net, N, 1, "fp32")
+        lrn.set_params(params)
+        fill_learner(lrn, dict(cfg, obs_dtype="fp32"), dict(ro, obs=obs))
+        outs = list(lrn.forward(torch.arange(N, device="cuda", dtype=torch.int32)))
+        lrn.gae(dev(ro["last_value"]), hp["gamma"], hp["lam"])
+        lrn.update(hp)
+        g = lrn.get_grads()
+        lrn.set_params(params)
+        return [x.cpu().numpy() for x in outs + list(lrn.act(0, dev(obs[0]), dev(ro["proprio"][0]), noise))], g
+
+    outs, g = run(ro["obs"])
+    sick, _ = run(spoiled)
+    run(np.full_like(spoiled, np.nan))
+    again, g2 = run(ro["obs"])
+    keep = np.setdiff1d(np.arange(N), bad)
+    for a, b, c in zip(outs, sick, again):
+        np.testing.assert_array_equal(a[keep], b[keep])
+        np.testing.assert_array_equal(a, c)
+    np.testing.assert_array_equal(g, g2)
+
+
 @pytest.mark.parametrize("c0,conv,h,w", [(1, (32, 64, 32), 22, 226), (1, (8, 16), 33, 47), (1, (16, 32, 64, 128), 40, 64), (1, (32, 64), 16, 130), (1, (64, 64), 21, 24),
                                          (3, (16, 32), 18, 66), (3, (32, 64, 64), 37, 53), (1, (16, 64), 9, 16)])
 def test_gradients_with_layer_norm(L, c0, conv, h, w):
@@ -277,9 +330,21 @@ def test_gradients_with_layer_norm(L, c0, conv, h, w):
                                               (1, (16, 32, 64), 122, 160, 3, 2), (1, (16, 32), 2, 64, 5, 3)])
 def test_first_layer_and_its_normalisation(L, ci, conv, h, w, N, T):
     """First convolution, normalisation and ReLU in one kernel per direction: ten, twenty or 38 tiles per wave at most, rows that are no
-    multiple of four pixels, several images per block, and one row more than the registers hold (the separate kernels)."""
+    multiple of four pixels, several images per block (with ten; the others in the next test), and one row more than the registers
+    hold (the separate kernels)."""
     cfg = configs.get_config(ci, num_envs=N, horizon=T)
     cfg["net"].update(in_h=h, in_w=w, conv_ch=list(conv), layer_norm=1)
+    _check_gradients(L, cfg, N, T)
+
+
+@pytest.mark.parametrize("views,conv,h,w,N,T", [(1, (16, 32), 84, 90, 257, 2), (1, (16, 32), 84, 96, 300, 2), (2, (16, 32), 83, 91, 130, 2),
+                                                (1, (16, 32), 118, 157, 131, 2), (1, (16, 32), 120, 160, 131, 2), (2, (16, 32), 119, 150, 65, 2),
+                                                (2, (16, 32), 41, 69, 129, 2)])
+def test_several_images_per_block_of_the_first_layer_and_its_normalisation(L, views, conv, h, w, N, T):
+    """Blocks with two images or three in the forms with twenty and 38 tiles per wave, rows that are multiples of four pixels and
+    others, one view and two: the image and the gradient that travel while the one before is worked on, and sums over images."""
+    cfg = configs.get_config(1, num_envs=N, horizon=T)
+    cfg["net"].update(in_h=h, in_w=w, conv_ch=list(conv), layer_norm=1, n_views=views, fc_dim=[32])
     _check_gradients(L, cfg, N, T)
 
 
@@ -301,6 +366,15 @@ def test_second_layer_of_sixteen_channels(L, conv, ln, h, w, N, T):
     than 32 channels (input gradient: the implicit form), bands of fewer than four rows (forward: the same)."""
     cfg = configs.get_config(1, num_envs=N, horizon=T)
     cfg["net"].update(in_h=h, in_w=w, conv_ch=list(conv), layer_norm=ln)
+    _check_gradients(L, cfg, N, T)
+
+
+@pytest.mark.parametrize("ln", [0, 1])
+@pytest.mark.parametrize("h,w,N,T", [(20, 28, 650, 4), (40, 160, 300, 2), (29, 71, 350, 4)])
+def test_second_layer_of_sixteen_channels_many_tiles_per_block(L, ln, h, w, N, T):
+    """The same with more tiles for a block than its ring has buffers: one, two and four bands per image."""
+    cfg = configs.get_config(1, num_envs=N, horizon=T)
+    cfg["net"].update(in_h=h, in_w=w, conv_ch=[16, 32], layer_norm=ln, fc_dim=[32])
     _check_gradients(L, cfg, N, T)
 
 

@@ -115,6 +115,43 @@ def test_output_layer_and_loss(L, hid, A, N, T, kind):
     _check_gradients(L, cfg, N, T)
 
 
+@pytest.mark.parametrize("kind,A,hp", [("ppo", 7, {}), ("ppo", 23, dict(vclip_eps=0.05, clip_eps=0.05, ent_coef=0.01)), ("distill", 9, {}), ("distill", 23, dict(aux_dim=3, aux_coef=0.5))])
+def test_both_kernels_of_the_loss_agree(L, kind, A, hp):
+    """72 hidden units of which eight have no weights compute what 64 do, but their loss is taken one lane per sample behind a product of
+    its own, not four lanes per sample beside it: statistics and gradients of one batch through both.  Both take the same bf16
+    operands; their fp32 sums differ in order (a few 1e-6), and a gradient's bf16 rounding may go the other way (2^-8 of one value
+    in some thousand, hence 1e-3 of a tensor)."""
+    import torch
+    N, T, got = 70, 3, {}
+    for hid in (64, 72):
+        cfg = configs.get_config(1, num_envs=N, horizon=T)
+        net = cfg["net"]
+        net.update(in_h=24, in_w=32, fc_dim=[hid], act_dim=A, has_value_head=int(kind == "ppo"))
+        cfg["kind"] = kind
+        sl = synth.param_slices(net)
+        narrow = dict(net, fc_dim=[64])
+        p64 = synth.init_params(narrow, 9)
+        params = np.zeros(max(b for _, b, _ in sl.values()), np.float32)
+        live = {}
+        for n, (a, b, shape) in synth.param_slices(narrow).items():
+            at = np.arange(sl[n][0], sl[n][1]).reshape(sl[n][2])[tuple(slice(0, k) for k in shape)]
+            live[n] = at
+            params[at.reshape(-1)] = p64[a:b]
+        ro = synth.rollout(dict(cfg, net=narrow), conditioned=True)
+        lrn = L.Learner(net, N, T, cfg["obs_dtype"])
+        lrn.set_params(params)
+        fill_learner(lrn, cfg, ro, distill=kind == "distill")
+        h = dict(cfg["hp"], epochs=1, minibatches=1, seed=3, **hp)
+        if kind == "ppo":
+            lrn.gae(torch.from_numpy(ro["last_value"]).cuda(), h["gamma"], h["lam"])
+        st = (lrn.update if kind == "ppo" else lrn.distill_update)(h)[0]
+        g = lrn.get_grads()
+        got[hid] = (np.array([st[f] for f in L.STAT_FIELDS]), {n: g[at.reshape(-1)] for n, at in live.items()})
+    np.testing.assert_allclose(got[64][0], got[72][0], rtol=2e-5, atol=2e-6)
+    bad = {n: rel_l2(got[64][1][n], x) for n, x in got[72][1].items() if rel_l2(got[64][1][n], x) > 1e-3}
+    assert not bad, bad
+
+
 @pytest.mark.parametrize("ci,h,w", [(1, 51, 61), (1, 49, 58), (1, 89, 117), (1, 31, 33), (1, 45, 90), (3, 49, 58), (2, 62, 101)])
 def test_gradients_odd_second_layer_width(L, ci, h, w):
     """Widths whose first-layer output is odd."""

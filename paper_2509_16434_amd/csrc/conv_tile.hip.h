@@ -641,7 +641,7 @@ __global__ __launch_bounds__(512) void k_conv_wgrad_tile(ConvWgradArgs a) {
       vm_wait_few(younger(0) + nd + (nq > 1 ? pr.nl : 0));
       __builtin_amdgcn_s_barrier();  // the first image has landed, the buffers are zeroed
       produce_alone(0);
-      const bool interleave = pr.ng > 3 ? max(nd, pr.nl) <= pr.GPW : max(nd, pr.nl) <= 3;  // as many loads of a kind as groups at most  // as many loads of a kind as groups at most
+      const bool interleave = pr.ng > 3 ? max(nd, pr.nl) <= pr.GPW : max(nd, pr.nl) <= 3;  // as many loads of a kind as groups at most
       for (int q = 0; q < nq; ++q) {
         vm_wait_few(younger(q));       // dY of tile q and the image of tile q + 1 have landed
         asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");

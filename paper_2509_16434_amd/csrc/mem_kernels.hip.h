@@ -934,12 +934,12 @@ __device__ __forceinline__ void gnorm_finalize_block(const GnormFinalize& f) {
 
 // ---------------------------------------------------------------- Adam
 // m = b1 m + (1-b1) g; v = b2 v + (1-b2) g^2; p -= lr (m/c1) / (sqrt(v/c2) + eps), c1 = 1-b1^k,
-// c2 = 1-b2^k passed in.  Also refreshes the bf16 copy of the parameters and leaves per-block sums
-// of g^2 for the gradient-norm statistic.  With gradient-norm clipping (gn.on) the gradient enters as
-// g * min(1, c / (||g|| + 1e-6)): every block adds up the norm's per-block sums, left by
-// k_gnorm_partial, itself (a launch of one block for it cost 4.9 us, some 300 sums in every block
-// less than 1); the sums of g^2 are of the gradient before clipping either way.  lr_dev (if not null) holds the rate
-// instead of the argument: the KL-adaptive schedule keeps it on the device.
+// c2 = 1-b2^k passed in.  Also refreshes the bf16 copy of the parameters.  Without gradient-norm clipping it leaves per-block sums
+// of g^2 for the gradient-norm statistic.  With clipping (gn.on) those sums are there already, left by k_gnorm_partial, and the
+// gradient enters as g * min(1, c / (||g|| + 1e-6)): every block adds the sums up itself before it touches its parameters.  A
+// launch of one block for it took 4.6 us; in every block it costs k_adam 2.7 us at 2048 blocks (5.6 million parameters: 27.2 ->
+// 29.9; 14 million: 70.0 -> 72.5) and 0.1 at 70 (70 thousand: 3.4 -> 3.5).  lr_dev (if not null) holds the rate instead of the
+// argument: the KL-adaptive schedule keeps it on the device.
 __global__ __launch_bounds__(256) void k_adam(int64_t n, float* __restrict__ p, float* __restrict__ m,
                                               float* __restrict__ v, const float* __restrict__ g,
                                               bf16_t* __restrict__ shadow, float lr, float b1, float b2, float eps,

@@ -810,8 +810,6 @@ bool plan_cols(int Ho, int Wo, int maxpix, FITS fits, ColsPlan* out, int multipl
   return best >= 0;
 }
 
-// Bands of whole result rows for the forward kernel: *TR rows each, balanced, *NB of them; false where they do not fit (tiles
-// of columns then).
 // Bands of whole rows cut from each image (nb a piece), or from the stack of all images (common.hip.h)?  What a tile costs hardly
 // depends on how full it is, so the stack is taken where the `blocks` of the grid then have at most `pct` per cent of the tiles to
 // do one after another: heights that are no multiple of the rows a tile can hold, and images of less than a tile.  Its bands are
@@ -835,6 +833,8 @@ bool plan_stack(int nimg, int Ho, int Wo, int maxpix, int nb, int blocks, int pc
 }
 bool dense_images(int64_t stride_b, int64_t stride_v, int V, int64_t elems) { return stride_b == V * elems && (V == 1 || stride_v == elems); }
 
+// Bands of whole result rows for the forward kernel: *TR rows each, balanced, *NB of them; false where they do not fit (tiles
+// of columns then).
 template <int CIN, int WIDE>
 bool plan_fwd_rows(int W, int Ho, int Wo, int* TR, int* NB) {
   typedef ConvTileShape<CIN, WIDE> S;
@@ -1467,8 +1467,8 @@ int conv_small_forward(Ctx* c, const int32_t* idx, int n, int64_t first) {
   return PPO_OK;
 }
 // The forward of n samples in one kernel (small_net.hip.h): one hidden layer of 32 or 64 units behind one view, a product that the
-// separate launch would give to k_gemm_small, and few samples (four of a
-// block: 1024 environments 20.1 -> 14.8 us a policy step; with eight of a block it would take as long as the separate launches).
+// separate launch would give to k_gemm_small, and few samples (four to a block: 1024 environments 20.1 -> 14.8 us a policy step;
+// with eight to a block it would take as long as the separate launches).
 bool small_net_covers(const Ctx* c, int n) {
   return conv_small_covers(c) && c->V == 1 && c->nfc == 1 && (c->fout[0] == 32 || c->fout[0] == 64) && c->fin[0] <= 2048 && c->P % 8 == 0 && c->P > 0 &&
          c->fin[0] == c->flat + c->P && n <= 256 * SmallNetShape::MAXS && gemm_small_covers(n, c->fout[0], c->fin[0]);

@@ -1,6 +1,7 @@
 // 3x3 stride-2 pad-1 convolution from 16 to 32 channels: weight gradient and (unmasked) input gradient on LDS images of bands of
 // whole rows.  (The forward is k_conv_fwd_tile<16>.)  All three are bound by memory: the 16-channel tensor, of four times the
-// pixels, is two thirds of their bytes.  The implicit-GEMM kernels that such a layer took before gathered its windows through
+// pixels, is two thirds of their bytes, which move at 5.1 to 6.1 TB/s while vector instructions fill at most 0.17 and products
+// 0.14 of the cycles.  The implicit-GEMM kernels that such a layer took before gathered its windows through
 // integer divisions at two thirds of that rate: 4096 images of 60x80, forward 245 -> 180 us, input gradient
 // 266 -> 196, weight gradient 274 -> 156.
 #pragma once

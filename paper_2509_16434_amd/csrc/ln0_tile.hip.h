@@ -13,9 +13,10 @@
 //  * Weight gradient: the pixels' gradients pass through a strip of LDS (8 bytes written per lane, one transposing read) to become
 //    the operand of a product over 32 pixels; its other operand, the windows, is 16 neighbouring bytes of two planes' rows.
 //  * The next image's pixels, and backward its gradient tile by tile as this image's is consumed, are on their way in registers.
-// Backward is bound by vector issue (some hundred instructions per tile), forward by its stores.  4096 images of 120x160, with
-// the layer's kernels before (convolution, normalisation; their backward): forward 169 + 234 -> 220 us, backward
-// 376 + 157 -> 276.
+// Backward is bound by vector issue: some hundred instructions per tile fill 0.83 of its SIMDs' cycles.  Forward by neither issue
+// (0.56) nor memory alone (800 MB at 3.6 TB/s, of which 629 are stores): an image's stores follow its sums, and one block is all
+// that a CU's registers hold.  4096 images of 120x160, with the layer's kernels before (convolution, normalisation; their
+// backward): forward 169 + 234 -> 219 us, backward 376 + 157 -> 265 to 277.
 #pragma once
 #include "conv_small.hip.h"
 #include "recurrent.hip.h"

@@ -178,7 +178,8 @@ int ppo_buffer_write_range(ppo_ctx* ctx, int32_t t, int32_t env_offset, int32_t 
  *   a = mu + exp(logstd) * xi,   logp = sum_j [-((a_j-mu_j)/sigma_j)^2/2 - logstd_j - ln(2 pi)/2],
  * with the standard-normal draws xi supplied by the caller (d_noise [N][A] fp32, device).  Action,
  * log-prob and value go into the step-t slab and, where the pointers are not NULL, to the DEVICE
- * arrays d_action [N][A], d_logp [N], d_value [N] (fp32).  The step counts as written only after
+ * arrays d_action [N][A], d_logp [N], d_value [N] (fp32), which may lie in the memory of d_obs or
+ * d_proprio but not of each other.  The step counts as written only after
  * ppo_buffer_write_outcome(t).  Actor-critic contexts only (else PPO_ESTATE); t = 0 starts a new rollout. */
 int ppo_act(ppo_ctx* ctx, int32_t t, const void* d_obs, const float* d_proprio, const float* d_noise, float* d_action,
             float* d_logp, float* d_value);
